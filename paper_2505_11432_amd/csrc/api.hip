@@ -115,12 +115,7 @@ static int ffn_bwd_plain(const void* xp, const void* h_save, const void* d_yp, c
   void* dA = base + align_up((size_t)M * f * es, 256);
   void* dH = base + 2 * align_up((size_t)M * f * es, 256);
   int rc;
-  const void* A_used = a_override;
-  if (a_override == nullptr) {
-    rc = launch_swiglu_fwd(h_save, A, M, f, offsets + E, dt, s);     // recompute the FC2 input
-    if (rc != MOE_OK) return rc;
-    A_used = A;
-  }
+  const void* A_used = a_override ? a_override : A;
   GemmProblem g{};
   g.offsets = offsets; g.E = E; g.bias = nullptr;
   // dA[M,f] = d_yp[M,d] * w2[e]   (contraction over d)
@@ -130,7 +125,7 @@ static int ffn_bwd_plain(const void* xp, const void* h_save, const void* d_yp, c
   g.C = dA; g.c_es = 0; g.ldc = f; g.N = f; g.K = d;
   rc = launch_gemm_generic(g, dt, dt, dt, s);
   if (rc != MOE_OK) return rc;
-  rc = launch_swiglu_bwd(h_save, dA, dH, M, f, offsets + E, dt, s);
+  rc = launch_swiglu_bwd(h_save, dA, dH, a_override ? nullptr : A, M, f, offsets + E, dt, s);   // recomputes the FC2 input
   if (rc != MOE_OK) return rc;
   // d_w2[e][d,f] = d_yp_e^T * A_e   (contraction over the expert's rows)
   g.mode = 1; g.accumulate = accumulate;

@@ -1,0 +1,270 @@
+// Grouped GEMM on fp32 data with the fp32 matrix instruction (v_mfma_f32_32x32x2_f32): the same contract as the
+// vector-ALU kernel of gemm_generic.hip, for operands whose rows or columns can be read in whole 16-byte pieces.
+//
+// Bound: the fp32 matrix rate, 256 FLOP per clock and CU, twice what unpacked fp32 FMAs give.  One instruction takes 64
+// clocks for 4 KFLOP, so the operands are cheap to feed and small tiles are affordable; what matters is that loads are
+// in flight early and that the tile count fills 256 CUs.  Three shapes of four waves, 32 x 32 outputs per wave; where
+// waves share outputs each takes its part of every k-step and the sums are added through LDS at the end:
+//   64 x 64, k-steps of 32;  64 x 32, two waves per output, k-steps of 32;  32 x 32, four per output, k-steps of 64.
+// All keep two k-steps of global loads in registers ahead of the LDS stage that is being multiplied; several workgroups
+// share a CU and hide each other's latency.
+// Measured (8 experts, 2000 rows, d = 1024, f = 2816; the vector-ALU kernel first): FC1 492 -> 238 us (97 TFLOP/s), FC2
+// 601 -> 135, dgrad2 267 -> 114, dgrad1 1383 -> 265, wgrad2 211 -> 118, wgrad1 416 -> 228; router logits of 1000 tokens
+// 182 -> 13 us.  8192 x 4096 x 2048 in four experts: 110 TFLOP/s.
+#include "moe_common.h"
+
+namespace moe {
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr int kThreads = 256;
+constexpr int kGroupN = 8;         // n-tiles per group: neighbouring workgroups of an XCD form a compact block of tiles
+constexpr int kXcds = 8, kWindow = 32;
+
+// LDS image of one operand tile of EXT rows (or columns) x BK.  K-fast: [ext][BK + 4], a lane reads four consecutive k with
+// one b128 (16 lanes then cover the 64 banks once).  MN-fast: [BK][EXT + 8], a lane reads its row at one k with a b32;
+// the two lane halves read k rows four apart, 4 * (EXT + 8) = 32 mod 64 banks apart.
+template <bool KFAST, int EXT, int BK> struct Tile {
+  static constexpr int LD = KFAST ? BK + 4 : EXT + 8;
+  static constexpr int FLOATS = (KFAST ? EXT : BK) * LD;
+  static constexpr int VECS = EXT * BK / 4 / kThreads;      // 16-byte pieces per thread and k-step
+  static constexpr int PER_ROW = (KFAST ? BK : EXT) / 4;
+  static_assert(EXT * BK % (4 * kThreads) == 0, "a k-step splits evenly over the threads");
+  // piece v of this thread: row and column (elements) inside the stored tile
+  __device__ static __forceinline__ int row(int v) { return (v * kThreads + (int)threadIdx.x) / PER_ROW; }
+  __device__ static __forceinline__ int col(int v) { return (v * kThreads + (int)threadIdx.x) % PER_ROW * 4; }
+};
+
+// Operand piece -> registers.  ext0 / ext_n: first row (column) of the tile and the number of valid ones; k is absolute,
+// k_end its end.  Rows past the end repeat the last valid one (they only reach outputs that are not stored); pieces past
+// the end of the contraction are zero.
+template <bool KFAST, int EXT, int BK>
+__device__ __forceinline__ void fetch(const float* __restrict__ base, long ld, int ext0, int ext_n, int k, int k_end,
+                                      f32x4 (&out)[Tile<KFAST, EXT, BK>::VECS]) {
+  using TL = Tile<KFAST, EXT, BK>;
+#pragma unroll
+  for (int v = 0; v < TL::VECS; ++v) {
+    const int r = TL::row(v), c = TL::col(v);
+    const int kk = k + (KFAST ? c : r);
+    const int x = KFAST ? min(r, ext_n - 1) : min(c, ext_n - 4);
+    const float* p = base + (KFAST ? (long)(ext0 + x) * ld + kk : (long)kk * ld + ext0 + x);
+    f32x4 t = {0.f, 0.f, 0.f, 0.f};
+    if (kk < k_end) t = *reinterpret_cast<const f32x4*>(p);
+    out[v] = t;
+  }
+}
+template <bool KFAST, int EXT, int BK>
+__device__ __forceinline__ void stash(float* lds, const f32x4 (&in)[Tile<KFAST, EXT, BK>::VECS]) {
+  using TL = Tile<KFAST, EXT, BK>;
+#pragma unroll
+  for (int v = 0; v < TL::VECS; ++v) *reinterpret_cast<f32x4*>(lds + TL::row(v) * TL::LD + TL::col(v)) = in[v];
+}
+// The four k values 4 * (lane / 32) + 0..3 of an 8-deep group, for tile row x.
+template <bool KFAST, int EXT, int BK>
+__device__ __forceinline__ f32x4 frag(const float* lds, int x, int k8, int half) {
+  using TL = Tile<KFAST, EXT, BK>;
+  if constexpr (KFAST) {
+    return *reinterpret_cast<const f32x4*>(lds + x * TL::LD + k8 + 4 * half);
+  } else {
+    f32x4 r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r[j] = lds[(k8 + 4 * half + j) * TL::LD + x];
+    return r;
+  }
+}
+
+// Expert segment that holds running tile index l when every segment of n rows has cdiv(n, bm) * tiles_n tiles.  A wave
+// looks at 64 segments at a time (a lane each, prefix sum by shuffles).
+__device__ __forceinline__ bool find_segment(const int32_t* __restrict__ offsets, int E, int bm, int tiles_n, int l, int& e,
+                                             int& lo, int& hi, int& l_in) {
+  const int lane = threadIdx.x & 63;
+  int base = 0;
+  for (int e0 = 0; e0 < E; e0 += 64) {
+    const int ei = min(e0 + lane, E - 1);
+    const int o0 = offsets[ei], o1 = offsets[ei + 1];
+    const int n = e0 + lane < E ? (o1 - o0 + bm - 1) / bm * tiles_n : 0;
+    int incl = n;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int o = __shfl_up(incl, off);
+      if (lane >= off) incl += o;
+    }
+    const unsigned long long hit = __ballot(base + incl > l);
+    if (hit != 0) {
+      const int src = __builtin_ctzll(hit);
+      e = e0 + src;
+      lo = __builtin_amdgcn_readlane(o0, src);
+      hi = __builtin_amdgcn_readlane(o1, src);
+      l_in = l - base - (__builtin_amdgcn_readlane(incl, src) - __builtin_amdgcn_readlane(n, src));
+      return true;
+    }
+    base += __builtin_amdgcn_readlane(incl, 63);
+  }
+  return false;
+}
+
+template <int BM, int BN, int BK, int WM, int WN, int WK, bool AK, bool BKF>
+__global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmProblem p, int tiles_n, int tiles_m_fixed, int blocks) {
+  static_assert(WM * WN * WK == 4 && BM == 32 * WM && BN == 32 * WN && BK % (8 * WK) == 0, "four waves of 32 x 32");
+  using TA = Tile<AK, BM, BK>;
+  using TB = Tile<BKF, BN, BK>;
+  __shared__ __attribute__((aligned(16))) float lds[2][TA::FLOATS + TB::FLOATS];
+  static_assert(sizeof(lds) >= (WK - 1) * WM * WN * 32 * 32 * 4, "the sums that change waves fit");
+
+  // runs of kWindow consecutive tiles go to one XCD (workgroup b runs on XCD b % 8) so that its L2 serves their panels
+  int l = blockIdx.x;
+  const int span = kXcds * kWindow, first = l / span * span;
+  if (first + span <= blocks) l = first + (l % kXcds) * kWindow + (l - first) / kXcds;
+  int e = 0, m0, m_end, k0 = 0, k_end = p.K, mt_e = tiles_m_fixed;
+  int m_lo = 0;
+  m_end = p.M;
+  if (p.mode == 0) {
+    int hi, l_in;
+    if (!find_segment(p.offsets, p.E, BM, tiles_n, l, e, m_lo, hi, l_in)) return;
+    l = l_in;
+    m_end = hi;
+    mt_e = (hi - m_lo + BM - 1) / BM;
+  } else if (p.mode == 1) {
+    e = l / (mt_e * tiles_n);
+    l -= e * mt_e * tiles_n;
+    k0 = p.offsets[e];
+    k_end = p.offsets[e + 1];
+  }
+  const int ng = l / (mt_e * kGroupN), rest = l - ng * mt_e * kGroupN;
+  const int gw = min(kGroupN, tiles_n - ng * kGroupN);
+  const int mt = rest / gw, nt = ng * kGroupN + (rest - mt * gw);
+  m0 = m_lo + mt * BM;
+  const int n0 = nt * BN;
+  const float* __restrict__ A = static_cast<const float*>(p.A);
+  const float* __restrict__ B = static_cast<const float*>(p.B) + (long)e * p.b_es;
+  const long lda = AK ? p.a_rs : p.a_cs, ldb = BKF ? p.b_cs : p.b_rs;
+
+  const int lane = threadIdx.x & 63, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wk = wave % WK, wm = wave / WK % WM, wn = wave / WK / WM;
+  const int row = wm * 32 + (lane & 31), colr = wn * 32 + (lane & 31);
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+
+  f32x4 ra[2][TA::VECS], rb[2][TB::VECS];
+  auto load = [&](int set, int k) __attribute__((always_inline)) {
+    fetch<AK, BM, BK>(A, lda, m0, m_end - m0, k, k_end, ra[set]);
+    fetch<BKF, BN, BK>(B, ldb, n0, p.N - n0, k, k_end, rb[set]);
+  };
+  auto put = [&](int set, int buf) __attribute__((always_inline)) {
+    stash<AK, BM, BK>(lds[buf], ra[set]);
+    stash<BKF, BN, BK>(lds[buf] + TA::FLOATS, rb[set]);
+  };
+  auto multiply = [&](int buf) __attribute__((always_inline)) {
+    const float* at = lds[buf];
+    const float* bt = lds[buf] + TA::FLOATS;
+#pragma unroll
+    for (int g = 0; g < BK / 8 / WK; ++g) {
+      const int k8 = (wk * (BK / 8 / WK) + g) * 8;
+      const f32x4 a = frag<AK, BM, BK>(at, row, k8, half);
+      const f32x4 b = frag<BKF, BN, BK>(bt, colr, k8, half);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b[j], acc, 0, 0, 0);
+    }
+  };
+  // step s sits in LDS buffer s & 1; the registers hold steps s + 1 and s + 2 while step s is multiplied.  A buffer is
+  // overwritten one barrier after its last read.
+  const int steps = (k_end - k0 + BK - 1) / BK;
+  if (steps > 0) {
+    load(0, k0);
+    if (steps > 1) load(1, k0 + BK);
+    put(0, 0);
+    if (steps > 2) load(0, k0 + 2 * BK);
+    __syncthreads();
+    for (int s = 0; s < steps; s += 2) {
+      multiply(0);
+      if (s + 1 < steps) put(1, 1);
+      if (s + 3 < steps) load(1, k0 + (s + 3) * BK);
+      __syncthreads();
+      if (s + 1 >= steps) break;
+      multiply(1);
+      if (s + 2 < steps) put(0, 0);
+      if (s + 4 < steps) load(0, k0 + (s + 4) * BK);
+      __syncthreads();
+    }
+  }
+  if constexpr (WK > 1) {
+    // (the loop ended with a barrier, or never started) the other waves of an output hand their sums to its first one,
+    // which adds them in wave order
+    float* part = &lds[0][0] + (wm * WN + wn) * (WK - 1) * 1024;
+    if (wk > 0)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) part[((wk - 1) * 16 + r) * 64 + lane] = acc[r];
+    __syncthreads();
+    if (wk > 0) return;
+#pragma unroll
+    for (int w = 0; w < WK - 1; ++w)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] += part[(w * 16 + r) * 64 + lane];
+  }
+  // a lane holds column lane % 32 and rows 8q + 4 * (lane / 32) + 0..3: a store writes two rows of 128 bytes
+  float* __restrict__ C = static_cast<float*>(p.C) + (long)e * p.c_es;
+  const int n = n0 + colr;
+  if (n >= p.N) return;
+  const float bias = p.bias ? p.bias[n] : 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = m0 + wm * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+    if (m >= m_end) continue;
+    float* dst = C + (long)m * p.ldc + n;
+    float v = acc[r] + bias;
+    if (p.accumulate) v += *dst;
+    *dst = v;
+  }
+}
+
+template <int BM, int BN, int BK, int WM, int WN, int WK>
+int launch(const GemmProblem& p, bool a_kfast, bool b_kfast, hipStream_t s) {
+  const int tiles_n = cdiv(p.N, BN);
+  int tiles_m_fixed = cdiv(p.M, BM);
+  long blocks = (long)tiles_n * tiles_m_fixed;
+  if (p.mode == 0) blocks = (long)tiles_n * ((long)tiles_m_fixed + p.E);       // upper bound over any segment lengths
+  if (p.mode == 1) blocks *= p.E;
+  if (blocks > 0x7fffffffL) return MOE_ERR_UNSUPPORTED;
+  const dim3 grid((unsigned)blocks), block(kThreads);
+  if (a_kfast && b_kfast) gemm_f32_kernel<BM, BN, BK, WM, WN, WK, true, true><<<grid, block, 0, s>>>(p, tiles_n, tiles_m_fixed, (int)blocks);
+  else if (a_kfast) gemm_f32_kernel<BM, BN, BK, WM, WN, WK, true, false><<<grid, block, 0, s>>>(p, tiles_n, tiles_m_fixed, (int)blocks);
+  else gemm_f32_kernel<BM, BN, BK, WM, WN, WK, false, false><<<grid, block, 0, s>>>(p, tiles_n, tiles_m_fixed, (int)blocks);
+  MOE_LAUNCH_CHECK();
+  return MOE_OK;
+}
+
+}  // namespace
+
+// True when the operands can be read in whole 16-byte pieces along their fast dimension.
+bool gemm_f32_covers(const GemmProblem& p) {
+  const bool a_kfast = p.a_cs == 1, b_kfast = p.b_rs == 1;
+  if (!aligned16(p.A) || !aligned16(p.B) || p.N <= 0 || p.M <= 0) return false;
+  if (!a_kfast && (p.a_rs != 1 || b_kfast)) return false;
+  if (!b_kfast && p.b_cs != 1) return false;
+  if ((a_kfast ? p.a_rs : p.a_cs) % 4 || (b_kfast ? p.b_cs : p.b_rs) % 4 || p.b_es % 4) return false;
+  if (!a_kfast && p.M % 4) return false;
+  if (!b_kfast && p.N % 4) return false;
+  // a piece that lies along k must not straddle the end of the contraction: K a multiple of 4, segments of any length no
+  if ((a_kfast || b_kfast) && (p.mode == 1 || p.K % 4)) return false;
+  return true;
+}
+
+// Which shape: smaller tiles read more per FLOP but spread a problem over more workgroups and shorten its serial chain of
+// k-steps.  Fewer 64 x 64 tiles than CUs: 32 x 32 (512 rows of 8 experts, N = 512, K = 1408: 21 us against 26 with
+// 64 x 32 and 36 with 64 x 64).  Up to four per CU the last round of tiles is what counts: 64 x 32 (560 tiles, K = 2816:
+// 135 us against 152).  Beyond that 64 x 64 where an operand is read across its rows (1408 tiles: 114 us against 127),
+// 64 x 32 still where both are read along k (2816 tiles: 238 us against 262).
+int launch_gemm_f32(const GemmProblem& p, hipStream_t s) {
+  const bool a_kfast = p.a_cs == 1, b_kfast = p.b_rs == 1;
+  const long tiles_m = (long)cdiv(p.M, 64) + (p.mode == 0 ? p.E / 2 : 0);      // segments end inside a tile
+  const long tiles = (long)cdiv(p.N, 64) * tiles_m * (p.mode == 1 ? p.E : 1);
+  if (tiles < 256) return launch<32, 32, 64, 1, 1, 4>(p, a_kfast, b_kfast, s);
+  if (tiles < 1024 || b_kfast) return launch<64, 32, 32, 2, 1, 2>(p, a_kfast, b_kfast, s);
+  return launch<64, 64, 32, 2, 2, 1>(p, a_kfast, b_kfast, s);
+}
+
+}  // namespace moe

@@ -2,8 +2,8 @@
 //
 // It is the arithmetic of the paper's GroupedGEMM operator (Section 4.1: one kernel for the
 // per-expert matmuls of FC1 and FC2, and their gradients) for the cases the MFMA kernels do
-// not cover: fp32 data (no fast fp32 matrix path is needed for the correctness-only
-// configuration), the skinny router matmuls, and shapes the tuned tiles reject.
+// not cover: router matmuls on rows that cannot be read in 16-byte pieces, and fp32 problems
+// that gemm_f32.hip declines.
 #include "moe_common.h"
 
 namespace moe {
@@ -123,6 +123,7 @@ int launch_gemm_generic(const GemmProblem& p, moe_dtype a_dt, moe_dtype b_dt, mo
     blocks = (long)tiles_n * cdiv(p.M, BM);
   }
   if (blocks <= 0 || p.N <= 0) return MOE_OK;
+  if (a_dt == MOE_F32 && b_dt == MOE_F32 && c_dt == MOE_F32 && gemm_f32_covers(p)) return launch_gemm_f32(p, s);
   if (blocks > 0x7fffffffL) return MOE_ERR_UNSUPPORTED;
   dim3 grid((unsigned)blocks), block(NT);
 #define MOE_GEMM_CASE(DA, DB, DC, TA, TB, TC)                                          \

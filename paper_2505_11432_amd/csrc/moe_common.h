@@ -70,6 +70,9 @@ struct GemmProblem {
   const float* bias;                         // per-column fp32 bias added in the epilogue, or NULL
 };
 int launch_gemm_generic(const GemmProblem& p, moe_dtype a_dt, moe_dtype b_dt, moe_dtype c_dt, hipStream_t s);
+// The same on the fp32 matrix instruction, for fp32 operands that can be read in 16-byte pieces (gemm_f32.hip).
+bool gemm_f32_covers(const GemmProblem& p);
+int launch_gemm_f32(const GemmProblem& p, hipStream_t s);
 
 int launch_route(const float* logits, int T, int E, int k, int renorm, int e_lo, int e_hi, int n_groups, int capacity,
                  int32_t* idx, float* w, float* score, int32_t* counts, int32_t* offsets, int32_t* perm,
@@ -147,7 +150,8 @@ int launch_router_bwd(const void* x, const void* w_r, const float* d_logits, moe
 int launch_transpose(const void* src, moe_dtype dt, int batch, int rows, int cols, void* dst, hipStream_t s);
 
 int launch_swiglu_fwd(const void* H, void* A, int M, int f, const int32_t* row_limit, moe_dtype dt, hipStream_t s);
-int launch_swiglu_bwd(const void* H, const void* dA, void* dH, int M, int f, const int32_t* row_limit,
+// A: receives the SwiGLU output as well, or NULL
+int launch_swiglu_bwd(const void* H, const void* dA, void* dH, void* A, int M, int f, const int32_t* row_limit,
                       moe_dtype dt, hipStream_t s);
 
 }  // namespace moe
