@@ -393,7 +393,7 @@ int moe_expert_ffn_bwd(const void* xp, const void* h_save, const void* d_yp, con
 static size_t fused_a_bytes(size_t m, int f) { return align_up(m * f * 2, 256); }
 static size_t fused_dh_bytes(size_t m, int f) { return align_up(m * 2 * f * 2, 256); }
 static size_t fused_rows_bytes(size_t m, int d) { return align_up(m * d * 2, 256); }
-static size_t fused_part_bytes(size_t m, int f) { return align_up((size_t)mfma_dgrad2_fold_parts(f) * m * 4, 256); }
+static size_t fused_part_bytes(size_t m, int f) { return align_up((size_t)cdiv(f, 256) * 4 * m * 4, 256); }
 
 size_t moe_expert_ffn_fused_workspace_bytes(int T, int k, int d, int f) {
   if (T < 0 || k < 1 || d <= 0 || f <= 0) return 0;
@@ -463,7 +463,7 @@ int moe_expert_ffn_fused_bwd(const void* x, const void* dy, const void* h_save, 
     if (rc != MOE_OK) return rc;
     rc = mfma_dgrad2_swiglu_bwd_fold(rows, w2, offsets, M, d, E, f, h_save, dH, Aw, row_w, part, s);
     if (rc != MOE_OK) return rc;
-    rc = launch_gate_grad_reduce(part, mfma_dgrad2_fold_parts(f), M, inv_perm, M, d_topk_w, s);
+    rc = launch_gate_grad_reduce(part, mfma_dgrad2_fold_parts(M, E, f), M, inv_perm, M, d_topk_w, s);
     if (rc != MOE_OK) return rc;
   }
   rc = mfma_wgrad(rows, Aw, offsets, d, f, E, d_w2, grad_dt, accumulate != 0, s);

@@ -39,7 +39,7 @@ std::vector<configure_fn>& configure_registry() {
 
 template <int BM, int BN, int BKT, int NS, int WM, int WN, Layout LA, Layout LB, Mode MODE, Epi EPI, typename TC, typename TIN>
 struct KernelSetup {
-  static constexpr int smem = dma_smem_bytes<BM, BN, BKT, NS, LA, LB, (int)sizeof(TIN)>();
+  static constexpr int smem = dma_smem_bytes<BM, BN, BKT, NS, WM * WN, LA, LB, (int)sizeof(TIN)>();
   static auto kernel() { return grouped_gemm_dma_kernel<BM, BN, BKT, NS, WM, WN, LA, LB, MODE, EPI, TC, TIN>; }
   // Idempotent and safe to race: the attribute value is the same on every call, the per-device bit only saves work.
   static int configure(int dev) {
@@ -99,8 +99,33 @@ int launch(const Args& a, long tiles_upper_bound, hipStream_t s) {
   return MOE_OK;
 }
 
-long rowseg_blocks(int M, int E, int N, int bm, int bn_out) {
-  return (long)cdiv(N, bn_out) * (cdiv(M, bm) + E);
+// Tile of the row-segmented kernels by the average number of rows per expert (the bound M over E: the real counts live
+// on the device; any counts are correct with any tile).
+//   up to 32 rows: the launch is a stream over the weights.  64 x 128 tiles, 256 bytes of every row per k-step in three
+//     stages: 96 KB of weights in flight per CU instead of at most 64, four to eight times the tiles to deal out, and
+//     quarter-size A tiles.
+//   up to 96 rows: still bound by the weights, but an expert needs more than one 64-row tile: 128 x 128 in four stages.
+//   more: the 256 x 256 tile, which is the one for arithmetic.
+// Measured, weights from memory, FC1 + SwiGLU / FC2 (us; 256 x 256, 128 x 128, 64 x 128):
+//   8 experts, 4096 x 14336:   4 rows 431/322, 345/188, 333/179;  64 rows 507/399, 388/190, 406/244;  256 rows 657/333, 862/443, -
+//   64 experts, 2048 x 1408:  32 rows 201/88, 178/82, 165/73;     64 rows 214/94, 190/87, 181/92;    128 rows 215/96, 237/114, -
+enum class RowTile { FEW, MID, FULL };
+RowTile row_tile(int M, int E) {
+  const long rows = (long)M / E;
+  return rows <= 32 ? RowTile::FEW : rows <= 96 ? RowTile::MID : RowTile::FULL;
+}
+
+template <Layout LB, Epi EPI, typename TIN = bf16>
+int launch_rowseg(const Args& a, hipStream_t s) {
+  constexpr int B128 = 128 / (int)sizeof(TIN);        // elements in 128 bytes
+  if (a.M <= 0 || a.N <= 0) return MOE_OK;
+  switch (row_tile(a.M, a.E)) {
+    case RowTile::FEW: return launch<64, 128, 2 * B128, 3, 2, 2, KMAJOR, LB, ROWSEG, EPI, bf16, TIN>(a, 1, s);
+    case RowTile::MID: return launch<128, 128, B128, 4, 2, 2, KMAJOR, LB, ROWSEG, EPI, bf16, TIN>(a, 1, s);
+    default: break;
+  }
+  if constexpr (LB == KMAJOR) return launch<256, 256, B128, 2, 4, 2, KMAJOR, LB, ROWSEG, EPI, bf16, TIN>(a, 1, s);
+  else return launch<256, 256, B128, 2, 2, 4, KMAJOR, LB, ROWSEG, EPI, bf16, TIN>(a, 1, s);
 }
 
 }  // namespace
@@ -113,7 +138,7 @@ int mfma_fc1_swiglu(const void* xp, const void* w1, const int32_t* offsets, int 
   a.B = (const bf16*)w1; a.ldb = d; a.b_es = 2L * f * d;
   a.offsets = offsets; a.E = E; a.M = M; a.N = f; a.K = d; a.f = f;
   a.H = (bf16*)H; a.A_out = (bf16*)A_out;
-  return launch<256, 256, 64, 2, 4, 2, KMAJOR, KMAJOR, ROWSEG, EPI_SWIGLU, bf16>(a, rowseg_blocks(M, E, f, 256, 128), s);
+  return launch_rowseg<KMAJOR, EPI_SWIGLU>(a, s);
 }
 
 // The same with the Section 4.1 / 4.2 operator order: row r of the A operand is row row_token[r] of x [T,d] (selected
@@ -125,7 +150,7 @@ int mfma_fc1_swiglu_gather(const void* x, int T, const int32_t* row_token, const
   a.B = (const bf16*)w1; a.ldb = d; a.b_es = 2L * f * d;
   a.offsets = offsets; a.E = E; a.M = M; a.N = f; a.K = d; a.f = f;
   a.H = (bf16*)H; a.A_out = (bf16*)A_out;
-  return launch<256, 256, 64, 2, 4, 2, KMAJOR, KMAJOR, ROWSEG, EPI_SWIGLU_W, bf16>(a, rowseg_blocks(M, E, f, 256, 128), s);
+  return launch_rowseg<KMAJOR, EPI_SWIGLU_W>(a, s);
 }
 
 // C[M,N] = A[M,K] * W[e]^T with W[e] = [N,K]
@@ -136,7 +161,7 @@ int mfma_rowseg_nt(const void* A, const void* W, long w_es, const int32_t* offse
   a.A = (const bf16*)A; a.lda = K;
   a.B = (const bf16*)W; a.ldb = K; a.b_es = w_es;
   a.C = C; a.ldc = N; a.offsets = offsets; a.E = E; a.M = M; a.N = N; a.K = K;
-  return launch<256, 256, 64, 2, 4, 2, KMAJOR, KMAJOR, ROWSEG, EPI_STORE, bf16>(a, rowseg_blocks(M, E, N, 256, 256), s);
+  return launch_rowseg<KMAJOR, EPI_STORE>(a, s);
 }
 
 // C[M,N] = A[M,K] * W[e] with W[e] = [K,N]
@@ -147,7 +172,7 @@ int mfma_rowseg_nn(const void* A, const void* W, long w_es, const int32_t* offse
   a.A = (const bf16*)A; a.lda = K;
   a.B = (const bf16*)W; a.ldb = N; a.b_es = w_es;
   a.C = C; a.ldc = N; a.offsets = offsets; a.E = E; a.M = M; a.N = N; a.K = K;
-  return launch<256, 256, 64, 2, 2, 4, KMAJOR, MNMAJOR, ROWSEG, EPI_STORE, bf16>(a, rowseg_blocks(M, E, N, 256, 256), s);
+  return launch_rowseg<MNMAJOR, EPI_STORE>(a, s);
 }
 
 // dA = d_yp * w2[e] fused with the SwiGLU derivative: reads H=[G|U], writes dH=[dG|dU] and (optionally) A
@@ -158,12 +183,13 @@ int mfma_dgrad2_swiglu_bwd(const void* d_yp, const void* w2, const int32_t* offs
   a.B = (const bf16*)w2; a.ldb = f; a.b_es = (long)d * f;
   a.offsets = offsets; a.E = E; a.M = M; a.N = f; a.K = d;
   a.H = (bf16*)const_cast<void*>(H); a.dH = (bf16*)dH; a.A_out = (bf16*)A_out;
-  return launch<256, 256, 64, 2, 2, 4, KMAJOR, MNMAJOR, ROWSEG, EPI_SWIGLU_BWD, bf16>(a, rowseg_blocks(M, E, f, 256, 256), s);
+  return launch_rowseg<MNMAJOR, EPI_SWIGLU_BWD>(a, s);
 }
 
 // dgrad2 in the Section 4.1 order: d_yp holds the unweighted output gradient of each row; dH gets SwiGLU'(dA') (the
-// row's weight is applied downstream), A_out = w_r * A, and dw_part [mfma_dgrad2_fold_parts(f)][M] the partial sums of <dA'[r,:], A[r,:]>
-int mfma_dgrad2_fold_parts(int f) { return cdiv(f, 256) * 4; }
+// row's weight is applied downstream), A_out = w_r * A, and dw_part [mfma_dgrad2_fold_parts(M, E, f)][M] the partial sums of
+// <dA'[r,:], A[r,:]>: one per n-tile and wave along n
+int mfma_dgrad2_fold_parts(int M, int E, int f) { return row_tile(M, E) == RowTile::FULL ? cdiv(f, 256) * 4 : cdiv(f, 128) * 2; }
 int mfma_dgrad2_swiglu_bwd_fold(const void* d_yp, const void* w2, const int32_t* offsets, int M, int d, int E, int f,
                                 const void* H, void* dH, void* A_out, const float* row_w, float* dw_part, hipStream_t s) {
   Args a{};
@@ -172,7 +198,7 @@ int mfma_dgrad2_swiglu_bwd_fold(const void* d_yp, const void* w2, const int32_t*
   a.offsets = offsets; a.E = E; a.M = M; a.N = f; a.K = d;
   a.H = (bf16*)const_cast<void*>(H); a.dH = (bf16*)dH; a.A_out = (bf16*)A_out;
   a.row_w = row_w; a.dw_part = dw_part;
-  return launch<256, 256, 64, 2, 2, 4, KMAJOR, MNMAJOR, ROWSEG, EPI_SWIGLU_BWD_W, bf16>(a, rowseg_blocks(M, E, f, 256, 256), s);
+  return launch_rowseg<MNMAJOR, EPI_SWIGLU_BWD_W>(a, s);
 }
 
 // C[e][Mo,N] (+)= P[rows_e, Mo]^T * Q[rows_e, N]
@@ -198,7 +224,7 @@ int mfma_fc1_swiglu_fp8(const void* xp, const float* xp_scale, const void* w1, c
   a.offsets = offsets; a.E = E; a.M = M; a.N = f; a.K = d; a.f = f;
   a.H = (bf16*)H; a.A_out = (bf16*)A_out;
   a.row_scale = xp_scale; a.col_scale = w1_scale; a.cs_es = 2L * f;
-  return launch<256, 256, 128, 2, 4, 2, KMAJOR, KMAJOR, ROWSEG, EPI_SWIGLU, bf16, uint8_t>(a, rowseg_blocks(M, E, f, 256, 128), s);
+  return launch_rowseg<KMAJOR, EPI_SWIGLU, uint8_t>(a, s);
 }
 
 // C[M,N] = (A*sa) * (W[e]*sw)^T, bf16 out
@@ -210,7 +236,7 @@ int mfma_rowseg_nt_fp8(const void* A, const float* a_scale, const void* W, const
   a.B = W; a.ldb = K; a.b_es = w_es;
   a.C = C; a.ldc = N; a.offsets = offsets; a.E = E; a.M = M; a.N = N; a.K = K;
   a.row_scale = a_scale; a.col_scale = w_scale; a.cs_es = N;
-  return launch<256, 256, 128, 2, 4, 2, KMAJOR, KMAJOR, ROWSEG, EPI_STORE, bf16, uint8_t>(a, rowseg_blocks(M, E, N, 256, 256), s);
+  return launch_rowseg<KMAJOR, EPI_STORE, uint8_t>(a, s);
 }
 
 
@@ -225,7 +251,7 @@ int mfma_dgrad2_swiglu_bwd_fp8(const void* dyq, const float* dyq_scale, const vo
   a.offsets = offsets; a.E = E; a.M = M; a.N = f; a.K = d;
   a.H = (bf16*)const_cast<void*>(H); a.dH = (bf16*)dH; a.A_out = (bf16*)A_out;
   a.row_scale = dyq_scale; a.col_scale = w2t_scale; a.cs_es = f;
-  return launch<256, 256, 128, 2, 4, 2, KMAJOR, KMAJOR, ROWSEG, EPI_SWIGLU_BWD, bf16, uint8_t>(a, rowseg_blocks(M, E, f, 256, 256), s);
+  return launch_rowseg<KMAJOR, EPI_SWIGLU_BWD, uint8_t>(a, s);
 }
 
 // e4m3 weight gradient: C[e][Mo,N] (+)= P_t[Mo, tokens_e] * Q_t[N, tokens_e]^T on transposed (token-minor) codes

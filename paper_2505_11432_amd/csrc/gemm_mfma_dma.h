@@ -314,6 +314,26 @@ __host__ __device__ __forceinline__ void splitk_plan(int total_tiles, int workgr
   total_items = full_tiles + (total_tiles - full_tiles) * split;
 }
 
+// cum[e] = number of BM-row tiles of the experts before e, by the first wave (64 experts at a time).
+template <int BM>
+__device__ __forceinline__ void tile_table(const int32_t* __restrict__ offsets, int E, int* cum) {
+  const int lane = threadIdx.x;
+  if (lane >= 64) return;
+  if (lane == 0) cum[0] = 0;
+  int base = 0;
+  for (int e0 = 0; e0 < E; e0 += 64) {
+    const int e = e0 + lane;
+    int incl = e < E ? (offsets[e + 1] - offsets[e] + BM - 1) / BM : 0;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int o = __shfl_up(incl, off);
+      if (lane >= off) incl += o;
+    }
+    if (e < E) cum[e + 1] = base + incl;
+    base += __builtin_amdgcn_readlane(incl, 63);
+  }
+}
+
 // Adds the K parts of every split tile and writes the bf16 result with the tile's row / column masks.  Four
 // workgroups per split tile; the tile list is rebuilt exactly as in the GEMM kernel (same grouping constants).
 template <int BM, int BN>
@@ -321,14 +341,7 @@ __global__ void __launch_bounds__(256) splitk_fixup_kernel(const float* __restri
                                                            int E, int N, int gemm_workgroups, bf16* __restrict__ C, long ldc) {
   constexpr int GN = 8;
   __shared__ int cum_tiles[MOE_MAX_EXPERTS + 1];
-  if (threadIdx.x == 0) {
-    int run = 0;
-    cum_tiles[0] = 0;
-    for (int i = 0; i < E; ++i) {
-      run += (offsets[i + 1] - offsets[i] + BM - 1) / BM;
-      cum_tiles[i + 1] = run;
-    }
-  }
+  tile_table<BM>(offsets, E, cum_tiles);
   __syncthreads();
   const int tiles_n = (N + BN - 1) / BN;
   const int total_tiles = cum_tiles[E] * tiles_n;
@@ -410,7 +423,10 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
                                  : EPI == EPI_SWIGLU_BWD_W ? TM * TN * 6 + TM
                                  : 0;
   constexpr int EPI_STORES = (NSTAGE - 2) * LOADS + EPI_STORES_RAW <= 63 ? EPI_STORES_RAW : 0;   // vmcnt is a 6-bit field
-  bool epi_stores = false;         // the previous tile's epilogue issued exactly EPI_STORES stores (wave-uniform)
+  // what this wave's epilogue of the previous tile put into the memory queue (wave-uniform): exactly EPI_STORES stores,
+  // nothing, or an unknown number
+  enum { EPI_UNKNOWN = 0, EPI_ALL = 1, EPI_NONE = 2 };
+  int epi_state = EPI_NONE;
   constexpr int GN = 8, XCDS = 8;   // GN n-tiles per group: a window of 32 tiles is 4 m-tiles x 8 n-tiles (measured against 8 x 4, 16 x 2, 2 x 16)
   static_assert(A_BYTES % (1024 * NL) == 0 && B_BYTES % (1024 * NL) == 0, "tile does not split over the loader waves");
   static_assert(NSTAGE >= 2 && (NSTAGE - 2) * LOADS < 64, "pipeline depth exceeds the vmcnt range");
@@ -439,14 +455,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
   const int tiles_m_fixed = (p.M + BM - 1) / BM;              // KSEG / PLAIN
   int total_tiles;
   if constexpr (MODE == ROWSEG) {
-    if (tid == 0) {
-      int run = 0;
-      cum_tiles[0] = 0;
-      for (int i = 0; i < p.E; ++i) {
-        run += (p.offsets[i + 1] - p.offsets[i] + BM - 1) / BM;
-        cum_tiles[i + 1] = run;
-      }
-    }
+    tile_table<BM>(p.offsets, p.E, cum_tiles);
     __syncthreads();
     total_tiles = __builtin_amdgcn_readfirstlane(cum_tiles[p.E]) * tiles_n;
   } else if constexpr (MODE == KSEG) {
@@ -487,9 +496,9 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
   constexpr bool TOUCH_K = MODE == KSEG && !FP8 && SPLIT && LA == MNMAJOR && LB == MNMAJOR && NSTAGE == 4;
   constexpr bool TOUCH_K2 = MODE == KSEG && !FP8 && SPLIT && LA == MNMAJOR && LB == MNMAJOR && NSTAGE == 2 && BKT == 64;
   const bool is_toucher = (TOUCH || TOUCH_K || TOUCH_K2) && wave == NL;
-  const unsigned lds_dump = smem_lds + RING_BYTES + TABLE_BYTES + 8 * STG_BYTES;
+  const unsigned lds_dump = smem_lds + RING_BYTES + TABLE_BYTES + NW * STG_BYTES;
   const unsigned scale_lds = lds_dump + 256;                                   // block-scale ring: 2 stages x (256 + 256) bytes
-  const char* scale_smem = smem + RING_BYTES + TABLE_BYTES + 8 * STG_BYTES + 256;
+  const char* scale_smem = smem + RING_BYTES + TABLE_BYTES + NW * STG_BYTES + 256;
   unsigned ta_off = 0;
   // rotation of this workgroup's load order within the A / B tile (see open_tile); only where it pays: the e4m3
   // row-segmented kernels (in the others the extra scalar state pushes tile offsets out of registers)
@@ -721,13 +730,15 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
     // Wait until this wave's loads for step s have landed.  vmcnt counts loads and stores together, in issue order, so
     // the wait names how many younger operations may still be outstanding: the loads of the (NSTAGE - 2) following
     // steps, and, in the first NSTAGE - 1 steps of a tile (whose loads were issued before the previous tile's
-    // epilogue), that epilogue's stores when their number is known (epi_stores; 0 = unknown: wait for everything).
+    // epilogue), that epilogue's stores when their number is known (unknown: wait for everything).  With few rows per
+    // expert no tile is full, but a wave still issues all of its (masked) stores or none: waiting for everything at each
+    // tile's start would drain the ring there.
     auto wait_step = [&](int s) __attribute__((always_inline)) {
       if (s + NSTAGE - 2 < nk) {
         if constexpr (EPI_STORES > 0) {
-          if (s < NSTAGE - 1 && epi_stores) { wait_vmcnt<(NSTAGE - 2) * LOADS + EPI_STORES>(); return; }
+          if (s < NSTAGE - 1 && epi_state == EPI_ALL) { wait_vmcnt<(NSTAGE - 2) * LOADS + EPI_STORES>(); return; }
         }
-        if (s > 0) { wait_vmcnt<(NSTAGE - 2) * LOADS>(); return; }
+        if (s > 0 || epi_state == EPI_NONE) { wait_vmcnt<(NSTAGE - 2) * LOADS>(); return; }
       }
       wait_vmcnt<0>();
     };
@@ -868,9 +879,13 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
     }
     // ---- hand the ring to the next tile, then write this one out -------------------------------------
     const int ep_e = e, ep_m0 = m0, ep_m_end = m_end, ep_n0 = n0, ep_part_slot = part_slot;
-    // a full tile that is no split-K part and does not read-modify-write issues every store of its epilogue
-    epi_stores = EPI_STORES > 0 && part_slot < 0 && !p.accumulate && m0 + BM <= m_end &&
-                 n0 + BN_OUT <= (SWI ? p.f : p.N);
+    // a full tile that is no split-K part and does not read-modify-write issues every store of its epilogue; a wave of
+    // one 32-row block does so if it has a valid row, and issues none otherwise
+    epi_state = EPI_UNKNOWN;
+    if (EPI_STORES > 0 && part_slot < 0 && !p.accumulate && n0 + BN_OUT <= (SWI ? p.f : p.N)) {
+      if (m0 + BM <= m_end || (TM == 1 && m0 + wm * WTM < m_end)) epi_state = EPI_ALL;
+      else if (TM == 1) epi_state = EPI_NONE;
+    }
     // SwiGLU' (bf16): the saved G and U of the wave's first block are asked for before the hand-over, ahead of the
     // next tile's first loads in the memory queue
     constexpr bool EARLY_GU = !FP8 && (EPI == EPI_SWIGLU_BWD || EPI == EPI_SWIGLU_BWD_W);
@@ -1139,11 +1154,11 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
   }
 }
 
-template <int BM, int BN, int BKT, int NSTAGE, Layout LA, Layout LB, int ESZ = 2>
+template <int BM, int BN, int BKT, int NSTAGE, int NW, Layout LA, Layout LB, int ESZ = 2>
 constexpr int dma_smem_bytes() {
-  // the ring, the per-expert tile table and one epilogue patch per wave (at most 8 waves)
+  // the ring, the per-expert tile table and one epilogue patch per wave
   return NSTAGE * (DmaTileBytes<LA, BM, BKT, ESZ>::value + DmaTileBytes<LB, BN, BKT, ESZ>::value) + (MOE_MAX_EXPERTS + 8) * 4 +
-         8 * STG_BYTES + 256 + 1024;       // + the dump area of the L2 touches + the block-scale ring
+         NW * STG_BYTES + 256 + 1024;       // + the dump area of the L2 touches + the block-scale ring
 }
 
 }  // namespace mfma

@@ -1,0 +1,124 @@
+"""The row-segmented grouped GEMMs with few rows per expert (64- and 128-row tiles), bf16, fused order and e4m3, against float64."""
+import math
+
+import pytest
+import torch
+
+from tests.gpu_util import DEV
+
+pytestmark = pytest.mark.gpu
+
+# rows per expert: averages up to 32 and up to 96 select the 64- and the 128-row tile; segments end before, on and after tile
+# and 32-row block edges, experts are empty, one expert holds far more than the average
+ROWS = [[1], [0, 1, 63, 64, 65, 0, 30, 33], [2] * 70, [0, 0, 0, 128], [0, 127, 128, 129, 1, 95], [300, 0, 0, 31], [33, 97]]
+# d, f: several k-steps with remainders, 16-column tails of the 128- and 64-wide tiles, one k-step and less
+DIMS = [(272, 336), (512, 128), (16, 48)]
+STEP = 2.0 ** -9            # one bf16 rounding
+
+
+def rel(got, ref):
+    n = float(ref.norm())
+    return float((got.double() - ref).norm()) / (n if n > 0 else 1.0)
+
+
+def setup(rows, d, f):
+    E, M = len(rows), sum(rows)
+    g = torch.Generator(device=DEV).manual_seed(M * 7 + d)
+    rnd = lambda *s: torch.randn(s, generator=g, device=DEV)
+    off = [sum(rows[:e]) for e in range(E + 1)]
+    offsets = torch.tensor(off, dtype=torch.int32, device=DEV)
+    w1, w2 = rnd(E, 2 * f, d) / math.sqrt(d), rnd(E, d, f) / math.sqrt(f)
+    return E, M, off, offsets, w1.bfloat16(), w2.bfloat16(), rnd(M, d).bfloat16(), rnd(M, d).bfloat16()
+
+
+def swiglu_bwd(H, dA, f):
+    G, U = H[:, :f], H[:, f:]
+    s = torch.sigmoid(G)
+    return G * s * U, torch.cat([dA * U * s * (1 + G * (1 - s)), dA * G * s], 1)
+
+
+@pytest.mark.parametrize("d,f", DIMS)
+@pytest.mark.parametrize("rows", ROWS)
+def test_bf16_and_fused(rows, d, f):
+    from paper_2505_11432_amd import binding as B
+    E, M, off, offsets, w1, w2, x, dy = setup(rows, d, f)
+    bf = dict(dtype=torch.bfloat16, device=DEV)
+    h, yp, dxp = torch.full((M, 2 * f), 7.0, **bf), torch.full((M, d), 7.0, **bf), torch.full((M, d), 7.0, **bf)
+    dw1, dw2 = torch.empty((E, 2 * f, d), device=DEV), torch.empty((E, d, f), device=DEV)
+    ws = torch.empty(B.moe_workspace_bytes(M, d, E, 1, f, B.BF16), dtype=torch.uint8, device=DEV)
+    B.moe_expert_ffn_fwd(x, None, offsets, w1, None, w2, None, h, yp, None, ws)
+    B.moe_expert_ffn_bwd(x, h, dy, None, offsets, w1, w2, dxp, dw1, dw2, 0, ws)
+    # the fused order on the same rows: top-1, rows in a shuffled token order, weights in (0, 1)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    tok = torch.randperm(M, generator=g, device=DEV)
+    wt = torch.rand((M, 1), generator=g, device=DEV) + 0.1
+    xt, dyt, inv = torch.empty_like(x), torch.empty_like(dy), torch.empty((M,), dtype=torch.int32, device=DEV)
+    xt[tok], dyt[tok] = x, dy
+    inv[tok] = torch.arange(M, dtype=torch.int32, device=DEV)
+    row_w = wt.view(-1)[tok].contiguous()
+    hf, yf, dxf = torch.full_like(h, 7.0), torch.full_like(yp, 7.0), torch.full_like(dxp, 7.0)
+    fw1, fw2, fdw = torch.empty_like(dw1), torch.empty_like(dw2), torch.empty((M, 1), device=DEV)
+    fws = torch.empty(B.moe_expert_ffn_fused_workspace_bytes(M, 1, d, f), dtype=torch.uint8, device=DEV)
+    B.moe_expert_ffn_fused_fwd(xt, tok.int(), row_w, offsets, w1, w2, 1, hf, yf, fws)
+    B.moe_expert_ffn_fused_bwd(xt, dyt, hf, inv, wt, row_w, offsets, w1, w2, 1, dxf, fw1, fw2, 0, fdw, fws)
+    H, Y, DX = (torch.zeros(s, dtype=torch.float64, device=DEV) for s in ((M, 2 * f), (M, d), (M, d)))
+    DW1, DW2, DWT = torch.zeros_like(dw1).double(), torch.zeros_like(dw2).double(), torch.zeros(M, dtype=torch.float64, device=DEV)
+    FW2 = torch.zeros_like(DW2)
+    for e in range(E):
+        s = slice(off[e], off[e + 1])
+        X, DY, a, b, w = x[s].double(), dy[s].double(), w1[e].double(), w2[e].double(), row_w[s].double()[:, None]
+        H[s] = X @ a.t()
+        dA = DY @ b
+        A, dH = swiglu_bwd(H[s], dA, f)
+        Y[s], DX[s] = A @ b.t(), dH @ a
+        DWT[s] = (dA * A).sum(1)
+        DW1[e], DW2[e], FW2[e] = dH.t() @ X, DY.t() @ A, DY.t() @ (w * A)
+    # a result carries at most four stored bf16 roundings on its way (H, A or dA, dH, itself)
+    assert torch.equal(h, hf)
+    for name, got, ref in (("h", h, H), ("yp", yp, Y), ("d_xp", dxp, DX), ("d_w1", dw1, DW1), ("d_w2", dw2, DW2),
+                           ("ypw", yf, Y * row_w.double()[:, None]), ("fused d_xp", dxf, DX), ("fused d_w2", fw2, FW2)):
+        assert rel(got, ref) < 4 * STEP, (name, rel(got, ref))
+    # a dot product of f terms of random sign, each with the roundings of dA and of H
+    assert rel(fdw.view(-1)[tok], DWT) < 4 * STEP
+
+
+@pytest.mark.parametrize("d,f", DIMS)
+@pytest.mark.parametrize("rows", ROWS)
+def test_e4m3(rows, d, f):
+    from paper_2505_11432_amd import binding as B
+    E, M, off, offsets, w1, w2, x, dy = setup(rows, d, f)
+    u8, bf = dict(dtype=torch.uint8, device=DEV), dict(dtype=torch.bfloat16, device=DEV)
+
+    def q(t):
+        v = t.reshape(-1, t.shape[-1]).contiguous()
+        c, s = torch.empty(v.shape, **u8), torch.empty((v.shape[0],), device=DEV)
+        B.moe_quant_fp8(v, B.Q_ROW, c, s)
+        return c.view(t.shape), s.view(t.shape[:-1])
+
+    deq = lambda c, s: c.view(torch.float8_e4m3fn).double() * s.double()[..., None]
+    (xc, xs), (c1, s1), (c2, s2) = q(x), q(w1), q(w2)
+    (t1, ts1), (t2, ts2) = q(w1.transpose(1, 2).contiguous()), q(w2.transpose(1, 2).contiguous())
+    h, yp, dxp = torch.full((M, 2 * f), 7.0, **bf), torch.full((M, d), 7.0, **bf), torch.full((M, d), 7.0, **bf)
+    ac, asc = torch.empty((M, f), **u8), torch.empty((M,), device=DEV)
+    ws = torch.empty(B.moe_workspace_bytes(M, d, E, 1, f, B.F8E4M3), dtype=torch.uint8, device=DEV)
+    B.moe_expert_ffn_fwd(xc, xs, offsets, c1, s1, c2, s2, h, yp, None, ws, ac, asc)
+    ldt = B.moe_tgroup_tokens(M, E)
+    f32 = dict(device=DEV)
+    it = dict(dy_codes=torch.empty((M, d), **u8), dy_scale=torch.empty((M,), **f32), dh=torch.empty((M, 2 * f), **bf),
+              dh_codes=torch.empty((M, 2 * f), **u8), dh_scale=torch.empty((M,), **f32),
+              pad_offsets=torch.empty((E + 1,), dtype=torch.int32, device=DEV), splitk_ws=torch.empty((B.SPLITK_WS_BYTES,), **u8))
+    for n, c in (("dy", d), ("dh", 2 * f), ("a", f), ("x", d)):
+        it[n + "_t"], it[n + "_e8m0"] = torch.empty((c, ldt), **u8), torch.empty((ldt // 128, c), **u8)
+    dw1, dw2 = torch.empty((E, 2 * f, d), **f32), torch.empty((E, d, f), **f32)
+    B.moe_expert_ffn_bwd_fp8(dy, h, (xc, xs), (ac, asc), offsets, t1, ts1, t2, ts2, dxp, dw1, dw2, 0, it)
+    # every stage from the codes the kernels themselves read: one stored rounding per result (dH: dA as well)
+    X, A, DY, DH = deq(xc, xs), deq(ac, asc), deq(it["dy_codes"], it["dy_scale"]), deq(it["dh_codes"], it["dh_scale"])
+    W1, W2, T1, T2 = deq(c1, s1), deq(c2, s2), deq(t1, ts1), deq(t2, ts2)
+    for e in range(E):
+        s = slice(off[e], off[e + 1])
+        if off[e] == off[e + 1]:
+            continue
+        ref_dh = swiglu_bwd(h[s].double(), DY[s] @ T2[e].t(), f)[1]
+        for name, got, ref in (("h", h[s], X[s] @ W1[e].t()), ("yp", yp[s], A[s] @ W2[e].t()), ("dh", it["dh"][s], ref_dh),
+                               ("d_xp", dxp[s], DH[s] @ T1[e].t())):
+            assert rel(got, ref) < 2 * STEP, (name, e, rel(got, ref))
