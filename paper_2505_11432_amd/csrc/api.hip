@@ -197,7 +197,8 @@ int moe_router_fwd(const void* x, const void* w_r, const float* bias, moe_dtype 
   if (!x || !w_r || !logits) return MOE_ERR_INVALID;
   if (dt != MOE_F32 && dt != MOE_BF16) return MOE_ERR_UNSUPPORTED;
   if (dt == MOE_BF16 && d % 8 == 0 && aligned16(x) && aligned16(w_r))
-    return mfma_router_fwd(x, w_r, bias, T, d, E, logits, as_stream(stream));
+    return router_fwd_small(T, E) ? launch_router_fwd_small(x, w_r, bias, T, d, E, logits, as_stream(stream))
+                                  : mfma_router_fwd(x, w_r, bias, T, d, E, logits, as_stream(stream));
   GemmProblem g{};
   g.mode = 2; g.E = 1; g.offsets = nullptr; g.accumulate = 0; g.bias = bias;
   g.A = x; g.a_rs = d; g.a_cs = 1;

@@ -135,6 +135,9 @@ int mfma_dgrad2_swiglu_bwd_fp8(const void* dyq, const float* dyq_scale, const vo
 int mfma_wgrad_fp8(const void* Pt, const uint8_t* p_e8m0, const void* Qt, const uint8_t* q_e8m0, long ldt,
                    const int32_t* pad_offsets, int Mo, int N, int E, void* C, moe_dtype c_dt, int accumulate,
                    hipStream_t s);
+// router_fwd_small: problems that launch_router_fwd_small is the faster one for (router_fwd.hip)
+bool router_fwd_small(int T, int E);
+int launch_router_fwd_small(const void* x, const void* w_r, const float* bias, int T, int d, int E, float* logits, hipStream_t s);
 int mfma_router_fwd(const void* x, const void* w_r, const float* bias, int T, int d, int E, float* logits,
                     hipStream_t s);
 // partial[c][E][d] (+)= g[tokens of chunk c, E]^T * x[tokens of chunk c, d], g and x bf16, chunk_offsets [chunks+1]
