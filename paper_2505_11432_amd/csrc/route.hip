@@ -2,42 +2,79 @@
 // input rows to output rows is computed once from the routing result; Section 4.2: rows ordered by
 // expert, then by source).  The paper lists the "multitude of small operators" of the gate as a
 // launch-latency straggler (Section 7); here the whole step is three launches and no host read-back:
-//   1. route_topk_kernel   per token: k-fold arg-max under the total order (logit desc, id asc) with
-//                          shuffles inside groups of <= 16 lanes (4+ tokens per wave at a time), softmax
-//                          over the selected logits, per-chunk expert histogram
-//   2. route_scan_kernel   one wave per expert: exclusive scan of its per-chunk counts
+//   1. route_topk_kernel   per token: k-fold arg-max under the total order (logit desc, id asc) by DPP exchanges
+//                          inside groups of <= 16 lanes (4+ tokens per wave at a time), softmax over the
+//                          selected logits, per-chunk expert histogram
+//   2. route_scan_kernel   one wave per expert: exclusive scan of its per-chunk counts (left out while the
+//                          histogram is small enough for every workgroup of 3. to sum it itself)
 //   3. route_rank_kernel   offsets = scan of the counts; stable rank of every assignment inside its
 //                          expert: equal-expert lanes found with one ballot per bit of the expert id
+// All three are bound by latency (dependent steps, launches), not by bytes.  Kernel times before (shuffles, four
+// rounds of tokens per workgroup, one wave ranking a chunk 64 at a time) and now, E = 64, k = 8: T = 257 1. 23.8 -> 6.7 us,
+// 2. 5.1 -> none, 3. 9.2 -> 4.9; T = 4096 20.5 -> 7.0, 4.6 -> none, 6.5 -> 4.2; T = 16384 24.8 -> 8.2, 5.1 -> none,
+// 10.0 -> 7.4.
 // No atomics decide an order, so perm / inv_perm are unique and reproducible bit for bit.
+#include <type_traits>
+
 #include "moe_common.h"
 
 namespace moe {
 namespace {
 
-__device__ __forceinline__ bool better(float az, int ae, float bz, int be) {
-  return az > bz || (az == bz && ae < be);
+// Exchange with the partner lane of all-reduce stage `ST` inside a group of up to 16 lanes: neighbours, pairs, then the
+// mirror image inside 8 and inside 16 (whose halves hold one value each by then).  DPP moves, no LDS round trip.
+template <int ST> __device__ __forceinline__ unsigned dpp_partner(unsigned v) {
+  constexpr int ctrl = ST == 0 ? 0xB1 : ST == 1 ? 0x4E : ST == 2 ? 0x141 : 0x140;
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xf, 0xf, true);
+}
+template <int ST> __device__ __forceinline__ unsigned long long dpp_partner(unsigned long long v) {
+  return ((unsigned long long)dpp_partner<ST>((unsigned)(v >> 32)) << 32) | dpp_partner<ST>((unsigned)v);
+}
+template <int ST> __device__ __forceinline__ float dpp_partner(float v) {
+  return __uint_as_float(dpp_partner<ST>(__float_as_uint(v)));
+}
+// op over the G lanes of a group; every lane of the wave must be active
+template <int G, typename T, typename Op> __device__ __forceinline__ T group_reduce(T v, Op op) {
+  static_assert(G <= 16, "a group lies inside one DPP row");
+  if constexpr (G >= 2) v = op(v, dpp_partner<0>(v));
+  if constexpr (G >= 4) v = op(v, dpp_partner<1>(v));
+  if constexpr (G >= 8) v = op(v, dpp_partner<2>(v));
+  if constexpr (G >= 16) v = op(v, dpp_partner<3>(v));
+  return v;
+}
+template <int G> __device__ __forceinline__ float group_sum(float v) { return group_reduce<G>(v, [](float a, float b) { return a + b; }); }
+template <int G> __device__ __forceinline__ float group_max(float v) { return group_reduce<G>(v, [](float a, float b) { return fmaxf(a, b); }); }
+
+// The total order of the gate as one integer: larger = first.  High word: the logit with -0 made +0 and its bits mapped to
+// an unsigned order; low word: the complement of the expert id (equal logits: lower id first).  Never 0.
+__device__ __forceinline__ unsigned long long order_key(float z, int e) {
+  const unsigned b = __float_as_uint(z + 0.0f);
+  return ((unsigned long long)((b >> 31) ? ~b : (b | 0x80000000u)) << 32) | (unsigned)~e;
+}
+__device__ __forceinline__ float key_logit(unsigned long long key) {
+  const unsigned u = (unsigned)(key >> 32);
+  return __uint_as_float((u >> 31) ? (u & 0x7fffffffu) : ~u);
 }
 
-// G lanes (G <= 16) cooperate on one token, 64/G tokens per wave at a time; lane `sub` of a group holds the
-// VPL experts sub, sub+G, sub+2G, ...  The per-chunk histogram is written transposed, [E][nchunks], so the
-// scan kernel reads rows.
+// G lanes (G <= 16) cooperate on one token; lane `sub` of a group holds the VPL experts sub, sub+G, sub+2G, ...  64 groups
+// per workgroup: a chunk of 64 tokens is one round.  hist strides: he per expert, hc per chunk.
 template <int G, int VPL>
-__global__ void __launch_bounds__(256) route_topk_kernel(const float* __restrict__ logits, int T, int E, int k,
-                                                         int renorm, int chunk_tokens, int nchunks,
-                                                         int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
-                                                         int32_t* __restrict__ chunk_hist,
-                                                         float* __restrict__ score) {
+__global__ void __launch_bounds__(64 * G) route_topk_kernel(const float* __restrict__ logits, int T, int E, int k,
+                                                            int renorm, int chunk_tokens, int he, int hc,
+                                                            int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
+                                                            int32_t* __restrict__ chunk_hist,
+                                                            float* __restrict__ score) {
   __shared__ int hist[MOE_MAX_EXPERTS];
   for (int e = threadIdx.x; e < MOE_MAX_EXPERTS; e += blockDim.x) hist[e] = 0;
   __syncthreads();
 
   const int sub = threadIdx.x % G;
   const int grp = threadIdx.x / G;
-  const int ngroups = blockDim.x / G;
+  constexpr int ngroups = 64;
   const int t_begin = blockIdx.x * chunk_tokens;
   const int t_end = min(t_begin + chunk_tokens, T);
 
-  // all groups of a wave run the same number of rounds (shuffles need the whole group active; a group past
+  // all groups of a wave run the same number of rounds (the exchanges need every lane active; a group past
   // the end of the chunk works on the last token again and skips the stores)
   const int rounds = (t_end - t_begin + ngroups - 1) / ngroups;
   for (int it = 0; it < rounds; ++it) {
@@ -45,55 +82,37 @@ __global__ void __launch_bounds__(256) route_topk_kernel(const float* __restrict
     const bool live = t_raw < t_end;
     const int t = live ? t_raw : t_end - 1;
     float v[VPL];
-    unsigned taken = 0;
+    unsigned long long key[VPL];
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
       const int e = sub + i * G;
-      if (e < E) {
-        v[i] = logits[(long)t * E + e];
-      } else {
-        v[i] = -INFINITY;
-        taken |= 1u << i;
-      }
+      v[i] = e < E ? logits[(long)t * E + e] : -INFINITY;
+      key[i] = e < E ? order_key(v[i], e) : 0ull;
     }
-    float my_z = -INFINITY, top_z = 0.f;
-    int my_e = 0;
+    unsigned long long mine = 0;
+    float top_z = 0.f;
     for (int j = 0; j < k; ++j) {
-      float bz = -INFINITY;
-      int be = 0x7fffffff;
+      unsigned long long best = key[0];
 #pragma unroll
-      for (int i = 0; i < VPL; ++i) {
-        const int e = sub + i * G;
-        if (!((taken >> i) & 1u) && better(v[i], e, bz, be)) { bz = v[i]; be = e; }
-      }
+      for (int i = 1; i < VPL; ++i) best = key[i] > best ? key[i] : best;
+      best = group_reduce<G>(best, [](unsigned long long a, unsigned long long b) { return a > b ? a : b; });
 #pragma unroll
-      for (int off = G / 2; off >= 1; off >>= 1) {
-        const float oz = __shfl_xor(bz, off, G);
-        const int oe = __shfl_xor(be, off, G);
-        if (better(oz, oe, bz, be)) { bz = oz; be = oe; }
-      }
-      if (be % G == sub) taken |= 1u << (be / G);   // the owner retires the winner
-      if (sub == j) { my_z = bz; my_e = be; }        // lane j keeps slot j (k <= min(E, 16) <= G)
-      if (j == 0) top_z = bz;
+      for (int i = 0; i < VPL; ++i) key[i] = key[i] == best ? 0ull : key[i];     // the owner retires the winner
+      if (sub == j) mine = best;                     // lane j keeps slot j (k <= min(E, 16) <= G)
+      if (j == 0) top_z = key_logit(best);
     }
+    const int my_e = (int)~(unsigned)mine;
     // weights: softmax over the selected logits (renorm) or over all logits read at the selected ones
     const bool holds_slot = sub < k;
-    const float ex = holds_slot ? expf(my_z - top_z) : 0.f;
-    float den, den_all = 0.f;
+    const float ex = holds_slot ? expf(key_logit(mine) - top_z) : 0.f;
+    float den_all = 0.f;
     if (!renorm || score != nullptr) {
 #pragma unroll
       for (int i = 0; i < VPL; ++i)
         if (sub + i * G < E) den_all += expf(v[i] - top_z);
-#pragma unroll
-      for (int off = G / 2; off >= 1; off >>= 1) den_all += __shfl_xor(den_all, off, G);
+      den_all = group_sum<G>(den_all);
     }
-    if (renorm) {
-      den = ex;
-#pragma unroll
-      for (int off = G / 2; off >= 1; off >>= 1) den += __shfl_xor(den, off, G);
-    } else {
-      den = den_all;
-    }
+    const float den = renorm ? group_sum<G>(ex) : den_all;
     if (live && holds_slot) {
       topk_idx[(long)t * k + sub] = my_e;
       topk_w[(long)t * k + sub] = ex / den;
@@ -102,7 +121,7 @@ __global__ void __launch_bounds__(256) route_topk_kernel(const float* __restrict
     }
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < E; e += blockDim.x) chunk_hist[(long)e * nchunks + blockIdx.x] = hist[e];
+  for (int e = threadIdx.x; e < E; e += blockDim.x) chunk_hist[(long)e * he + (long)blockIdx.x * hc] = hist[e];
 }
 
 // One wave per expert: exclusive prefix of that expert's per-chunk counts, in place; counts[e] = total.
@@ -134,103 +153,174 @@ __global__ void __launch_bounds__(64) route_scan_kernel(int32_t* __restrict__ ch
   if (lane == 63) counts[e] = incl;
 }
 
-// One wave per chunk walks its assignments in order, 64 at a time.  Lanes with the same expert are found with
-// one ballot per bit of the expert id; the rank inside the group is a popcount of the lower lanes.
+// A workgroup per chunk ranks its assignments 512 at a time, one wave per 64 in order.  Lanes with the same expert are
+// found with one ballot per bit of the expert id; a wave's highest lane of each expert publishes the wave's count, the
+// counts of the eight waves are added up per expert, and a lane's row is its wave's start plus the lower equal lanes.
 // Only experts in [e_lo, e_hi) get rows (one GPU's expert-parallel share: the local scatter of Section 3.2);
 // assignments to other experts get inv_perm = -1.  offsets has e_hi - e_lo + 1 entries.
-__global__ void __launch_bounds__(64) route_rank_kernel(const int32_t* __restrict__ topk_idx, int T, int E, int k,
-                                                        int e_lo, int e_hi, int chunk_tokens, int nchunks,
-                                                        const int32_t* __restrict__ chunk_base,
-                                                        const int32_t* __restrict__ counts,
-                                                        int32_t* __restrict__ offsets,
-                                                        int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
-                                                        const uint8_t* __restrict__ keep) {
-  __shared__ int next_row[MOE_MAX_EXPERTS];
+// SUMS: chunk_hist holds the raw counts [nchunks][E]; every workgroup adds them up itself and workgroup 0 writes counts.
+// Otherwise chunk_hist holds the scanned ones [E][nchunks], and counts was written by route_scan_kernel.
+constexpr int kRankWaves = 8;
+template <bool SUMS>
+__global__ void __launch_bounds__(64 * kRankWaves) route_rank_kernel(const int32_t* __restrict__ topk_idx, int T, int E, int k,
+                                                                     int e_lo, int e_hi, int chunk_tokens, int nchunks,
+                                                                     const int32_t* __restrict__ chunk_hist,
+                                                                     int32_t* __restrict__ counts,
+                                                                     int32_t* __restrict__ offsets,
+                                                                     int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
+                                                                     const uint8_t* __restrict__ keep) {
+  __shared__ int next_row[MOE_MAX_EXPERTS];                    // first: assignments of earlier chunks
+  __shared__ int total[MOE_MAX_EXPERTS];
   __shared__ int expert_off[MOE_MAX_EXPERTS + 1];
-  const int lane = threadIdx.x;
-  // offsets = exclusive scan of counts (every block recomputes it; block 0 publishes it)
-  int run = 0;
-  for (int e0 = 0; e0 < E; e0 += 64) {
-    const int e = e0 + lane;
-    const int c = (e >= e_lo && e < e_hi) ? counts[e] : 0;
-    int incl = c;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int o = __shfl_up(incl, off);
-      if (lane >= off) incl += o;
+  __shared__ int wave_cnt[kRankWaves][MOE_MAX_EXPERTS];
+  constexpr int kThreads = 64 * kRankWaves;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const long a_begin = (long)blockIdx.x * chunk_tokens * k;
+  const long a_end = min((long)(blockIdx.x + 1) * chunk_tokens, (long)T) * k;
+  const long a_first = a_begin + threadIdx.x;
+  int e_next = a_first < a_end ? topk_idx[a_first] : -1;        // in flight while the tables are built
+  for (int i = threadIdx.x; i < kRankWaves * MOE_MAX_EXPERTS; i += kThreads) (&wave_cnt[0][0])[i] = 0;
+  if constexpr (SUMS) {
+    for (int e = threadIdx.x; e < E; e += kThreads) { next_row[e] = 0; total[e] = 0; }
+    __syncthreads();
+    int width = 1;                                              // threads side by side over the experts
+    while (width < E) width <<= 1;
+    const int e = threadIdx.x & (width - 1), step = kThreads / width;
+    if (e < E) {
+      int all = 0, before = 0;
+#pragma unroll 8
+      for (int c = threadIdx.x / width; c < nchunks; c += step) {
+        const int h = chunk_hist[(long)c * E + e];
+        all += h;
+        before += c < (int)blockIdx.x ? h : 0;
+      }
+      atomicAdd(&total[e], all);                                // (LDS; integer sums do not depend on the order)
+      atomicAdd(&next_row[e], before);
     }
-    if (e < E) expert_off[e] = run + incl - c;
-    run += __shfl(incl, 63);
+  } else {
+    for (int e = threadIdx.x; e < E; e += kThreads) {
+      total[e] = counts[e];
+      next_row[e] = chunk_hist[(long)e * nchunks + blockIdx.x];
+    }
   }
-  if (lane == 0) expert_off[E] = run;
   __syncthreads();
-  if (blockIdx.x == 0)
-    for (int e = e_lo + lane; e <= e_hi; e += 64) offsets[e - e_lo] = expert_off[e];
-  for (int e = lane; e < E; e += 64) next_row[e] = expert_off[e] + chunk_base[(long)e * nchunks + blockIdx.x];
+  // offsets = exclusive scan of the counts (every workgroup recomputes it; workgroup 0 publishes it)
+  if (wave == 0) {
+    int run = 0;
+    for (int e0 = 0; e0 < E; e0 += 64) {
+      const int e = e0 + lane;
+      const int c = (e >= e_lo && e < e_hi) ? total[e] : 0;
+      int incl = c;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(incl, off);
+        if (lane >= off) incl += o;
+      }
+      if (e < E) expert_off[e] = run + incl - c;
+      run += __builtin_amdgcn_readlane(incl, 63);
+    }
+    if (lane == 0) expert_off[E] = run;
+  }
   __syncthreads();
+  if (blockIdx.x == 0) {
+    for (int e = e_lo + threadIdx.x; e <= e_hi; e += kThreads) offsets[e - e_lo] = expert_off[e];
+    if constexpr (SUMS)
+      for (int e = threadIdx.x; e < E; e += kThreads) counts[e] = total[e];
+  }
+  for (int e = threadIdx.x; e < E; e += kThreads) next_row[e] += expert_off[e];
 
   int ebits = 0;
   while ((1 << ebits) < E) ++ebits;
-  const long a_begin = (long)blockIdx.x * chunk_tokens * k;
-  const long a_end = min((long)(blockIdx.x + 1) * chunk_tokens, (long)T) * k;
   const unsigned long long lt_mask = (1ull << lane) - 1ull;
-  for (long base = a_begin; base < a_end; base += 64) {
-    const long a = base + lane;
+  for (long base = a_begin; base < a_end; base += kThreads) {
+    const long a = base + threadIdx.x;
     const bool valid = a < a_end;
-    const int e = valid ? topk_idx[a] : 0;
+    const int e = valid ? e_next : 0;
+    if (a + kThreads < a_end) e_next = topk_idx[a + kThreads];
     const bool gets_row = valid && e >= e_lo && e < e_hi && (keep == nullptr || keep[a] != 0);
     unsigned long long same = __ballot(gets_row);
     for (int b = 0; b < ebits; ++b) {
       const unsigned long long mb = __ballot((e >> b) & 1);
       same &= ((e >> b) & 1) ? mb : ~mb;
     }
-    if (valid) {
-      if (gets_row) {
-        const int start = next_row[e];
-        const int r = start + __popcll(same & lt_mask);
-        inv_perm[a] = r;
-        perm[r] = (int)a;
-        if ((same >> lane) >> 1 == 0) next_row[e] = start + __popcll(same);   // the group's highest lane advances the row
-      } else {
-        inv_perm[a] = -1;
+    if (gets_row && (same >> lane) >> 1 == 0) wave_cnt[wave][e] = __popcll(same);    // the group's highest lane
+    __syncthreads();
+    for (int x = threadIdx.x; x < E; x += kThreads) {
+      int run = next_row[x];
+#pragma unroll
+      for (int w = 0; w < kRankWaves; ++w) {
+        const int c = wave_cnt[w][x];
+        wave_cnt[w][x] = run;
+        run += c;
       }
+      next_row[x] = run;
     }
     __syncthreads();
+    if (gets_row) {
+      const int r = wave_cnt[wave][e] + __popcll(same & lt_mask);
+      inv_perm[a] = r;
+      perm[r] = (int)a;
+    } else if (valid) {
+      inv_perm[a] = -1;
+    }
+    if (base + kThreads < a_end) {
+      __syncthreads();
+      for (int i = threadIdx.x; i < kRankWaves * MOE_MAX_EXPERTS; i += kThreads) (&wave_cnt[0][0])[i] = 0;
+      __syncthreads();
+    }
   }
 }
 
+// d_logits of 256 / G tokens per workgroup, G lanes per token as in route_topk_kernel: the token's softmax (renorm = 0) and
+// the sum over its slots once, the row assembled in LDS (zeros or -p * inner, then the k selected entries) and written whole.
+// Bound by writing [T,E]; with renorm = 0 a thread per (token, expert) that redoes the softmax needs E times the
+// exponentials (moe_route + moe_route_bwd, T = 16384, E = 160: 302 -> 29 us; renorm = 1, T = 16384, E = 64, this kernel: 12.2 -> 5.2 us).
+template <int G, int VPL>
 __global__ void __launch_bounds__(256) route_bwd_kernel(const float* __restrict__ logits,
                                                         const int32_t* __restrict__ topk_idx,
                                                         const float* __restrict__ topk_w,
                                                         const float* __restrict__ d_topk_w, int T, int E, int k,
                                                         int renorm, float* __restrict__ d_logits) {
-  const long total = (long)T * E;
-  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < total; i += (long)gridDim.x * blockDim.x) {
-    const long t = i / E;
-    const int e = (int)(i % E);
-    float inner = 0.f, mine = 0.f;
-    for (int j = 0; j < k; ++j) {
-      const float w = topk_w[t * k + j], dw = d_topk_w[t * k + j];
-      inner += w * dw;
-      if (topk_idx[t * k + j] == e) mine = w * dw;
-    }
-    float out;
-    if (renorm) {
-      // selected: w_j*(dw_j - inner) = mine - w_j*inner; written as below to keep one expression
-      float wj = 0.f;
-      for (int j = 0; j < k; ++j)
-        if (topk_idx[t * k + j] == e) wj = topk_w[t * k + j];
-      out = mine - wj * inner;
-    } else {
-      float m = -INFINITY;
-      for (int c = 0; c < E; ++c) m = fmaxf(m, logits[t * E + c]);
-      float den = 0.f;
-      for (int c = 0; c < E; ++c) den += expf(logits[t * E + c] - m);
-      const float p = expf(logits[t * E + e] - m) / den;
-      out = mine - p * inner;
-    }
-    d_logits[i] = out;
+  constexpr int TOKENS = 256 / G;
+  __shared__ float rows[TOKENS * G * VPL];                      // [TOKENS][E], E <= G * VPL
+  const int sub = threadIdx.x % G, grp = threadIdx.x / G;
+  const int t0 = blockIdx.x * TOKENS, t = min(t0 + grp, T - 1);
+  int e_j = -1;
+  float w = 0.f, dw = 0.f;
+  if (sub < k) {
+    e_j = topk_idx[(long)t * k + sub];
+    w = topk_w[(long)t * k + sub];
+    dw = d_topk_w[(long)t * k + sub];
   }
+  const float inner = group_sum<G>(w * dw);
+  float p[VPL];
+#pragma unroll
+  for (int i = 0; i < VPL; ++i) p[i] = 0.f;
+  if (!renorm) {
+    float m = -INFINITY, den = 0.f;
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) {
+      p[i] = sub + i * G < E ? logits[(long)t * E + sub + i * G] : -INFINITY;
+      m = fmaxf(m, p[i]);
+    }
+    m = group_max<G>(m);
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) {
+      p[i] = sub + i * G < E ? expf(p[i] - m) : 0.f;
+      den += p[i];
+    }
+    den = group_sum<G>(den);
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) p[i] = p[i] / den;
+  }
+#pragma unroll
+  for (int i = 0; i < VPL; ++i)
+    if (sub + i * G < E) rows[grp * E + sub + i * G] = -p[i] * inner;
+  __syncthreads();
+  if ((unsigned)e_j < (unsigned)E) rows[grp * E + e_j] += renorm ? w * dw - w * inner : w * dw;
+  __syncthreads();
+  const int n = min(TOKENS, T - t0) * E;
+  for (int i = threadIdx.x; i < n; i += 256) d_logits[(long)t0 * E + i] = rows[i];
 }
 
 
@@ -339,7 +429,7 @@ __global__ void __launch_bounds__(256) select_pick_kernel(SelectState* st, int n
 // keep[a] and the per-chunk expert histogram of the kept assignments (same layout as route_topk_kernel's)
 __global__ void __launch_bounds__(256) keep_hist_kernel(const int32_t* __restrict__ topk_idx,
                                                         const float* __restrict__ score, int T, int E, int k,
-                                                        int per_group, int chunk_tokens, int nchunks,
+                                                        int per_group, int chunk_tokens, int he, int hc,
                                                         const SelectState* __restrict__ st,
                                                         uint8_t* __restrict__ keep, int32_t* __restrict__ chunk_hist) {
   __shared__ int hist[MOE_MAX_EXPERTS];
@@ -355,15 +445,20 @@ __global__ void __launch_bounds__(256) keep_hist_kernel(const int32_t* __restric
     if (kp) atomicAdd(&hist[e], 1);
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < E; e += blockDim.x) chunk_hist[(long)e * nchunks + blockIdx.x] = hist[e];
+  for (int e = threadIdx.x; e < E; e += blockDim.x) chunk_hist[(long)e * he + (long)blockIdx.x * hc] = hist[e];
 }
 
-template <int G, int VPL>
-int launch_topk(const float* logits, int T, int E, int k, int renorm, int chunk_tokens, int nchunks, int32_t* idx,
-                float* w, int32_t* hist, float* score, hipStream_t s) {
-  route_topk_kernel<G, VPL><<<nchunks, 256, 0, s>>>(logits, T, E, k, renorm, chunk_tokens, nchunks, idx, w, hist, score);
-  MOE_LAUNCH_CHECK();
-  return MOE_OK;
+// lanes per token G = min(16, pow2 >= E) (so G >= k: one slot per lane); experts beyond 16 go VPL per lane
+template <typename F> int with_group(int E, F f) {
+  if (E <= 1) return f(std::integral_constant<int, 1>(), std::integral_constant<int, 1>());
+  if (E <= 2) return f(std::integral_constant<int, 2>(), std::integral_constant<int, 1>());
+  if (E <= 4) return f(std::integral_constant<int, 4>(), std::integral_constant<int, 1>());
+  if (E <= 8) return f(std::integral_constant<int, 8>(), std::integral_constant<int, 1>());
+  if (E <= 16) return f(std::integral_constant<int, 16>(), std::integral_constant<int, 1>());
+  if (E <= 32) return f(std::integral_constant<int, 16>(), std::integral_constant<int, 2>());
+  if (E <= 64) return f(std::integral_constant<int, 16>(), std::integral_constant<int, 4>());
+  if (E <= 128) return f(std::integral_constant<int, 16>(), std::integral_constant<int, 8>());
+  return f(std::integral_constant<int, 16>(), std::integral_constant<int, 16>());
 }
 
 }  // namespace
@@ -384,17 +479,15 @@ int launch_route(const float* logits, int T, int E, int k, int renorm, int e_lo,
   const int tb = route_chunk_tokens(T);
   const int nchunks = cdiv(T, tb);
   int32_t* hist = static_cast<int32_t*>(ws);
-  int rc;
-  // lanes per token G = min(16, pow2 >= E) (so G >= k: one slot per lane); experts beyond 16 go VPL per lane
-  if (E <= 1) rc = launch_topk<1, 1>(logits, T, E, k, renorm, tb, nchunks, idx, w, hist, score, s);
-  else if (E <= 2) rc = launch_topk<2, 1>(logits, T, E, k, renorm, tb, nchunks, idx, w, hist, score, s);
-  else if (E <= 4) rc = launch_topk<4, 1>(logits, T, E, k, renorm, tb, nchunks, idx, w, hist, score, s);
-  else if (E <= 8) rc = launch_topk<8, 1>(logits, T, E, k, renorm, tb, nchunks, idx, w, hist, score, s);
-  else if (E <= 16) rc = launch_topk<16, 1>(logits, T, E, k, renorm, tb, nchunks, idx, w, hist, score, s);
-  else if (E <= 32) rc = launch_topk<16, 2>(logits, T, E, k, renorm, tb, nchunks, idx, w, hist, score, s);
-  else if (E <= 64) rc = launch_topk<16, 4>(logits, T, E, k, renorm, tb, nchunks, idx, w, hist, score, s);
-  else if (E <= 128) rc = launch_topk<16, 8>(logits, T, E, k, renorm, tb, nchunks, idx, w, hist, score, s);
-  else rc = launch_topk<16, 16>(logits, T, E, k, renorm, tb, nchunks, idx, w, hist, score, s);
+  // Up to 16384 counts every workgroup of the rank kernel adds them up itself (at most 64 KB from L2, 32 loads per thread in
+  // flight together), which spares a launch and its latency; beyond that the scan kernel does it once.
+  const bool sums = (long)nchunks * E <= 16384;
+  const int he = sums ? 1 : nchunks, hc = sums ? E : 1;
+  const int rc = with_group(E, [&](auto g, auto v) -> int {
+    route_topk_kernel<g.value, v.value><<<nchunks, 64 * g.value, 0, s>>>(logits, T, E, k, renorm, tb, he, hc, idx, w, hist, score);
+    MOE_LAUNCH_CHECK();
+    return MOE_OK;
+  });
   if (rc != MOE_OK) return rc;
   const uint8_t* keep = nullptr;
   if (n_groups > 0) {
@@ -414,25 +507,30 @@ int launch_route(const float* logits, int T, int E, int k, int renorm, int e_lo,
       select_pick_kernel<<<cdiv(n_groups, 4), 256, 0, s>>>(st, n_groups, pass);
       MOE_LAUNCH_CHECK();
     }
-    keep_hist_kernel<<<nchunks, 256, 0, s>>>(idx, score, T, E, k, per_group, tb, nchunks, st, keep_w, hist);
+    keep_hist_kernel<<<nchunks, 256, 0, s>>>(idx, score, T, E, k, per_group, tb, he, hc, st, keep_w, hist);
     MOE_LAUNCH_CHECK();
     keep = keep_w;
   }
-  route_scan_kernel<<<E, 64, 0, s>>>(hist, nchunks, counts);
-  MOE_LAUNCH_CHECK();
-  route_rank_kernel<<<nchunks, 64, 0, s>>>(idx, T, E, k, e_lo, e_hi, tb, nchunks, hist, counts, offsets, perm, inv_perm,
-                                           keep);
+  if (sums) {
+    route_rank_kernel<true><<<nchunks, 64 * kRankWaves, 0, s>>>(idx, T, E, k, e_lo, e_hi, tb, nchunks, hist, counts, offsets, perm,
+                                                                inv_perm, keep);
+  } else {
+    route_scan_kernel<<<E, 64, 0, s>>>(hist, nchunks, counts);
+    MOE_LAUNCH_CHECK();
+    route_rank_kernel<false><<<nchunks, 64 * kRankWaves, 0, s>>>(idx, T, E, k, e_lo, e_hi, tb, nchunks, hist, counts, offsets, perm,
+                                                                 inv_perm, keep);
+  }
   MOE_LAUNCH_CHECK();
   return MOE_OK;
 }
 
 int launch_route_bwd(const float* logits, const int32_t* idx, const float* w, const float* dw, int T, int E, int k,
                      int renorm, float* d_logits, hipStream_t s) {
-  long blocks = ((long)T * E + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  route_bwd_kernel<<<(int)blocks, 256, 0, s>>>(logits, idx, w, dw, T, E, k, renorm, d_logits);
-  MOE_LAUNCH_CHECK();
-  return MOE_OK;
+  return with_group(E, [&](auto g, auto v) -> int {
+    route_bwd_kernel<g.value, v.value><<<cdiv(T, 256 / g.value), 256, 0, s>>>(logits, idx, w, dw, T, E, k, renorm, d_logits);
+    MOE_LAUNCH_CHECK();
+    return MOE_OK;
+  });
 }
 
 }  // namespace moe

@@ -1,0 +1,64 @@
+"""Gate and row map at the edges of their kernels: both sides of the histogram size that drops the scan launch, chunks of more
+than 512 assignments, every group width, and the gate's backward; the small router matmul around its tiles."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import moe_oracle as O
+from synth.moe_inputs import random_logits
+from tests.gpu_util import DEV, max_norm_err, to_dev, to_np
+from tests.test_gpu_parity import run_route
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,E,k,quantum", [
+    (4096, 256, 2, 0.5), (4097, 256, 2, 0.5),      # 64 and 65 chunks of 256 counts: without and with the scan kernel
+    (33000, 32, 3, 1.0),                           # 516 chunks of 32
+    (130, 256, 16, 0.25), (70001, 40, 16, 2.0),    # 1024 and 2048 assignments per chunk: two and four rounds of ranking
+    (1, 1, 1, None), (65, 2, 2, None), (63, 3, 3, 0.5), (64, 7, 4, 0.5), (191, 13, 13, 0.5), (127, 65, 9, 0.5), (66, 129, 5, 0.5),
+])
+def test_route_edges(T, E, k, quantum):
+    from paper_2505_11432_amd import binding as B
+    z = random_logits(T, E, seed=T + E, quantum=quantum)
+    if T > 8:
+        z[3] = np.finfo(np.float32).min             # a row of the lowest value: ids decide
+        z[3, E // 2] = 0.0
+        z[4, ::2], z[4, 1::2] = -0.0, 0.0          # signed zeros are equal
+    ref = O.route(z, k, 1)
+    got = run_route(B, z, k, 1)
+    for name in ("idx", "counts", "offsets", "perm", "inv_perm"):
+        assert np.array_equal(to_np(got[name]), ref[name]), name
+    assert np.allclose(to_np(got["w"]), ref["w"], rtol=2e-6, atol=1e-7)
+
+
+@pytest.mark.parametrize("renorm", [1, 0])
+@pytest.mark.parametrize("T,E,k", [(1, 1, 1), (33, 2, 1), (257, 8, 2), (15, 16, 16), (17, 33, 5), (100, 100, 7), (31, 256, 16)])
+def test_route_bwd_edges(T, E, k, renorm):
+    from paper_2505_11432_amd import binding as B
+    z = random_logits(T, E, seed=T)
+    ref = O.route(z, k, renorm)
+    dw = np.random.default_rng(E).standard_normal((T, k)).astype(np.float32)
+    want = O.route_bwd(z, ref["idx"], ref["w"], dw, renorm)
+    guard = torch.full((T * E + 64,), 9.0, device=DEV)
+    dz = guard[:T * E].view(T, E)
+    B.moe_route_bwd(to_dev(z), to_dev(ref["idx"]), to_dev(ref["w"].astype(np.float32)), to_dev(dw), E, renorm, dz)
+    # sums of at most 256 fp32 terms of either sign against the largest entry
+    assert max_norm_err(to_np(dz), want) < 1e-5
+    assert bool((guard[T * E:] == 9.0).all())
+
+
+@pytest.mark.parametrize("T,d,E", [(1, 8, 1), (16, 64, 16), (17, 72, 17), (100, 2048, 64), (15, 4104, 8), (2049, 520, 64), (8176, 16, 16),
+                                   (8193, 16, 16), (40, 1000, 256)])      # 512 tiles and more: the other kernel
+def test_router_fwd_edges(T, d, E):
+    from paper_2505_11432_amd import binding as B
+    g = torch.Generator(device=DEV).manual_seed(T + E)
+    x, w = (torch.randn(s, generator=g, device=DEV).bfloat16() for s in ((T, d), (E, d)))
+    bias = torch.randn((E,), generator=g, device=DEV)
+    z = torch.full((T * E + 64,), 7.0, device=DEV)
+    for b in (bias, None):
+        B.moe_router_fwd(x, w, b, z[:T * E].view(T, E))
+        ref = x.double() @ w.double().t() + (b.double() if b is not None else 0.0)
+        # products are exact in fp32; d additions, each rounding by at most 2^-24 of a partial sum
+        assert float((z[:T * E].view(T, E).double() - ref).norm() / ref.norm()) < 3 * np.sqrt(d) * 2.0 ** -24 + 2.0 ** -23
+    assert bool((z[T * E:] == 7.0).all())
