@@ -13,6 +13,7 @@ namespace {
 
 constexpr float kE4M3Max = 448.0f;
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float clamp448(float p) { return fminf(fmaxf(p, -kE4M3Max), kE4M3Max); }
 
@@ -21,6 +22,18 @@ __device__ __forceinline__ unsigned pack4_e4m3(float a, float b, float c, float 
   int w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(a), clamp448(b), 0, false);
   w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(c), clamp448(d), w, true);
   return (unsigned)w;
+}
+
+// The codes of one 16-byte vector of T: V bytes, V-byte aligned, one store.
+template <typename T> __device__ __forceinline__ void store_codes(const Vec16<T>& v, float inv, uint8_t* dst) {
+  constexpr int V = 16 / sizeof(T);
+  unsigned out[V / 4];
+#pragma unroll
+  for (int i = 0; i < V / 4; ++i)
+    out[i] = pack4_e4m3(to_f32(v.v[4 * i]) * inv, to_f32(v.v[4 * i + 1]) * inv, to_f32(v.v[4 * i + 2]) * inv,
+                        to_f32(v.v[4 * i + 3]) * inv);
+  if constexpr (V == 8) { const u32x2 o = {out[0], out[1]}; __builtin_nontemporal_store(o, reinterpret_cast<u32x2*>(dst)); }
+  else __builtin_nontemporal_store(out[0], reinterpret_cast<unsigned*>(dst));
 }
 
 template <int THREADS>
@@ -73,17 +86,7 @@ __global__ void __launch_bounds__(THREADS) quant_rows_kernel(const T* __restrict
     amax = block_max<THREADS>(amax, red);
     const float inv = amax > 0.f ? kE4M3Max / amax : 1.0f;
     if (threadIdx.x == 0) scales[r] = amax > 0.f ? amax / kE4M3Max : 1.0f;
-    auto convert = [&](const Vec16<T>& v, int c) {
-      unsigned out[V / 4];
-#pragma unroll
-      for (int i = 0; i < V / 4; ++i)
-        out[i] = pack4_e4m3(to_f32(v.v[4 * i]) * inv, to_f32(v.v[4 * i + 1]) * inv, to_f32(v.v[4 * i + 2]) * inv,
-                            to_f32(v.v[4 * i + 3]) * inv);
-      uint8_t* dst = codes + (long)r * cols + (long)c * V;           // V bytes, V-byte aligned: one store
-      typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-      if constexpr (V == 8) { const u32x2 o = {out[0], out[1]}; __builtin_nontemporal_store(o, reinterpret_cast<u32x2*>(dst)); }
-      else __builtin_nontemporal_store(out[0], reinterpret_cast<unsigned*>(dst));
-    };
+    auto convert = [&](const Vec16<T>& v, int c) { store_codes(v, inv, codes + (long)r * cols + (long)c * V); };
     if (in_regs) {
 #pragma unroll
       for (int h = 0; h < kHold; ++h) {
@@ -103,52 +106,96 @@ __global__ void __launch_bounds__(THREADS) quant_rows_kernel(const T* __restrict
   }
 }
 
-// One block per (128-row group, 64-column slab): thread (rg, cq) holds rows rg, rg+16, ... (8 rows) of the four
-// columns 4*cq..4*cq+3 in registers; the column maxima are combined through LDS.
+// One wave per row, for rows of at most 64 x kHold vectors: no barrier, and four rows per block in flight.  Holding eight
+// vectors per thread of a 256-thread block for rows that fill two of them cost six more loads per thread: rows of 4096
+// bf16 columns, 8192 of them, 22.8 -> 18.0 us.
+template <typename T, int kHold>
+__global__ void __launch_bounds__(256) quant_rows_wave_kernel(const T* __restrict__ src, int rows, int cols,
+                                                              uint8_t* __restrict__ codes, float* __restrict__ scales) {
+  constexpr int V = 16 / sizeof(T);
+  const int lane = threadIdx.x & 63, nvec = cols / V;
+  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= rows) return;
+  const T* row = src + (long)r * cols;
+  u32x4 raw[kHold];
+#pragma unroll
+  for (int h = 0; h < kHold; ++h)      // vectors past the row's end re-read its last one (same maximum, never stored)
+    raw[h] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(row + (long)min(lane + h * 64, nvec - 1) * V));
+  float amax = 0.f;
+#pragma unroll
+  for (int h = 0; h < kHold; ++h) {
+    const Vec16<T> v = __builtin_bit_cast(Vec16<T>, raw[h]);
+#pragma unroll
+    for (int i = 0; i < V; ++i) amax = fmaxf(amax, fabsf(to_f32(v.v[i])));
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+  const float inv = amax > 0.f ? kE4M3Max / amax : 1.0f;
+  if (lane == 0) scales[r] = amax > 0.f ? amax / kE4M3Max : 1.0f;
+#pragma unroll
+  for (int h = 0; h < kHold; ++h) {
+    asm volatile("" : "+v"(raw[h]));            // the raw vectors are what lives on, not their fp32 values
+    const int c = lane + h * 64;
+    if (c < nvec) store_codes(__builtin_bit_cast(Vec16<T>, raw[h]), inv, codes + (long)r * cols + (long)c * V);
+  }
+}
+
+// One block per (128-row group, 128-column slab): thread (rg, cq) holds rows rg, rg+16, ... (8 rows) of the eight columns
+// 8*cq .. 8*cq+7, 16 bytes (fp32: two times 16) per row with all loads in flight together; the column maxima are combined
+// through LDS.  (Four columns per thread, read one by one: 8192 x 4096 bf16 30 us; now 23.)
 template <typename T>
 __global__ void __launch_bounds__(256) quant_colgroup_kernel(const T* __restrict__ src, int rows, int cols,
                                                              uint8_t* __restrict__ codes,
                                                              float* __restrict__ scales, int slabs) {
-  __shared__ float cmax[16][64];
+  __shared__ float cmax[16][128];
   const int g = blockIdx.x / slabs;
   const int cq = threadIdx.x % 16, rg = threadIdx.x / 16;
-  const int c = (blockIdx.x % slabs) * 64 + cq * 4;
+  const int c = (blockIdx.x % slabs) * 128 + cq * 8;
   const int r0 = g * 128;
-  const bool col_ok = c < cols;
-  float v[8][4];
-  float amax[4] = {0.f, 0.f, 0.f, 0.f};
+  const bool col_ok = c < cols;                     // cols is a multiple of 16: all eight columns or none
+  constexpr int V = 16 / sizeof(T), L = 8 / V;      // loads per row
+  u32x4 raw[8][L];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int r = r0 + rg + 16 * i;
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[i][j] = 0.f;
-    if (col_ok && r < rows) {
-      const T* p = src + (long)r * cols + c;
+    for (int l = 0; l < L; ++l)
+      raw[i][l] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + (long)min(r0 + rg + 16 * i, rows - 1) * cols + min(c, cols - 8) + l * V));
+  float v[8][8];
+  float amax[8];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        v[i][j] = to_f32(p[j]);
-        amax[j] = fmaxf(amax[j], fabsf(v[i][j]));
+  for (int j = 0; j < 8; ++j) amax[j] = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+      const Vec16<T> w = __builtin_bit_cast(Vec16<T>, raw[i][l]);
+      // rows past the end repeat the last row: the same column maxima, never stored
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        v[i][l * V + j] = to_f32(w.v[j]);
+        amax[l * V + j] = fmaxf(amax[l * V + j], fabsf(v[i][l * V + j]));
       }
     }
-  }
 #pragma unroll
-  for (int j = 0; j < 4; ++j) cmax[rg][cq * 4 + j] = amax[j];
+  for (int j = 0; j < 8; ++j) cmax[rg][cq * 8 + j] = amax[j];
   __syncthreads();
-  float inv[4];
+  float inv[8];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < 8; ++j) {
     float m = 0.f;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) m = fmaxf(m, cmax[q][cq * 4 + j]);
+    for (int q = 0; q < 16; ++q) m = fmaxf(m, cmax[q][cq * 8 + j]);
     inv[j] = m > 0.f ? kE4M3Max / m : 1.0f;
     if (rg == 0 && col_ok) scales[(long)g * cols + c + j] = m > 0.f ? m / kE4M3Max : 1.0f;
   }
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int r = r0 + rg + 16 * i;
-    if (col_ok && r < rows)
-      *reinterpret_cast<unsigned*>(codes + (long)r * cols + c) =
-          pack4_e4m3(v[i][0] * inv[0], v[i][1] * inv[1], v[i][2] * inv[2], v[i][3] * inv[3]);
+    if (col_ok && r < rows) {
+      const u32x2 o = {pack4_e4m3(v[i][0] * inv[0], v[i][1] * inv[1], v[i][2] * inv[2], v[i][3] * inv[3]),
+                       pack4_e4m3(v[i][4] * inv[4], v[i][5] * inv[5], v[i][6] * inv[6], v[i][7] * inv[7])};
+      *reinterpret_cast<u32x2*>(codes + (long)r * cols + c) = o;
+    }
   }
 }
 
@@ -178,9 +225,10 @@ __global__ void tgroup_offsets_kernel(const int32_t* __restrict__ offsets, int E
 // (rows 8*rgrp .. 8*rgrp+7) of eight consecutive channels: a wave's load touches four rows with 16 bytes per lane,
 // and a channel's eight codes of those tokens are eight consecutive bytes of the transposed output, written to the
 // LDS tile as one 8-byte word (16-byte chunks of a tile row are XOR-swizzled by the channel octet, so the sixteen
-// threads of a row group do not meet in one bank).  Channel maxima are reduced over the wave's four row groups with
-// shuffles and over the four waves through LDS.  Global memory sees 16-byte lanes forming 128-byte rows (one channel
-// x 128 tokens).
+// threads of a row group do not meet in one bank).  The eight loads of a thread are issued together, past the
+// segment's end too (a branch around each made them wait for one another: 16384 x 28672 bf16 309 -> 287 us, 16384 x
+// 14336 codes 133 -> 100).  Channel maxima are reduced over the wave's four row groups with shuffles and over the four
+// waves through LDS.  Global memory sees 16-byte lanes forming 128-byte rows (one channel x 128 tokens).
 template <typename T>
 __global__ void __launch_bounds__(256) quant_tgroup_kernel(const T* __restrict__ src,
                                                            const float* __restrict__ src_row_scale, int cols,
@@ -206,42 +254,50 @@ __global__ void __launch_bounds__(256) quant_tgroup_kernel(const T* __restrict__
   const int c0 = (blockIdx.x % slabs) * CH;
   const int c = c0 + cq * 8;
   const bool col_ok = c < cols;                     // cols is a multiple of 16: all eight channels or none
+  // every load is issued before the first value is used; rows past the segment's end re-read its last row and count as 0
+  constexpr int LB = 8 * (int)sizeof(T);            // bytes per row and thread
+  const char* col_base = reinterpret_cast<const char*>(src + min(c, cols - 8));
+  unsigned raw[8][LB / 4];
+  float rs[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = min(r0 + rgrp * 8 + i, r_end - 1);
+    const char* p = col_base + (long)r * cols * (int)sizeof(T);
+    if constexpr (LB == 8) {
+      const u32x2 w = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p));
+      raw[i][0] = w[0]; raw[i][1] = w[1];
+      rs[i] = src_row_scale[r];
+    } else {
+#pragma unroll
+      for (int l = 0; l < LB / 16; ++l) {
+        const u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p + 16 * l));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) raw[i][4 * l + q] = w[q];
+      }
+    }
+  }
   float v[8][8];
   float amax[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) amax[j] = 0.f;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const int r = r0 + rgrp * 8 + i;
+    const bool in = r0 + rgrp * 8 + i < r_end;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[i][j] = 0.f;
-    if (col_ok && r < r_end) {
-      const T* p = src + (long)r * cols + c;
-      if constexpr (sizeof(T) == 1) {
+    for (int j = 0; j < 8; ++j) {
+      float t;
+      if constexpr (LB == 8) {
         // e4m3 codes with one scale per source row: the value is code * scale, rounded once to fp32
-        const int2 w = *reinterpret_cast<const int2*>(p);
-        const float rs = src_row_scale[r];
-        v[i][0] = __builtin_amdgcn_cvt_f32_fp8(w.x, 0) * rs;
-        v[i][1] = __builtin_amdgcn_cvt_f32_fp8(w.x, 1) * rs;
-        v[i][2] = __builtin_amdgcn_cvt_f32_fp8(w.x, 2) * rs;
-        v[i][3] = __builtin_amdgcn_cvt_f32_fp8(w.x, 3) * rs;
-        v[i][4] = __builtin_amdgcn_cvt_f32_fp8(w.y, 0) * rs;
-        v[i][5] = __builtin_amdgcn_cvt_f32_fp8(w.y, 1) * rs;
-        v[i][6] = __builtin_amdgcn_cvt_f32_fp8(w.y, 2) * rs;
-        v[i][7] = __builtin_amdgcn_cvt_f32_fp8(w.y, 3) * rs;
-      } else if constexpr (sizeof(T) == 2) {
-        typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
-        const bf16x8v w = *reinterpret_cast<const bf16x8v*>(p);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[i][j] = static_cast<float>(w[j]);
+        const int w = (int)raw[i][j / 4];
+        t = (j % 4 == 0 ? __builtin_amdgcn_cvt_f32_fp8(w, 0) : j % 4 == 1 ? __builtin_amdgcn_cvt_f32_fp8(w, 1)
+             : j % 4 == 2 ? __builtin_amdgcn_cvt_f32_fp8(w, 2) : __builtin_amdgcn_cvt_f32_fp8(w, 3)) * rs[i];
+      } else if constexpr (LB == 16) {
+        t = __uint_as_float(j % 2 ? raw[i][j / 2] & 0xffff0000u : raw[i][j / 2] << 16);      // bf16 is the upper half of fp32
       } else {
-        const float4 a = *reinterpret_cast<const float4*>(p);
-        const float4 b = *reinterpret_cast<const float4*>(p + 4);
-        v[i][0] = a.x; v[i][1] = a.y; v[i][2] = a.z; v[i][3] = a.w;
-        v[i][4] = b.x; v[i][5] = b.y; v[i][6] = b.z; v[i][7] = b.w;
+        t = __uint_as_float(raw[i][j]);
       }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) amax[j] = fmaxf(amax[j], fabsf(v[i][j]));
+      v[i][j] = in ? t : 0.f;
+      amax[j] = fmaxf(amax[j], fabsf(v[i][j]));
     }
   }
 #pragma unroll
@@ -285,27 +341,56 @@ __global__ void __launch_bounds__(256) quant_tgroup_kernel(const T* __restrict__
   }
 }
 
-template <typename T>
+// A thread makes 16 bytes of output at a time (8 bf16 or 4 fp32 of a row: a wave's store is one run of 1 KiB), four such
+// pieces a block apart with all loads in flight together.  (Four codes per thread, an element-index division for each and
+// scalar stores: 8192 x 4096 to bf16 30 us; now 21, and 18 with
+// the scales of channel groups read as vectors, against 64 one by one.)
+enum ScaleRead { ROW_SCALE, GROUP_SCALES, GROUP_SCALES_VEC };     // VEC: the scales are 16-byte aligned
+template <typename T, ScaleRead SR>
 __global__ void __launch_bounds__(256) dequant_kernel(const uint8_t* __restrict__ codes,
-                                                      const float* __restrict__ scales, int rows, int cols, int mode,
+                                                      const float* __restrict__ scales, int rows, int cols,
                                                       T* __restrict__ dst) {
-  const long nquad = (long)rows * cols / 4;
-  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < nquad; i += (long)gridDim.x * blockDim.x) {
-    const long el = i * 4;
-    const int r = (int)(el / cols);
-    const int c = (int)(el % cols);
-    const int w = *reinterpret_cast<const int*>(codes + el);
-    float s[4];
-    if (mode == MOE_Q_ROW) {
-      s[0] = s[1] = s[2] = s[3] = scales[r];
-    } else {
-      const float* sp = scales + (long)(r / 128) * cols + c;
-      s[0] = sp[0]; s[1] = sp[1]; s[2] = sp[2]; s[3] = sp[3];
+  constexpr int P = 16 / sizeof(T), U = 4;
+  const int per_row = cols / P;
+  const long n = (long)rows * per_row;
+  for (long base = blockIdx.x * (256L * U) + threadIdx.x; base < n; base += (long)gridDim.x * (256 * U)) {
+    unsigned w[U][P / 4];
+    float s[U][P];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const long i = min(base + u * 256, n - 1);            // past the end: the last piece again, not stored
+      const int r = n <= 0x7fffffffL ? (int)((unsigned)i / (unsigned)per_row) : (int)(i / per_row);
+      const int c = (int)(i - (long)r * per_row) * P;
+      const uint8_t* src = codes + (long)r * cols + c;
+      if constexpr (P == 8) {
+        const u32x2 t = *reinterpret_cast<const u32x2*>(src);
+        w[u][0] = t[0]; w[u][1] = t[1];
+      } else {
+        w[u][0] = *reinterpret_cast<const unsigned*>(src);
+      }
+      const float* sp = SR == ROW_SCALE ? scales + r : scales + (long)(r / 128) * cols + c;
+#pragma unroll
+      for (int q = 0; q < P / 4; ++q) {
+        float4 t;
+        if constexpr (SR == GROUP_SCALES_VEC) t = *reinterpret_cast<const float4*>(sp + 4 * q);
+        else if constexpr (SR == GROUP_SCALES) t = make_float4(sp[4 * q], sp[4 * q + 1], sp[4 * q + 2], sp[4 * q + 3]);
+        else t = make_float4(sp[0], sp[0], sp[0], sp[0]);
+        s[u][4 * q] = t.x; s[u][4 * q + 1] = t.y; s[u][4 * q + 2] = t.z; s[u][4 * q + 3] = t.w;
+      }
     }
-    dst[el + 0] = from_f32<T>(__builtin_amdgcn_cvt_f32_fp8(w, 0) * s[0]);
-    dst[el + 1] = from_f32<T>(__builtin_amdgcn_cvt_f32_fp8(w, 1) * s[1]);
-    dst[el + 2] = from_f32<T>(__builtin_amdgcn_cvt_f32_fp8(w, 2) * s[2]);
-    dst[el + 3] = from_f32<T>(__builtin_amdgcn_cvt_f32_fp8(w, 3) * s[3]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (base + u * 256 >= n) break;
+      Vec16<T> o;
+#pragma unroll
+      for (int q = 0; q < P / 4; ++q) {
+        o.v[4 * q + 0] = from_f32<T>(__builtin_amdgcn_cvt_f32_fp8((int)w[u][q], 0) * s[u][4 * q + 0]);
+        o.v[4 * q + 1] = from_f32<T>(__builtin_amdgcn_cvt_f32_fp8((int)w[u][q], 1) * s[u][4 * q + 1]);
+        o.v[4 * q + 2] = from_f32<T>(__builtin_amdgcn_cvt_f32_fp8((int)w[u][q], 2) * s[u][4 * q + 2]);
+        o.v[4 * q + 3] = from_f32<T>(__builtin_amdgcn_cvt_f32_fp8((int)w[u][q], 3) * s[u][4 * q + 3]);
+      }
+      *reinterpret_cast<Vec16<T>*>(dst + (base + u * 256) * P) = o;
+    }
   }
 }
 
@@ -316,18 +401,26 @@ int launch_quant_fp8(const void* src, moe_dtype src_dt, int rows, int cols, moe_
   if (rows == 0 || cols == 0) return MOE_OK;
   if (mode == MOE_Q_ROW) {
     const int grid = rows < 256 * 16 ? rows : 256 * 16;
-    const bool wide = cols / (16 / (int)dtype_size(src_dt)) > 256 * 8;     // more vectors than 256 threads can hold
-    if (src_dt == MOE_F32) {
+    const int nvec = cols / (16 / (int)dtype_size(src_dt));
+    const bool wide = nvec > 256 * 8;                    // more vectors than 256 threads can hold
+    if (nvec <= 64 * 8) {
+      const int waves = cdiv(rows, 4);
+#define MOE_WAVE_ROWS(TT)                                                                                              \
+  if (nvec <= 64 * 2) quant_rows_wave_kernel<TT, 2><<<waves, 256, 0, s>>>((const TT*)src, rows, cols, codes, scales);  \
+  else if (nvec <= 64 * 4) quant_rows_wave_kernel<TT, 4><<<waves, 256, 0, s>>>((const TT*)src, rows, cols, codes, scales); \
+  else quant_rows_wave_kernel<TT, 8><<<waves, 256, 0, s>>>((const TT*)src, rows, cols, codes, scales);
+      if (src_dt == MOE_F32) { MOE_WAVE_ROWS(float) } else { MOE_WAVE_ROWS(bf16) }
+#undef MOE_WAVE_ROWS
+    } else if (src_dt == MOE_F32) {
       if (wide) quant_rows_kernel<float, 1024><<<grid, 1024, 0, s>>>((const float*)src, rows, cols, codes, scales);
       else quant_rows_kernel<float, 256><<<grid, 256, 0, s>>>((const float*)src, rows, cols, codes, scales);
     } else {
-      const int nvec = cols / 8;
       if (wide && nvec <= 256 * 16) quant_rows_kernel<bf16, 256, 16><<<rows < 256 * 64 ? rows : 256 * 64, 256, 0, s>>>((const bf16*)src, rows, cols, codes, scales);
       else if (wide) quant_rows_kernel<bf16, 1024><<<grid, 1024, 0, s>>>((const bf16*)src, rows, cols, codes, scales);
       else quant_rows_kernel<bf16, 256><<<grid, 256, 0, s>>>((const bf16*)src, rows, cols, codes, scales);
     }
   } else {
-    const int slabs = cdiv(cols, 64);
+    const int slabs = cdiv(cols, 128);
     const int grid = cdiv(rows, 128) * slabs;
     if (src_dt == MOE_F32) quant_colgroup_kernel<float><<<grid, 256, 0, s>>>((const float*)src, rows, cols, codes, scales, slabs);
     else quant_colgroup_kernel<bf16><<<grid, 256, 0, s>>>((const bf16*)src, rows, cols, codes, scales, slabs);
@@ -362,10 +455,17 @@ int launch_quant_tgroup(const void* src, const float* src_row_scale, moe_dtype s
 int launch_dequant_fp8(const uint8_t* codes, const float* scales, int rows, int cols, moe_qmode mode, void* dst,
                        moe_dtype dst_dt, hipStream_t s) {
   if (rows == 0 || cols == 0) return MOE_OK;
-  long blocks = ((long)rows * cols / 4 + 255) / 256;
-  if (blocks > 256 * 16) blocks = 256 * 16;
-  if (dst_dt == MOE_F32) dequant_kernel<float><<<(int)blocks, 256, 0, s>>>(codes, scales, rows, cols, (int)mode, (float*)dst);
-  else dequant_kernel<bf16><<<(int)blocks, 256, 0, s>>>(codes, scales, rows, cols, (int)mode, (bf16*)dst);
+  const long pieces = (long)rows * (cols / (16 / (int)dtype_size(dst_dt)));
+  long blocks = (pieces + 1023) / 1024;
+  if (blocks > 256 * 64) blocks = 256 * 64;
+#define MOE_DEQUANT(TT, SR) dequant_kernel<TT, SR><<<(int)blocks, 256, 0, s>>>(codes, scales, rows, cols, (TT*)dst)
+#define MOE_DEQUANT_SR(TT)                                            \
+  if (mode == MOE_Q_ROW) MOE_DEQUANT(TT, ROW_SCALE);                  \
+  else if (aligned16(scales)) MOE_DEQUANT(TT, GROUP_SCALES_VEC);      \
+  else MOE_DEQUANT(TT, GROUP_SCALES);
+  if (dst_dt == MOE_F32) { MOE_DEQUANT_SR(float) } else { MOE_DEQUANT_SR(bf16) }
+#undef MOE_DEQUANT_SR
+#undef MOE_DEQUANT
   MOE_LAUNCH_CHECK();
   return MOE_OK;
 }

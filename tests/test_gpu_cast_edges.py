@@ -1,0 +1,71 @@
+"""E4M3 cast at the edges of its kernels: codes, scales and decoded values equal to the oracle bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import moe_oracle as O
+from synth.moe_inputs import bf16_round
+from tests.gpu_util import DEV, to_dev, to_np, torch_dtype
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+# vectors per row at and past 2, 4 and 8 per lane of a wave (bf16: 1024, 2048, 4096 columns; fp32: half), a 16-column
+# tail, one row, a short last group of 128, a last block of pieces that is not full
+@pytest.mark.parametrize("rows,cols", [(1, 16), (5, 512), (127, 528), (128, 1024), (129, 1040), (3, 2048), (6, 2064),
+                                       (257, 4096), (2, 4112), (9, 16400)])
+def test_cast_edges(dtype, rows, cols):
+    from paper_2505_11432_amd import binding as B
+    rng = np.random.default_rng(rows * cols)
+    v = (rng.standard_normal((rows, cols)) * np.exp(rng.standard_normal((rows, 1)) * 3)).astype(np.float32)
+    v[0, :8] = 0.0
+    if rows > 2:
+        v[1] = 0.0                                # a row of zeros: scale 1
+        v[:, 9] = 0.0
+    if dtype == "bf16":
+        v = bf16_round(v)
+    t = to_dev(v, torch_dtype(dtype))
+    for mode, quant, dequant, shape in ((B.Q_ROW, O.quant_rows, O.dequant_rows, (rows,)),
+                                        (B.Q_COLGROUP128, O.quant_colgroup128, O.dequant_colgroup128, ((rows + 127) // 128, cols))):
+        codes = torch.full((rows + 1, cols), 9, dtype=torch.uint8, device=DEV)
+        scales = torch.full(shape, 9.0, device=DEV)
+        B.moe_quant_fp8(t, mode, codes[:rows], scales)
+        want_c, want_s = quant(v)
+        assert np.array_equal(to_np(codes[:rows]), want_c) and np.array_equal(to_np(scales).astype(np.float32), want_s.reshape(shape))
+        assert bool((codes[rows] == 9).all())
+        want = dequant(want_c, want_s)
+        shifted = torch.empty((scales.numel() + 1,), device=DEV)[1:].view(shape)      # scales that are not 16-byte aligned
+        shifted.copy_(scales)
+        for sc in (scales, shifted):
+            for td in (torch.float32, torch.bfloat16):
+                out = torch.full((rows + 1, cols), 7.0, dtype=td, device=DEV)
+                B.moe_dequant_fp8(codes[:rows], sc, mode, out[:rows])
+                ref = want.astype(np.float32)
+                assert np.array_equal(to_np(out[:rows]).astype(np.float32), ref if td == torch.float32 else bf16_round(ref))
+                assert bool((out[rows] == 7.0).all())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_tgroup_cast_short_segments(dtype):
+    from paper_2505_11432_amd import binding as B
+    counts = [1, 0, 128, 129, 7, 300, 0]
+    rows, cols, E = sum(counts), 144, len(counts)
+    off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    v = np.random.default_rng(3).standard_normal((rows, cols)).astype(np.float32) * 30
+    v = bf16_round(v) if dtype == "bf16" else v
+    ldt = B.moe_tgroup_tokens(rows, E)
+    pad = torch.empty((E + 1,), dtype=torch.int32, device=DEV)
+    ct, e8 = torch.full((cols, ldt), 9, dtype=torch.uint8, device=DEV), torch.full((ldt // 128, cols), 9, dtype=torch.uint8, device=DEV)
+    B.moe_quant_fp8_tgroup(to_dev(v, torch_dtype(dtype)), to_dev(off), pad, ct, e8)
+    p = to_np(pad)
+    got_c, got_e = to_np(ct), to_np(e8)
+    for e in range(E):
+        for j, s in enumerate(range(0, counts[e], 128)):
+            block = v[off[e] + s: off[e] + min(s + 128, counts[e])]
+            k = O.pow2_exponent(np.abs(block).max(axis=0).astype(np.float32))
+            want = O.e4m3_encode((block * np.exp2(-k.astype(np.float64))).astype(np.float32)).T
+            c0 = p[e] + s
+            assert np.array_equal(got_c[:, c0:c0 + want.shape[1]], want)
+            assert not got_c[:, c0 + want.shape[1]:c0 + 128].any()
+            assert np.array_equal(got_e[c0 // 128], (k + 127).astype(np.uint8))
