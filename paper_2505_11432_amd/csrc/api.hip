@@ -464,7 +464,7 @@ int moe_expert_ffn_fused_bwd(const void* x, const void* dy, const void* h_save, 
     if (rc != MOE_OK) return rc;
     rc = mfma_dgrad2_swiglu_bwd_fold(rows, w2, offsets, M, d, E, f, h_save, dH, Aw, row_w, part, s);
     if (rc != MOE_OK) return rc;
-    rc = launch_gate_grad_reduce(part, mfma_dgrad2_fold_parts(M, E, f), M, inv_perm, M, d_topk_w, s);
+    rc = launch_gate_grad_reduce(part, mfma_dgrad2_fold_parts(M, d, E, f), M, inv_perm, M, d_topk_w, s);
     if (rc != MOE_OK) return rc;
   }
   rc = mfma_wgrad(rows, Aw, offsets, d, f, E, d_w2, grad_dt, accumulate != 0, s);

@@ -304,13 +304,18 @@ __device__ __forceinline__ i32x8 read_frag_fp8(const char* tile, int base, int k
 }
 
 // Work list with the last round split along K: tiles [0, full_tiles) are whole; each of the remaining
-// total_tiles - full_tiles tiles becomes `split` items.  No split unless it at least halves the last round.
-__host__ __device__ __forceinline__ void splitk_plan(int total_tiles, int workgroups, int& full_tiles, int& split, int& total_items) {
+// total_tiles - full_tiles tiles becomes `split` items of at least two k-steps.  No split unless it at least halves the
+// last round.
+__host__ __device__ __forceinline__ void splitk_plan(int total_tiles, int workgroups, int steps, int& full_tiles, int& split, int& total_items) {
   full_tiles = total_tiles / workgroups * workgroups;
   const int rem = total_tiles - full_tiles;
   split = 1;
-  if (rem > 0 && workgroups / rem >= 2) split = workgroups / rem >= 4 ? 4 : workgroups / rem;
-  if (split == 1) full_tiles = total_tiles;
+  if (rem > 0) {
+    split = workgroups / rem;
+    split = split < 8 ? split : 8;                     // (the fix-up reads every part)
+    split = split < steps / 2 ? split : steps / 2;
+  }
+  if (split <= 1) { split = 1; full_tiles = total_tiles; }
   total_items = full_tiles + (total_tiles - full_tiles) * split;
 }
 
@@ -334,11 +339,11 @@ __device__ __forceinline__ void tile_table(const int32_t* __restrict__ offsets, 
   }
 }
 
-// Adds the K parts of every split tile and writes the bf16 result with the tile's row / column masks.  Four
-// workgroups per split tile; the tile list is rebuilt exactly as in the GEMM kernel (same grouping constants).
+// Adds the K parts of every split tile and writes the bf16 result with the tile's row / column masks.  16 workgroups per
+// split tile while they last (four per GEMM workgroup are launched), else 8; the tile list is rebuilt exactly as in the GEMM kernel (same grouping constants).
 template <int BM, int BN>
 __global__ void __launch_bounds__(256) splitk_fixup_kernel(const float* __restrict__ parts, const int32_t* __restrict__ offsets,
-                                                           int E, int N, int gemm_workgroups, bf16* __restrict__ C, long ldc) {
+                                                           int E, int N, int steps, int gemm_workgroups, bf16* __restrict__ C, long ldc) {
   constexpr int GN = 8;
   __shared__ int cum_tiles[MOE_MAX_EXPERTS + 1];
   tile_table<BM>(offsets, E, cum_tiles);
@@ -346,10 +351,11 @@ __global__ void __launch_bounds__(256) splitk_fixup_kernel(const float* __restri
   const int tiles_n = (N + BN - 1) / BN;
   const int total_tiles = cum_tiles[E] * tiles_n;
   int full_tiles, split, total_items;
-  splitk_plan(total_tiles, gemm_workgroups, full_tiles, split, total_items);
-  constexpr int SLICES = 4;                          // workgroups per split tile (each takes BM / SLICES rows)
-  const int r_tile = blockIdx.x / SLICES, slice = blockIdx.x % SLICES;
-  if (split == 1 || r_tile >= total_tiles - full_tiles) return;
+  splitk_plan(total_tiles, gemm_workgroups, steps, full_tiles, split, total_items);
+  const int n_split = total_tiles - full_tiles;      // at most half of the GEMM workgroups
+  const int slices = n_split * 16 <= (int)gridDim.x ? 16 : 8;      // workgroups per split tile, BM / slices rows each
+  const int r_tile = blockIdx.x / slices, slice = blockIdx.x % slices;
+  if (split == 1 || r_tile >= n_split) return;
   int l = full_tiles + r_tile;
   int lo = 0, hi = E;
   while (hi - lo > 1) {
@@ -366,8 +372,9 @@ __global__ void __launch_bounds__(256) splitk_fixup_kernel(const float* __restri
   const int nt = ng * GN + (r - mt * gw);
   const int m0 = offsets[e] + mt * BM, m_end = offsets[e + 1], n0 = nt * BN;
   const float* base = parts + (long)r_tile * split * (BM * BN);
-  for (int i = threadIdx.x; i < (BM / SLICES) * BN / 8; i += blockDim.x) {
-    const int row = slice * (BM / SLICES) + i / (BN / 8), col = (i % (BN / 8)) * 8;
+  const int rows = BM / slices;
+  for (int i = threadIdx.x; i < rows * BN / 8; i += blockDim.x) {
+    const int row = slice * rows + i / (BN / 8), col = (i % (BN / 8)) * 8;
     if (m0 + row >= m_end || n0 + col >= N) continue;          // N is a multiple of 8
     float v[8];
 #pragma unroll
@@ -467,7 +474,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
   constexpr bool SPLITK = MODE == ROWSEG && EPI == EPI_STORE && sizeof(TC) == 2;
   int full_tiles = total_tiles, split = 1, total_items = total_tiles;
   if constexpr (SPLITK) {
-    if (p.splitk_ws != nullptr) splitk_plan(total_tiles, (int)gridDim.x, full_tiles, split, total_items);
+    if (p.splitk_ws != nullptr) splitk_plan(total_tiles, (int)gridDim.x, (p.K + BKT - 1) / BKT, full_tiles, split, total_items);
   }
   const int xcd = blockIdx.x % XCDS;
   const int window = gridDim.x / XCDS;           // tiles per window = CUs per XCD

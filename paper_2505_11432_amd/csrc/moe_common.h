@@ -121,7 +121,7 @@ int mfma_wgrad(const void* P, const void* Q, const int32_t* offsets, int Mo, int
 // Section 4.1 / 4.2 operator order
 int mfma_fc1_swiglu_gather(const void* x, int T, const int32_t* row_token, const float* row_w, const void* w1,
                            const int32_t* offsets, int M, int d, int E, int f, void* H, void* A_out, hipStream_t s);
-int mfma_dgrad2_fold_parts(int M, int E, int f);      // at most cdiv(f, 256) * 4
+int mfma_dgrad2_fold_parts(int M, int d, int E, int f);      // at most cdiv(f, 256) * 4
 int mfma_dgrad2_swiglu_bwd_fold(const void* d_yp, const void* w2, const int32_t* offsets, int M, int d, int E, int f,
                                 const void* H, void* dH, void* A_out, const float* row_w, float* dw_part, hipStream_t s);
 
