@@ -62,3 +62,21 @@ def test_router_fwd_edges(T, d, E):
         # products are exact in fp32; d additions, each rounding by at most 2^-24 of a partial sum
         assert float((z[:T * E].view(T, E).double() - ref).norm() / ref.norm()) < 3 * np.sqrt(d) * 2.0 ** -24 + 2.0 ** -23
     assert bool((z[T * E:] == 7.0).all())
+
+
+# assignments on both sides of what the one-launch selection holds (8192 and 32768), one device, a device per expert, many
+# equal affinities (odd T quantises the logits), nothing kept, everything kept
+@pytest.mark.parametrize("T,E,k,G,cap,skew", [(4096, 8, 2, 4, 1500, 1.0), (8193, 8, 1, 2, 2000, 1.0), (16384, 4, 2, 2, 9000, 0.5),
+                                             (16385, 16, 2, 8, 3000, 1.0), (1023, 256, 4, 256, 10, 0.0), (777, 12, 3, 1, 1200, 0.0),
+                                             (999, 6, 2, 3, 0, 0.0), (999, 6, 2, 3, 1998, 0.0), (1, 3, 1, 3, 1, 0.0)])
+def test_route_capacity_edges(T, E, k, G, cap, skew):
+    from paper_2505_11432_amd import binding as B
+    from tests.test_gpu_parity import test_route_capacity as check
+    check(B, T, E, k, G, cap, skew)
+
+
+@pytest.mark.parametrize("T,E,k,G", [(1, 1, 1, 1), (63, 2, 1, 2), (64, 3, 2, 3), (129, 12, 3, 4), (4097, 24, 3, 8), (70000, 16, 2, 4), (200, 130, 5, 10)])
+def test_balance_loss_edges(T, E, k, G):
+    from paper_2505_11432_amd import binding as B
+    from tests.test_gpu_parity import test_balance_loss_and_gradient as check
+    check(B, T, E, k, G)
