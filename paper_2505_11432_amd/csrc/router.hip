@@ -23,25 +23,34 @@ template <typename T, int COLS> struct RowChunk {
 };
 
 // partial[chunk][e][col] = sum over the chunk's tokens of d_logits[t][e] * x[t][col].
-// A block owns 256 * COLS columns of x and one chunk of tokens; a thread keeps ETILE x COLS fp32 sums.  The
-// chunk's gate gradients (up to 64 tokens x ETILE experts) are staged in LDS and read back as broadcasts.
-// ETILE is the smallest of 8 / 16 / 32 / 64 that holds E (more than 64 experts: passes of 64), so that few
-// experts do not pay for 64: with ETILE = 8 the kernel is bound by reading x, not by FMAs.
+// A thread keeps ETILE x COLS fp32 sums.  The chunk's gate gradients (64 tokens x ETILE experts at a time) are staged in LDS
+// and read back as broadcasts.  ETILE is the smallest of 8 / 16 / 32 / 64 that holds E (more than 64 experts: passes of
+// 64), so that few experts do not pay for 64: with ETILE = 8 the kernel is bound by reading x, not by FMAs.
+// TOK = false: a block owns 256 * COLS columns, its four waves side by side, and each walks all tokens of the chunk.
+// TOK = true: a block owns 64 * COLS columns, its waves take every fourth run of eight tokens, and their sums are added in
+// wave order through LDS: four times the blocks with a quarter of the serial walk, for problems of fewer than 256 blocks
+// (us: T = 256, d = 128, E = 8 fp32 11.9 -> 6.9; T = 300, d = 4096, E = 8 11.2 -> 7.0; T = 1531, d = 1040, E = 24 19.0 -> 15.3;
+// T = 4096, d = 1024, E = 44 36.4 -> 24.7).  With more the wider rows per block win (T = 8192, d = 4096, E = 8: 21.6 against
+// 24.6; T = 4096, d = 4096, E = 20: 28.9 against 64).
 constexpr int kChunkTokens = 64;
 constexpr int kTokUnroll = 8;         // rows of x in flight per thread
 
-template <typename T, int ETILE, int COLS>
+template <typename T, int ETILE, int COLS, bool TOK>
 __global__ void __launch_bounds__(256) router_dwr_partial_kernel(const T* __restrict__ x,
                                                                  const float* __restrict__ d_logits, int Tn, int d,
                                                                  int E, int tokens_per_chunk,
                                                                  float* __restrict__ partial) {
+  constexpr int kPart = !TOK ? 1 : ETILE <= 32 ? ETILE : 16;      // experts added through LDS at a time
   __shared__ __attribute__((aligned(16))) float g_lds[kChunkTokens][ETILE];
-  constexpr int kSlab = 256 * COLS;
+  __shared__ float part[TOK ? 3 : 1][kPart * COLS][64];
+  constexpr int kSlab = (TOK ? 64 : 256) * COLS;
   const int slabs = (d + kSlab - 1) / kSlab;
   const int slab = blockIdx.x % slabs, chunk = blockIdx.x / slabs;
-  const int col = slab * kSlab + threadIdx.x * COLS;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int col = slab * kSlab + (TOK ? lane : (int)threadIdx.x) * COLS;
   const int t0 = chunk * tokens_per_chunk, t1 = min(t0 + tokens_per_chunk, Tn);
   const bool active = col < d;                 // d is a multiple of 16 >= COLS: a chunk is inside the row or outside
+  const T* xcol = x + min(col, d - COLS);
   for (int e0 = 0; e0 < E; e0 += ETILE) {
     float acc[ETILE][COLS];
 #pragma unroll
@@ -56,11 +65,11 @@ __global__ void __launch_bounds__(256) router_dwr_partial_kernel(const T* __rest
         g_lds[tt][ee] = (ts + tt < te && e0 + ee < E) ? d_logits[(long)(ts + tt) * E + e0 + ee] : 0.f;   // zero rows past the chunk
       }
       __syncthreads();
-      if (!active) continue;
-      for (int tb = ts; tb < te; tb += kTokUnroll) {
+      if (!TOK && !active) continue;
+      for (int tb = ts + (TOK ? wave * kTokUnroll : 0); tb < te; tb += (TOK ? 4 : 1) * kTokUnroll) {
         float xv[kTokUnroll][COLS];
 #pragma unroll
-        for (int u = 0; u < kTokUnroll; ++u) RowChunk<T, COLS>::load(x + (long)min(tb + u, Tn - 1) * d + col, xv[u]);
+        for (int u = 0; u < kTokUnroll; ++u) RowChunk<T, COLS>::load(xcol + (long)min(tb + u, Tn - 1) * d, xv[u]);
 #pragma unroll
         for (int u = 0; u < kTokUnroll; ++u) {
           // rows past the chunk's end multiply zeros (tb + u - ts < kChunkTokens: both are multiples of 8 apart)
@@ -79,7 +88,25 @@ __global__ void __launch_bounds__(256) router_dwr_partial_kernel(const T* __rest
         }
       }
     }
-    if (active) {
+    if constexpr (TOK) {
+#pragma unroll
+      for (int p0 = 0; p0 < ETILE; p0 += kPart) {
+        __syncthreads();                       // the previous sums have been read
+        if (wave > 0)
+#pragma unroll
+          for (int i = 0; i < kPart; ++i)
+#pragma unroll
+            for (int c = 0; c < COLS; ++c) part[wave - 1][i * COLS + c][lane] = acc[p0 + i][c];
+        __syncthreads();
+        if (wave == 0)
+#pragma unroll
+          for (int i = 0; i < kPart; ++i)
+#pragma unroll
+            for (int c = 0; c < COLS; ++c)
+              acc[p0 + i][c] = ((acc[p0 + i][c] + part[0][i * COLS + c][lane]) + part[1][i * COLS + c][lane]) + part[2][i * COLS + c][lane];
+      }
+    }
+    if (active && (!TOK || wave == 0)) {
 #pragma unroll
       for (int i = 0; i < ETILE; ++i)
         if (e0 + i < E) {
@@ -116,21 +143,25 @@ __global__ void __launch_bounds__(256) router_dwr_reduce_kernel(const float* __r
 
 // dx[t, cols] += sum_e d_logits[t][e] * w_r[e][cols].  A block owns a slab of 512 columns (64 lanes x 8) and
 // keeps that slab of w_r (up to 64 experts x 1 KiB) in LDS; its four waves walk the tokens.  More than 64
-// experts are done in passes of 64 that each read-modify-write dx.
+// experts are done in passes of 64 that each read-modify-write dx.  Bound by reading and writing dx, so what counts is how
+// many blocks fit a CU: the slab is as high as the experts need (ETILE), and a token's gate gradients sit one per lane in a
+// register (a scalar load per token and expert is a chain of memory latencies).  T = 8192, d = 4096, E = 8, bf16 32 -> 27 us;
+// T = 16384, d = 2048, E = 16 43 -> 35.
 constexpr int kDxCols = 512;
 
-template <typename T>
+template <typename T, int ETILE>
 __global__ void __launch_bounds__(256) router_dx_kernel(const T* __restrict__ w_r, const float* __restrict__ d_logits,
                                                         int Tn, int d, int E, int token_groups, T* __restrict__ dx) {
   constexpr int V = 8;                                  // columns per lane
-  __shared__ __attribute__((aligned(16))) T w_lds[kETile][kDxCols];
+  __shared__ __attribute__((aligned(16))) T w_lds[ETILE][kDxCols];
   const int slabs = (d + kDxCols - 1) / kDxCols;
   const int slab = blockIdx.x % slabs, tg = blockIdx.x / slabs;
   const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
   const int col = slab * kDxCols + lane * V;
   const bool active = col < d;
-  for (int e0 = 0; e0 < E; e0 += kETile) {
-    const int ne = min(kETile, E - e0);
+  const int col_in = min(col, d - V);                   // lanes past the row load its end and store nothing
+  for (int e0 = 0; e0 < E; e0 += ETILE) {
+    const int ne = min(ETILE, E - e0);
     __syncthreads();
     for (int i = threadIdx.x; i < ne * (kDxCols / V); i += 256) {
       const int ee = i / (kDxCols / V), cc = (i % (kDxCols / V)) * V;
@@ -148,12 +179,14 @@ __global__ void __launch_bounds__(256) router_dx_kernel(const T* __restrict__ w_
     // a wave takes kTok tokens at a time: one LDS read of w_r feeds kTok x 8 FMAs
     constexpr int kTok = 4;
     for (int tb = (tg * 4 + wave) * kTok; tb < Tn; tb += token_groups * 4 * kTok) {
-      if (!active) continue;
       float acc[kTok][V];
+      float g[kTok];                                     // lane e: this pass's gate gradient of expert e
+#pragma unroll
+      for (int q = 0; q < kTok; ++q) g[q] = d_logits[(long)min(tb + q, Tn - 1) * E + e0 + min(lane, ne - 1)];
 #pragma unroll
       for (int q = 0; q < kTok; ++q) {
         const int t = min(tb + q, Tn - 1);
-        const T* src = dx + (long)t * d + col;
+        const T* src = dx + (long)t * d + col_in;
         if constexpr (sizeof(T) == 2) {
           const Vec16<T> cur = *reinterpret_cast<const Vec16<T>*>(src);
 #pragma unroll
@@ -175,14 +208,14 @@ __global__ void __launch_bounds__(256) router_dx_kernel(const T* __restrict__ w_
         }
 #pragma unroll
         for (int q = 0; q < kTok; ++q) {
-          const float gv = d_logits[(long)min(tb + q, Tn - 1) * E + e0 + e];     // wave-uniform: scalar load
+          const float gv = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(g[q]), e));
 #pragma unroll
           for (int j = 0; j < V; ++j) acc[q][j] = fmaf(gv, wv[j], acc[q][j]);
         }
       }
 #pragma unroll
       for (int q = 0; q < kTok; ++q) {
-        if (tb + q >= Tn) break;
+        if (tb + q >= Tn || !active) break;
         T* dst = dx + (long)(tb + q) * d + col;
         if constexpr (sizeof(T) == 2) {
           Vec16<T> out;
@@ -275,7 +308,12 @@ int launch_router_bwd(const void* x, const void* w_r, const float* d_logits, moe
     const int tpc = dwr_tokens_per_chunk(T);
     float* partial = static_cast<float*>(ws);
 #define MOE_DWR_CASE(TT, ET, CO)                                                                                    \
-  router_dwr_partial_kernel<TT, ET, CO><<<cdiv(d, 256 * CO) * chunks, 256, 0, s>>>((const TT*)x, d_logits, T, d, E, tpc, partial)
+  do {                                                                                                              \
+    if (cdiv(d, 256 * CO) * chunks < 256)                                                                           \
+      router_dwr_partial_kernel<TT, ET, CO, true><<<cdiv(d, 64 * CO) * chunks, 256, 0, s>>>((const TT*)x, d_logits, T, d, E, tpc, partial); \
+    else                                                                                                            \
+      router_dwr_partial_kernel<TT, ET, CO, false><<<cdiv(d, 256 * CO) * chunks, 256, 0, s>>>((const TT*)x, d_logits, T, d, E, tpc, partial); \
+  } while (0)
     if (dt == MOE_F32) {
       if (E <= 8) MOE_DWR_CASE(float, 8, 4);
       else if (E <= 16) MOE_DWR_CASE(float, 16, 4);
@@ -300,11 +338,19 @@ int launch_router_bwd(const void* x, const void* w_r, const float* d_logits, moe
     if (rc != MOE_OK) return rc;
   } else if (dx && T > 0) {
     const int slabs = cdiv(d, kDxCols);
-    int token_groups = cdiv(512, slabs);                 // about two blocks per CU
+    const int per_cu = E <= 16 ? 8 : E <= 32 ? 4 : 2;    // what the LDS slab of bf16 experts allows
+    int token_groups = cdiv(256 * per_cu, slabs);
     if (token_groups > cdiv(T, 16)) token_groups = cdiv(T, 16);
     const int blocks = slabs * token_groups;
-    if (dt == MOE_F32) router_dx_kernel<float><<<blocks, 256, 0, s>>>((const float*)w_r, d_logits, T, d, E, token_groups, (float*)dx);
-    else router_dx_kernel<bf16><<<blocks, 256, 0, s>>>((const bf16*)w_r, d_logits, T, d, E, token_groups, (bf16*)dx);
+#define MOE_DX_CASE(TT, ET) router_dx_kernel<TT, ET><<<blocks, 256, 0, s>>>((const TT*)w_r, d_logits, T, d, E, token_groups, (TT*)dx)
+#define MOE_DX_TYPE(TT)                  \
+  if (E <= 8) MOE_DX_CASE(TT, 8);        \
+  else if (E <= 16) MOE_DX_CASE(TT, 16); \
+  else if (E <= 32) MOE_DX_CASE(TT, 32); \
+  else MOE_DX_CASE(TT, kETile);
+    if (dt == MOE_F32) { MOE_DX_TYPE(float) } else { MOE_DX_TYPE(bf16) }
+#undef MOE_DX_TYPE
+#undef MOE_DX_CASE
     MOE_LAUNCH_CHECK();
   }
   return MOE_OK;

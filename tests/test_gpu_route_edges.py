@@ -80,3 +80,23 @@ def test_balance_loss_edges(T, E, k, G):
     from paper_2505_11432_amd import binding as B
     from tests.test_gpu_parity import test_balance_loss_and_gradient as check
     check(B, T, E, k, G)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("T,d,E", [(1, 16, 1), (63, 272, 8), (65, 528, 9), (129, 1040, 17), (200, 144, 33), (130, 80, 100), (8200, 2064, 3)])
+def test_router_bwd_edges(T, d, E, dtype):
+    from paper_2505_11432_amd import binding as B
+    g = torch.Generator(device=DEV).manual_seed(T)
+    x, w, dz = (torch.randn(s, generator=g, device=DEV) for s in ((T, d), (E, d), (T, E)))
+    x, w = x.to(dtype), w.to(dtype)
+    buf = torch.randn((T * d + 64,), generator=g, device=DEV).to(dtype)
+    dx, tail, dx0 = buf[:T * d].view(T, d), buf[T * d:].clone(), buf[:T * d].double().view(T, d)
+    dwr = torch.full((E, d), 7.0, device=DEV)
+    ws = torch.empty(max(B.moe_workspace_bytes(T, d, E, 1, 16, B.dtype_code(dtype)), 256), dtype=torch.uint8, device=DEV)
+    B.moe_router_bwd(x, w, dz, dwr, dx, ws)
+    want_w, want_x = dz.double().t() @ x.double(), dx0 + dz.double() @ w.double()
+    # d_w_r: T fp32 additions of random sign; dx: E of them and one rounding to its type per pass of 64 experts
+    assert float((dwr.double() - want_w).norm() / want_w.norm()) < 3 * np.sqrt(T) * 2.0 ** -24 + 2.0 ** -23
+    step = 2.0 ** -9 if dtype == torch.bfloat16 else 2.0 ** -24 * 3 * np.sqrt(E) + 2.0 ** -23
+    assert float((dx.double() - want_x).norm() / want_x.norm()) < 2 * step
+    assert torch.equal(buf[T * d:], tail)
