@@ -1,8 +1,10 @@
-"""ctypes binding of libmoe_hip.so: same names as the C ABI (include/moe.h), argument marshalling only.
+"""Binding of libmoe_hip.so: same names as the C ABI (include/moe.h), argument marshalling only.
 
 Every function takes torch tensors that already live on the GPU (torch is used for device memory
 and streams, nothing else), passes their device pointers and the current stream to the library and
-raises MoEError on a non-zero status.  There is no CPU fallback: if the library is missing the
+raises MoEError on a non-zero status.  The calls of a step go through the extension module
+_moe_native (csrc/native), which checks the tensors and converts the arguments; queries, set-up and the
+call that takes a struct go through ctypes.  There is no CPU fallback: if either library is missing the
 import of this module fails.
 """
 from __future__ import annotations
@@ -74,31 +76,10 @@ def _load() -> ctypes.CDLL:
         "moe_last_hip_error": (I, []),
         "moe_status_string": (c_char_p, [I]),
         "moe_workspace_bytes": (Z, [I, I, I, I, I, I]),
-        "moe_router_fwd": (I, [P, P, P, I, I, I, I, P, P]),
-        "moe_router_bwd": (I, [P, P, P, I, I, I, I, P, P, P, Z, P]),
-        "moe_route": (I, [P, I, I, I, I, P, P, P, P, P, P, P, Z, P]),
-        "moe_route_noalloc": (I, [P, I, I, I, I, P, P, P, P, P, P, P]),
-        "moe_route_range": (I, [P, I, I, I, I, I, I, P, P, P, P, P, P, P, Z, P]),
         "moe_route_capacity_workspace_bytes": (Z, [I, I, I]),
-        "moe_route_capacity": (I, [P, I, I, I, I, I, I, P, P, P, P, P, P, P, P, Z, P]),
-        "moe_balance_loss": (I, [P, P, I, I, I, I, ctypes.c_float, P, P, P, P, Z, P]),
-        "moe_balance_loss_bwd": (I, [P, P, I, I, I, ctypes.c_float, P, P]),
-        "moe_route_bwd": (I, [P, P, P, P, I, I, I, I, P, P]),
-        "moe_dispatch": (I, [P, P, I, P, P, I, I, I, P, P, P]),
-        "moe_combine": (I, [P, P, I, P, P, I, I, I, P, I, P]),
-        "moe_gate_grad": (I, [P, I, P, P, I, P, I, I, I, P, P]),
-        "moe_expert_ffn_fwd": (I, [P, P, I, P, P, P, P, P, I, I, I, I, I, P, P, P, I, P, P, P, Z, P]),
-        "moe_expert_ffn_bwd": (I, [P, P, P, P, P, P, P, I, I, I, I, I, P, P, P, I, I, P, Z, P]),
-        "moe_quant_fp8": (I, [P, I, I, I, I, P, P, P]),
-        "moe_dequant_fp8": (I, [P, P, I, I, I, P, I, P]),
         "moe_expert_ffn_bwd_fp8": (I, [ctypes.POINTER(FfnBwdFp8Args), P]),
         "moe_tgroup_tokens": (Z, [I, I]),
-        "moe_transpose": (I, [P, I, I, I, I, P, P]),
-        "moe_row_map": (I, [P, P, P, I, I, I, P, P, P]),
         "moe_expert_ffn_fused_workspace_bytes": (Z, [I, I, I, I]),
-        "moe_expert_ffn_fused_fwd": (I, [P, P, P, P, P, P, I, I, I, I, I, P, P, P, Z, P]),
-        "moe_expert_ffn_fused_bwd": (I, [P, P, P, P, P, P, P, P, P, I, I, I, I, I, P, P, P, I, I, P, P, Z, P]),
-        "moe_quant_fp8_tgroup": (I, [P, I, I, I, P, I, P, P, ctypes.c_long, P, P]),
     }
     for name, (res, args) in sig.items():
         fn = getattr(lib, name)
@@ -108,6 +89,7 @@ def _load() -> ctypes.CDLL:
 
 
 _lib = _load()
+from . import _moe_native as _native  # noqa: E402  (linked against the library that _load has made sure of)
 
 
 def dtype_code(t: torch.dtype) -> int:
@@ -152,92 +134,86 @@ def moe_workspace_bytes(T, d, E, k, f, act) -> int:
 def moe_router_fwd(x, w_r, bias, logits):
     T, d = x.shape
     E = w_r.shape[0]
-    _check("moe_router_fwd", _lib.moe_router_fwd(_p(x), _p(w_r), _p(bias), dtype_code(x.dtype), T, d, E,
-                                                 _p(logits), _stream()))
+    _check("moe_router_fwd", _native.moe_router_fwd(x, w_r, bias, dtype_code(x.dtype), T, d, E, logits))
 
 
 def moe_router_bwd(x, w_r, d_logits, d_w_r, dx, workspace):
     T, d = x.shape
     E = w_r.shape[0]
-    _check("moe_router_bwd", _lib.moe_router_bwd(_p(x), _p(w_r), _p(d_logits), dtype_code(x.dtype), T, d, E,
-                                                 _p(d_w_r), _p(dx), _p(workspace),
-                                                 workspace.numel() * workspace.element_size(), _stream()))
+    _check("moe_router_bwd", _native.moe_router_bwd(
+        x, w_r, d_logits, dtype_code(x.dtype), T, d, E, d_w_r, dx, workspace, workspace.numel() *
+        workspace.element_size()))
 
 
 def moe_route(logits, k, renorm, topk_idx, topk_w, counts, offsets, perm, inv_perm, workspace):
     T, E = logits.shape
-    _check("moe_route", _lib.moe_route(_p(logits), T, E, k, renorm, _p(topk_idx), _p(topk_w), _p(counts),
-                                       _p(offsets), _p(perm), _p(inv_perm), _p(workspace),
-                                       workspace.numel() * workspace.element_size(), _stream()))
+    _check("moe_route", _native.moe_route(
+        logits, T, E, k, renorm, topk_idx, topk_w, counts, offsets, perm, inv_perm, workspace, workspace.numel() *
+        workspace.element_size()))
 
 
 def moe_route_noalloc(logits, k, renorm, topk_idx, topk_w, counts, offsets, perm, inv_perm):
     T, E = logits.shape
-    _check("moe_route_noalloc", _lib.moe_route_noalloc(_p(logits), T, E, k, renorm, _p(topk_idx), _p(topk_w), _p(counts),
-                                                       _p(offsets), _p(perm), _p(inv_perm), _stream()))
+    _check("moe_route_noalloc", _native.moe_route_noalloc(
+        logits, T, E, k, renorm, topk_idx, topk_w, counts, offsets, perm, inv_perm))
 
 
 def moe_route_bwd(logits, topk_idx, topk_w, d_topk_w, E, renorm, d_logits):
     T, k = topk_idx.shape
-    _check("moe_route_bwd", _lib.moe_route_bwd(_p(logits), _p(topk_idx), _p(topk_w), _p(d_topk_w), T, E, k,
-                                               renorm, _p(d_logits), _stream()))
+    _check("moe_route_bwd", _native.moe_route_bwd(logits, topk_idx, topk_w, d_topk_w, T, E, k, renorm, d_logits))
 
 
 def moe_dispatch(x, x_scale, inv_perm, row_mul, k, xp, xp_scale):
     T, d = x.shape
-    _check("moe_dispatch", _lib.moe_dispatch(_p(x), _p(x_scale), dtype_code(x.dtype), _p(inv_perm), _p(row_mul),
-                                             T, k, d, _p(xp), _p(xp_scale), _stream()))
+    _check("moe_dispatch", _native.moe_dispatch(
+        x, x_scale, dtype_code(x.dtype), inv_perm, row_mul, T, k, d, xp, xp_scale))
 
 
 def moe_combine(yp, yp_scale, inv_perm, topk_w, k, y):
     T, d = y.shape
-    _check("moe_combine", _lib.moe_combine(_p(yp), _p(yp_scale), dtype_code(yp.dtype), _p(inv_perm), _p(topk_w),
-                                           T, k, d, _p(y), dtype_code(y.dtype), _stream()))
+    _check("moe_combine", _native.moe_combine(
+        yp, yp_scale, dtype_code(yp.dtype), inv_perm, topk_w, T, k, d, y, dtype_code(y.dtype)))
 
 
 def moe_gate_grad(dy, yp, yp_scale, inv_perm, k, d_topk_w):
     T, d = dy.shape
-    _check("moe_gate_grad", _lib.moe_gate_grad(_p(dy), dtype_code(dy.dtype), _p(yp), _p(yp_scale),
-                                               dtype_code(yp.dtype), _p(inv_perm), T, k, d, _p(d_topk_w),
-                                               _stream()))
+    _check("moe_gate_grad", _native.moe_gate_grad(
+        dy, dtype_code(dy.dtype), yp, yp_scale, dtype_code(yp.dtype), inv_perm, T, k, d, d_topk_w))
 
 
 def moe_expert_ffn_fwd(xp, xp_scale, offsets, w1, w1_scale, w2, w2_scale, h_save, yp, yp_scale, workspace,
                        a_codes_out=None, a_scale_out=None):
     M, d = xp.shape
     E, two_f, _ = w1.shape
-    _check("moe_expert_ffn_fwd", _lib.moe_expert_ffn_fwd(
-        _p(xp), _p(xp_scale), dtype_code(xp.dtype), _p(offsets), _p(w1), _p(w1_scale), _p(w2), _p(w2_scale),
-        dtype_code(w1.dtype), M, d, E, two_f // 2, _p(h_save), _p(yp), _p(yp_scale), dtype_code(yp.dtype),
-        _p(a_codes_out), _p(a_scale_out), _p(workspace), workspace.numel() * workspace.element_size(), _stream()))
+    _check("moe_expert_ffn_fwd", _native.moe_expert_ffn_fwd(
+        xp, xp_scale, dtype_code(xp.dtype), offsets, w1, w1_scale, w2, w2_scale, dtype_code(w1.dtype), M, d, E, two_f
+        // 2, h_save, yp, yp_scale, dtype_code(yp.dtype), a_codes_out, a_scale_out, workspace, workspace.numel() *
+        workspace.element_size()))
 
 
 def moe_expert_ffn_bwd(xp, h_save, d_yp, a_override, offsets, w1, w2, d_xp, d_w1, d_w2, accumulate, workspace):
     M, d = xp.shape
     E, two_f, _ = w1.shape
-    _check("moe_expert_ffn_bwd", _lib.moe_expert_ffn_bwd(
-        _p(xp), _p(h_save), _p(d_yp), _p(a_override), _p(offsets), _p(w1), _p(w2), dtype_code(xp.dtype), M, d, E,
-        two_f // 2, _p(d_xp), _p(d_w1), _p(d_w2), dtype_code(d_w1.dtype), int(accumulate), _p(workspace),
-        workspace.numel() * workspace.element_size(), _stream()))
+    _check("moe_expert_ffn_bwd", _native.moe_expert_ffn_bwd(
+        xp, h_save, d_yp, a_override, offsets, w1, w2, dtype_code(xp.dtype), M, d, E, two_f // 2, d_xp, d_w1, d_w2,
+        dtype_code(d_w1.dtype), int(accumulate), workspace, workspace.numel() * workspace.element_size()))
 
 
 def moe_quant_fp8(src, mode, codes, scales):
     rows, cols = src.shape
-    _check("moe_quant_fp8", _lib.moe_quant_fp8(_p(src), dtype_code(src.dtype), rows, cols, mode, _p(codes),
-                                               _p(scales), _stream()))
+    _check("moe_quant_fp8", _native.moe_quant_fp8(src, dtype_code(src.dtype), rows, cols, mode, codes, scales))
 
 
 def moe_dequant_fp8(codes, scales, mode, dst):
     rows, cols = codes.shape
-    _check("moe_dequant_fp8", _lib.moe_dequant_fp8(_p(codes), _p(scales), rows, cols, mode, _p(dst),
-                                                   dtype_code(dst.dtype), _stream()))
+    _check("moe_dequant_fp8", _native.moe_dequant_fp8(codes, scales, rows, cols, mode, dst, dtype_code(dst.dtype)))
 
 
 def moe_transpose(src, dst):
     """src [batch, rows, cols] -> dst [batch, cols, rows]."""
     batch, rows, cols = src.shape
     assert tuple(dst.shape) == (batch, cols, rows) and dst.dtype == src.dtype
-    _check("moe_transpose", _lib.moe_transpose(_p(src), dtype_code(src.dtype), batch, rows, cols, _p(dst), _stream()))
+    _check("moe_transpose", _native.moe_transpose(src, dtype_code(src.dtype), batch, rows, cols, dst))
 
 
 def moe_tgroup_tokens(rows: int, E: int) -> int:
@@ -249,8 +225,8 @@ def moe_quant_fp8_tgroup(src, offsets, pad_offsets, codes_t, e8m0):
     rows, cols = src.shape
     E = offsets.numel() - 1
     ldt = codes_t.shape[1]
-    _check("moe_quant_fp8_tgroup", _lib.moe_quant_fp8_tgroup(_p(src), dtype_code(src.dtype), rows, cols, _p(offsets), E,
-                                                             _p(pad_offsets), _p(codes_t), ldt, _p(e8m0), _stream()))
+    _check("moe_quant_fp8_tgroup", _native.moe_quant_fp8_tgroup(
+        src, dtype_code(src.dtype), rows, cols, offsets, E, pad_offsets, codes_t, ldt, e8m0))
 
 
 def moe_expert_ffn_bwd_fp8(d_yp, h_save, xp_deq, a_deq, offsets, w1t, w1t_scale, w2t, w2t_scale, d_xp, d_w1, d_w2,
@@ -286,9 +262,9 @@ def moe_expert_ffn_bwd_fp8(d_yp, h_save, xp_deq, a_deq, offsets, w1t, w1t_scale,
 
 def moe_route_range(logits, k, renorm, e_lo, e_hi, topk_idx, topk_w, counts, offsets, perm, inv_perm, workspace):
     T, E = logits.shape
-    _check("moe_route_range", _lib.moe_route_range(_p(logits), T, E, k, renorm, e_lo, e_hi, _p(topk_idx), _p(topk_w),
-                                                   _p(counts), _p(offsets), _p(perm), _p(inv_perm), _p(workspace),
-                                                   workspace.numel(), _stream()))
+    _check("moe_route_range", _native.moe_route_range(
+        logits, T, E, k, renorm, e_lo, e_hi, topk_idx, topk_w, counts, offsets, perm, inv_perm, workspace,
+        workspace.numel()))
 
 
 def moe_route_capacity_workspace_bytes(T, E, k) -> int:
@@ -298,28 +274,27 @@ def moe_route_capacity_workspace_bytes(T, E, k) -> int:
 def moe_route_capacity(logits, k, renorm, n_groups, capacity, topk_idx, topk_w, score, counts, offsets, perm, inv_perm,
                        workspace):
     T, E = logits.shape
-    _check("moe_route_capacity", _lib.moe_route_capacity(
-        _p(logits), T, E, k, renorm, n_groups, capacity, _p(topk_idx), _p(topk_w), _p(score), _p(counts), _p(offsets),
-        _p(perm), _p(inv_perm), _p(workspace), workspace.numel() * workspace.element_size(), _stream()))
+    _check("moe_route_capacity", _native.moe_route_capacity(
+        logits, T, E, k, renorm, n_groups, capacity, topk_idx, topk_w, score, counts, offsets, perm, inv_perm,
+        workspace, workspace.numel() * workspace.element_size()))
 
 
 def moe_balance_loss(logits, counts, k, n_groups, alpha, loss, group_f, group_p, workspace):
     T, E = logits.shape
-    _check("moe_balance_loss", _lib.moe_balance_loss(_p(logits), _p(counts), T, E, k, n_groups, alpha, _p(loss), _p(group_f),
-                                                     _p(group_p), _p(workspace),
-                                                     workspace.numel() * workspace.element_size(), _stream()))
+    _check("moe_balance_loss", _native.moe_balance_loss(
+        logits, counts, T, E, k, n_groups, alpha, loss, group_f, group_p, workspace, workspace.numel() *
+        workspace.element_size()))
 
 
 def moe_balance_loss_bwd(logits, group_f, n_groups, alpha, d_logits):
     T, E = logits.shape
-    _check("moe_balance_loss_bwd", _lib.moe_balance_loss_bwd(_p(logits), _p(group_f), T, E, n_groups, alpha, _p(d_logits),
-                                                             _stream()))
+    _check("moe_balance_loss_bwd", _native.moe_balance_loss_bwd(logits, group_f, T, E, n_groups, alpha, d_logits))
 
 
 def moe_row_map(perm, topk_w, offsets, row_token, row_w):
     T, k = topk_w.shape
     E = offsets.numel() - 1
-    _check("moe_row_map", _lib.moe_row_map(_p(perm), _p(topk_w), _p(offsets), E, T, k, _p(row_token), _p(row_w), _stream()))
+    _check("moe_row_map", _native.moe_row_map(perm, topk_w, offsets, E, T, k, row_token, row_w))
 
 
 def moe_expert_ffn_fused_workspace_bytes(T, k, d, f) -> int:
@@ -329,16 +304,15 @@ def moe_expert_ffn_fused_workspace_bytes(T, k, d, f) -> int:
 def moe_expert_ffn_fused_fwd(x, row_token, row_w, offsets, w1, w2, k, h_save, ypw, workspace):
     T, d = x.shape
     E, two_f, _ = w1.shape
-    _check("moe_expert_ffn_fused_fwd", _lib.moe_expert_ffn_fused_fwd(
-        _p(x), _p(row_token), _p(row_w), _p(offsets), _p(w1), _p(w2), T, k, d, E, two_f // 2, _p(h_save), _p(ypw),
-        _p(workspace), workspace.numel() * workspace.element_size(), _stream()))
+    _check("moe_expert_ffn_fused_fwd", _native.moe_expert_ffn_fused_fwd(
+        x, row_token, row_w, offsets, w1, w2, T, k, d, E, two_f // 2, h_save, ypw, workspace, workspace.numel() *
+        workspace.element_size()))
 
 
 def moe_expert_ffn_fused_bwd(x, dy, h_save, inv_perm, topk_w, row_w, offsets, w1, w2, k, d_xp, d_w1, d_w2, accumulate,
                              d_topk_w, workspace):
     T, d = x.shape
     E, two_f, _ = w1.shape
-    _check("moe_expert_ffn_fused_bwd", _lib.moe_expert_ffn_fused_bwd(
-        _p(x), _p(dy), _p(h_save), _p(inv_perm), _p(topk_w), _p(row_w), _p(offsets), _p(w1), _p(w2), T, k, d, E, two_f // 2,
-        _p(d_xp), _p(d_w1), _p(d_w2), dtype_code(d_w1.dtype), int(accumulate), _p(d_topk_w), _p(workspace),
-        workspace.numel() * workspace.element_size(), _stream()))
+    _check("moe_expert_ffn_fused_bwd", _native.moe_expert_ffn_fused_bwd(
+        x, dy, h_save, inv_perm, topk_w, row_w, offsets, w1, w2, T, k, d, E, two_f // 2, d_xp, d_w1, d_w2,
+        dtype_code(d_w1.dtype), int(accumulate), d_topk_w, workspace, workspace.numel() * workspace.element_size()))

@@ -12,6 +12,7 @@ import os
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
+from importlib import metadata
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -19,10 +20,14 @@ OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libmoe_hip.so")
 CEILINGS_SRC = os.path.join(CSRC, "ceilings", "ceilings.hip")       # measurement aids: a library of their own
 CEILINGS_LIB_PATH = os.path.join(HERE, "libmoe_ceilings.so")
+NATIVE_SRC = os.path.join(CSRC, "native", "moe_native.cpp")            # Python entry points (host code)
+NATIVE_PATH = os.path.join(HERE, "_moe_native.so")
 STAMP_PATH = LIB_PATH + ".sha256"      # hash of the sources the library was built from
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CXX = os.environ.get("CXX", "g++")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 COMMON_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed fp32 ALU forms have been unreliable on these boxes: keep the compiler from emitting them
@@ -41,7 +46,8 @@ def source_hash() -> str:
     h = hashlib.sha256(" ".join(COMMON_FLAGS).encode())
     files = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".hip", ".h"))]
     files += [os.path.join(INCLUDE, f) for f in os.listdir(INCLUDE) if f.endswith(".h")]
-    files.append(CEILINGS_SRC)
+    files += [CEILINGS_SRC, NATIVE_SRC]
+    h.update(metadata.version("torch").encode())        # the Python entry points read its tensor objects
     for path in sorted(files):
         h.update(os.path.basename(path).encode())
         with open(path, "rb") as fh:
@@ -51,7 +57,7 @@ def source_hash() -> str:
 
 def is_current() -> bool:
     """True when the library exists and was built from the sources as they are now."""
-    if not (os.path.exists(LIB_PATH) and os.path.exists(CEILINGS_LIB_PATH) and os.path.exists(STAMP_PATH)):
+    if not all(os.path.exists(p) for p in (LIB_PATH, CEILINGS_LIB_PATH, NATIVE_PATH, STAMP_PATH)):
         return False
     with open(STAMP_PATH) as fh:
         return fh.read().strip() == source_hash()
@@ -77,6 +83,33 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _compile_native() -> str:
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    obj = os.path.join(OBJ_DIR, "moe_native.o")
+    cmd = [CXX, "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-isystem", os.path.join(root, "include"),
+           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(ROCM, "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-c", NATIVE_SRC, "-o", obj]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"{CXX} failed on {NATIVE_SRC}:\n{res.stderr}")
+    if res.stderr.strip():
+        sys.stderr.write(res.stderr)
+    return obj
+
+
+def _link_native(obj: str) -> None:
+    import torch
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    res = subprocess.run([CXX, "-shared", "-o", NATIVE_PATH, obj, "-L" + torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10",
+                          "-lc10_hip", "-L" + HERE, "-lmoe_hip", "-Wl,-rpath,$ORIGIN"], capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"link failed:\n{res.stderr}")
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     if os.path.exists(STAMP_PATH):
@@ -84,9 +117,9 @@ def build(verbose: bool = True) -> str:
     stamp = source_hash()
     srcs = sources()
     with ThreadPoolExecutor(max_workers=min(8, len(srcs) + 1)) as pool:
-        ceil_obj = pool.submit(_compile, CEILINGS_SRC)
+        ceil_obj, native_obj = pool.submit(_compile, CEILINGS_SRC), pool.submit(_compile_native)
         objs = list(pool.map(_compile, srcs))
-        ceil_obj = ceil_obj.result()
+        ceil_obj, native_obj = ceil_obj.result(), native_obj.result()
     res = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", CEILINGS_LIB_PATH, ceil_obj],
                          capture_output=True, text=True)
     if res.returncode != 0:
@@ -95,6 +128,7 @@ def build(verbose: bool = True) -> str:
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"link failed:\n{res.stderr}")
+    _link_native(native_obj)
     with open(STAMP_PATH, "w") as fh:
         fh.write(stamp + "\n")
     if verbose:
