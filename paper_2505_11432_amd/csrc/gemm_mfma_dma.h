@@ -483,6 +483,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
 
   // tile state
   int e = 0, m0 = 0, m_end = 0, n0 = 0, klen = 0, nk = 0;
+  int k_start = 0;                  // k-step this workgroup's walk begins at (see issue)
   int part_slot = -1;               // >= 0: this work item is one K part of a split tile; index of its partial tile
   const bool is_loader = !SPLIT || wave < NL;            // wave-uniform; the lower waves win issue arbitration
   const int lw = wave & (NL - 1);                        // loader index
@@ -583,6 +584,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
       klen = min(klen, s1 * BKT) - s0 * BKT;
       nk = s1 - s0;
     }
+    k_start = xcd * nk / XCDS;
     const char* Ag = static_cast<const char*>(p.A);
     const char* Bg = static_cast<const char*>(p.B) + (long)e * p.b_es * ESZ;
     // Base of each operand at the tile's first k (wave-uniform) and this lane's fixed byte offset from it.
@@ -667,10 +669,21 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
     }
     return true;
   };
+  // The small tiles stream the weights, and with every workgroup at the same columns of its rows the requests of a moment
+  // crowd on few memory channels (row strides are multiples of kilobytes).  Each XCD starts its walk over the contraction an
+  // eighth further on and wraps around; within an XCD the workgroups stay together and share the A panel in L2.  Measured
+  // on the 64-row tile (us): 8 experts, 4 rows, FC1 of 4096 x 14336 334 -> 303, FC2 180 -> 167; 64 experts, 32 rows, FC1 of
+  // 2048 x 1408 164 -> 143; 8 experts, 8 rows, FC1 of 2048 x 8192 116 -> 93.  A different start for every workgroup of an XCD
+  // instead: 362, 159, 141, 106.
+  constexpr bool KROT = MODE == ROWSEG && BM <= 128;
   // Issue the loads of k-step `ks` of the open tile into ring slot ks % NSTAGE.  Only the last step can be ragged.
   auto issue = [&](int ks) __attribute__((always_inline)) {
     if (!is_loader) return;
     const unsigned stage = smem_lds + (unsigned)(ks % NSTAGE) * STAGE_BYTES;
+    if constexpr (KROT) {
+      ks += k_start;
+      if (ks >= nk) ks -= nk;
+    }
     const int k_left = klen - ks * BKT;          // valid k in this step
     const char* ab = a_base + (long)ks * a_step;     // scalar arithmetic
     const char* bb = b_base + (long)ks * b_step;
