@@ -584,7 +584,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
       klen = min(klen, s1 * BKT) - s0 * BKT;
       nk = s1 - s0;
     }
-    k_start = xcd * nk / XCDS;
+    k_start = (xcd * 2 + in_window * 2 / window) * nk / (2 * XCDS);
     const char* Ag = static_cast<const char*>(p.A);
     const char* Bg = static_cast<const char*>(p.B) + (long)e * p.b_es * ESZ;
     // Base of each operand at the tile's first k (wave-uniform) and this lane's fixed byte offset from it.
@@ -671,10 +671,10 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
   };
   // The small tiles stream the weights, and with every workgroup at the same columns of its rows the requests of a moment
   // crowd on few memory channels (row strides are multiples of kilobytes).  Each XCD starts its walk over the contraction an
-  // eighth further on and wraps around; within an XCD the workgroups stay together and share the A panel in L2.  Measured
-  // on the 64-row tile (us): 8 experts, 4 rows, FC1 of 4096 x 14336 334 -> 303, FC2 180 -> 167; 64 experts, 32 rows, FC1 of
-  // 2048 x 1408 164 -> 143; 8 experts, 8 rows, FC1 of 2048 x 8192 116 -> 93.  A different start for every workgroup of an XCD
-  // instead: 362, 159, 141, 106.
+  // eighth further on and wraps around, and the second half of its workgroups (other n-tiles, mostly of the same expert) a
+  // sixteenth after that.  Measured on the 64-row tile (us; one start, one per XCD, this): 8 experts, 4 rows, FC1 of 4096 x
+  // 14336 334, 303, 304, FC2 180, 168, 155; 64 experts, 32 rows, FC1 of 2048 x 1408 164, 143, 143; 8 experts, 8 rows, FC1 of
+  // 2048 x 8192 116, 96, 97.  A start of its own for every workgroup of an XCD: 362, 159, 141, 106.
   constexpr bool KROT = MODE == ROWSEG && BM <= 128;
   // Issue the loads of k-step `ks` of the open tile into ring slot ks % NSTAGE.  Only the last step can be ragged.
   auto issue = [&](int ks) __attribute__((always_inline)) {
