@@ -45,7 +45,7 @@ struct Args {
   const uint8_t* a_e8m0; long a_e8_ld;
   const uint8_t* b_e8m0; long b_e8_ld;
   // Split-K for the last, partly filled round of tiles (ROWSEG, bf16 store epilogue only): when the tiles left
-  // after the complete rounds fill at most half of the workgroups, each of them is cut into 2..4 parts along K
+  // after the complete rounds fill at most half of the workgroups, each of them is cut into 2..8 parts along K
   // that run on different workgroups and write fp32 partial tiles here ([part][BM][BN]); splitk_fixup_kernel
   // adds the parts and writes C.  NULL: no splitting.
   float* splitk_ws;

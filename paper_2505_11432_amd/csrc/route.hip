@@ -1,7 +1,7 @@
 // Gating and row map (Section 2.1: top-k gate; Section 3.2 "Efficient operators": the mapping from
 // input rows to output rows is computed once from the routing result; Section 4.2: rows ordered by
 // expert, then by source).  The paper lists the "multitude of small operators" of the gate as a
-// launch-latency straggler (Section 7); here the whole step is three launches and no host read-back:
+// launch-latency straggler (Section 7); here the whole step is two or three launches and no host read-back:
 //   1. route_topk_kernel   per token: k-fold arg-max under the total order (logit desc, id asc) by DPP exchanges
 //                          inside groups of <= 16 lanes (4+ tokens per wave at a time), softmax over the
 //                          selected logits, per-chunk expert histogram

@@ -8,8 +8,8 @@ from tests.gpu_util import DEV
 
 pytestmark = pytest.mark.gpu
 
-# rows per expert: averages up to 32 and up to 96 select the 64- and the 128-row tile; segments end before, on and after tile
-# and 32-row block edges, experts are empty, one expert holds far more than the average
+# rows per expert: averages up to 32 select the 64-row tile, the others (so few tiles) the 128-row one; segments end before, on
+# and after tile and 32-row block edges, experts are empty, one expert holds far more than the average
 ROWS = [[1], [0, 1, 63, 64, 65, 0, 30, 33], [2] * 70, [0, 0, 0, 128], [0, 127, 128, 129, 1, 95], [300, 0, 0, 31], [33, 97],
         [700, 0, 24, 1000]]
 # d, f: several k-steps with remainders, 16-column tails of the 128- and 64-wide tiles, one k-step and less, contractions long
