@@ -21,10 +21,12 @@ namespace moe {
 namespace {
 
 // The total order of the gate as one integer: larger = first.  High word: the logit with -0 made +0 and its bits mapped to
-// an unsigned order; low word: the complement of the expert id (equal logits: lower id first).  Never 0.
+// an unsigned order, a NaN of either sign last (0: below -inf, so that it is selected only when nothing else is left; read
+// back as a NaN); low word: the complement of the expert id (equal logits: lower id first).  Never 0.
 __device__ __forceinline__ unsigned long long order_key(float z, int e) {
   const unsigned b = __float_as_uint(z + 0.0f);
-  return ((unsigned long long)((b >> 31) ? ~b : (b | 0x80000000u)) << 32) | (unsigned)~e;
+  const unsigned high = z != z ? 0u : (b >> 31) ? ~b : (b | 0x80000000u);
+  return ((unsigned long long)high << 32) | (unsigned)~e;
 }
 __device__ __forceinline__ float key_logit(unsigned long long key) {
   const unsigned u = (unsigned)(key >> 32);

@@ -32,6 +32,24 @@ def test_route_edges(T, E, k, quantum):
     assert np.allclose(to_np(got["w"]), ref["w"], rtol=2e-6, atol=1e-7)
 
 
+@pytest.mark.parametrize("T,E,k", [(70, 8, 2), (65, 40, 5), (64, 256, 16)])
+def test_route_nan_last(T, E, k):
+    """A NaN logit (either sign) is selected only when fewer than k others are left; the ids stay valid even then."""
+    from paper_2505_11432_amd import binding as B
+    z = random_logits(T, E, seed=T + E, quantum=0.5)
+    z[1, ::2], z[2, 1::2], z[3, : E - k] = np.nan, -np.nan, np.nan
+    z[4, :], z[5, 1:] = np.nan, np.nan
+    got = {n: to_np(v) for n, v in run_route(B, z, k, 1).items()}
+    # k numbers are left in rows 1 to 3: there a NaN counts as less than everything
+    ref = O.route(np.where(np.isnan(z), np.finfo(np.float32).min, z), k, 1)
+    rows = np.arange(T) != 5                       # (row 4: all equal either way, the lowest ids)
+    assert np.array_equal(got["idx"][rows], ref["idx"][rows]) and np.array_equal(got["idx"][5], np.arange(k))
+    numbers = np.setdiff1d(np.arange(T), [4, 5])
+    assert np.allclose(got["w"][numbers], ref["w"][numbers], rtol=2e-6, atol=1e-7)
+    assert np.array_equal(got["counts"], np.bincount(got["idx"].ravel(), minlength=E))
+    assert np.array_equal(np.sort(got["perm"]), np.arange(T * k))
+
+
 @pytest.mark.parametrize("renorm", [1, 0])
 @pytest.mark.parametrize("T,E,k", [(1, 1, 1), (33, 2, 1), (257, 8, 2), (15, 16, 16), (17, 33, 5), (100, 100, 7), (31, 256, 16)])
 def test_route_bwd_edges(T, E, k, renorm):
