@@ -292,7 +292,7 @@ __global__ void __launch_bounds__(256) route_bwd_kernel(const float* __restrict_
   }
 #pragma unroll
   for (int i = 0; i < VPL; ++i)
-    if (sub + i * G < E) rows[grp * E + sub + i * G] = -p[i] * inner;
+    if (sub + i * G < E) rows[grp * E + sub + i * G] = 0.f - p[i] * inner;      // (no -0 for an expert without a share)
   __syncthreads();
   if ((unsigned)e_j < (unsigned)E) rows[grp * E + e_j] += renorm ? w * dw - w * inner : w * dw;
   __syncthreads();

@@ -66,6 +66,18 @@ def test_route_bwd_edges(T, E, k, renorm):
     assert bool((guard[T * E:] == 9.0).all())
 
 
+def test_route_bwd_zeros_are_positive():
+    from paper_2505_11432_amd import binding as B
+    z = random_logits(40, 24, seed=2)
+    ref = O.route(z, 3, 1)
+    dz = torch.full((40, 24), 9.0, device=DEV)
+    for dw in (np.ones((40, 3), np.float32), -np.ones((40, 3), np.float32)):
+        B.moe_route_bwd(to_dev(z), to_dev(ref["idx"]), to_dev(ref["w"].astype(np.float32)), to_dev(dw), 24, 1, dz)
+        other = np.ones((40, 24), bool)
+        np.put_along_axis(other, ref["idx"].astype(np.int64), False, axis=1)
+        assert not to_np(dz)[other].any() and not np.signbit(to_np(dz)[other]).any()
+
+
 @pytest.mark.parametrize("T,d,E", [(1, 8, 1), (16, 64, 16), (17, 72, 17), (100, 2048, 64), (15, 4104, 8), (2049, 520, 64), (8176, 16, 16),
                                    (8193, 16, 16), (40, 1000, 256)])      # 512 tiles and more: the other kernel
 def test_router_fwd_edges(T, d, E):
