@@ -404,13 +404,19 @@ int launch_quant_fp8(const void* src, moe_dtype src_dt, int rows, int cols, moe_
     const int nvec = cols / (16 / (int)dtype_size(src_dt));
     const bool wide = nvec > 256 * 8;                    // more vectors than 256 threads can hold
     if (nvec <= 64 * 8) {
-      const int waves = cdiv(rows, 4);
-#define MOE_WAVE_ROWS(TT)                                                                                              \
-  if (nvec <= 64 * 2) quant_rows_wave_kernel<TT, 2><<<waves, 256, 0, s>>>((const TT*)src, rows, cols, codes, scales);  \
-  else if (nvec <= 64 * 4) quant_rows_wave_kernel<TT, 4><<<waves, 256, 0, s>>>((const TT*)src, rows, cols, codes, scales); \
-  else quant_rows_wave_kernel<TT, 8><<<waves, 256, 0, s>>>((const TT*)src, rows, cols, codes, scales);
-      if (src_dt == MOE_F32) { MOE_WAVE_ROWS(float) } else { MOE_WAVE_ROWS(bf16) }
+      constexpr int kMaxRows = 1 << 25;                  // per launch, which holds less than 2^32 threads
+      for (long r0 = 0; r0 < rows; r0 += kMaxRows) {
+        const int n = rows - r0 < kMaxRows ? (int)(rows - r0) : kMaxRows, waves = cdiv(n, 4);
+        uint8_t* const c = codes + r0 * cols;
+#define MOE_WAVE_ROWS(TT)                                                                                      \
+  const TT* const p = (const TT*)src + r0 * cols;                                                              \
+  if (nvec <= 64 * 2) quant_rows_wave_kernel<TT, 2><<<waves, 256, 0, s>>>(p, n, cols, c, scales + r0);         \
+  else if (nvec <= 64 * 4) quant_rows_wave_kernel<TT, 4><<<waves, 256, 0, s>>>(p, n, cols, c, scales + r0);    \
+  else quant_rows_wave_kernel<TT, 8><<<waves, 256, 0, s>>>(p, n, cols, c, scales + r0);
+        if (src_dt == MOE_F32) { MOE_WAVE_ROWS(float) } else { MOE_WAVE_ROWS(bf16) }
 #undef MOE_WAVE_ROWS
+        MOE_LAUNCH_CHECK();
+      }
     } else if (src_dt == MOE_F32) {
       if (wide) quant_rows_kernel<float, 1024><<<grid, 1024, 0, s>>>((const float*)src, rows, cols, codes, scales);
       else quant_rows_kernel<float, 256><<<grid, 256, 0, s>>>((const float*)src, rows, cols, codes, scales);

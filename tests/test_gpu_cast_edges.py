@@ -69,3 +69,20 @@ def test_tgroup_cast_short_segments(dtype):
             assert np.array_equal(got_c[:, c0:c0 + want.shape[1]], want)
             assert not got_c[:, c0 + want.shape[1]:c0 + 128].any()
             assert np.array_equal(got_e[c0 // 128], (k + 127).astype(np.uint8))
+
+
+def test_row_cast_of_many_rows():
+    """More rows than one launch of a wave per row can take (2^26: a launch holds less than 2^32 threads), 16 bf16 columns."""
+    from paper_2505_11432_amd import binding as B
+    rows, cols = 2 ** 26 + 5, 16
+    part = torch.randn((4099, cols), generator=torch.Generator(device=DEV).manual_seed(1), device=DEV).bfloat16()
+    src = torch.empty((rows, cols), dtype=torch.bfloat16, device=DEV)
+    whole = rows // 4099 * 4099
+    src[:whole].view(-1, 4099, cols).copy_(part.expand(whole // 4099, -1, -1))
+    src[whole:] = part[:rows - whole]
+    codes, scales = torch.empty((rows, cols), dtype=torch.uint8, device=DEV), torch.empty((rows,), device=DEV)
+    want_c, want_s = torch.empty((4099, cols), dtype=torch.uint8, device=DEV), torch.empty((4099,), device=DEV)
+    B.moe_quant_fp8(part, B.Q_ROW, want_c, want_s)
+    B.moe_quant_fp8(src, B.Q_ROW, codes, scales)
+    assert bool((codes[:whole].view(-1, 4099, cols) == want_c).all()) and bool((scales[:whole].view(-1, 4099) == want_s).all())
+    assert torch.equal(codes[whole:], want_c[:rows - whole]) and torch.equal(scales[whole:], want_s[:rows - whole])
