@@ -564,8 +564,13 @@ int launch_route(const float* logits, int T, int E, int k, int renorm, int e_lo,
 int launch_route_bwd(const float* logits, const int32_t* idx, const float* w, const float* dw, int T, int E, int k,
                      int renorm, float* d_logits, hipStream_t s) {
   return with_group(E, [&](auto g, auto v) -> int {
-    route_bwd_kernel<g.value, v.value><<<cdiv(T, 256 / g.value), 256, 0, s>>>(logits, idx, w, dw, T, E, k, renorm, d_logits);
-    MOE_LAUNCH_CHECK();
+    constexpr int kMaxTokens = 1 << 27;        // per launch, which holds less than 2^32 threads (up to 16 of them per token)
+    for (long t = 0; t < T; t += kMaxTokens) {
+      const int n = T - t < kMaxTokens ? (int)(T - t) : kMaxTokens;
+      route_bwd_kernel<g.value, v.value><<<cdiv(n, 256 / g.value), 256, 0, s>>>(logits ? logits + t * E : nullptr, idx + t * k, w + t * k,
+                                                                                dw + t * k, n, E, k, renorm, d_logits + t * E);
+      MOE_LAUNCH_CHECK();
+    }
     return MOE_OK;
   });
 }

@@ -78,6 +78,32 @@ def test_route_bwd_zeros_are_positive():
         assert not to_np(dz)[other].any() and not np.signbit(to_np(dz)[other]).any()
 
 
+@pytest.mark.parametrize("renorm", [1, 0])
+def test_route_bwd_of_many_tokens(renorm):
+    """More tokens than one launch of 16 threads each can take (2^28: a launch holds less than 2^32 threads): 22 GB."""
+    from paper_2505_11432_amd import binding as B
+    T, E, k, n = 2 ** 28 + 3, 9, 1, 4099
+    g = torch.Generator(device=DEV).manual_seed(renorm)
+    whole = T // n * n
+
+    def spread(part):
+        out = torch.empty((T,) + part.shape[1:], dtype=part.dtype, device=DEV)
+        out[:whole].view((-1, n) + part.shape[1:]).copy_(part.expand((whole // n,) + part.shape))
+        out[whole:] = part[:T - whole]
+        return out
+
+    z, w, dw = (torch.rand(s, generator=g, device=DEV) for s in ((n, E), (n, k), (n, k)))
+    idx = torch.randint(0, E, (n, k), generator=g, device=DEV, dtype=torch.int32)
+    want = torch.empty((n, E), device=DEV)
+    B.moe_route_bwd(z, idx, w, dw, E, renorm, want)
+    got = torch.full((T, E), 9.0, device=DEV)
+    B.moe_route_bwd(None if renorm else spread(z), spread(idx), spread(w), spread(dw), E, renorm, got)
+    step = n * 4096
+    for a in range(0, whole, step):
+        assert bool((got[a:min(a + step, whole)].view(-1, n, E) == want).all()), a
+    assert torch.equal(got[whole:], want[:T - whole])
+
+
 @pytest.mark.parametrize("T,d,E", [(1, 8, 1), (16, 64, 16), (17, 72, 17), (100, 2048, 64), (15, 4104, 8), (2049, 520, 64), (8176, 16, 16),
                                    (8193, 16, 16), (40, 1000, 256)])      # 512 tiles and more: the other kernel
 def test_router_fwd_edges(T, d, E):
