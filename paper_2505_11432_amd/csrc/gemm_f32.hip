@@ -257,13 +257,15 @@ bool gemm_f32_covers(const GemmProblem& p) {
 // k-steps.  Fewer 64 x 64 tiles than CUs: 32 x 32 (512 rows of 8 experts, N = 512, K = 1408: 21 us against 26 with
 // 64 x 32 and 36 with 64 x 64).  Up to four per CU the last round of tiles is what counts: 64 x 32 (560 tiles, K = 2816:
 // 135 us against 152).  Beyond that 64 x 64 where an operand is read across its rows (1408 tiles: 114 us against 127),
-// 64 x 32 still where both are read along k (2816 tiles: 238 us against 262).
+// 64 x 32 still where both are read along k (2816 tiles: 238 us against 262), unless a launch could not hold its workgroups
+// (less than 2^32 threads).
 int launch_gemm_f32(const GemmProblem& p, hipStream_t s) {
   const bool a_kfast = p.a_cs == 1, b_kfast = p.b_rs == 1;
   const long tiles_m = (long)cdiv(p.M, 64) + (p.mode == 0 ? p.E / 2 : 0);      // segments end inside a tile
   const long tiles = (long)cdiv(p.N, 64) * tiles_m * (p.mode == 1 ? p.E : 1);
   if (tiles < 256) return launch<32, 32, 64, 1, 1, 4>(p, a_kfast, b_kfast, s);
-  if (tiles < 1024 || b_kfast) return launch<64, 32, 32, 2, 1, 2>(p, a_kfast, b_kfast, s);
+  const long narrow = (long)cdiv(p.N, 32) * (cdiv(p.M, 64) + (p.mode == 0 ? (long)p.E : 0)) * (p.mode == 1 ? p.E : 1);      // 64 x 32 workgroups
+  if (tiles < 1024 || (b_kfast && narrow * kThreads < 1L << 32)) return launch<64, 32, 32, 2, 1, 2>(p, a_kfast, b_kfast, s);
   return launch<64, 64, 32, 2, 2, 1>(p, a_kfast, b_kfast, s);
 }
 

@@ -73,3 +73,22 @@ def test_router_f32_edges(T, d, E):
     B.moe_router_fwd(x, w, bias, z)
     ref = x.double() @ w.double().t() + bias.double()
     assert rel(z, ref) < 3 * math.sqrt(d) * 2.0 ** -24 + 2.0 ** -23
+
+
+def test_router_f32_of_many_tokens():
+    """More tokens than one launch of 64 x 32 tiles can take (2^29 with 33 to 64 experts: a launch holds less than 2^32 threads)."""
+    from paper_2505_11432_amd import binding as B
+    T, d, E, n = 2 ** 29 + 65, 4, 33, 2 ** 16
+    if torch.cuda.mem_get_info()[0] < 90e9:
+        pytest.skip("needs 80 GB")
+    g = torch.Generator(device=DEV).manual_seed(0)
+    part, w = (torch.randint(-4, 5, s, generator=g, device=DEV).float() for s in ((n, d), (E, d)))      # exact sums
+    want = (part.double() @ w.double().t()).float()
+    x, z = torch.empty((T, d), device=DEV), torch.empty((T, E), device=DEV)
+    whole = T // n * n
+    x[:whole].view(-1, n, d).copy_(part.expand(whole // n, -1, -1))
+    x[whole:] = part[:T - whole]
+    B.moe_router_fwd(x, w, None, z)
+    for a in range(0, whole, 64 * n):
+        assert bool((z[a:a + 64 * n][:min(64 * n, whole - a)].view(-1, n, E) == want).all()), a
+    assert torch.equal(z[whole:], want[:T - whole])
