@@ -60,11 +60,11 @@ class MoEError(RuntimeError):
 
 def _load() -> ctypes.CDLL:
     from . import build as _build
-    if not _build.is_current():
+    if not (_build.is_current() and _build.native_is_current()):
         # missing, or built from other sources than the ones in the tree: never load a stale library
         import sys
-        sys.stderr.write(f"{LIB_PATH} is missing or older than its sources: building it\n")
-        _build.build(verbose=False)
+        sys.stderr.write(f"{LIB_PATH} or its Python entry points are missing or older than their sources: building them\n")
+        _build.ensure_built()
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is not built; run `python -m paper_2505_11432_amd.build` "
                           "(there is no fallback path)")
