@@ -5,6 +5,7 @@
 #include <vector>
 
 #include "gemm_mfma_dma.h"
+#include "row_plan.h"
 
 namespace moe {
 namespace {
@@ -100,67 +101,15 @@ int launch(const Args& a, long tiles_upper_bound, hipStream_t s) {
   return MOE_OK;
 }
 
-// Tile of the row-segmented kernels.  The host knows the bound M on the rows and E, not the segments (any segments are
-// correct with any tile), so the choice goes by the average: max(E, M / rows-of-a-tile + E / 2) row tiles.
-//   FEW, up to 32 rows per expert: the launch is a stream over the weights.  64 x 128 tiles, 256 bytes of every row per
-//     k-step in three stages: 96 KB of weights in flight per CU instead of at most 64, four to eight times the tiles to deal
-//     out, and quarter-size A tiles.
-//   FULL, 256 x 256: the tile for arithmetic, 1.3 times the rate of the next on a filled chip.
-//   MID, 128 x 128 in three stages of eight waves: where FULL leaves CUs idle: fewer tiles than CUs, or a second round for
-//     a few.  A tile is a quarter of the work in a third of the time.
-// Between FULL and MID the estimated time of the rounds decides, from measured tile times: FULL 13 us + 1.5 per 128-byte
-// k-step, MID 6 + 0.58 (0.66 where the weights are read across their rows and only stored), plus the epilogue's share; a
-// split last round costs 18 or 9 us for writing and adding the parts.
-// Measured, FC1 + SwiGLU / FC2 without split (us; FULL, MID, FEW), weights from memory:
-//   8 experts, 4096 x 14336:   4 rows 431/322, -, 333/179;       128 rows 533/383, 450/317, -;  256 rows 648/333, 781/429, -
-//   64 experts, 2048 x 1408:  32 rows 201/88, -, 165/73;          64 rows 214/94, 185/85, 181/92; 128 rows 215/95, 228/110, -
-//   24 experts, 1040 x 1424:  62 rows 70/42, 54/23, -;           191 rows 85/49, 79/40, -;      375 rows 113/47, 116/58, -
-//   8 experts, 1024 x 2816:  250 rows 59/59, 51/28, -;           500 rows 71/72, 79/50, -
-enum class RowTile { FEW, MID, FULL };
-struct RowPlan { RowTile tile; bool split; };        // split: the last round's tiles may be cut along K
-
-struct TileCost { double fixed, step, cut_step, cut; };      // us: per tile, per k-step, per k-step of a cut tile, for cutting
-
-double rounds_us(double tiles, const TileCost& c, int steps, bool split) {
-  const double cus = 256, whole = (double)(long)(tiles / cus), rem = tiles - whole * cus;
-  const double tile_us = c.fixed + c.step * steps;
-  if (rem < 1) return whole * tile_us;
-  double last = tile_us;
-  if (split && rem <= cus / 2) {
-    const double s = cus / rem < 8 ? (double)(long)(cus / rem) : 8;
-    const double cut = c.fixed + c.cut_step * steps / s + c.cut;
-    last = cut < last ? cut : last;
-  }
-  return whole * tile_us + last;
-}
-
-// N: output columns (SwiGLU: f); K in elements of esz bytes
-template <Layout LB, Epi EPI> RowPlan plan_rows(int M, int E, int N, int K, int esz) {
-  constexpr bool SWI = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_W, STORE = EPI == EPI_STORE;
-  const long rows = (long)M / E;
-  const int steps = cdiv(K * esz, 128);
-  // Cutting pays from here on: the steps it takes off the last round against the parts' way through memory and a launch
-  // (8 experts, 52 to 104 tiles of 256 x 256: 16 steps -2 to -4 us, 22 steps 0, 32 steps +4 to +9, 64 steps +23 to +37).
-  if (rows <= 32) return {RowTile::FEW, STORE && steps >= 16};
-  const bool split_full = STORE && steps >= 28, split_mid = STORE && steps >= 40;
-  auto tiles = [&](int bm, int bn) {
-    const double mt = (double)M / bm + 0.5 * E;
-    return (mt > E ? mt : E) * cdiv(N, bn);
-  };
-  constexpr double epi = STORE ? 0 : SWI ? 2 : 15;        // over the plain store of a FULL tile
-  // FC1 with one row tile per expert: nobody shares a weight panel and the FULL step waits for memory
-  const TileCost full = {13 + epi, SWI && rows < 192 ? 1.8 : 1.5, 1.7, 18};
-  constexpr double mid_step = STORE && LB == MNMAJOR ? 0.66 : 0.58;
-  const TileCost mid = {6 + epi / 3, mid_step, mid_step, 9};
-  return rounds_us(tiles(128, SWI ? 64 : 128), mid, steps, split_mid) < rounds_us(tiles(256, SWI ? 128 : 256), full, steps, split_full)
-             ? RowPlan{RowTile::MID, split_mid} : RowPlan{RowTile::FULL, split_full};
+template <Layout LB, Epi EPI> RowPlan plan_for(int M, int E, int N, int K, int esz) {
+  return plan_rows({EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_W, EPI == EPI_STORE, LB == MNMAJOR}, M, E, N, K, esz);
 }
 
 template <Layout LB, Epi EPI, typename TIN = bf16>
 int launch_rowseg(Args a, hipStream_t s) {
   constexpr int B128 = 128 / (int)sizeof(TIN);        // elements in 128 bytes
   if (a.M <= 0 || a.N <= 0) return MOE_OK;
-  const RowPlan plan = plan_rows<LB, EPI>(a.M, a.E, a.N, a.K, (int)sizeof(TIN));
+  const RowPlan plan = plan_for<LB, EPI>(a.M, a.E, a.N, a.K, (int)sizeof(TIN));
   if (!plan.split) a.splitk_ws = nullptr;
   switch (plan.tile) {
     case RowTile::FEW: return launch<64, 128, 2 * B128, 3, 2, 2, KMAJOR, LB, ROWSEG, EPI, bf16, TIN>(a, 1, s);
@@ -233,7 +182,7 @@ int mfma_dgrad2_swiglu_bwd(const void* d_yp, const void* w2, const int32_t* offs
 // row's weight is applied downstream), A_out = w_r * A, and dw_part [mfma_dgrad2_fold_parts(M, d, E, f)][M] the partial sums
 // of <dA'[r,:], A[r,:]>: one per n-tile and wave along n
 int mfma_dgrad2_fold_parts(int M, int d, int E, int f) {
-  return plan_rows<MNMAJOR, EPI_SWIGLU_BWD_W>(M, E, f, d, 2).tile == RowTile::FULL ? cdiv(f, 256) * 4 : cdiv(f, 128) * 2;
+  return plan_for<MNMAJOR, EPI_SWIGLU_BWD_W>(M, E, f, d, 2).tile == RowTile::FULL ? cdiv(f, 256) * 4 : cdiv(f, 128) * 2;
 }
 int mfma_dgrad2_swiglu_bwd_fold(const void* d_yp, const void* w2, const int32_t* offsets, int M, int d, int E, int f,
                                 const void* H, void* dH, void* A_out, const float* row_w, float* dw_part, hipStream_t s) {

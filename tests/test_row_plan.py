@@ -1,0 +1,69 @@
+"""Choice of the row tile (csrc/row_plan.h, host code): compiled on its own and asked about sizes."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2505_11432_amd import build
+
+MAIN = r'''
+#include <cstdio>
+#include "row_plan.h"
+int main() {
+  int swiglu, store, across, M, E, N, K, esz;
+  while (scanf("%d %d %d %d %d %d %d %d", &swiglu, &store, &across, &M, &E, &N, &K, &esz) == 8) {
+    const moe::RowPlan p = moe::plan_rows({swiglu != 0, store != 0, across != 0}, M, E, N, K, esz);
+    printf("%s %d\n", p.tile == moe::RowTile::FEW ? "few" : p.tile == moe::RowTile::MID ? "mid" : "full", (int)p.split);
+  }
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("plan")
+    src, exe = tmp / "main.cpp", tmp / "main"
+    src.write_text(MAIN)
+    subprocess.run([build.CXX, "-std=c++17", "-I", build.CSRC, str(src), "-o", str(exe)], check=True)
+
+    def ask(rows):
+        text = "\n".join(" ".join(map(str, r)) for r in rows)
+        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
+        return [(l.split()[0], l.split()[1] == "1") for l in out if l]
+    return ask
+
+
+FC1, FC2, DGRAD2, DGRAD1 = (1, 0, 0), (0, 1, 0), (0, 0, 1), (0, 1, 1)
+
+
+def gemms(M, E, d, f):
+    return [FC1 + (M, E, f, d, 2), FC2 + (M, E, d, f, 2), DGRAD2 + (M, E, f, d, 2), DGRAD1 + (M, E, d, 2 * f, 2)]
+
+
+def test_few_rows_stream_the_weights(plan):
+    """A handful of rows: the 64-row tile for all four products (a round of it lasts less than one of the large tile)."""
+    for M, E, d, f in ((1, 1, 16, 16), (32, 8, 4096, 14336), (64, 64, 2048, 1408), (512, 16, 4096, 1536), (576, 24, 1040, 1424)):
+        assert [t for t, _ in plan(gemms(M, E, d, f))] == ["few"] * 4, (M, E, d, f)
+    assert [t for t, _ in plan(gemms(2056, 64, 2048, 1408))[:2]] == ["few"] * 2
+
+
+def test_no_small_tile_where_gathered_rows_would_be_slow(plan):
+    """Averages of 32 rows and less whose sum, gathered on one expert, keeps the 64-row tile busy for several rounds of which
+    the large tile needs one."""
+    for M, E, d, f in ((8192, 256, 1024, 1024), (8192, 256, 2048, 1408), (4096, 128, 2048, 2048), (512, 16, 4096, 14336)):
+        assert plan([FC1 + (M, E, f, d, 2)])[0][0] == "mid", (M, E, d, f)
+    for M in range(64, 33000, 64):
+        E = (M + 31) // 32
+        if E <= 256:
+            (t, _), = plan([FC1 + (M, E, 2048, 2048, 2)])
+            # rounds of 64 x 64 outputs in 17.8 us each against rounds of 256 x 128 in 72.6
+            few, full = -(-(M // 64 * 32) // 256) * 17.8, -(-(-(-M // 256) * 16) // 256) * 72.6
+            assert (t == "few") == (few <= full + 1e-6), (M, t, few, full)
+
+
+def test_ordinary_sizes(plan):
+    assert [t for t, _ in plan(gemms(16384, 8, 4096, 14336))] == ["full"] * 4
+    assert [t for t, _ in plan(gemms(131072, 64, 2048, 1408))] == ["full"] * 4
+    assert [t for t, _ in plan(gemms(4593, 24, 1040, 1424))] == ["mid", "mid", "full", "mid"]
+    assert plan([FC2 + (16384, 8, 4096, 14336, 2)]) == [("full", True)]
+    assert not any(s for _, s in plan([k + (M, 8, 4096, 4096, 2) for k in (FC1, DGRAD2) for M in (16, 600, 9000)]))
