@@ -34,8 +34,8 @@ static bool sizes_ok(int T, int d, int E, int k, int f) {
          (long)T * k <= 0x7fffffffL;
 }
 
-static int ffn_fwd_plain(const void* xp, const int32_t* offsets, const void* w1, const void* w2, moe_dtype dt, int M,
-                         int d, int E, int f, void* h_save, void* yp, void* ws, hipStream_t s) {
+static int ffn_fwd_f32(const void* xp, const int32_t* offsets, const void* w1, const void* w2, int M, int d, int E, int f,
+                       void* h_save, void* yp, void* ws, hipStream_t s) {
   void* A = ws;
   GemmProblem g{};
   g.offsets = offsets; g.E = E; g.mode = 0; g.M = M; g.accumulate = 0; g.bias = nullptr;
@@ -43,15 +43,15 @@ static int ffn_fwd_plain(const void* xp, const int32_t* offsets, const void* w1,
   g.A = xp; g.a_rs = d; g.a_cs = 1;
   g.B = w1; g.b_es = 2L * f * d; g.b_rs = 1; g.b_cs = d;
   g.C = h_save; g.c_es = 0; g.ldc = 2L * f; g.N = 2 * f; g.K = d;
-  int rc = launch_gemm_generic(g, dt, dt, dt, s);
+  int rc = launch_gemm_f32(g, s);
   if (rc != MOE_OK) return rc;
-  rc = launch_swiglu_fwd(h_save, A, M, f, offsets + E, dt, s);
+  rc = launch_swiglu_fwd(h_save, A, M, f, offsets + E, MOE_F32, s);
   if (rc != MOE_OK) return rc;
   // FC2: yp[M,d] = A[M,f] * w2[e]^T
   g.A = A; g.a_rs = f; g.a_cs = 1;
   g.B = w2; g.b_es = (long)d * f; g.b_rs = 1; g.b_cs = f;
   g.C = yp; g.ldc = d; g.N = d; g.K = f;
-  return launch_gemm_generic(g, dt, dt, dt, s);
+  return launch_gemm_f32(g, s);
 }
 
 // bf16: every GEMM on the matrix cores, SwiGLU and its derivative fused into the FC1 / dgrad2 epilogues.
@@ -105,11 +105,10 @@ static int ffn_bwd_bf16(const void* xp, const void* h_save, const void* d_yp, co
   return mfma_wgrad(dH, xp, offsets, 2 * f, d, E, d_w1, grad_dt, accumulate, s);
 }
 
-static int ffn_bwd_plain(const void* xp, const void* h_save, const void* d_yp, const void* a_override,
-                         const int32_t* offsets, const void* w1, const void* w2, moe_dtype dt, int M, int d, int E,
-                         int f, void* d_xp, void* d_w1, void* d_w2, moe_dtype grad_dt, int accumulate, void* ws,
-                         hipStream_t s) {
-  const size_t es = dtype_size(dt);
+static int ffn_bwd_f32(const void* xp, const void* h_save, const void* d_yp, const void* a_override, const int32_t* offsets,
+                       const void* w1, const void* w2, int M, int d, int E, int f, void* d_xp, void* d_w1, void* d_w2,
+                       int accumulate, void* ws, hipStream_t s) {
+  const size_t es = sizeof(float);
   char* base = static_cast<char*>(ws);
   void* A = base;
   void* dA = base + align_up((size_t)M * f * es, 256);
@@ -123,30 +122,30 @@ static int ffn_bwd_plain(const void* xp, const void* h_save, const void* d_yp, c
   g.A = d_yp; g.a_rs = d; g.a_cs = 1;
   g.B = w2; g.b_es = (long)d * f; g.b_rs = f; g.b_cs = 1;
   g.C = dA; g.c_es = 0; g.ldc = f; g.N = f; g.K = d;
-  rc = launch_gemm_generic(g, dt, dt, dt, s);
+  rc = launch_gemm_f32(g, s);
   if (rc != MOE_OK) return rc;
-  rc = launch_swiglu_bwd(h_save, dA, dH, a_override ? nullptr : A, M, f, offsets + E, dt, s);   // recomputes the FC2 input
+  rc = launch_swiglu_bwd(h_save, dA, dH, a_override ? nullptr : A, M, f, offsets + E, MOE_F32, s);   // recomputes the FC2 input
   if (rc != MOE_OK) return rc;
   // d_w2[e][d,f] = d_yp_e^T * A_e   (contraction over the expert's rows)
   g.mode = 1; g.accumulate = accumulate;
   g.A = d_yp; g.a_rs = 1; g.a_cs = d;
   g.B = A_used; g.b_es = 0; g.b_rs = f; g.b_cs = 1;
   g.C = d_w2; g.c_es = (long)d * f; g.ldc = f; g.M = d; g.N = f; g.K = M;
-  rc = launch_gemm_generic(g, dt, dt, grad_dt, s);
+  rc = launch_gemm_f32(g, s);
   if (rc != MOE_OK) return rc;
   // d_xp[M,d] = dH[M,2f] * w1[e]   (contraction over 2f)
   g.mode = 0; g.accumulate = 0;
   g.A = dH; g.a_rs = 2L * f; g.a_cs = 1;
   g.B = w1; g.b_es = 2L * f * d; g.b_rs = d; g.b_cs = 1;
   g.C = d_xp; g.c_es = 0; g.ldc = d; g.M = M; g.N = d; g.K = 2 * f;
-  rc = launch_gemm_generic(g, dt, dt, dt, s);
+  rc = launch_gemm_f32(g, s);
   if (rc != MOE_OK) return rc;
   // d_w1[e][2f,d] = dH_e^T * xp_e
   g.mode = 1; g.accumulate = accumulate;
   g.A = dH; g.a_rs = 1; g.a_cs = 2L * f;
   g.B = xp; g.b_es = 0; g.b_rs = d; g.b_cs = 1;
   g.C = d_w1; g.c_es = 2L * f * d; g.ldc = d; g.M = 2 * f; g.N = d; g.K = M;
-  return launch_gemm_generic(g, dt, dt, grad_dt, s);
+  return launch_gemm_f32(g, s);
 }
 
 }  // namespace moe
@@ -204,7 +203,8 @@ int moe_router_fwd(const void* x, const void* w_r, const float* bias, moe_dtype 
   g.A = x; g.a_rs = d; g.a_cs = 1;
   g.B = w_r; g.b_es = 0; g.b_rs = 1; g.b_cs = d;
   g.C = logits; g.c_es = 0; g.ldc = E; g.M = T; g.N = E; g.K = d;
-  return launch_gemm_generic(g, dt, dt, MOE_F32, as_stream(stream));
+  if (dt == MOE_F32 && gemm_f32_covers(g)) return launch_gemm_f32(g, as_stream(stream));
+  return launch_router_any(x, w_r, bias, dt, T, d, E, logits, as_stream(stream));
 }
 
 int moe_router_bwd(const void* x, const void* w_r, const float* d_logits, moe_dtype dt, int T, int d, int E,
@@ -364,7 +364,7 @@ int moe_expert_ffn_fwd(const void* xp, const float* xp_scale, moe_dtype act_dt, 
   }
   if (act_dt == MOE_BF16)
     return ffn_fwd_bf16(xp, offsets, w1, w2, M, d, E, f, h_save, yp, a_codes_out, workspace, as_stream(stream));
-  return ffn_fwd_plain(xp, offsets, w1, w2, act_dt, M, d, E, f, h_save, yp, workspace, as_stream(stream));
+  return ffn_fwd_f32(xp, offsets, w1, w2, M, d, E, f, h_save, yp, workspace, as_stream(stream));
 }
 
 int moe_expert_ffn_bwd(const void* xp, const void* h_save, const void* d_yp, const void* a_override,
@@ -385,8 +385,8 @@ int moe_expert_ffn_bwd(const void* xp, const void* h_save, const void* d_yp, con
   if (dt == MOE_BF16)
     return ffn_bwd_bf16(xp, h_save, d_yp, a_override, offsets, w1, w2, M, d, E, f, d_xp, d_w1, d_w2, grad_dt,
                         accumulate != 0, workspace, as_stream(stream));
-  return ffn_bwd_plain(xp, h_save, d_yp, a_override, offsets, w1, w2, dt, M, d, E, f, d_xp, d_w1, d_w2, grad_dt,
-                       accumulate != 0, workspace, as_stream(stream));
+  return ffn_bwd_f32(xp, h_save, d_yp, a_override, offsets, w1, w2, M, d, E, f, d_xp, d_w1, d_w2, accumulate != 0, workspace,
+                     as_stream(stream));
 }
 
 // ---- Section 4.1 / 4.2 operator order (bf16) ---------------------------------------------------------------

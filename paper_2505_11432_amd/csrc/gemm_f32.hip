@@ -1,5 +1,6 @@
-// Grouped GEMM on fp32 data with the fp32 matrix instruction (v_mfma_f32_32x32x2_f32): the same contract as the
-// vector-ALU kernel of gemm_generic.hip, for operands whose rows or columns can be read in whole 16-byte pieces.
+// Grouped GEMM on fp32 data with the fp32 matrix instruction (v_mfma_f32_32x32x2_f32), for operands whose rows or columns
+// can be read in whole 16-byte pieces: the expert products (widths are multiples of 16, buffers 16-byte aligned) and
+// router logits of such rows.
 //
 // Bound: the fp32 matrix rate, 256 FLOP per clock and CU, twice what unpacked fp32 FMAs give.  One instruction takes 64
 // clocks for 4 KFLOP, so the operands are cheap to feed and small tiles are affordable; what matters is that loads are
@@ -8,7 +9,7 @@
 //   64 x 64, k-steps of 32;  64 x 32, two waves per output, k-steps of 32;  32 x 32, four per output, k-steps of 64.
 // All keep two k-steps of global loads in registers ahead of the LDS stage that is being multiplied; several workgroups
 // share a CU and hide each other's latency.
-// Measured (8 experts, 2000 rows, d = 1024, f = 2816; the vector-ALU kernel first): FC1 492 -> 238 us (97 TFLOP/s), FC2
+// Measured (8 experts, 2000 rows, d = 1024, f = 2816; a vector-ALU kernel of 64 x 64 x 16 first): FC1 492 -> 238 us (97 TFLOP/s), FC2
 // 601 -> 135, dgrad2 267 -> 114, dgrad1 1383 -> 265, wgrad2 211 -> 118, wgrad1 416 -> 228; router logits of 1000 tokens
 // 182 -> 13 us.  8192 x 4096 x 2048 in four experts: 110 TFLOP/s.
 #include "moe_common.h"
@@ -260,6 +261,7 @@ bool gemm_f32_covers(const GemmProblem& p) {
 // 64 x 32 still where both are read along k (2816 tiles: 238 us against 262), unless a launch could not hold its workgroups
 // (less than 2^32 threads).
 int launch_gemm_f32(const GemmProblem& p, hipStream_t s) {
+  if (p.M <= 0 || p.N <= 0) return MOE_OK;
   const bool a_kfast = p.a_cs == 1, b_kfast = p.b_rs == 1;
   const long tiles_m = (long)cdiv(p.M, 64) + (p.mode == 0 ? p.E / 2 : 0);      // segments end inside a tile
   const long tiles = (long)cdiv(p.N, 64) * tiles_m * (p.mode == 1 ? p.E : 1);

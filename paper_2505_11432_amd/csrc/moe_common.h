@@ -58,7 +58,7 @@ __device__ __forceinline__ float sigmoid_f32(float g) {
 template <typename T> struct Vec16 { static constexpr int N = 16 / sizeof(T); T v[16 / sizeof(T)]; };
 
 // ---- kernel launchers (one per translation unit) -------------------------------------------
-// Generic strided grouped GEMM on the vector ALU (fp32 FMA); covers fp32 data and odd shapes.
+// Grouped GEMM on fp32 data (gemm_f32.hip).
 struct GemmProblem {
   const void* A; long a_rs, a_cs;            // A(m,k) = A[m*a_rs + k*a_cs]
   const void* B; long b_es, b_rs, b_cs;      // B(e,k,n) = B[e*b_es + k*b_rs + n*b_cs]
@@ -69,9 +69,7 @@ struct GemmProblem {
   int accumulate;                            // C += instead of C =
   const float* bias;                         // per-column fp32 bias added in the epilogue, or NULL
 };
-int launch_gemm_generic(const GemmProblem& p, moe_dtype a_dt, moe_dtype b_dt, moe_dtype c_dt, hipStream_t s);
-// The same on the fp32 matrix instruction, for fp32 operands that can be read in 16-byte pieces (gemm_f32.hip).
-bool gemm_f32_covers(const GemmProblem& p);
+bool gemm_f32_covers(const GemmProblem& p);      // the operands can be read in 16-byte pieces; launch_gemm_f32 needs that
 int launch_gemm_f32(const GemmProblem& p, hipStream_t s);
 
 int launch_route(const float* logits, int T, int E, int k, int renorm, int e_lo, int e_hi, int n_groups, int capacity,
@@ -138,6 +136,8 @@ int mfma_wgrad_fp8(const void* Pt, const uint8_t* p_e8m0, const void* Qt, const 
 // router_fwd_small: problems that launch_router_fwd_small is the faster one for (router_fwd.hip)
 bool router_fwd_small(int T, int E);
 int launch_router_fwd_small(const void* x, const void* w_r, const float* bias, int T, int d, int E, float* logits, hipStream_t s);
+// rows of any length and alignment, fp32 or bf16 (router_any.hip)
+int launch_router_any(const void* x, const void* w_r, const float* bias, moe_dtype dt, int T, int d, int E, float* logits, hipStream_t s);
 int mfma_router_fwd(const void* x, const void* w_r, const float* bias, int T, int d, int E, float* logits,
                     hipStream_t s);
 // partial[c][E][d] (+)= g[tokens of chunk c, E]^T * x[tokens of chunk c, d], g and x bf16, chunk_offsets [chunks+1]

@@ -120,6 +120,24 @@ def test_router_fwd_edges(T, d, E):
     assert bool((z[T * E:] == 7.0).all())
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("T,d,E,shift", [(1, 1, 1, 0), (64, 16, 64, 1), (65, 17, 65, 0), (130, 1030, 5, 0), (200, 64, 130, 3)])
+def test_router_fwd_any_rows(T, d, E, shift, dtype):
+    """Rows that cannot be read in 16-byte pieces: odd widths, buffers that start `shift` elements past an aligned address."""
+    from paper_2505_11432_amd import binding as B
+    g = torch.Generator(device=DEV).manual_seed(T + d)
+    x = torch.randn((shift + T * d,), generator=g, device=DEV).to(dtype)[shift:].view(T, d)
+    w = torch.randn((E, d), generator=g, device=DEV).to(dtype)
+    bias = torch.randn((E,), generator=g, device=DEV)
+    z = torch.full((T * E + 64,), 7.0, device=DEV)
+    for b in (bias, None):
+        B.moe_router_fwd(x, w, b, z[:T * E].view(T, E))
+        ref = x.double() @ w.double().t() + (b.double() if b is not None else 0.0)
+        # d fp32 additions, each rounding by at most 2^-24 of a partial sum
+        assert float((z[:T * E].view(T, E).double() - ref).norm() / ref.norm()) < 3 * np.sqrt(d) * 2.0 ** -24 + 2.0 ** -23
+    assert bool((z[T * E:] == 7.0).all())
+
+
 # assignments on both sides of what the one-launch selection holds (8192 and 32768), one device, a device per expert, many
 # equal affinities (odd T quantises the logits), nothing kept, everything kept
 @pytest.mark.parametrize("T,E,k,G,cap,skew", [(4096, 8, 2, 4, 1500, 1.0), (8193, 8, 1, 2, 2000, 1.0), (16384, 4, 2, 2, 9000, 0.5),
