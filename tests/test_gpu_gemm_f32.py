@@ -58,9 +58,10 @@ def test_ffn_f32_tile_edges(rows, d, f):
     for e in range(E):
         if rows[e] == 0:
             assert not dw1[e].any() and not dw2[e].any()
-    before = dw1.clone()
+    before1, before2 = dw1.clone(), dw2.clone()
     B.moe_expert_ffn_bwd(xp, h, dyp, None, offsets, w1, w2, dxp, dw1, dw2, 1, ws)
-    assert rel(dw1, before.double() + DW1) < tol
+    assert rel(dw1, before1.double() + DW1) < tol
+    assert rel(dw2, before2.double() + DW2) < tol
 
 
 @pytest.mark.parametrize("T,d,E", [(1, 16, 1), (33, 260, 5), (1000, 1024, 64), (65, 4, 3), (50, 30, 4)])

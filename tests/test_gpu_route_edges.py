@@ -149,7 +149,7 @@ def test_route_capacity_edges(T, E, k, G, cap, skew):
     check(B, T, E, k, G, cap, skew)
 
 
-@pytest.mark.parametrize("T,E,k,G", [(1, 1, 1, 1), (63, 2, 1, 2), (64, 3, 2, 3), (129, 12, 3, 4), (4097, 24, 3, 8), (70000, 16, 2, 4), (200, 130, 5, 10)])
+@pytest.mark.parametrize("T,E,k,G", [(1, 1, 1, 1), (63, 2, 1, 2), (64, 3, 2, 3), (129, 12, 3, 4), (4097, 24, 3, 8), (70000, 16, 2, 4), (200, 130, 5, 10), (300, 256, 4, 8)])
 def test_balance_loss_edges(T, E, k, G):
     from paper_2505_11432_amd import binding as B
     from tests.test_gpu_parity import test_balance_loss_and_gradient as check

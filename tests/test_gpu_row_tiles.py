@@ -1,10 +1,12 @@
 """The row-segmented grouped GEMMs with few rows per expert (64- and 128-row tiles), bf16, fused order and e4m3, against float64."""
 import math
 
+import numpy as np
 import pytest
 import torch
 
-from tests.gpu_util import DEV
+from oracle import moe_oracle as O
+from tests.gpu_util import DEV, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -16,6 +18,9 @@ ROWS = [[1], [0, 1, 63, 64, 65, 0, 30, 33], [2] * 70, [0, 0, 0, 128], [0, 127, 1
 # enough to be cut into parts (bf16 from 2560 elements on with the 128-row tile, 1024 with the 64-row one)
 DIMS = [(272, 336), (512, 128), (16, 48), (144, 2752)]
 STEP = 2.0 ** -9            # one bf16 rounding
+# rows past the last segment (an expert-parallel share is given the bound T * k): the tile is chosen for all of them, the
+# buffers hold NaN there before the call, outputs keep what they held
+SPARE = [([0, 1, 63, 64, 65, 0, 30, 33], 300), ([33, 97], 1), ([2] * 70, 4000), ([129, 0, 5], 2000)]
 
 
 def rel(got, ref):
@@ -23,14 +28,17 @@ def rel(got, ref):
     return float((got.double() - ref).norm()) / (n if n > 0 else 1.0)
 
 
-def setup(rows, d, f):
-    E, M = len(rows), sum(rows)
+def setup(rows, d, f, spare=0):
+    E, n = len(rows), sum(rows)
+    M = n + spare
     g = torch.Generator(device=DEV).manual_seed(M * 7 + d)
     rnd = lambda *s: torch.randn(s, generator=g, device=DEV)
     off = [sum(rows[:e]) for e in range(E + 1)]
     offsets = torch.tensor(off, dtype=torch.int32, device=DEV)
     w1, w2 = rnd(E, 2 * f, d) / math.sqrt(d), rnd(E, d, f) / math.sqrt(f)
-    return E, M, off, offsets, w1.bfloat16(), w2.bfloat16(), rnd(M, d).bfloat16(), rnd(M, d).bfloat16()
+    x, dy = rnd(M, d).bfloat16(), rnd(M, d).bfloat16()
+    x[n:], dy[n:] = math.nan, math.nan
+    return E, M, off, offsets, w1.bfloat16(), w2.bfloat16(), x, dy
 
 
 def swiglu_bwd(H, dA, f):
@@ -42,8 +50,18 @@ def swiglu_bwd(H, dA, f):
 @pytest.mark.parametrize("d,f", DIMS)
 @pytest.mark.parametrize("rows", ROWS)
 def test_bf16_and_fused(rows, d, f):
+    check_bf16_and_fused(rows, d, f, 0)
+
+
+@pytest.mark.parametrize("rows,spare", SPARE)
+def test_bf16_and_fused_below_the_bound(rows, spare):
+    check_bf16_and_fused(rows, 272, 336, spare)
+
+
+def check_bf16_and_fused(rows, d, f, spare):
     from paper_2505_11432_amd import binding as B
-    E, M, off, offsets, w1, w2, x, dy = setup(rows, d, f)
+    E, M, off, offsets, w1, w2, x, dy = setup(rows, d, f, spare)
+    n = sum(rows)
     bf = dict(dtype=torch.bfloat16, device=DEV)
     h, yp, dxp = torch.full((M, 2 * f), 7.0, **bf), torch.full((M, d), 7.0, **bf), torch.full((M, d), 7.0, **bf)
     dw1, dw2 = torch.empty((E, 2 * f, d), device=DEV), torch.empty((E, d, f), device=DEV)
@@ -57,6 +75,7 @@ def test_bf16_and_fused(rows, d, f):
     xt, dyt, inv = torch.empty_like(x), torch.empty_like(dy), torch.empty((M,), dtype=torch.int32, device=DEV)
     xt[tok], dyt[tok] = x, dy
     inv[tok] = torch.arange(M, dtype=torch.int32, device=DEV)
+    inv[tok[n:]] = -1                                   # tokens without a row
     row_w = wt.view(-1)[tok].contiguous()
     hf, yf, dxf = torch.full_like(h, 7.0), torch.full_like(yp, 7.0), torch.full_like(dxp, 7.0)
     fw1, fw2, fdw = torch.empty_like(dw1), torch.empty_like(dw2), torch.empty((M, 1), device=DEV)
@@ -65,7 +84,7 @@ def test_bf16_and_fused(rows, d, f):
     B.moe_expert_ffn_fused_bwd(xt, dyt, hf, inv, wt, row_w, offsets, w1, w2, 1, dxf, fw1, fw2, 0, fdw, fws)
     H, Y, DX = (torch.zeros(s, dtype=torch.float64, device=DEV) for s in ((M, 2 * f), (M, d), (M, d)))
     DW1, DW2, DWT = torch.zeros_like(dw1).double(), torch.zeros_like(dw2).double(), torch.zeros(M, dtype=torch.float64, device=DEV)
-    FW2 = torch.zeros_like(DW2)
+    FW1, FW2 = torch.zeros_like(DW1), torch.zeros_like(DW2)
     for e in range(E):
         s = slice(off[e], off[e + 1])
         X, DY, a, b, w = x[s].double(), dy[s].double(), w1[e].double(), w2[e].double(), row_w[s].double()[:, None]
@@ -74,21 +93,36 @@ def test_bf16_and_fused(rows, d, f):
         A, dH = swiglu_bwd(H[s], dA, f)
         Y[s], DX[s] = A @ b.t(), dH @ a
         DWT[s] = (dA * A).sum(1)
-        DW1[e], DW2[e], FW2[e] = dH.t() @ X, DY.t() @ A, DY.t() @ (w * A)
+        DW1[e], DW2[e] = dH.t() @ X, DY.t() @ A
+        FW1[e], FW2[e] = dH.t() @ (w * X), DY.t() @ (w * A)
     # a result carries at most four stored bf16 roundings on its way (H, A or dA, dH, itself)
     assert torch.equal(h, hf)
-    for name, got, ref in (("h", h, H), ("yp", yp, Y), ("d_xp", dxp, DX), ("d_w1", dw1, DW1), ("d_w2", dw2, DW2),
-                           ("ypw", yf, Y * row_w.double()[:, None]), ("fused d_xp", dxf, DX), ("fused d_w2", fw2, FW2)):
+    for name, got, ref in (("h", h, H), ("yp", yp, Y), ("d_xp", dxp, DX), ("ypw", yf, Y * row_w.double()[:, None]), ("fused d_xp", dxf, DX)):
+        assert rel(got[:n], ref[:n]) < 4 * STEP, (name, rel(got[:n], ref[:n]))
+        assert bool((got[n:] == 7.0).all()), name
+    # (the fused order's d_w1: its weighted rows carry one more rounding)
+    for name, got, ref in (("d_w1", dw1, DW1), ("d_w2", dw2, DW2), ("fused d_w1", fw1, FW1), ("fused d_w2", fw2, FW2)):
         assert rel(got, ref) < 4 * STEP, (name, rel(got, ref))
     # a dot product of f terms of random sign, each with the roundings of dA and of H
-    assert rel(fdw.view(-1)[tok], DWT) < 4 * STEP
+    assert rel(fdw.view(-1)[tok[:n]], DWT[:n]) < 4 * STEP
+    assert not fdw.view(-1)[tok[n:]].any()
 
 
 @pytest.mark.parametrize("d,f", DIMS)
 @pytest.mark.parametrize("rows", ROWS)
 def test_e4m3(rows, d, f):
+    check_e4m3(rows, d, f, 0)
+
+
+@pytest.mark.parametrize("rows,spare", SPARE)
+def test_e4m3_below_the_bound(rows, spare):
+    check_e4m3(rows, 272, 336, spare)
+
+
+def check_e4m3(rows, d, f, spare):
     from paper_2505_11432_amd import binding as B
-    E, M, off, offsets, w1, w2, x, dy = setup(rows, d, f)
+    E, M, off, offsets, w1, w2, x, dy = setup(rows, d, f, spare)
+    used = sum(rows)
     u8, bf = dict(dtype=torch.uint8, device=DEV), dict(dtype=torch.bfloat16, device=DEV)
 
     def q(t):
@@ -124,3 +158,22 @@ def test_e4m3(rows, d, f):
         for name, got, ref in (("h", h[s], X[s] @ W1[e].t()), ("yp", yp[s], A[s] @ W2[e].t()), ("dh", it["dh"][s], ref_dh),
                                ("d_xp", dxp[s], DH[s] @ T1[e].t())):
             assert rel(got, ref) < 2 * STEP, (name, e, rel(got, ref))
+    for name, got in (("h", h), ("yp", yp), ("d_xp", dxp)):
+        assert bool((got[used:] == 7.0).all()), name
+    # the operands of the weight gradients: transposed codes of 128-token groups, the forward's from its row codes (the
+    # value a code stands for, rounded once to fp32), bit for bit
+    from tests.test_gpu_parity import _check_tgroup
+    I = {k: to_np(it[k]) for k in ("a_t", "a_e8m0", "x_t", "x_e8m0", "pad_offsets")}
+    for name, c, sc in (("a", ac, asc), ("x", xc, xs)):
+        v = O.e4m3_decode(to_np(c[:used])).astype(np.float32) * to_np(sc[:used]).astype(np.float32)[:, None]
+        _check_tgroup(I[name + "_t"], I[name + "_e8m0"], I["pad_offsets"], v, np.array(off))
+    # and the weight gradients from them.  The e4m3 matrix instruction adds its 64 products aligned to the largest one, not
+    # each in full fp32 (3.8e-5 of the norm seen with 63 rows): at 2^-16 of the largest per product that is 2^-10 of it, and
+    # one bf16 rounding, the bar of the other results, is above it
+    po = I["pad_offsets"]
+    for name, got, p, q in (("d_w1", dw1, "dh", "x"), ("d_w2", dw2, "dy", "a")):
+        for e in range(E):
+            s = slice(int(po[e]), int(po[e]) + rows[e])
+            P, Q = ((it[t + "_t"][:, s].view(torch.float8_e4m3fn).double() *
+                     torch.exp2(it[t + "_e8m0"].double() - 127).repeat_interleave(128, 0)[s].t()) for t in (p, q))
+            assert rel(got[e], P @ Q.t()) < STEP, (name, e, rel(got[e], P @ Q.t()))
