@@ -17,53 +17,59 @@ __device__ __forceinline__ float bcast(float v, int src) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src));
 }
 
-// One wave per token and group of CU chunks of 64 lanes x 16 bytes, read together before their k copies are written: a wave
-// has one round of loads and its stores, and few tokens still make many waves.  (One wave walking a whole row before.  The
-// five row movers of T = 8192, k = 2, d = 4096 bf16, two of them dispatches: 196.8 -> 182.5 us, T = 1000 35.6 -> 32.4, T = 16384,
-// k = 8, d = 2048 563.8 -> 558.3; the weighted dispatch inside a training step of the first size 47 -> 38 us.)
+// `parts` waves per token; each takes every parts-th group of CU chunks of 64 lanes x 16 bytes of the row, read together before
+// their k copies are written.  Bound by HBM; with few tokens by the latency of a wave's walk, so the row is split while that
+// makes no more than 16384 waves (two for every wave a full chip holds), four times that where a wave writes four copies and more.
+// With more tokens a wave takes whole rows: every wave reads the token's map entries, and on an expert-parallel share most tokens
+// end there.  At most 8192 blocks, which loop.
+// Measured (us; one wave per token, one wave per group with as many blocks as that gives, this):
+//   every copy, from memory:  257 tokens, k = 2, d = 16384 fp32 13.2, 9.1, 9.2;  8192, k = 2, d = 4096 bf16 weighted 34.0, 32.6, 33.0
+//   an eighth of the copies:  65536, k = 1, d = 1040 bf16 6.8, 13.3, 8.0;  8192, k = 1, d = 4096 3.4, 4.8, 4.1
+//   narrow rows:              262144, k = 1, d = 256 e4m3 44.0, 62.3, 44.3
 template <typename T, bool kScaled, int CU>
 __global__ void __launch_bounds__(64 * kWavesPerBlock) dispatch_kernel(const T* __restrict__ x,
                                                                        const float* __restrict__ x_scale,
                                                                        const int32_t* __restrict__ inv_perm,
                                                                        const float* __restrict__ row_mul, int T_, int k,
-                                                                       int d, T* __restrict__ xp,
+                                                                       int d, int parts, T* __restrict__ xp,
                                                                        float* __restrict__ xp_scale) {
   constexpr int V = 16 / sizeof(T);
   const int lane = threadIdx.x % 64;
-  const int nvec = d / V, groups = (nvec + 64 * CU - 1) / (64 * CU);
-  const long items = (long)T_ * groups, nwaves = (long)gridDim.x * kWavesPerBlock;
-  for (long w = (long)blockIdx.x * kWavesPerBlock + threadIdx.x / 64; w < items; w += nwaves) {
-    const int t = (int)(w / groups), c0 = (int)(w % groups) * 64 * CU + lane;
+  const int nvec = d / V;
+  const unsigned nwaves = gridDim.x * kWavesPerBlock, items = (unsigned)T_ * parts;     // (more parts than one: at most 65536 items)
+  for (unsigned w = __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock + threadIdx.x / 64); w < items; w += nwaves) {
+    const int t = (int)(parts == 1 ? w : w / parts), part = (int)(w - (unsigned)t * parts);
     int my_row = -1;
     float my_mul = 1.f;
     if (lane < k) {
       my_row = inv_perm[(long)t * k + lane];          // < 0: the expert is not local, no copy
       if constexpr (kScaled) my_mul = row_mul[(long)t * k + lane];
-      if (x_scale != nullptr && c0 == lane && my_row >= 0) xp_scale[my_row] = x_scale[t];
+      if (x_scale != nullptr && part == 0 && my_row >= 0) xp_scale[my_row] = x_scale[t];
     }
-    if (__ballot(my_row >= 0) == 0) continue;      // no local expert wants this token: do not read it
-    Vec16<T> v[CU];
+    if (__ballot(my_row >= 0) == 0) continue;         // no local expert wants this token: do not read it
+    for (int c0 = part * 64 * CU + lane; c0 - lane < nvec; c0 += parts * 64 * CU) {
+      Vec16<T> v[CU];
 #pragma unroll
-    for (int q = 0; q < CU; ++q) v[q] = *reinterpret_cast<const Vec16<T>*>(x + (long)t * d + (long)min(c0 + q * 64, nvec - 1) * V);
-    for (int j = 0; j < k; ++j) {
-      const int r = bcast(my_row, j);
-      const float m = bcast(my_mul, j);
-      if (r < 0) continue;                         // (wave-uniform)
+      for (int q = 0; q < CU; ++q) v[q] = *reinterpret_cast<const Vec16<T>*>(x + (long)t * d + (long)min(c0 + q * 64, nvec - 1) * V);
+      for (int j = 0; j < k; ++j) {
+        const int r = bcast(my_row, j);
+        const float m = bcast(my_mul, j);
+        if (r < 0) continue;                         // (wave-uniform)
 #pragma unroll
-      for (int q = 0; q < CU; ++q) {
-        Vec16<T> o = v[q];
-        if constexpr (kScaled) {
+        for (int q = 0; q < CU; ++q) {
+          Vec16<T> o = v[q];
+          if constexpr (kScaled) {
 #pragma unroll
-          for (int i = 0; i < V; ++i) o.v[i] = from_f32<T>(to_f32(v[q].v[i]) * m);
+            for (int i = 0; i < V; ++i) o.v[i] = from_f32<T>(to_f32(v[q].v[i]) * m);
+          }
+          if (c0 + q * 64 < nvec)
+            __builtin_nontemporal_store(__builtin_bit_cast(u32x4, o), reinterpret_cast<u32x4*>(xp + (long)r * d + (long)(c0 + q * 64) * V));
         }
-        if (c0 + q * 64 < nvec)
-          __builtin_nontemporal_store(__builtin_bit_cast(u32x4, o), reinterpret_cast<u32x4*>(xp + (long)r * d + (long)(c0 + q * 64) * V));
       }
     }
   }
 }
 
-// fp8 codes are bytes; they are decoded by the hardware converter (OCP e4m3 on gfx950).
 template <typename TIN> struct RowLoader {
   static constexpr int V = 16 / sizeof(TIN);
   __device__ static void load(const TIN* p, float (&out)[V]) {
@@ -279,18 +285,19 @@ int row_grid(int T) {
 
 int launch_dispatch(const void* x, const float* x_scale, moe_dtype dt, const int32_t* inv_perm, const float* row_mul,
                     int T, int k, int d, void* xp, float* xp_scale, hipStream_t s) {
-  constexpr int CU = 2;      // chunks per wave (measured: 1, 2, 4)
-  const long items = (long)T * cdiv(d / (16 / (int)dtype_size(dt)), 64 * CU);
-  const long blocks = (items + kWavesPerBlock - 1) / kWavesPerBlock;
-  const dim3 grid((unsigned)(blocks < (1L << 22) ? blocks : (1L << 22))), block(64 * kWavesPerBlock);
+  constexpr int CU = 2;      // chunks read together (measured: 1, 2, 4)
+  const int groups = cdiv(d / (16 / (int)dtype_size(dt)), 64 * CU);
+  const int most = (k < 4 ? 16384 : 65536) / T, parts = most < 2 ? 1 : most < groups ? most : groups;
+  const int blocks = (int)(((long)T * parts + kWavesPerBlock - 1) / kWavesPerBlock);
+  const dim3 grid((unsigned)(blocks < 8192 ? blocks : 8192)), block(64 * kWavesPerBlock);
   if (dt == MOE_F32) {
-    if (row_mul) dispatch_kernel<float, true, CU><<<grid, block, 0, s>>>((const float*)x, nullptr, inv_perm, row_mul, T, k, d, (float*)xp, nullptr);
-    else dispatch_kernel<float, false, CU><<<grid, block, 0, s>>>((const float*)x, nullptr, inv_perm, nullptr, T, k, d, (float*)xp, nullptr);
+    if (row_mul) dispatch_kernel<float, true, CU><<<grid, block, 0, s>>>((const float*)x, nullptr, inv_perm, row_mul, T, k, d, parts, (float*)xp, nullptr);
+    else dispatch_kernel<float, false, CU><<<grid, block, 0, s>>>((const float*)x, nullptr, inv_perm, nullptr, T, k, d, parts, (float*)xp, nullptr);
   } else if (dt == MOE_BF16) {
-    if (row_mul) dispatch_kernel<bf16, true, CU><<<grid, block, 0, s>>>((const bf16*)x, nullptr, inv_perm, row_mul, T, k, d, (bf16*)xp, nullptr);
-    else dispatch_kernel<bf16, false, CU><<<grid, block, 0, s>>>((const bf16*)x, nullptr, inv_perm, nullptr, T, k, d, (bf16*)xp, nullptr);
+    if (row_mul) dispatch_kernel<bf16, true, CU><<<grid, block, 0, s>>>((const bf16*)x, nullptr, inv_perm, row_mul, T, k, d, parts, (bf16*)xp, nullptr);
+    else dispatch_kernel<bf16, false, CU><<<grid, block, 0, s>>>((const bf16*)x, nullptr, inv_perm, nullptr, T, k, d, parts, (bf16*)xp, nullptr);
   } else {
-    dispatch_kernel<uint8_t, false, CU><<<grid, block, 0, s>>>((const uint8_t*)x, x_scale, inv_perm, nullptr, T, k, d, (uint8_t*)xp, xp_scale);
+    dispatch_kernel<uint8_t, false, CU><<<grid, block, 0, s>>>((const uint8_t*)x, x_scale, inv_perm, nullptr, T, k, d, parts, (uint8_t*)xp, xp_scale);
   }
   MOE_LAUNCH_CHECK();
   return MOE_OK;
