@@ -140,36 +140,50 @@ __global__ void __launch_bounds__(256) quant_rows_wave_kernel(const T* __restric
   }
 }
 
-// One block per (128-row group, 128-column slab): thread (rg, cq) holds rows rg, rg+16, ... (8 rows) of the eight columns
-// 8*cq .. 8*cq+7, 16 bytes (fp32: two times 16) per row with all loads in flight together; the column maxima are combined
-// through LDS.  (Four columns per thread, read one by one: 8192 x 4096 bf16 30 us; now 23.)
-template <typename T>
+// Column of load l of thread cq of CQ in a slab, V elements a load: the CQ threads of a row take neighbouring 16 bytes, so that
+// a load reads whole lines whatever the type (fp32: a thread's eight columns are two runs of four).
+template <int V, int CQ = 16> __device__ __forceinline__ constexpr int slab_col(int cq, int l) { return l * CQ * V + cq * V; }
+
+// One block per (128-row group, slab of CQ * 8 columns): thread (rg, cq) holds R rows rg, rg + 128 / R, ... of eight columns, 16
+// bytes (fp32: two times 16) per row with all loads in flight together; the column maxima are reduced over a wave's row
+// groups with shuffles and over the waves through LDS.  (Four columns per thread, read one by one, 16 maxima per column read
+// back from LDS: 8192 x 4096 bf16 from memory 28.8 us, from the last-level cache 20.5, fp32 37 and 28.7; this kernel 19.5,
+// 19.5, 35 and 27.  Eight columns per thread as one run, also of fp32: 23, 22, - and 40.)
+template <typename T, int CQ, bool NT>
 __global__ void __launch_bounds__(256) quant_colgroup_kernel(const T* __restrict__ src, int rows, int cols,
                                                              uint8_t* __restrict__ codes,
                                                              float* __restrict__ scales, int slabs) {
-  __shared__ float cmax[16][128];
-  const int g = blockIdx.x / slabs;
-  const int cq = threadIdx.x % 16, rg = threadIdx.x / 16;
-  const int c = (blockIdx.x % slabs) * 128 + cq * 8;
-  const int r0 = g * 128;
-  const bool col_ok = c < cols;                     // cols is a multiple of 16: all eight columns or none
   constexpr int V = 16 / sizeof(T), L = 8 / V;      // loads per row
-  u32x4 raw[8][L];
+  constexpr int GROUPS = 256 / CQ, R = 128 / GROUPS, WAVES = 4, SLAB = CQ * 8;
+  __shared__ __attribute__((aligned(16))) float cmax[WAVES][SLAB];
+  const int g = blockIdx.x / slabs;
+  const int cq = threadIdx.x % CQ, rg = threadIdx.x / CQ;
+  const int c0 = (blockIdx.x % slabs) * SLAB;
+  const int r0 = g * 128;
+  u32x4 raw[R][L];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int l = 0; l < L; ++l) {
+    const int c = c0 + slab_col<V, CQ>(cq, l);
 #pragma unroll
-    for (int l = 0; l < L; ++l)
-      raw[i][l] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + (long)min(r0 + rg + 16 * i, rows - 1) * cols + min(c, cols - 8) + l * V));
-  float v[8][8];
+    for (int i = 0; i < R; ++i) raw[i][l] = u32x4{0, 0, 0, 0};
+    if (c < cols) {                                 // cols is a multiple of 16: all V columns or none
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        // rows past the end repeat the last row: the same column maxima, never stored
+        const u32x4* p = reinterpret_cast<const u32x4*>(src + (long)min(r0 + rg + GROUPS * i, rows - 1) * cols + c);
+        raw[i][l] = NT ? __builtin_nontemporal_load(p) : *p;
+      }
+    }
+  }
+  float v[R][8];
   float amax[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) amax[j] = 0.f;
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < R; ++i)
 #pragma unroll
     for (int l = 0; l < L; ++l) {
       const Vec16<T> w = __builtin_bit_cast(Vec16<T>, raw[i][l]);
-      // rows past the end repeat the last row: the same column maxima, never stored
 #pragma unroll
       for (int j = 0; j < V; ++j) {
         v[i][l * V + j] = to_f32(w.v[j]);
@@ -177,24 +191,43 @@ __global__ void __launch_bounds__(256) quant_colgroup_kernel(const T* __restrict
       }
     }
 #pragma unroll
-  for (int j = 0; j < 8; ++j) cmax[rg][cq * 8 + j] = amax[j];
+  for (int j = 0; j < 8; ++j) {
+#pragma unroll
+    for (int off = CQ; off < 64; off <<= 1) amax[j] = fmaxf(amax[j], __shfl_xor(amax[j], off));
+  }
+  if ((threadIdx.x & 63) < CQ) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) cmax[threadIdx.x >> 6][slab_col<V, CQ>(cq, j / V) + j % V] = amax[j];
+  }
   __syncthreads();
   float inv[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    float m = 0.f;
+  for (int j4 = 0; j4 < 8; j4 += 4) {
+    const int cs = slab_col<V, CQ>(cq, j4 / V) + j4 % V;
+    float m[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int q = 0; q < 16; ++q) m = fmaxf(m, cmax[q][cq * 8 + j]);
-    inv[j] = m > 0.f ? kE4M3Max / m : 1.0f;
-    if (rg == 0 && col_ok) scales[(long)g * cols + c + j] = m > 0.f ? m / kE4M3Max : 1.0f;
+    for (int q = 0; q < WAVES; ++q) {
+      const float4 t = *reinterpret_cast<const float4*>(&cmax[q][cs]);
+      m[0] = fmaxf(m[0], t.x); m[1] = fmaxf(m[1], t.y); m[2] = fmaxf(m[2], t.z); m[3] = fmaxf(m[3], t.w);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      inv[j4 + j] = m[j] > 0.f ? kE4M3Max / m[j] : 1.0f;
+      if (rg == 0 && c0 + cs < cols) scales[(long)g * cols + c0 + cs + j] = m[j] > 0.f ? m[j] / kE4M3Max : 1.0f;
+    }
   }
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int r = r0 + rg + 16 * i;
-    if (col_ok && r < rows) {
-      const u32x2 o = {pack4_e4m3(v[i][0] * inv[0], v[i][1] * inv[1], v[i][2] * inv[2], v[i][3] * inv[3]),
-                       pack4_e4m3(v[i][4] * inv[4], v[i][5] * inv[5], v[i][6] * inv[6], v[i][7] * inv[7])};
-      *reinterpret_cast<u32x2*>(codes + (long)r * cols + c) = o;
+  for (int i = 0; i < R; ++i) {
+    const int r = r0 + rg + GROUPS * i;
+    if (r >= rows) break;
+    const unsigned lo = pack4_e4m3(v[i][0] * inv[0], v[i][1] * inv[1], v[i][2] * inv[2], v[i][3] * inv[3]);
+    const unsigned hi = pack4_e4m3(v[i][4] * inv[4], v[i][5] * inv[5], v[i][6] * inv[6], v[i][7] * inv[7]);
+    uint8_t* dst = codes + (long)r * cols + c0;
+    if constexpr (V == 8) {
+      if (c0 + cq * 8 < cols) *reinterpret_cast<u32x2*>(dst + cq * 8) = u32x2{lo, hi};
+    } else {
+      if (c0 + cq * 4 < cols) *reinterpret_cast<unsigned*>(dst + cq * 4) = lo;
+      if (c0 + slab_col<V, CQ>(cq, 1) < cols) *reinterpret_cast<unsigned*>(dst + slab_col<V, CQ>(cq, 1)) = hi;
     }
   }
 }
@@ -426,10 +459,25 @@ int launch_quant_fp8(const void* src, moe_dtype src_dt, int rows, int cols, moe_
       else quant_rows_kernel<bf16, 256><<<grid, 256, 0, s>>>((const bf16*)src, rows, cols, codes, scales);
     }
   } else {
-    const int slabs = cdiv(cols, 128);
+    // Narrow tensors take a narrower slab, of which more threads have columns (2^20 x 16 bf16: slabs of 32 / 64 / 128 columns
+    // 22 / 23 / 32 us; x 64 columns and more the wide one: 8192 x 1040 15.4 / 9.3 / 7.9).  Streaming loads: for bf16 always (8192
+    // x 4096 from memory 19.5 against 21.4, from the last-level cache 19.5 against 17.4; 8192 x 28672 109 against 130), for
+    // fp32 only what that cache cannot hold (8192 x 4096 30 against 35 and 30 against 27; 8192 x 28672 210 against 225).
+    const int cq = cols <= 32 ? 4 : cols <= 64 ? 8 : 16;
+    const int slabs = cdiv(cols, cq * 8);
     const int grid = cdiv(rows, 128) * slabs;
-    if (src_dt == MOE_F32) quant_colgroup_kernel<float><<<grid, 256, 0, s>>>((const float*)src, rows, cols, codes, scales, slabs);
-    else quant_colgroup_kernel<bf16><<<grid, 256, 0, s>>>((const bf16*)src, rows, cols, codes, scales, slabs);
+#define MOE_COLGROUP(TT, CQ, NT) quant_colgroup_kernel<TT, CQ, NT><<<grid, 256, 0, s>>>((const TT*)src, rows, cols, codes, scales, slabs)
+    if (src_dt == MOE_F32) {
+      if (cq == 4) MOE_COLGROUP(float, 4, false);
+      else if (cq == 8) MOE_COLGROUP(float, 8, false);
+      else if ((long)rows * cols < (1L << 26)) MOE_COLGROUP(float, 16, false);
+      else MOE_COLGROUP(float, 16, true);
+    } else {
+      if (cq == 4) MOE_COLGROUP(bf16, 4, true);
+      else if (cq == 8) MOE_COLGROUP(bf16, 8, true);
+      else MOE_COLGROUP(bf16, 16, true);
+    }
+#undef MOE_COLGROUP
   }
   MOE_LAUNCH_CHECK();
   return MOE_OK;

@@ -86,3 +86,25 @@ def test_row_cast_of_many_rows():
     B.moe_quant_fp8(src, B.Q_ROW, codes, scales)
     assert bool((codes[:whole].view(-1, 4099, cols) == want_c).all()) and bool((scales[:whole].view(-1, 4099) == want_s).all())
     assert torch.equal(codes[whole:], want_c[:rows - whole]) and torch.equal(scales[whole:], want_s[:rows - whole])
+
+
+# column slabs of 32, 64 and 128 columns and one past them, with full, short and one-row last groups
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("rows,cols", [(129, 32), (130, 48), (127, 64), (3, 80), (256, 144)])
+def test_cast_column_slabs(dtype, rows, cols):
+    test_cast_edges(dtype, rows, cols)
+
+
+def test_colgroup_cast_of_a_large_fp32_tensor():
+    """2^26 elements: read past the caches.  Every group of 128 rows gives what it gives alone."""
+    from paper_2505_11432_amd import binding as B
+    rows, cols = 2 ** 16 + 3, 1024
+    src = torch.randn((rows, cols), generator=torch.Generator(device=DEV).manual_seed(2), device=DEV)
+    codes, scales = torch.empty((rows, cols), dtype=torch.uint8, device=DEV), torch.empty(((rows + 127) // 128, cols), device=DEV)
+    B.moe_quant_fp8(src, B.Q_COLGROUP128, codes, scales)
+    part_c, part_s = torch.empty((8192, cols), dtype=torch.uint8, device=DEV), torch.empty((64, cols), device=DEV)
+    for a in range(0, rows, 8192):
+        n = min(8192, rows - a)
+        g = (n + 127) // 128
+        B.moe_quant_fp8(src[a:a + n], B.Q_COLGROUP128, part_c[:n], part_s[:g])
+        assert torch.equal(codes[a:a + n], part_c[:n]) and torch.equal(scales[a // 128:a // 128 + g], part_s[:g]), a
