@@ -285,25 +285,26 @@ __global__ void __launch_bounds__(256) quant_tgroup_kernel(const T* __restrict__
   const int r_end = offsets[e + 1];
   const int cq = threadIdx.x % 16, rgrp = threadIdx.x / 16;
   const int c0 = (blockIdx.x % slabs) * CH;
-  const int c = c0 + cq * 8;
-  const bool col_ok = c < cols;                     // cols is a multiple of 16: all eight channels or none
+  // the thread's eight channels: one run, or for fp32 two of four, 64 apart, so that every load reads whole lines
+  constexpr int V = sizeof(T) == 4 ? 4 : 8;
+  auto chan = [&](int j) __attribute__((always_inline)) { return slab_col<V>(cq, j / V) + j % V; };
   // every load is issued before the first value is used; rows past the segment's end re-read its last row and count as 0
   constexpr int LB = 8 * (int)sizeof(T);            // bytes per row and thread
-  const char* col_base = reinterpret_cast<const char*>(src + min(c, cols - 8));
+  const int last = cols - V;                        // cols is a multiple of 16: all V channels of a run or none
   unsigned raw[8][LB / 4];
   float rs[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int r = min(r0 + rgrp * 8 + i, r_end - 1);
-    const char* p = col_base + (long)r * cols * (int)sizeof(T);
+    const T* p = src + (long)r * cols;
     if constexpr (LB == 8) {
-      const u32x2 w = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p));
+      const u32x2 w = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p + min(c0 + cq * 8, last)));
       raw[i][0] = w[0]; raw[i][1] = w[1];
       rs[i] = src_row_scale[r];
     } else {
 #pragma unroll
       for (int l = 0; l < LB / 16; ++l) {
-        const u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p + 16 * l));
+        const u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p + min(c0 + slab_col<V>(cq, l), last)));
 #pragma unroll
         for (int q = 0; q < 4; ++q) raw[i][4 * l + q] = w[q];
       }
@@ -340,13 +341,14 @@ __global__ void __launch_bounds__(256) quant_tgroup_kernel(const T* __restrict__
   }
   if ((threadIdx.x & 63) < 16) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) cmax[threadIdx.x >> 6][cq * 8 + j] = amax[j];
+    for (int j = 0; j < 8; ++j) cmax[threadIdx.x >> 6][chan(j)] = amax[j];
   }
   __syncthreads();
   float inv[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
-    const float m = fmaxf(fmaxf(cmax[0][cq * 8 + j], cmax[1][cq * 8 + j]), fmaxf(cmax[2][cq * 8 + j], cmax[3][cq * 8 + j]));
+    const int ch = chan(j);
+    const float m = fmaxf(fmaxf(cmax[0][ch], cmax[1][ch]), fmaxf(cmax[2][ch], cmax[3][ch]));
     int k = 0;
     if (m > 0.f) {
       const unsigned bits = __float_as_uint(m);
@@ -354,15 +356,15 @@ __global__ void __launch_bounds__(256) quant_tgroup_kernel(const T* __restrict__
       k = max(-126, min(127, k));
     }
     inv[j] = __uint_as_float((unsigned)(127 - k) << 23);          // 2^-k, exact
-    if (rgrp == 0 && col_ok) e8m0[(long)g * cols + c + j] = (uint8_t)(k + 127);
+    if (rgrp == 0 && c0 + ch < cols) e8m0[(long)g * cols + c0 + ch] = (uint8_t)(k + 127);
   }
-  const int chunk = ((rgrp >> 1) ^ (cq & 7)) << 4;                 // swizzled 16-byte chunk of the tile row
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     uint2 w;
     w.x = pack4_e4m3(v[0][j] * inv[j], v[1][j] * inv[j], v[2][j] * inv[j], v[3][j] * inv[j]);
     w.y = pack4_e4m3(v[4][j] * inv[j], v[5][j] * inv[j], v[6][j] * inv[j], v[7][j] * inv[j]);
-    *reinterpret_cast<uint2*>(&tile[cq * 8 + j][chunk + ((rgrp & 1) << 3)]) = w;
+    const int ch = chan(j), chunk = ((rgrp >> 1) ^ ((ch >> 3) & 7)) << 4;       // swizzled 16-byte chunk of the tile row
+    *reinterpret_cast<uint2*>(&tile[ch][chunk + ((rgrp & 1) << 3)]) = w;
   }
   __syncthreads();
 #pragma unroll
