@@ -376,16 +376,15 @@ __global__ void __launch_bounds__(256) quant_tgroup_kernel(const T* __restrict__
   }
 }
 
-// A thread makes 16 bytes of output at a time (8 bf16 or 4 fp32 of a row: a wave's store is one run of 1 KiB), four such
-// pieces a block apart with all loads in flight together.  (Four codes per thread, an element-index division for each and
-// scalar stores: 8192 x 4096 to bf16 30 us; now 21, and 18 with
-// the scales of channel groups read as vectors, against 64 one by one.)
+// A thread makes 16 bytes of output at a time (8 bf16 or 4 fp32 of a row: a wave's store is one run of 1 KiB), U such pieces a
+// block apart with all loads in flight together.  (Four codes per thread, an element-index division for each and scalar
+// stores: 8192 x 4096 to bf16, from memory, 27.7 us with row scales, 28.5 with channel scales; now 20.2 and 24.1.)
 enum ScaleRead { ROW_SCALE, GROUP_SCALES, GROUP_SCALES_VEC };     // VEC: the scales are 16-byte aligned
-template <typename T, ScaleRead SR>
+template <typename T, ScaleRead SR, int U>
 __global__ void __launch_bounds__(256) dequant_kernel(const uint8_t* __restrict__ codes,
                                                       const float* __restrict__ scales, int rows, int cols,
                                                       T* __restrict__ dst) {
-  constexpr int P = 16 / sizeof(T), U = 4;
+  constexpr int P = 16 / sizeof(T);
   const int per_row = cols / P;
   const long n = (long)rows * per_row;
   for (long base = blockIdx.x * (256L * U) + threadIdx.x; base < n; base += (long)gridDim.x * (256 * U)) {
@@ -512,13 +511,20 @@ int launch_dequant_fp8(const uint8_t* codes, const float* scales, int rows, int 
                        moe_dtype dst_dt, hipStream_t s) {
   if (rows == 0 || cols == 0) return MOE_OK;
   const long pieces = (long)rows * (cols / (16 / (int)dtype_size(dst_dt)));
-  long blocks = (pieces + 1023) / 1024;
+  // Few pieces: one per thread, so that they make enough waves (64 x 4096 2.5 -> 2.05 us).  With channel scales, four vectors of
+  // them beside each piece, one piece per thread is the faster one up to larger sizes (bf16, from memory: 8192 x 4096 30.7 ->
+  // 24.1, 8192 x 6000 44.5 -> 37.8, 2^20 x 256 147 -> 162; fp32 1000 x 8192 12.4 -> 11.5), but not on narrow rows (2^20 x 16 bf16
+  // 8.8 -> 9.5, fp32 17.9 -> 20.0).
+  const bool few = pieces <= (mode == MOE_Q_ROW || cols < 128 ? 1L << 18 : dst_dt == MOE_BF16 ? 1L << 23 : 1L << 21);
+  long blocks = few ? (pieces + 255) / 256 : (pieces + 1023) / 1024;
   if (blocks > 256 * 64) blocks = 256 * 64;
-#define MOE_DEQUANT(TT, SR) dequant_kernel<TT, SR><<<(int)blocks, 256, 0, s>>>(codes, scales, rows, cols, (TT*)dst)
-#define MOE_DEQUANT_SR(TT)                                            \
-  if (mode == MOE_Q_ROW) MOE_DEQUANT(TT, ROW_SCALE);                  \
-  else if (aligned16(scales)) MOE_DEQUANT(TT, GROUP_SCALES_VEC);      \
-  else MOE_DEQUANT(TT, GROUP_SCALES);
+#define MOE_DEQUANT(TT, SR)                                                                                          \
+  if (few) dequant_kernel<TT, SR, 1><<<(int)blocks, 256, 0, s>>>(codes, scales, rows, cols, (TT*)dst);               \
+  else dequant_kernel<TT, SR, 4><<<(int)blocks, 256, 0, s>>>(codes, scales, rows, cols, (TT*)dst)
+#define MOE_DEQUANT_SR(TT)                                                \
+  if (mode == MOE_Q_ROW) { MOE_DEQUANT(TT, ROW_SCALE); }                  \
+  else if (aligned16(scales)) { MOE_DEQUANT(TT, GROUP_SCALES_VEC); }      \
+  else { MOE_DEQUANT(TT, GROUP_SCALES); }
   if (dst_dt == MOE_F32) { MOE_DEQUANT_SR(float) } else { MOE_DEQUANT_SR(bf16) }
 #undef MOE_DEQUANT_SR
 #undef MOE_DEQUANT

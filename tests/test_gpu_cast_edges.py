@@ -108,3 +108,22 @@ def test_colgroup_cast_of_a_large_fp32_tensor():
         g = (n + 127) // 128
         B.moe_quant_fp8(src[a:a + n], B.Q_COLGROUP128, part_c[:n], part_s[:g])
         assert torch.equal(codes[a:a + n], part_c[:n]) and torch.equal(scales[a // 128:a // 128 + g], part_s[:g]), a
+
+
+# pieces of 16 bytes on both sides of where a thread takes one of them or four: 2^18 with row scales; with channel scales 2^23
+# to bf16 and 2^21 to fp32
+@pytest.mark.parametrize("mode,td,rows,cols", [(0, torch.bfloat16, 2048, 1024), (0, torch.bfloat16, 2049, 1024), (0, torch.float32, 1025, 1024),
+                                               (1, torch.bfloat16, 8192, 8192), (1, torch.bfloat16, 8193, 8192), (1, torch.float32, 4096, 2048),
+                                               (1, torch.float32, 4097, 2048)])
+def test_dequant_sizes(mode, td, rows, cols):
+    from paper_2505_11432_amd import binding as B
+    assert (B.Q_ROW, B.Q_COLGROUP128) == (0, 1)
+    g = torch.Generator(device=DEV).manual_seed(rows)
+    codes = torch.randint(0, 256, (rows, cols), generator=g, device=DEV, dtype=torch.uint8)
+    codes[(codes & 127) == 127] = 0                         # no NaN codes
+    scales = torch.rand((rows,) if mode == 0 else ((rows + 127) // 128, cols), generator=g, device=DEV) + 0.5
+    out = torch.full((rows + 1, cols), 7.0, dtype=td, device=DEV)
+    B.moe_dequant_fp8(codes, scales, mode, out[:rows])
+    per = scales[:, None] if mode == 0 else scales.repeat_interleave(128, dim=0)[:rows]
+    assert torch.equal(out[:rows], (codes.view(torch.float8_e4m3fn).float() * per).to(td))      # one fp32 product, one rounding
+    assert bool((out[rows] == 7.0).all())
