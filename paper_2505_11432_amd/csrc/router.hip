@@ -29,9 +29,10 @@ template <typename T, int COLS> struct RowChunk {
 // TOK = false: a block owns 256 * COLS columns, its four waves side by side, and each walks all tokens of the chunk.
 // TOK = true: a block owns 64 * COLS columns, its waves take every fourth run of eight tokens, and their sums are added in
 // wave order through LDS: four times the blocks with a quarter of the serial walk, for problems of fewer than 256 blocks
-// (us: T = 256, d = 128, E = 8 fp32 11.9 -> 6.9; T = 300, d = 4096, E = 8 11.2 -> 7.0; T = 1531, d = 1040, E = 24 19.0 -> 15.3;
-// T = 4096, d = 1024, E = 44 36.4 -> 24.7).  With more the wider rows per block win (T = 8192, d = 4096, E = 8: 21.6 against
-// 24.6; T = 4096, d = 4096, E = 20: 28.9 against 64).
+// (us: T = 256, d = 128, E = 8 fp32 11.9 -> 6.9; T = 300, d = 4096, E = 8 11.1 -> 6.7; T = 1531, d = 1040, E = 24 19.0 -> 11.5;
+// T = 4096, d = 1040, E = 24 21.0 -> 16.1).  With more the wider rows per block win (T = 8192, d = 4096, E = 8: 21.6 against
+// 24.6; T = 4096, d = 4096, E = 20: 28.9 against 64), and up to 8 tokens there is nothing to share (T = 1, d = 4096, E = 24 9.1
+// against 6.6).  32 sums of a thread at a time go through LDS: with all 64 of E = 24 a CU holds two blocks instead of four.
 constexpr int kChunkTokens = 64;
 constexpr int kTokUnroll = 8;         // rows of x in flight per thread
 
@@ -40,7 +41,7 @@ __global__ void __launch_bounds__(256) router_dwr_partial_kernel(const T* __rest
                                                                  const float* __restrict__ d_logits, int Tn, int d,
                                                                  int E, int tokens_per_chunk,
                                                                  float* __restrict__ partial) {
-  constexpr int kPart = !TOK ? 1 : ETILE <= 32 ? ETILE : 16;      // experts added through LDS at a time
+  constexpr int kPart = !TOK ? 1 : ETILE * COLS < 32 ? ETILE : 32 / COLS;      // experts added through LDS at a time
   __shared__ __attribute__((aligned(16))) float g_lds[kChunkTokens][ETILE];
   __shared__ float part[TOK ? 3 : 1][kPart * COLS][64];
   constexpr int kSlab = (TOK ? 64 : 256) * COLS;
@@ -309,7 +310,7 @@ int launch_router_bwd(const void* x, const void* w_r, const float* d_logits, moe
     float* partial = static_cast<float*>(ws);
 #define MOE_DWR_CASE(TT, ET, CO)                                                                                    \
   do {                                                                                                              \
-    if (cdiv(d, 256 * CO) * chunks < 256)                                                                           \
+    if (T > 8 && cdiv(d, 256 * CO) * chunks < 256)                                                                  \
       router_dwr_partial_kernel<TT, ET, CO, true><<<cdiv(d, 64 * CO) * chunks, 256, 0, s>>>((const TT*)x, d_logits, T, d, E, tpc, partial); \
     else                                                                                                            \
       router_dwr_partial_kernel<TT, ET, CO, false><<<cdiv(d, 256 * CO) * chunks, 256, 0, s>>>((const TT*)x, d_logits, T, d, E, tpc, partial); \

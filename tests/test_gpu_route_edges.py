@@ -174,3 +174,10 @@ def test_router_bwd_edges(T, d, E, dtype):
     step = 2.0 ** -9 if dtype == torch.bfloat16 else 2.0 ** -24 * 3 * np.sqrt(E) + 2.0 ** -23
     assert float((dx.double() - want_x).norm() / want_x.norm()) < 2 * step
     assert torch.equal(buf[T * d:], tail)
+
+
+# up to 8 tokens and more, which the waves of a block share
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("T,d,E", [(8, 272, 20), (9, 272, 20), (40, 1040, 12)])
+def test_router_bwd_splits(T, d, E, dtype):
+    test_router_bwd_edges(T, d, E, dtype)
