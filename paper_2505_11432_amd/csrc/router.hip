@@ -1,10 +1,10 @@
 // Gradients of the router matmul (the "routing scores" operator, Section 7): d_w_r = d_logits^T x and
 // dx += d_logits w_r.  Both are skinny (E <= 256 on one side), so they are HBM-bound on x / dx and run
-// on the vector ALU with the gate gradient held in scalar registers:
-//   d_w_r  two passes, no float atomics: each block owns a slab of 512 columns of x and a chunk of
-//          tokens and keeps E x 2 fp32 sums per thread; a second kernel adds the per-chunk partials in
-//          a fixed order, so the result is reproducible.
-//   dx     one pass over dx: each thread owns 8 columns and walks the experts.
+// on the vector ALU (bf16 with 32 experts and more: on the matrix cores, below):
+//   d_w_r  two passes, no float atomics: each block owns a slab of columns of x and a chunk of tokens and
+//          keeps the sums of an expert tile in registers, gate gradients staged in LDS; a second kernel adds
+//          the per-chunk partials in a fixed order, so the result is reproducible.
+//   dx     one pass over dx: a block keeps its 512 columns of w_r in LDS, a lane owns 8 of them and walks the experts.
 #include "moe_common.h"
 
 namespace moe {
@@ -145,12 +145,14 @@ __global__ void __launch_bounds__(256) router_dwr_reduce_kernel(const float* __r
 // dx[t, cols] += sum_e d_logits[t][e] * w_r[e][cols].  A block owns a slab of 512 columns (64 lanes x 8) and
 // keeps that slab of w_r (up to 64 experts x 1 KiB) in LDS; its four waves walk the tokens.  More than 64
 // experts are done in passes of 64 that each read-modify-write dx.  Bound by reading and writing dx, so what counts is how
-// many blocks fit a CU: the slab is as high as the experts need (ETILE), and a token's gate gradients sit one per lane in a
-// register (a scalar load per token and expert is a chain of memory latencies).  T = 8192, d = 4096, E = 8, bf16 32 -> 27 us;
-// T = 16384, d = 2048, E = 16 43 -> 35.
+// many blocks fit a CU: the slab is as high as the experts need (ETILE).  A token's gate gradients sit one per lane in a
+// register (kLaneGrads; T = 8192, d = 4096, E = 8, bf16 32 -> 27 us; T = 16384, d = 2048, E = 16 43 -> 35) or are scalar loads:
+// with more than one block per CU and bf16 slabs of more than 16 experts the lane reads cost more than the loads' latency (T =
+// 16384, d = 256, E = 33 16.9 against 15.4; T = 4096, d = 4096, E = 24 25.3 against 23.5; not with rows wider than 2048 and
+// more than 32 experts: E = 44 42.6 against 46.2; fp32 E = 64 58.9 against 62.4).
 constexpr int kDxCols = 512;
 
-template <typename T, int ETILE>
+template <typename T, int ETILE, bool kLaneGrads>
 __global__ void __launch_bounds__(256) router_dx_kernel(const T* __restrict__ w_r, const float* __restrict__ d_logits,
                                                         int Tn, int d, int E, int token_groups, T* __restrict__ dx) {
   constexpr int V = 8;                                  // columns per lane
@@ -182,8 +184,9 @@ __global__ void __launch_bounds__(256) router_dx_kernel(const T* __restrict__ w_
     for (int tb = (tg * 4 + wave) * kTok; tb < Tn; tb += token_groups * 4 * kTok) {
       float acc[kTok][V];
       float g[kTok];                                     // lane e: this pass's gate gradient of expert e
+      if constexpr (kLaneGrads)
 #pragma unroll
-      for (int q = 0; q < kTok; ++q) g[q] = d_logits[(long)min(tb + q, Tn - 1) * E + e0 + min(lane, ne - 1)];
+        for (int q = 0; q < kTok; ++q) g[q] = d_logits[(long)min(tb + q, Tn - 1) * E + e0 + min(lane, ne - 1)];
 #pragma unroll
       for (int q = 0; q < kTok; ++q) {
         const int t = min(tb + q, Tn - 1);
@@ -209,7 +212,8 @@ __global__ void __launch_bounds__(256) router_dx_kernel(const T* __restrict__ w_
         }
 #pragma unroll
         for (int q = 0; q < kTok; ++q) {
-          const float gv = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(g[q]), e));
+          const float gv = kLaneGrads ? __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(g[q]), e))
+                                      : d_logits[(long)min(tb + q, Tn - 1) * E + e0 + e];     // wave-uniform: scalar load
 #pragma unroll
           for (int j = 0; j < V; ++j) acc[q][j] = fmaf(gv, wv[j], acc[q][j]);
         }
@@ -339,17 +343,23 @@ int launch_router_bwd(const void* x, const void* w_r, const float* d_logits, moe
     if (rc != MOE_OK) return rc;
   } else if (dx && T > 0) {
     const int slabs = cdiv(d, kDxCols);
-    const int per_cu = E <= 16 ? 8 : E <= 32 ? 4 : 2;    // what the LDS slab of bf16 experts allows
+    // bf16: what the LDS slab allows.  fp32 moves twice the bytes and is slower with more (T = 4096, d = 4096: E = 8 27.4, 29.3,
+    // 36.1 us with 2, 4, 8, E = 16 32.8, 36.5, 49.8).
+    const int per_cu = dt == MOE_F32 ? 2 : E <= 16 ? 8 : E <= 32 ? 4 : 2;
     int token_groups = cdiv(256 * per_cu, slabs);
     if (token_groups > cdiv(T, 16)) token_groups = cdiv(T, 16);
     const int blocks = slabs * token_groups;
-#define MOE_DX_CASE(TT, ET) router_dx_kernel<TT, ET><<<blocks, 256, 0, s>>>((const TT*)w_r, d_logits, T, d, E, token_groups, (TT*)dx)
-#define MOE_DX_TYPE(TT)                  \
-  if (E <= 8) MOE_DX_CASE(TT, 8);        \
-  else if (E <= 16) MOE_DX_CASE(TT, 16); \
-  else if (E <= 32) MOE_DX_CASE(TT, 32); \
-  else MOE_DX_CASE(TT, kETile);
-    if (dt == MOE_F32) { MOE_DX_TYPE(float) } else { MOE_DX_TYPE(bf16) }
+    const bool scalar = dt == MOE_BF16 && E > 16 && blocks > 256 && (E <= 32 || d <= 2048);
+#define MOE_DX_CASE(TT, ET, LANE) router_dx_kernel<TT, ET, LANE><<<blocks, 256, 0, s>>>((const TT*)w_r, d_logits, T, d, E, token_groups, (TT*)dx)
+#define MOE_DX_TYPE(TT)                        \
+  if (E <= 8) MOE_DX_CASE(TT, 8, true);        \
+  else if (E <= 16) MOE_DX_CASE(TT, 16, true); \
+  else if (E <= 32) MOE_DX_CASE(TT, 32, true); \
+  else MOE_DX_CASE(TT, kETile, true);
+    if (scalar && E <= 32) MOE_DX_CASE(bf16, 32, false);
+    else if (scalar) MOE_DX_CASE(bf16, kETile, false);
+    else if (dt == MOE_F32) { MOE_DX_TYPE(float) }
+    else { MOE_DX_TYPE(bf16) }
 #undef MOE_DX_TYPE
 #undef MOE_DX_CASE
     MOE_LAUNCH_CHECK();

@@ -176,8 +176,8 @@ def test_router_bwd_edges(T, d, E, dtype):
     assert torch.equal(buf[T * d:], tail)
 
 
-# up to 8 tokens and more, which the waves of a block share
+# up to 8 tokens and more (which the waves of a block share), gate gradients as scalar loads (bf16, more than 16 experts)
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("T,d,E", [(8, 272, 20), (9, 272, 20), (40, 1040, 12)])
+@pytest.mark.parametrize("T,d,E", [(8, 272, 20), (9, 272, 20), (40, 1040, 12), (8200, 528, 24), (4099, 1040, 41), (4099, 4112, 41)])
 def test_router_bwd_splits(T, d, E, dtype):
     test_router_bwd_edges(T, d, E, dtype)
