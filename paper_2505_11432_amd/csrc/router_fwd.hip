@@ -20,7 +20,7 @@ __global__ void __launch_bounds__(kWaves * 64) router_fwd_kernel(const bf16* __r
                                                                  const float* __restrict__ bias, int T, int d, int E,
                                                                  float* __restrict__ logits) {
   __shared__ f32x4 sums[kWaves][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, q = lane >> 4;
   const int t0 = blockIdx.x * 16, e0 = blockIdx.y * 16;
   const bf16* xrow = x + (long)min(t0 + r, T - 1) * d;             // rows past the end are not stored
@@ -29,7 +29,8 @@ __global__ void __launch_bounds__(kWaves * 64) router_fwd_kernel(const bf16* __r
   for (int b0 = wave; b0 * kBlock < d; b0 += kAhead * kWaves) {
     bf16x8 xv[kAhead][2], wv[kAhead][2];
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u)
+    for (int u = 0; u < kAhead; ++u) {
+      if ((b0 + u * kWaves) * kBlock >= d) break;                      // (wave-uniform) nothing is loaded for what a short row lacks
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         const int k = (b0 + u * kWaves) * kBlock + c * 32 + q * 8;     // d is a multiple of 8: a piece is in or out
@@ -40,10 +41,13 @@ __global__ void __launch_bounds__(kWaves * 64) router_fwd_kernel(const bf16* __r
         xv[u][c] = in ? a : zero;
         wv[u][c] = in ? b : zero;
       }
+    }
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u)
+    for (int u = 0; u < kAhead; ++u) {
+      if ((b0 + u * kWaves) * kBlock >= d) break;
 #pragma unroll
       for (int c = 0; c < 2; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[u][c], xv[u][c], acc, 0, 0, 0);
+    }
   }
   sums[wave][lane] = acc;
   __syncthreads();

@@ -181,3 +181,9 @@ def test_router_bwd_edges(T, d, E, dtype):
 @pytest.mark.parametrize("T,d,E", [(8, 272, 20), (9, 272, 20), (40, 1040, 12), (8200, 528, 24), (4099, 1040, 41), (4099, 4112, 41)])
 def test_router_bwd_splits(T, d, E, dtype):
     test_router_bwd_edges(T, d, E, dtype)
+
+
+@pytest.mark.parametrize("T,d,E", [(100, 512, 9), (4096, 576, 16), (33, 2048, 5), (20, 2056, 40)])
+def test_router_fwd_short_rows(T, d, E):
+    """Rows that end inside a wave's four blocks of 64 columns, at their edges and past them."""
+    test_router_fwd_edges(T, d, E)
