@@ -187,3 +187,8 @@ def test_router_bwd_splits(T, d, E, dtype):
 def test_router_fwd_short_rows(T, d, E):
     """Rows that end inside a wave's four blocks of 64 columns, at their edges and past them."""
     test_router_fwd_edges(T, d, E)
+
+
+@pytest.mark.parametrize("T,d,E", [(16383, 16, 33), (16384, 16, 33), (16400, 28, 5), (16384, 32, 70)])
+def test_router_fwd_f32_narrow(T, d, E):
+    test_router_fwd_any_rows(T, d, E, 0, torch.float32)
