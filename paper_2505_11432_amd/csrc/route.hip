@@ -20,21 +20,19 @@
 namespace moe {
 namespace {
 
-// The total order of the gate as one integer: larger = first.  High word: the logit with -0 made +0 and its bits mapped to
-// an unsigned order, a NaN of either sign last (0: below -inf, so that it is selected only when nothing else is left; read
-// back as a NaN); low word: the complement of the expert id (equal logits: lower id first).  Never 0.
-__device__ __forceinline__ unsigned long long order_key(float z, int e) {
+// The total order of the gate: a logit's bits mapped to an unsigned order, -0 as +0, a NaN of either sign below -inf (1: it is
+// selected only when nothing else is left, and read back as a NaN).  0 is no logit.  Between lanes the complement of the
+// expert id follows as low word: larger = first, equal logits in ascending order of their ids.
+__device__ __forceinline__ unsigned order_key(float z) {
   const unsigned b = __float_as_uint(z + 0.0f);
-  const unsigned high = z != z ? 0u : (b >> 31) ? ~b : (b | 0x80000000u);
-  return ((unsigned long long)high << 32) | (unsigned)~e;
+  return z != z ? 1u : b ^ ((unsigned)((int)b >> 31) | 0x80000000u);
 }
-__device__ __forceinline__ float key_logit(unsigned long long key) {
-  const unsigned u = (unsigned)(key >> 32);
-  return __uint_as_float((u >> 31) ? (u & 0x7fffffffu) : ~u);
-}
+__device__ __forceinline__ float key_logit(unsigned u) { return __uint_as_float((u >> 31) ? (u & 0x7fffffffu) : ~u); }
 
 // G lanes (G <= 16) cooperate on one token; lane `sub` of a group holds the VPL experts sub, sub+G, sub+2G, ...  64 groups
-// per workgroup: a chunk of 64 tokens is one round.  hist strides: he per expert, hc per chunk.
+// per workgroup: a chunk of 64 tokens is one round.  hist strides: he per expert, hc per chunk.  Many tokens of many experts
+// are bound by the vector ALU: a lane picks its best on 32-bit keys, and only that one is exchanged together with its id (64-bit
+// keys throughout: whole route of T = 262144, E = 256, k = 1 141 us, now 57, T = 65536 38.5, now 27.9).
 template <int G, int VPL>
 __global__ void __launch_bounds__(64 * G) route_topk_kernel(const float* __restrict__ logits, int T, int E, int k,
                                                             int renorm, int chunk_tokens, int he, int hc,
@@ -59,29 +57,35 @@ __global__ void __launch_bounds__(64 * G) route_topk_kernel(const float* __restr
     const bool live = t_raw < t_end;
     const int t = live ? t_raw : t_end - 1;
     float v[VPL];
-    unsigned long long key[VPL];
+    unsigned key[VPL];
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
       const int e = sub + i * G;
       v[i] = e < E ? logits[(long)t * E + e] : -INFINITY;
-      key[i] = e < E ? order_key(v[i], e) : 0ull;
+      key[i] = e < E ? order_key(v[i]) : 0u;
     }
     unsigned long long mine = 0;
     float top_z = 0.f;
     for (int j = 0; j < k; ++j) {
-      unsigned long long best = key[0];
+      unsigned top = key[0];
+      int at = 0;
 #pragma unroll
-      for (int i = 1; i < VPL; ++i) best = key[i] > best ? key[i] : best;
+      for (int i = 1; i < VPL; ++i) {                // a lane's ids ascend: the first of equal keys stays
+        at = key[i] > top ? i : at;
+        top = key[i] > top ? key[i] : top;
+      }
+      unsigned long long best = ((unsigned long long)top << 32) | (unsigned)~(sub + at * G);
       best = group_reduce<G>(best, [](unsigned long long a, unsigned long long b) { return a > b ? a : b; });
+      const int won = (int)~(unsigned)best - sub;    // the owner retires the winner
 #pragma unroll
-      for (int i = 0; i < VPL; ++i) key[i] = key[i] == best ? 0ull : key[i];     // the owner retires the winner
+      for (int i = 0; i < VPL; ++i) key[i] = won == i * G ? 0u : key[i];
       if (sub == j) mine = best;                     // lane j keeps slot j (k <= min(E, 16) <= G)
-      if (j == 0) top_z = key_logit(best);
+      if (j == 0) top_z = key_logit((unsigned)(best >> 32));
     }
     const int my_e = (int)~(unsigned)mine;
     // weights: softmax over the selected logits (renorm) or over all logits read at the selected ones
     const bool holds_slot = sub < k;
-    const float ex = holds_slot ? expf(key_logit(mine) - top_z) : 0.f;
+    const float ex = holds_slot ? expf(key_logit((unsigned)(mine >> 32)) - top_z) : 0.f;
     float den_all = 0.f;
     if (!renorm || score != nullptr) {
 #pragma unroll
@@ -508,8 +512,9 @@ int launch_route(const float* logits, int T, int E, int k, int renorm, int e_lo,
   const int tb = route_chunk_tokens(T);
   const int nchunks = cdiv(T, tb);
   int32_t* hist = static_cast<int32_t*>(ws);
-  // Up to 16384 counts every workgroup of the rank kernel adds them up itself (at most 64 KB from L2, 32 loads per thread in
-  // flight together), which spares a launch and its latency; beyond that the scan kernel does it once.
+  // Up to 16384 counts every workgroup of the rank kernel adds them up itself (at most 64 KB from L2, 32 loads per thread when E is
+  // a power of two, up to twice as many otherwise, in batches of 8), which spares a launch and its latency; beyond that the scan
+  // kernel does it once.
   const bool sums = (long)nchunks * E <= 16384;
   const int he = sums ? 1 : nchunks, hc = sums ? E : 1;
   const int rc = with_group(E, [&](auto g, auto v) -> int {

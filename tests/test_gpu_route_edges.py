@@ -192,3 +192,14 @@ def test_router_fwd_short_rows(T, d, E):
 @pytest.mark.parametrize("T,d,E", [(16383, 16, 33), (16384, 16, 33), (16400, 28, 5), (16384, 32, 70)])
 def test_router_fwd_f32_narrow(T, d, E):
     test_router_fwd_any_rows(T, d, E, 0, torch.float32)
+
+
+# few experts in the most chunks, many ties and several winners among the logits of one lane
+@pytest.mark.parametrize("T,E,k,quantum", [(65536, 1, 1, None), (65537, 3, 2, 1.0), (33000, 250, 16, 0.5), (300, 256, 16, 2.0), (300, 100, 16, None)])
+def test_route_lane_keys(T, E, k, quantum):
+    test_route_edges(T, E, k, quantum)
+
+
+@pytest.mark.parametrize("T,E,k", [(33000, 20, 3), (32768, 256, 4)])
+def test_route_nan_last_of_many_tokens(T, E, k):
+    test_route_nan_last(T, E, k)
