@@ -1,8 +1,8 @@
 // Dispatch, combine and the gate-weight gradient (Section 3.2: scatter and gather operators that move
 // rows according to a row map computed once from the routing result; Section 4.1: the weighted sum).
-// All three are HBM-bound row movers: one wave walks one token's row in 16-byte vectors per lane, so
-// every global access is a full 1 KiB wave-wide burst.  Token-centric on both sides: dispatch reads a
-// token row once and writes its k copies; combine gathers k rows and writes one.
+// All three are HBM-bound row movers in 16-byte vectors per lane, so every global access is a full 1 KiB
+// wave-wide burst.  Token-centric on both sides: dispatch reads a token row once and writes its k copies
+// (a few waves share the row where tokens are few); combine gathers k rows and writes one, a wave per token.
 #include "moe_common.h"
 
 namespace moe {
