@@ -56,11 +56,15 @@ struct Args {
   float* dw_part;                    // EPI_SWIGLU_BWD_W: [n-tiles * waves along n][M] partial sums of <dA'[r,:], A[r,:]>
 };
 
-__device__ __forceinline__ bf16x8 lds_read_b128(const char* p) { return *reinterpret_cast<const bf16x8*>(p); }
+// (LDS addresses in bytes)
+__device__ __forceinline__ bf16x8 lds_read_b128(unsigned p) {
+  typedef bf16x8 __attribute__((address_space(3))) * lds_bf16x8_ptr;
+  return *(lds_bf16x8_ptr)(uintptr_t)p;
+}
 
-__device__ __forceinline__ bf16x4 lds_read_tr(const char* p) {
+__device__ __forceinline__ bf16x4 lds_read_tr(unsigned p) {
   typedef s16x4 __attribute__((address_space(3))) * lds_s16x4_ptr;
-  const s16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
+  const s16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(uintptr_t)p);
   return __builtin_bit_cast(bf16x4, r);
 }
 

@@ -15,7 +15,7 @@
 // A direct-to-LDS load deposits the wave's 64 x 16 bytes contiguously, so the LDS swizzles are applied
 // on the global side: the lane that owns physical chunk pc of a row fetches logical chunk pc ^ swz(row).
 //   K-major tile [rows][BKT]:  swz = (row / rows_per_256B) mod chunks_per_row  -> ds_read_b128 conflict-free
-//   M/N-major tile [BKT][cols]: swz = 4 * (k mod 4)                            -> ds_read_b64_tr_b16 conflict-free
+//   M/N-major tile [BKT][cols]: swz = 4 * (k mod 4) ^ 2 * (k / 8 mod 2)        -> ds_read_b64_tr_b16 conflict-free
 // Loads that fall outside the contraction range fetch from a 16-byte zero block instead, which gives
 // the exact zero fill that ragged expert segments (wgrad) and K tails need.
 #pragma once
@@ -102,7 +102,7 @@ template <int COLS, int BKT> struct MNTile {       // M/N-major [BKT][COLS] bf16
   static constexpr int BYTES = BKT * ROW_BYTES;
   static constexpr int ROWS_PER_DMA = 1024 / ROW_BYTES;
   static_assert(ROW_BYTES <= 1024 && CPR >= 16, "M/N-major tiles are 128..512 columns wide");
-  __device__ static __forceinline__ int swz(int krow) { return (krow & 3) << 2; }
+  __device__ static __forceinline__ int swz(int krow) { return ((krow & 3) << 2) ^ ((krow >> 2) & 2); }
 };
 
 template <Layout L, int EXTENT, int BKT, int ESZ = 2> struct DmaTileBytes;
@@ -112,18 +112,29 @@ template <int EXTENT, int BKT, int ESZ> struct DmaTileBytes<MNMAJOR, EXTENT, BKT
   static constexpr int value = MNTile<EXTENT, BKT>::BYTES;
 };
 
+// Fragment of the 16x16x32 bf16 MFMA: lane l holds k = 8 * (l / 16) + 0..7 of row (or column) l % 16.  `origin` is what
+// frag_origin gives for the wave's first row, moved to the tile; fragment i lies 16 rows (columns) on, sub-step kk 32 of k.
+// In M/N-major tiles fragment i is the origin with i at bits 5..7 flipped: the caller hides the origin from the optimiser
+// once per phase, so that one exclusive-or makes an address where it is used instead of eight of them filling registers.
 template <Layout L, int EXTENT, int BKT>
-__device__ __forceinline__ bf16x8 read_frag_dma(const char* tile, int base, int kk, int lane) {
+__device__ __forceinline__ unsigned frag_origin(int base, int lane) {
+  const int i = lane & 15, g = lane >> 4;
   if constexpr (L == KMAJOR) {
-    const int row = base + (lane & 31);
-    return lds_read_b128(tile + KTile<EXTENT, BKT>::offset(row, kk * 2 + (lane >> 5)));
+    return (unsigned)KTile<EXTENT, BKT>::offset(base + i, g);
   } else {
     using TL = MNTile<EXTENT, BKT>;
-    const int g = lane >> 4, i = lane & 15;
-    const int krow = kk * 16 + ((g >> 1) << 3) + (i >> 2);          // krow & 3 == (i >> 2)
-    const int col = base + ((g & 1) << 4) + ((i & 3) << 2);
-    const int chunk = (col >> 3) ^ TL::swz(krow);
-    const char* p = tile + krow * TL::ROW_BYTES + (chunk << 4) + ((col & 7) << 1);
+    const int krow = (g << 3) + (i >> 2), col = base + ((i & 3) << 2);
+    return (unsigned)(krow * TL::ROW_BYTES + (((col >> 3) ^ TL::swz(krow)) << 4) + ((col & 7) << 1));
+  }
+}
+template <Layout L, int EXTENT, int BKT>
+__device__ __forceinline__ bf16x8 read_frag_dma(unsigned origin, int i, int kk) {
+  if constexpr (L == KMAJOR) {
+    using TL = KTile<EXTENT, BKT>;
+    return lds_read_b128((origin ^ (unsigned)(kk << 6)) + (unsigned)(i * 16 * TL::ROW_BYTES));
+  } else {
+    using TL = MNTile<EXTENT, BKT>;
+    const unsigned p = (origin ^ (unsigned)(i << 5)) + (unsigned)(kk * 32 * TL::ROW_BYTES);
     const bf16x4 lo = lds_read_tr(p);
     const bf16x4 hi = lds_read_tr(p + 4 * TL::ROW_BYTES);             // krow + 4 has the same swizzle
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -132,12 +143,16 @@ __device__ __forceinline__ bf16x8 read_frag_dma(const char* tile, int base, int 
 
 
 // ---- epilogue staging --------------------------------------------------------------------------------
-// After the MFMA (weight fragment first) a lane holds one output row (lane % 32) and columns
-// 8q + 4*(lane/32) + 0..3 (q = 0..3) of a 32x32 tile: a direct store would touch 32 rows with 16 bytes
-// each.  Each wave therefore owns a small LDS patch of 32 rows x 64 bytes; tiles pass through it so that
+// After the MFMA (weight fragment first) a lane holds row lane % 16 and columns 4*(lane/16) + 0..3 of each 16x16
+// tile; the epilogues work on blocks of 2x2 of them, 32x32, in which group q = 0..3 of a lane's values is row
+// 16*(q/2) + lane%16, columns 16*(q%2) + 4*(lane/16) + 0..3.  A direct store would touch 16 rows with 16 bytes each
+// quarter.  Each wave therefore owns a small LDS patch of 32 rows x 64 bytes; blocks pass through it so that
 // global memory sees 16-byte lanes forming 64-byte row segments (4 lanes per row, 16 rows per instruction).
 constexpr int STG_STRIDE = 80;                  // bytes per staged row (64 payload + 16 pad)
 constexpr int STG_BYTES = 32 * STG_STRIDE;      // per wave
+__device__ __forceinline__ int patch_row(int q, int lane) { return ((q >> 1) << 4) + (lane & 15); }
+__device__ __forceinline__ int patch_col(int q, int lane) { return ((q & 1) << 4) + ((lane >> 4) << 2); }
+struct Block { f32x4 q[4]; };                   // a lane's values of one 32x32 block
 
 // Global accesses of the epilogues are raw buffer instructions on a descriptor that starts at the block's origin
 // (wave-uniform): a lane outside the valid rows or columns gets an offset past the end of the buffer, which the
@@ -159,9 +174,8 @@ __device__ __forceinline__ unsigned block_offset(int r, int c, long ld, int esz,
 // 32 rows x 32 bf16 columns from registers to global memory (row-major, leading dimension ld elements).
 __device__ __forceinline__ void stage_store_bf16(char* stg, const bf16x4 (&v)[4], bf16* g, long ld, int rows_valid,
                                                  int cols_valid, int lane) {
-  const int row = lane & 31, h = lane >> 5;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) *reinterpret_cast<bf16x4*>(stg + row * STG_STRIDE + (8 * q + 4 * h) * 2) = v[q];
+  for (int q = 0; q < 4; ++q) *reinterpret_cast<bf16x4*>(stg + patch_row(q, lane) * STG_STRIDE + patch_col(q, lane) * 2) = v[q];
   const __amdgpu_buffer_rsrc_t rs = block_rsrc(g);
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass) {
@@ -181,9 +195,8 @@ __device__ __forceinline__ void stage_load_bf16(char* stg, bf16x4 (&v)[4], const
     const u32x4v val = __builtin_amdgcn_raw_buffer_load_b128(rs, block_offset(r, c, ld, 2, rows_valid, cols_valid), 0, 0);
     *reinterpret_cast<u32x4v*>(stg + r * STG_STRIDE + c * 2) = val;
   }
-  const int row = lane & 31, h = lane >> 5;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const bf16x4*>(stg + row * STG_STRIDE + (8 * q + 4 * h) * 2);
+  for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const bf16x4*>(stg + patch_row(q, lane) * STG_STRIDE + patch_col(q, lane) * 2);
 }
 
 // The same load in two phases, so that the global reads of the next 32x32 block can be in flight while the
@@ -206,24 +219,19 @@ __device__ __forceinline__ void stage_unpack_bf16(char* stg, const StageFetch& f
     const int r = pass * 16 + (lane >> 2), c = (lane & 3) * 8;
     *reinterpret_cast<u32x4v*>(stg + r * STG_STRIDE + c * 2) = f.v[pass];
   }
-  const int row = lane & 31, h = lane >> 5;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const bf16x4*>(stg + row * STG_STRIDE + (8 * q + 4 * h) * 2);
+  for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const bf16x4*>(stg + patch_row(q, lane) * STG_STRIDE + patch_col(q, lane) * 2);
 }
 
 // 32 rows x 32 fp32 columns, as two halves of 16 columns; optional read-modify-write accumulation.
-__device__ __forceinline__ void stage_store_f32(char* stg, const f32x16& acc, float* g, long ld, int rows_valid,
+__device__ __forceinline__ void stage_store_f32(char* stg, const Block& acc, float* g, long ld, int rows_valid,
                                                 int cols_valid, bool accumulate, int lane) {
-  const int row = lane & 31, h = lane >> 5;
   const __amdgpu_buffer_rsrc_t rs = block_rsrc(g);
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
 #pragma unroll
-    for (int qq = 0; qq < 2; ++qq) {
-      const int q = half * 2 + qq;
-      const f32x4 t = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-      *reinterpret_cast<f32x4*>(stg + row * STG_STRIDE + (8 * qq + 4 * h) * 4) = t;
-    }
+    for (int i = 0; i < 2; ++i)
+      *reinterpret_cast<f32x4*>(stg + patch_row(2 * i, lane) * STG_STRIDE + patch_col(2 * i, lane) * 4) = acc.q[2 * i + half];
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
       const int r = pass * 16 + (lane >> 2), c = half * 16 + (lane & 3) * 4;
@@ -240,9 +248,8 @@ __device__ __forceinline__ void stage_store_f32(char* stg, const f32x16& acc, fl
 // 32 rows x 32 bf16 columns from registers to global memory (row-major, leading dimension ld elements).
 __device__ __forceinline__ void stage_store_bf16_g(char* stg, const bf16x4 (&v)[4], bf16* g, long ld, int rows_valid,
                                                  int cols_valid, int lane) {
-  const int row = lane & 31, h = lane >> 5;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) *reinterpret_cast<bf16x4*>(stg + row * STG_STRIDE + (8 * q + 4 * h) * 2) = v[q];
+  for (int q = 0; q < 4; ++q) *reinterpret_cast<bf16x4*>(stg + patch_row(q, lane) * STG_STRIDE + patch_col(q, lane) * 2) = v[q];
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass) {
     const int r = pass * 16 + (lane >> 2), c = (lane & 3) * 8;
@@ -261,23 +268,18 @@ __device__ __forceinline__ void stage_load_bf16_g(char* stg, bf16x4 (&v)[4], con
     if (r < rows_valid && c < cols_valid) val = *reinterpret_cast<const uint4*>(g + (long)r * ld + c);
     *reinterpret_cast<uint4*>(stg + r * STG_STRIDE + c * 2) = val;
   }
-  const int row = lane & 31, h = lane >> 5;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const bf16x4*>(stg + row * STG_STRIDE + (8 * q + 4 * h) * 2);
+  for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const bf16x4*>(stg + patch_row(q, lane) * STG_STRIDE + patch_col(q, lane) * 2);
 }
 
 // 32 rows x 32 fp32 columns, as two halves of 16 columns; optional read-modify-write accumulation.
-__device__ __forceinline__ void stage_store_f32_g(char* stg, const f32x16& acc, float* g, long ld, int rows_valid,
+__device__ __forceinline__ void stage_store_f32_g(char* stg, const Block& acc, float* g, long ld, int rows_valid,
                                                 int cols_valid, bool accumulate, int lane) {
-  const int row = lane & 31, h = lane >> 5;
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
 #pragma unroll
-    for (int qq = 0; qq < 2; ++qq) {
-      const int q = half * 2 + qq;
-      const f32x4 t = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-      *reinterpret_cast<f32x4*>(stg + row * STG_STRIDE + (8 * qq + 4 * h) * 4) = t;
-    }
+    for (int i = 0; i < 2; ++i)
+      *reinterpret_cast<f32x4*>(stg + patch_row(2 * i, lane) * STG_STRIDE + patch_col(2 * i, lane) * 4) = acc.q[2 * i + half];
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
       const int r = pass * 16 + (lane >> 2), c = half * 16 + (lane & 3) * 4;
@@ -291,14 +293,15 @@ __device__ __forceinline__ void stage_store_f32_g(char* stg, const f32x16& acc, 
   }
 }
 
-// e4m3 fragment (32 rows x 64 k, 32 bytes per lane) for the 32x32x64 f8f6f4 MFMA out of a K-major tile.
+// e4m3 fragment of the 16x16x128 f8f6f4 MFMA (32 bytes per lane) out of a K-major tile.  Lane l takes chunks l / 16 and
+// 4 + l / 16 of its row: the same order of k in both operands, and eight rows' worth of lanes never meet in a bank.
 template <int EXTENT, int BKT>
 __device__ __forceinline__ i32x8 read_frag_fp8(const char* tile, int base, int kk, int lane) {
   using TL = KTile<EXTENT, BKT, 1>;
-  const int row = base + (lane & 31);
-  const int c0 = kk * 4 + ((lane >> 5) << 1);
+  const int row = base + (lane & 15);
+  const int c0 = kk * 8 + (lane >> 4);
   const uint4 lo = *reinterpret_cast<const uint4*>(tile + TL::offset(row, c0));
-  const uint4 hi = *reinterpret_cast<const uint4*>(tile + TL::offset(row, c0 + 1));
+  const uint4 hi = *reinterpret_cast<const uint4*>(tile + TL::offset(row, c0 + 4));
   i32x8 r = {(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
   return r;
 }
@@ -397,7 +400,8 @@ template <int BM, int BN, int BKT, int NSTAGE, int WM, int WN, Layout LA, Layout
 __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) {
   constexpr int NW = WM * WN;
   constexpr int WTM = BM / WM, WTN = BN / WN;
-  constexpr int TM = WTM / 32, TN = WTN / 32;
+  constexpr int FM = WTM / 16, FN = WTN / 16;         // fragments of a wave along each side
+  constexpr int TM = WTM / 32, TN = WTN / 32;         // 32x32 blocks of its epilogue
   constexpr int ESZ = sizeof(TIN);
   constexpr bool FP8 = ESZ == 1;
   constexpr int CHUNK = 16 / ESZ;                     // elements per 16-byte chunk
@@ -414,7 +418,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
   constexpr int NL = SPLIT ? NW / 2 : NW;                                      // loader waves
   constexpr int A_DMA = A_BYTES / 1024 / NL, B_DMA = B_BYTES / 1024 / NL;     // loads per loader wave per stage
   constexpr int LOADS = A_DMA + B_DMA;
-  constexpr int KK = FP8 ? BKT / 64 : BKT / 16;    // MFMA sub-steps per k-step
+  constexpr int KK = FP8 ? BKT / 128 : BKT / 32;   // MFMA sub-steps per k-step
   constexpr bool SWI = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_W;              // FC1 + SwiGLU epilogue
   constexpr bool FOLD = EPI == EPI_SWIGLU_W || EPI == EPI_SWIGLU_BWD_W;       // gate weight folded in (Section 4.1)
   constexpr bool GATHER_A = EPI == EPI_SWIGLU_W;                              // A rows selected by index map (Section 4.2)
@@ -450,6 +454,12 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
   const int wm = wave / WN, wn = wave % WN;
   const char* zero = reinterpret_cast<const char*>(g_zero_block);
   char* stg = smem + RING_BYTES + TABLE_BYTES + wave * STG_BYTES;      // this wave's epilogue patch
+  // where this lane's fragments of the wave's first rows lie in a ring slot (bf16)
+  unsigned fo_a = 0, fo_b = 0;
+  if constexpr (!FP8) {
+    fo_a = frag_origin<LA, BM, BKT>(wm * WTM, lane);
+    fo_b = (unsigned)A_BYTES + frag_origin<LB, BN, BKT>(wn * WTN, lane);
+  }
 
   // ---- the tile list ------------------------------------------------------------------------------
   // Workgroup b runs on XCD b % 8 and each XCD has its own L2.  The logical tile order is cut into windows
@@ -519,11 +529,11 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
   // wave and k-step, 48 per workgroup next to the 64 tile loads, and the address unit is what the load issue is
   // bound by: the k-step was 0.4 us longer.
   static_assert(!BSCALE || (BM == 256 && BN == 256), "one 4-byte load per lane covers the 256 channels of a tile side");
-  int sa_cur[TM], sb_cur[TN];
+  int sa_cur[FM], sb_cur[FN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) sa_cur[i] = 127;
+  for (int i = 0; i < FM; ++i) sa_cur[i] = 127;
 #pragma unroll
-  for (int j = 0; j < TN; ++j) sb_cur[j] = 127;
+  for (int j = 0; j < FN; ++j) sb_cur[j] = 127;
   const char* sa_base = nullptr;        // scale row of the tile's first k-step (wave-uniform)
   const char* sb_base = nullptr;
   unsigned sa_voff = 0, sb_voff = 0;    // this lane's four channels
@@ -739,13 +749,11 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
   issue_prologue();
 
   for (;;) {
-    f32x16 acc[TM][TN];
+    f32x4 acc[FM][FN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // Wait until this wave's loads for step s have landed.  vmcnt counts loads and stores together, in issue order, so
     // the wait names how many younger operations may still be outstanding: the loads of the (NSTAGE - 2) following
@@ -773,7 +781,13 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
     // have no room for a second set of 32-byte fragments.
     constexpr bool XPIPE = !FP8 && (MODE != KSEG || NSTAGE == 2);
     if constexpr (XPIPE) {
-      static_assert(KK % 2 == 0, "fragment sets alternate by sub-step parity");
+      // A sub-step is cut into phases: the wave's fragments of its shorter side are held for the whole sub-step, those of
+      // the longer side pass through PC at a time.  Phase p multiplies while the fragments of phase p + 1 are read.
+      constexpr bool HOLD_A = FM <= FN;
+      constexpr int FH = HOLD_A ? FM : FN, FS = HOLD_A ? FN : FM;
+      constexpr int PC = FS % 4 == 0 ? 4 : 2, NPH = FS / PC;
+      constexpr int PHASES = KK * NPH;
+      static_assert(KK % 2 == 0 && FS % PC == 0, "fragment sets alternate by sub-step and by phase parity");
       // opens step s: its loads have landed (at most the younger steps' loads are outstanding; the first step of a
       // tile also drains the previous tile's epilogue stores), every wave is done with step s-1, whose stage is
       // refilled right away
@@ -791,37 +805,49 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
       if (!wave_active) {
         for (int s = 0; s < nk; ++s) open_step(s);
       } else if (nk > 0) {
-        bf16x8 af[2][TM], bfr[2][TN];
-        auto read_frags = [&](const char* at, int kk, int set) __attribute__((always_inline)) {
-          const char* bt = at + A_BYTES;
+        bf16x8 held[2][FH], strm[2][PC];
+        // the fragments that phase p of the step in ring slot `slot_lds` needs beyond the ones the phase before it has
+        auto read_phase = [&](unsigned slot_lds, int p) __attribute__((always_inline)) {
+          const int kk = p / NPH, ph = p % NPH;
+          unsigned ao = fo_a + slot_lds, bo = fo_b + slot_lds;
+          if constexpr (LA == MNMAJOR) asm volatile("" : "+v"(ao));
+          if constexpr (LB == MNMAJOR) asm volatile("" : "+v"(bo));
+          auto read_a = [&](int i) __attribute__((always_inline)) { return read_frag_dma<LA, BM, BKT>(ao, i, kk); };
+          auto read_b = [&](int j) __attribute__((always_inline)) { return read_frag_dma<LB, BN, BKT>(bo, j, kk); };
+          if (ph == 0) {
 #pragma unroll
-          for (int i = 0; i < TM; ++i) af[set][i] = read_frag_dma<LA, BM, BKT>(at, wm * WTM + i * 32, kk, lane);
+            for (int h = 0; h < FH; ++h) held[kk & 1][h] = HOLD_A ? read_a(h) : read_b(h);
+          }
 #pragma unroll
-          for (int j = 0; j < TN; ++j) bfr[set][j] = read_frag_dma<LB, BN, BKT>(bt, wn * WTN + j * 32, kk, lane);
+          for (int c = 0; c < PC; ++c) strm[p & 1][c] = HOLD_A ? read_b(ph * PC + c) : read_a(ph * PC + c);
         };
         open_step(0);
-        read_frags(smem, 0, 0);
+        read_phase(smem_lds, 0);
         for (int kt = 0; kt < nk; ++kt) {
-          const char* at = smem + (kt % NSTAGE) * STAGE_BYTES;
+          const unsigned at = smem_lds + (unsigned)(kt % NSTAGE) * STAGE_BYTES;
 #pragma unroll
-          for (int kk = 0; kk < KK; ++kk) {
-            constexpr int TOUCH_AT = KK >= 2 ? KK - 2 : 0;      // one sub-step ahead of the refill it runs before (later: slower)
+          for (int p = 0; p < PHASES; ++p) {
+            constexpr int TOUCH_AT = PHASES >= 2 ? PHASES - 2 : 0;      // one phase ahead of the refill it runs before (later: slower)
             if constexpr (TOUCH || TOUCH_K2) {
-              if (kk == TOUCH_AT && is_toucher && (kt + NSTAGE + 1) * BKT <= klen) {   // whole k-steps only: every touched address exists
+              if (p == TOUCH_AT && is_toucher && (kt + NSTAGE + 1) * BKT <= klen) {   // whole k-steps only: every touched address exists
                 touch4s(a_base + (long)(kt + NSTAGE) * a_step, ta_off, lds_dump);
               }
             }
-            if (kk + 1 < KK) {
-              read_frags(at, kk + 1, (kk + 1) & 1);
+            if (p + 1 < PHASES) {
+              read_phase(at, p + 1);
             } else if (kt + 1 < nk) {
               open_step(kt + 1);
-              read_frags(smem + ((kt + 1) % NSTAGE) * STAGE_BYTES, 0, 0);
+              read_phase(smem_lds + (unsigned)((kt + 1) % NSTAGE) * STAGE_BYTES, 0);
             }
+            const int kk = p / NPH, ph = p % NPH;
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int c = 0; c < PC; ++c)
 #pragma unroll
-              for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[kk & 1][j], af[kk & 1][i], acc[i][j], 0, 0, 0);
+              for (int h = 0; h < FH; ++h) {
+                const bf16x8 fa = HOLD_A ? held[kk & 1][h] : strm[p & 1][c], fb = HOLD_A ? strm[p & 1][c] : held[kk & 1][h];
+                const int i = HOLD_A ? h : ph * PC + c, j = HOLD_A ? ph * PC + c : h;
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb, fa, acc[i][j], 0, 0, 0);
+              }
           }
         }
       }
@@ -839,12 +865,14 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
         // this step's scale bytes landed with its tiles (same wait, same barrier)
         const unsigned char* sc = reinterpret_cast<const unsigned char*>(scale_smem) + (kt % NSTAGE) * 512;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) sa_cur[i] = sc[wm * WTM + i * 32 + (lane & 31)];
+        for (int i = 0; i < FM; ++i) sa_cur[i] = sc[wm * WTM + i * 16 + (lane & 15)];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) sb_cur[j] = sc[256 + wn * WTN + j * 32 + (lane & 31)];
+        for (int j = 0; j < FN; ++j) sb_cur[j] = sc[256 + wn * WTN + j * 16 + (lane & 15)];
       }
       const char* at = smem + (kt % NSTAGE) * STAGE_BYTES;
       const char* bt = at + A_BYTES;
+      const unsigned at_lds = smem_lds + (unsigned)(kt % NSTAGE) * STAGE_BYTES;
+      (void)at; (void)bt; (void)at_lds;
       if constexpr (MODE == ROWSEG) {
         // A wave whose rows all lie past the expert's last row has nothing to multiply (wave-uniform; it still
         // issued its loads and takes part in the barriers).  In a nearly empty last tile of an expert only one or
@@ -865,31 +893,40 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
           }
         }
         if constexpr (FP8) {
-          // 32x32x64 e4m3 x e4m3 (format selectors 0, 0), both block scales 2^0 (E8M0 code 127)
-          i32x8 af[TM], bfr[TN];
+          // 16x16x128 e4m3 x e4m3 (format selectors 0, 0), both block scales 2^0 (E8M0 code 127) unless scaled by group
+          i32x8 held[FM <= FN ? FM : FN];
+          if constexpr (FM <= FN) {
 #pragma unroll
-          for (int i = 0; i < TM; ++i) af[i] = read_frag_fp8<BM, BKT>(at, wm * WTM + i * 32, kk, lane);
+            for (int i = 0; i < FM; ++i) held[i] = read_frag_fp8<BM, BKT>(at, wm * WTM + i * 16, kk, lane);
 #pragma unroll
-          for (int j = 0; j < TN; ++j) bfr[j] = read_frag_fp8<BN, BKT>(bt, wn * WTN + j * 32, kk, lane);
+            for (int j = 0; j < FN; ++j) {
+              const i32x8 fb = read_frag_fp8<BN, BKT>(bt, wn * WTN + j * 16, kk, lane);
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
+              for (int i = 0; i < FM; ++i)
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fb, held[i], acc[i][j], 0, 0, 0, BSCALE ? sb_cur[j] : 127, 0, BSCALE ? sa_cur[i] : 127);
+            }
+          } else {
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-              if constexpr (BSCALE)
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bfr[j], af[i], acc[i][j], 0, 0, 0, sb_cur[j], 0, sa_cur[i]);
-              else
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bfr[j], af[i], acc[i][j], 0, 0, 0, 127, 0, 127);
+            for (int j = 0; j < FN; ++j) held[j] = read_frag_fp8<BN, BKT>(bt, wn * WTN + j * 16, kk, lane);
+#pragma unroll
+            for (int i = 0; i < FM; ++i) {
+              const i32x8 fa = read_frag_fp8<BM, BKT>(at, wm * WTM + i * 16, kk, lane);
+#pragma unroll
+              for (int j = 0; j < FN; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(held[j], fa, acc[i][j], 0, 0, 0, BSCALE ? sb_cur[j] : 127, 0, BSCALE ? sa_cur[i] : 127);
+            }
+          }
         } else {
-          bf16x8 af[TM], bfr[TN];
+          bf16x8 af[FM], bfr[FN];
 #pragma unroll
-          for (int i = 0; i < TM; ++i) af[i] = read_frag_dma<LA, BM, BKT>(at, wm * WTM + i * 32, kk, lane);
+          for (int i = 0; i < FM; ++i) af[i] = read_frag_dma<LA, BM, BKT>(fo_a + at_lds, i, kk);
 #pragma unroll
-          for (int j = 0; j < TN; ++j) bfr[j] = read_frag_dma<LB, BN, BKT>(bt, wn * WTN + j * 32, kk, lane);
+          for (int j = 0; j < FN; ++j) bfr[j] = read_frag_dma<LB, BN, BKT>(fo_b + at_lds, j, kk);
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
+          for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
+            for (int j = 0; j < FN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
         }
       }
     }
@@ -928,28 +965,32 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
       // e4m3 operands with per-row / per-output-channel scales: output = acc * scale of the row (token) * scale of
       // the output channel, applied block by block right before a block is written, so that only one block's 16
       // channel scales are live at a time
-      auto dequant_block = [&](int i, int j) __attribute__((always_inline)) {
+      auto block = [&](int i, int j) __attribute__((always_inline)) -> Block {
+        Block b = {{acc[2 * i][2 * j], acc[2 * i][2 * j + 1], acc[2 * i + 1][2 * j], acc[2 * i + 1][2 * j + 1]}};
         if constexpr (FP8 && !BSCALE) {
-          const int lrow = lane & 31, lcol = (lane >> 5) << 2;
-          const int m = min(m0 + wm * WTM + i * 32 + lrow, p.M - 1);
-          const float rs = p.row_scale ? p.row_scale[m] : 1.f;
+          float rs[2] = {1.f, 1.f};
+          f32x4 cs[2];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
+          for (int h = 0; h < 2; ++h) {
+            if (p.row_scale) rs[h] = p.row_scale[min(m0 + wm * WTM + i * 32 + patch_row(2 * h, lane), p.M - 1)];
             int n;
             if constexpr (SWI) {
-              const int nn = min(n0 + ((wn * WTN + (j & ~1) * 32) >> 1) + q * 8 + lcol, p.f - 4);
+              const int nn = min(n0 + ((wn * WTN + (j & ~1) * 32) >> 1) + patch_col(h, lane), p.f - 4);
               n = (j & 1) ? p.f + nn : nn;
             } else {
-              n = min(n0 + wn * WTN + j * 32 + q * 8 + lcol, p.N - 4);
+              n = min(n0 + wn * WTN + j * 32 + patch_col(h, lane), p.N - 4);
             }
-            f32x4 cs = {1.f, 1.f, 1.f, 1.f};
-            if (p.col_scale) cs = *reinterpret_cast<const f32x4*>(p.col_scale + (long)e * p.cs_es + n);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) acc[i][j][4 * q + t] *= rs * cs[t];
+            cs[h] = f32x4{1.f, 1.f, 1.f, 1.f};
+            if (p.col_scale) cs[h] = *reinterpret_cast<const f32x4*>(p.col_scale + (long)e * p.cs_es + n);
           }
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) b.q[q][t] *= rs[q >> 1] * cs[q & 1][t];
         }
+        return b;
       };
-      // every 32x32 MFMA tile goes through the wave's LDS patch (see stage_store_* above); bf16 kernels use the
+      // every 32x32 block goes through the wave's LDS patch (see stage_store_* above); bf16 kernels use the
       // branch-free buffer accesses, e4m3 kernels the plain ones
       auto store_bf16 = [&](const bf16x4 (&v)[4], bf16* g, long ld, int rv, int cv) __attribute__((always_inline)) {
         if constexpr (PLAIN_EPI) stage_store_bf16_g(stg, v, g, ld, rv, cv, lane); else stage_store_bf16(stg, v, g, ld, rv, cv, lane);
@@ -957,7 +998,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
       auto load_bf16 = [&](bf16x4 (&v)[4], const bf16* g, long ld, int rv, int cv) __attribute__((always_inline)) {
         if constexpr (PLAIN_EPI) stage_load_bf16_g(stg, v, g, ld, rv, cv, lane); else stage_load_bf16(stg, v, g, ld, rv, cv, lane);
       };
-      auto store_f32 = [&](const f32x16& a, float* g, long ld, int rv, int cv, bool accumulate) __attribute__((always_inline)) {
+      auto store_f32 = [&](const Block& a, float* g, long ld, int rv, int cv, bool accumulate) __attribute__((always_inline)) {
         if constexpr (PLAIN_EPI) stage_store_f32_g(stg, a, g, ld, rv, cv, accumulate, lane); else stage_store_f32(stg, a, g, ld, rv, cv, accumulate, lane);
       };
       if (SPLITK && ep_part_slot >= 0) {
@@ -967,8 +1008,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
-            dequant_block(i, j);
-            store_f32(acc[i][j], part_tile + (long)(wm * WTM + i * 32) * BN + wn * WTN + j * 32, BN, 32, 32, false);
+            store_f32(block(i, j), part_tile + (long)(wm * WTM + i * 32) * BN + wn * WTN + j * 32, BN, 32, 32, false);
           }
       } else if constexpr (EPI == EPI_STORE) {
 #pragma unroll
@@ -981,10 +1021,10 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
             const int nb = n0 + wn * WTN + j * 32;
             const int cols_valid = p.N - nb;
             if (cols_valid <= 0) continue;
-            dequant_block(i, j);
+            const Block b = block(i, j);
             if constexpr (sizeof(TC) == 4) {
               float* g = static_cast<float*>(p.C) + (long)e * p.c_es + (long)mb * p.ldc + nb;
-              store_f32(acc[i][j], g, p.ldc, rows_valid, cols_valid, p.accumulate != 0);
+              store_f32(b, g, p.ldc, rows_valid, cols_valid, p.accumulate != 0);
             } else {
               bf16* g = static_cast<bf16*>(p.C) + (long)e * p.c_es + (long)mb * p.ldc + nb;
               bf16x4 v[4];
@@ -995,57 +1035,58 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
                 for (int q = 0; q < 4; ++q)
 #pragma unroll
                   for (int t = 0; t < 4; ++t)
-                    v[q][t] = static_cast<bf16>(acc[i][j][4 * q + t] + static_cast<float>(old[q][t]));
+                    v[q][t] = static_cast<bf16>(b.q[q][t] + static_cast<float>(old[q][t]));
               } else {
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
 #pragma unroll
-                  for (int t = 0; t < 4; ++t) v[q][t] = static_cast<bf16>(acc[i][j][4 * q + t]);
+                  for (int t = 0; t < 4; ++t) v[q][t] = static_cast<bf16>(b.q[q][t]);
               }
               store_bf16(v, g, p.ldc, rows_valid, cols_valid);
             }
           }
         }
       } else if constexpr (EPI == EPI_BIAS_F32) {
-        const int lrow = lane & 31, lcol = (lane >> 5) << 2;
         float* __restrict__ Cg = static_cast<float*>(p.C);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const int m = m0 + wm * WTM + i * 32 + lrow;
+        for (int i = 0; i < FM; ++i) {
+          const int m = m0 + wm * WTM + i * 16 + (lane & 15);
           if (m >= m_end) continue;
 #pragma unroll
-          for (int j = 0; j < TN; ++j)
+          for (int j = 0; j < FN; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int n = n0 + wn * WTN + j * 32 + (r >> 2) * 8 + lcol + (r & 3);
+            for (int r = 0; r < 4; ++r) {
+              const int n = n0 + wn * WTN + j * 16 + ((lane >> 4) << 2) + r;
               if (n < p.N) Cg[(long)m * p.ldc + n] = acc[i][j][r] + (p.bias ? p.bias[n] : 0.f);
             }
         }
       } else if constexpr (SWI) {
-        // MFMA tile 2j holds G and tile 2j+1 holds U for the same 32 output columns
+        // block 2j holds G and block 2j+1 holds U for the same 32 output columns
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
           const int mb = m0 + wm * WTM + i * 32;
           const int rows_valid = m_end - mb;
           if (rows_valid <= 0) continue;
-          float w_row = 1.0f;                                   // this lane's row is lane % 32 of the block
-          if constexpr (FOLD) w_row = p.row_w[min(mb + (lane & 31), p.M - 1)];
+          float w_row[2] = {1.0f, 1.0f};                        // of this lane's two rows of the block
+          if constexpr (FOLD) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) w_row[h] = p.row_w[min(mb + patch_row(2 * h, lane), p.M - 1)];
+          }
 #pragma unroll
           for (int j = 0; j < TN; j += 2) {
             const int nb = n0 + ((wn * WTN + j * 32) >> 1);
             const int cols_valid = p.f - nb;
             if (cols_valid <= 0) continue;
-            dequant_block(i, j);
-            dequant_block(i, j + 1);
+            const Block bg = block(i, j), bu = block(i, j + 1);
             bf16x4 g[4], u[4], a[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
               for (int t = 0; t < 4; ++t) {
-                g[q][t] = static_cast<bf16>(acc[i][j][4 * q + t]);
-                u[q][t] = static_cast<bf16>(acc[i][j + 1][4 * q + t]);
+                g[q][t] = static_cast<bf16>(bg.q[q][t]);
+                u[q][t] = static_cast<bf16>(bu.q[q][t]);
                 const float gf = static_cast<float>(g[q][t]);
-                a[q][t] = static_cast<bf16>(w_row * (gf * sigmoid_f32(gf) * static_cast<float>(u[q][t])));
+                a[q][t] = static_cast<bf16>(w_row[q >> 1] * (gf * sigmoid_f32(gf) * static_cast<float>(u[q][t])));
               }
             bf16* hrow = p.H + (long)mb * 2 * p.f + nb;
             store_bf16(g, hrow, 2L * p.f, rows_valid, cols_valid);
@@ -1059,21 +1100,21 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
         // once per row in the combine of d_xp and in the rows handed to wgrad1, not per element here), the stored
         // FC2 input is A', and <dA'[r,:], A[r,:]> over this wave's columns goes to dw_part as one partial sum of the
         // gate-weight gradient of row r.
-        auto swiglu_bwd_block = [&](const f32x16& dacc, const bf16x4 (&g)[4], const bf16x4 (&u)[4], int mb, int nb,
-                                    int rows_valid, int cols_valid, float w_row, float& dw_sum) __attribute__((always_inline)) {
+        auto swiglu_bwd_block = [&](const Block& dacc, const bf16x4 (&g)[4], const bf16x4 (&u)[4], int mb, int nb,
+                                    int rows_valid, int cols_valid, const float (&w_row)[2], float (&dw_sum)[2]) __attribute__((always_inline)) {
           bf16x4 dg[4], du[4], a[4];
 #pragma unroll
           for (int q = 0; q < 4; ++q)
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
               const float gf = static_cast<float>(g[q][t]), uf = static_cast<float>(u[q][t]);
-              float d = static_cast<float>(static_cast<bf16>(dacc[4 * q + t]));
+              float d = static_cast<float>(static_cast<bf16>(dacc.q[q][t]));
               const float sg = sigmoid_f32(gf);
               const float av = gf * sg * uf;
-              if constexpr (FOLD) dw_sum += d * av;      // masked G, U are zero: columns past N and rows past the segment add 0
+              if constexpr (FOLD) dw_sum[q >> 1] += d * av;      // masked G, U are zero: columns past N and rows past the segment add 0
               dg[q][t] = static_cast<bf16>(d * uf * sg * (1.0f + gf * (1.0f - sg)));
               du[q][t] = static_cast<bf16>(d * gf * sg);
-              a[q][t] = static_cast<bf16>(FOLD ? w_row * av : av);
+              a[q][t] = static_cast<bf16>(FOLD ? w_row[q >> 1] * av : av);
             }
           bf16* drow = p.dH + (long)mb * 2 * p.N + nb;
           store_bf16(dg, drow, 2L * p.N, rows_valid, cols_valid);
@@ -1084,21 +1125,29 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
             store_bf16(a, p.A_out + (long)mb * p.N + nb, p.N, p.A_out ? rows_valid : 0, cols_valid);   // no A_out: all lanes masked
           }
         };
-        // lanes l and l + 32 hold the two column halves of row l.  Every row of the expert's segment gets exactly one
+        // the four lanes with the same lane % 16 hold a row's columns.  Every row of the expert's segment gets exactly one
         // partial per (n-tile, wave along n); blocks past N contribute zero.
-        auto row_weight = [&](int i) __attribute__((always_inline)) -> float {
-          if constexpr (FOLD) return p.row_w[min(m0 + wm * WTM + i * 32 + (lane & 31), p.M - 1)];
-          return 1.0f;
-        };
-        auto write_dw = [&](int i, float dw_sum) __attribute__((always_inline)) {
+        auto row_weight = [&](int i, float (&w)[2]) __attribute__((always_inline)) {
           if constexpr (FOLD) {
-            const float tot = dw_sum + __shfl_xor(dw_sum, 32);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) w[h] = p.row_w[min(m0 + wm * WTM + i * 32 + patch_row(2 * h, lane), p.M - 1)];
+          }
+        };
+        auto write_dw = [&](int i, const float (&dw_sum)[2]) __attribute__((always_inline)) {
+          if constexpr (FOLD) {
+            float tot[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              tot[h] = dw_sum[h] + __shfl_xor(dw_sum[h], 16);
+              tot[h] += __shfl_xor(tot[h], 32);
+            }
             const int mb = m0 + wm * WTM + i * 32;
             const __amdgpu_buffer_rsrc_t rs = block_rsrc(p.dw_part + (long)((n0 / BN) * WN + wn) * p.M + mb);
-            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, tot), rs,
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, lane < 16 ? tot[0] : tot[1]), rs,
                                                   (lane < 32 && mb + lane < m_end) ? (unsigned)lane * 4u : BUF_OOB, 0, 0);
           }
         };
+        float w_row[2] = {1.0f, 1.0f}, dw_sum[2] = {0.f, 0.f};
         if constexpr (FP8) {
           // (the e4m3 instantiation has no registers to spare for reading ahead)
 #pragma unroll
@@ -1106,7 +1155,6 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
             const int mb = m0 + wm * WTM + i * 32;
             const int rows_valid = m_end - mb;
             if (rows_valid <= 0) continue;
-            float dw_sum = 0.f;
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
               const int nb = n0 + wn * WTN + j * 32;
@@ -1116,8 +1164,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
               const bf16* hrow = p.H + (long)mb * 2 * p.N + nb;
               load_bf16(g, hrow, 2L * p.N, rows_valid, cols_valid);
               load_bf16(u, hrow + p.N, 2L * p.N, rows_valid, cols_valid);
-              dequant_block(i, j);
-              swiglu_bwd_block(acc[i][j], g, u, mb, nb, rows_valid, cols_valid, 1.0f, dw_sum);
+              swiglu_bwd_block(block(i, j), g, u, mb, nb, rows_valid, cols_valid, w_row, dw_sum);
             }
           }
         } else {
@@ -1143,11 +1190,10 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
           // uniform skip of single blocks would again make the number of stores in flight unknown to the compiler.
           // A wave without any valid row skips all of it.
           StageFetch fg = fg_first, fu = fu_first;
-          float w_row = 1.0f, dw_sum = 0.f;
           if (m0 + wm * WTM < m_end)
 #pragma unroll
           for (int b = 0; b < NB; ++b) {
-            if (b % TN == 0) { w_row = row_weight(b / TN); dw_sum = 0.f; }
+            if (b % TN == 0) { row_weight(b / TN, w_row); dw_sum[0] = dw_sum[1] = 0.f; }
             int mb, nb, rows_valid, cols_valid;
             block_geom(b, mb, nb, rows_valid, cols_valid);
             bf16x4 g[4], u[4];
@@ -1155,7 +1201,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
             stage_unpack_bf16(stg, fu, u, lane);
             if (b + 1 < NB) fetch_block(b + 1, fg, fu);
             __builtin_amdgcn_sched_barrier(0);      // the read-ahead stays ahead of this block's arithmetic and stores
-            swiglu_bwd_block(acc[b / TN][b % TN], g, u, mb, nb, rows_valid, cols_valid, w_row, dw_sum);
+            swiglu_bwd_block(block(b / TN, b % TN), g, u, mb, nb, rows_valid, cols_valid, w_row, dw_sum);
             if (b % TN == TN - 1) write_dw(b / TN, dw_sum);
           }
           // Every wave leaves this epilogue with none of its vector memory operations in flight.  The first step of
