@@ -7,6 +7,12 @@
 // One s_barrier per k-step: after it every wave's loads for the step have landed and every wave has
 // left the previous step, whose buffer the new loads may overwrite.
 //
+// The products run on the 16x16 matrix instructions (16x16x32 bf16, 16x16x128 e4m3).  What bounds the large layers is the power
+// the chip grants its matrix cores, and these need less of it than the 32x32 ones: register-only loops of eight waves per CU on
+// N(0,1) bf16 operands reach 2.00 PFLOP/s against 1.78, fed from LDS 1.71 against 1.55, with this kernel's load traffic beside
+// them 1.50 against 1.42 (random e4m3 codes 3.95 against 3.67, fed from LDS 3.37 against 3.20).  A layer of 8 experts, 16384 rows,
+// 4096 x 14336, forward and backward: bf16 15.79 -> 15.21 ms.
+//
 // The kernel is persistent: one workgroup per CU walks a static list of tiles.  When the last k-step of
 // a tile is done the ring is free, so the first stages of the NEXT tile are put in flight before the
 // current tile's epilogue runs; workgroup launch, tile lookup, pointer set-up and the cold first loads
@@ -90,6 +96,8 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
+__device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14)); }
+
 template <int ROWS, int BKT, int ESZ = 2> struct KTile {        // K-major [ROWS][BKT] of ESZ-byte elements
   static constexpr int ROW_BYTES = BKT * ESZ, CPR = ROW_BYTES / 16, RPL = 256 / ROW_BYTES;
   static constexpr int BYTES = ROWS * ROW_BYTES;
@@ -116,11 +124,11 @@ template <int EXTENT, int BKT, int ESZ> struct DmaTileBytes<MNMAJOR, EXTENT, BKT
 // frag_origin gives for the wave's first row, moved to the tile; fragment i lies 16 rows (columns) on, sub-step kk 32 of k.
 // In M/N-major tiles fragment i is the origin with i at bits 5..7 flipped: the caller hides the origin from the optimiser
 // once per phase, so that one exclusive-or makes an address where it is used instead of eight of them filling registers.
-template <Layout L, int EXTENT, int BKT>
+template <Layout L, int EXTENT, int BKT, int ESZ = 2>
 __device__ __forceinline__ unsigned frag_origin(int base, int lane) {
   const int i = lane & 15, g = lane >> 4;
   if constexpr (L == KMAJOR) {
-    return (unsigned)KTile<EXTENT, BKT>::offset(base + i, g);
+    return (unsigned)KTile<EXTENT, BKT, ESZ>::offset(base + i, g);
   } else {
     using TL = MNTile<EXTENT, BKT>;
     const int krow = (g << 3) + (i >> 2), col = base + ((i & 3) << 2);
@@ -139,6 +147,17 @@ __device__ __forceinline__ bf16x8 read_frag_dma(unsigned origin, int i, int kk) 
     const bf16x4 hi = lds_read_tr(p + 4 * TL::ROW_BYTES);             // krow + 4 has the same swizzle
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   }
+}
+// e4m3 fragment of the 16x16x128 f8f6f4 MFMA (32 bytes per lane, K-major tiles).  Lane l takes chunks l / 16 and 4 + l / 16 of
+// its row's 128 bytes: the same order of k in both operands, and no two of the lanes served together meet in a bank.
+template <int EXTENT, int BKT>
+__device__ __forceinline__ i32x8 read_frag_fp8(unsigned origin, int i, int kk) {
+  typedef __attribute__((ext_vector_type(4))) int i32x4;
+  using TL = KTile<EXTENT, BKT, 1>;
+  const unsigned step = (unsigned)(i * 16 * TL::ROW_BYTES);
+  const i32x4 lo = __builtin_bit_cast(i32x4, lds_read_b128((origin ^ (unsigned)(kk << 7)) + step));
+  const i32x4 hi = __builtin_bit_cast(i32x4, lds_read_b128((origin ^ (unsigned)(kk << 7) ^ 64u) + step));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
 
@@ -241,69 +260,6 @@ __device__ __forceinline__ void stage_store_f32(char* stg, const Block& acc, flo
       __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4v, val), rs, off, 0, 0);
     }
   }
-}
-
-// ---- the same three with plain global accesses inside `if (valid)` (the e4m3 kernels: their register budget does
-// not take the descriptors)
-// 32 rows x 32 bf16 columns from registers to global memory (row-major, leading dimension ld elements).
-__device__ __forceinline__ void stage_store_bf16_g(char* stg, const bf16x4 (&v)[4], bf16* g, long ld, int rows_valid,
-                                                 int cols_valid, int lane) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) *reinterpret_cast<bf16x4*>(stg + patch_row(q, lane) * STG_STRIDE + patch_col(q, lane) * 2) = v[q];
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int r = pass * 16 + (lane >> 2), c = (lane & 3) * 8;
-    const uint4 val = *reinterpret_cast<const uint4*>(stg + r * STG_STRIDE + c * 2);
-    if (r < rows_valid && c < cols_valid) *reinterpret_cast<uint4*>(g + (long)r * ld + c) = val;
-  }
-}
-
-// 32 rows x 32 bf16 columns from global memory into registers (same lane layout as the accumulators).
-__device__ __forceinline__ void stage_load_bf16_g(char* stg, bf16x4 (&v)[4], const bf16* g, long ld, int rows_valid,
-                                                int cols_valid, int lane) {
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int r = pass * 16 + (lane >> 2), c = (lane & 3) * 8;
-    uint4 val = make_uint4(0, 0, 0, 0);
-    if (r < rows_valid && c < cols_valid) val = *reinterpret_cast<const uint4*>(g + (long)r * ld + c);
-    *reinterpret_cast<uint4*>(stg + r * STG_STRIDE + c * 2) = val;
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const bf16x4*>(stg + patch_row(q, lane) * STG_STRIDE + patch_col(q, lane) * 2);
-}
-
-// 32 rows x 32 fp32 columns, as two halves of 16 columns; optional read-modify-write accumulation.
-__device__ __forceinline__ void stage_store_f32_g(char* stg, const Block& acc, float* g, long ld, int rows_valid,
-                                                int cols_valid, bool accumulate, int lane) {
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-      *reinterpret_cast<f32x4*>(stg + patch_row(2 * i, lane) * STG_STRIDE + patch_col(2 * i, lane) * 4) = acc.q[2 * i + half];
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-      const int r = pass * 16 + (lane >> 2), c = half * 16 + (lane & 3) * 4;
-      f32x4 val = *reinterpret_cast<const f32x4*>(stg + r * STG_STRIDE + (lane & 3) * 16);
-      if (r < rows_valid && c < cols_valid) {
-        float* dst = g + (long)r * ld + c;
-        if (accumulate) val += *reinterpret_cast<const f32x4*>(dst);
-        *reinterpret_cast<f32x4*>(dst) = val;
-      }
-    }
-  }
-}
-
-// e4m3 fragment of the 16x16x128 f8f6f4 MFMA (32 bytes per lane) out of a K-major tile.  Lane l takes chunks l / 16 and
-// 4 + l / 16 of its row: the same order of k in both operands, and eight rows' worth of lanes never meet in a bank.
-template <int EXTENT, int BKT>
-__device__ __forceinline__ i32x8 read_frag_fp8(const char* tile, int base, int kk, int lane) {
-  using TL = KTile<EXTENT, BKT, 1>;
-  const int row = base + (lane & 15);
-  const int c0 = kk * 8 + (lane >> 4);
-  const uint4 lo = *reinterpret_cast<const uint4*>(tile + TL::offset(row, c0));
-  const uint4 hi = *reinterpret_cast<const uint4*>(tile + TL::offset(row, c0 + 4));
-  i32x8 r = {(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
-  return r;
 }
 
 // Work list with the last round split along K: tiles [0, full_tiles) are whole; each of the remaining
@@ -426,9 +382,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
   constexpr int BN_OUT = SWI ? BN / 2 : BN;
   // Store instructions a wave issues in the epilogue of a full tile (branch-free buffer stores, bf16 kernels): two
   // per 32x32 bf16 block, four per fp32 block; 0 = not known at compile time.
-  constexpr bool PLAIN_EPI = FP8 && !(MODE == ROWSEG && (SWI || EPI == EPI_STORE));   // epilogue with plain (branchy) global accesses
-  constexpr int EPI_STORES_RAW = PLAIN_EPI ? 0
-                                 : EPI == EPI_STORE ? TM * TN * (sizeof(TC) == 4 ? 4 : 2)
+  constexpr int EPI_STORES_RAW = EPI == EPI_STORE ? TM * TN * (sizeof(TC) == 4 ? 4 : 2)
                                  : SWI ? TM * TN * 3
                                  : EPI == EPI_SWIGLU_BWD ? TM * TN * 6
                                  : EPI == EPI_SWIGLU_BWD_W ? TM * TN * 6 + TM
@@ -454,12 +408,9 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
   const int wm = wave / WN, wn = wave % WN;
   const char* zero = reinterpret_cast<const char*>(g_zero_block);
   char* stg = smem + RING_BYTES + TABLE_BYTES + wave * STG_BYTES;      // this wave's epilogue patch
-  // where this lane's fragments of the wave's first rows lie in a ring slot (bf16)
-  unsigned fo_a = 0, fo_b = 0;
-  if constexpr (!FP8) {
-    fo_a = frag_origin<LA, BM, BKT>(wm * WTM, lane);
-    fo_b = (unsigned)A_BYTES + frag_origin<LB, BN, BKT>(wn * WTN, lane);
-  }
+  // where this lane's fragments of the wave's first rows lie in a ring slot
+  const unsigned fo_a = frag_origin<LA, BM, BKT, ESZ>(wm * WTM, lane);
+  const unsigned fo_b = (unsigned)A_BYTES + frag_origin<LB, BN, BKT, ESZ>(wn * WTN, lane);
 
   // ---- the tile list ------------------------------------------------------------------------------
   // Workgroup b runs on XCD b % 8 and each XCD has its own L2.  The logical tile order is cut into windows
@@ -500,7 +451,12 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
   const char* a_base = zero;        // wave-uniform: operand origin of the open tile at its first k
   const char* b_base = zero;
   unsigned a_off[A_DMA], b_off[B_DMA];   // this lane's byte offset from the base, fixed over the k loop
-  int a_k[A_DMA], b_k[B_DMA];       // k coordinate (relative to the k-step start) this lane's chunk begins at
+  // k coordinate (relative to the k-step start) at which this lane's chunk of load slot 0 begins, and how far the following
+  // slots lie on: K-major slots are whole swizzle periods apart
+  constexpr int A_KSTEP = LA == KMAJOR ? 0 : A_BYTES / A_DMA / (BM * 2), B_KSTEP = LB == KMAJOR ? 0 : B_BYTES / B_DMA / (BN * 2);
+  static_assert(LA != KMAJOR || NL * 1024 % (16 * BKT * ESZ) == 0, "a loader's K-major slots have different chunk orders");
+  static_assert(LB != KMAJOR || NL * 1024 % (16 * BKT * ESZ) == 0, "a loader's K-major slots have different chunk orders");
+  int a_k0 = 0, b_k0 = 0;
   // L2 touches (bf16 kernels).  The workgroups of a window stream the same A and B panels at the same k, so every
   // new line is requested by several of them at once and all of them wait for the one fill.  At the end of k-step kt
   // the first wave that does not load (wave NL) touches this workgroup's quarter of the A-panel lines that the
@@ -610,18 +566,18 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
       if constexpr (LA == KMAJOR) {
         using TL = KTile<BM, BKT, ESZ>;
         const int row = q * TL::ROWS_PER_DMA + lane / TL::CPR;
-        const int lc = (lane % TL::CPR) ^ TL::swz(row);
+        const int lc = (lane % TL::CPR) ^ TL::swz(lw * TL::ROWS_PER_DMA + lane / TL::CPR);
         int rel = min(row, p.M - 1 - m0);                             // rows past the end of A repeat its last row
         if constexpr (GATHER_A) rel = p.a_rowmap[m0 + rel];           // < a_phys_rows: the launcher's contract
         a_off[j] = (unsigned)rel * (unsigned)(p.lda * ESZ) + (unsigned)(lc * 16);
-        a_k[j] = lc * CHUNK;
+        a_k0 = lc * CHUNK;
       } else {
         using TL = MNTile<BM, BKT>;
         const int krow = q * TL::ROWS_PER_DMA + lane / TL::CPR;
         const int lc = (lane % TL::CPR) ^ TL::swz(krow);
         const int col = min(m0 + lc * 8, p.M - 8);
         a_off[j] = (unsigned)krow * (unsigned)(p.lda * ESZ) + (unsigned)(col * ESZ);
-        a_k[j] = krow;
+        a_k0 = lw * TL::ROWS_PER_DMA + lane / TL::CPR;
       }
     }
 #pragma unroll
@@ -630,7 +586,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
       if constexpr (LB == KMAJOR) {
         using TL = KTile<BN, BKT, ESZ>;
         const int row = q * TL::ROWS_PER_DMA + lane / TL::CPR;
-        const int lc = (lane % TL::CPR) ^ TL::swz(row);
+        const int lc = (lane % TL::CPR) ^ TL::swz(lw * TL::ROWS_PER_DMA + lane / TL::CPR);
         int gr;
         if constexpr (SWI) {
           const int qq = row >> 5;
@@ -640,14 +596,14 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
           gr = min(n0 + row, p.N - 1);
         }
         b_off[j] = (unsigned)gr * (unsigned)(p.ldb * ESZ) + (unsigned)(lc * 16);     // < 4 GiB: checked by the launcher
-        b_k[j] = lc * CHUNK;
+        b_k0 = lc * CHUNK;
       } else {
         using TL = MNTile<BN, BKT>;
         const int krow = q * TL::ROWS_PER_DMA + lane / TL::CPR;
         const int lc = (lane % TL::CPR) ^ TL::swz(krow);
         const int col = min(n0 + lc * 8, p.N - 8);
         b_off[j] = (unsigned)krow * (unsigned)(p.ldb * ESZ) + (unsigned)(col * ESZ);
-        b_k[j] = krow;
+        b_k0 = lw * TL::ROWS_PER_DMA + lane / TL::CPR;
       }
     }
     if constexpr (TOUCH) {
@@ -729,13 +685,13 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
       for (int j = 0; j < A_DMA; ++j) {
         unsigned off = a_off[j];
         asm volatile("" : "+v"(off));
-        dma16(a_k[j] >= k_left ? zero : ab + off, stage + (unsigned)(lw + ((j + rot_a) % A_DMA) * NL) * 1024u);
+        dma16(a_k0 + ((j + rot_a) % A_DMA) * A_KSTEP >= k_left ? zero : ab + off, stage + (unsigned)(lw + ((j + rot_a) % A_DMA) * NL) * 1024u);
       }
 #pragma unroll
       for (int j = 0; j < B_DMA; ++j) {
         unsigned off = b_off[j];
         asm volatile("" : "+v"(off));
-        dma16(b_k[j] >= k_left ? zero : bb + off, stage + A_BYTES + (unsigned)(lw + ((j + rot_b) % B_DMA) * NL) * 1024u);
+        dma16(b_k0 + ((j + rot_b) % B_DMA) * B_KSTEP >= k_left ? zero : bb + off, stage + A_BYTES + (unsigned)(lw + ((j + rot_b) % B_DMA) * NL) * 1024u);
       }
     }
   };
@@ -771,23 +727,25 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
       wait_vmcnt<0>();
     };
     // ---- k loop ------------------------------------------------------------------------------------
-    // bf16 kernels: the fragments of a sub-step are read one sub-step ahead, also across the step barrier.  The
-    // barrier that opens step s+1 sits before the last sub-step's MFMAs of step s (whose fragments are in registers
-    // by then), so the first fragment reads of a step, which all eight waves issue at once, overlap MFMAs instead of
-    // leaving the matrix cores idle at every step start: -1.6 to -2.2 % on the forward kernels and dgrad1, -4 to -6 %
-    // on the weight-gradient kernel with 64-deep steps (with 32-deep steps, two sub-steps each, it gains nothing).
-    // The dgrad2 kernels gain from it as well (-2.4 % plain, -0.9 % of the fused-order backward) once their epilogue
-    // ends with an explicit vmcnt wait (see there); before that a build with it measured no gain.  The e4m3 kernels
-    // have no room for a second set of 32-byte fragments.
-    constexpr bool XPIPE = !FP8 && (MODE != KSEG || NSTAGE == 2);
+    // Fragments are read one phase ahead (see below), also across the step barrier.  The barrier that opens step s+1 sits
+    // before the last phase's products of step s (whose fragments are in registers by then), so the first fragment reads of
+    // a step, which all eight waves issue at once, overlap products instead of leaving the matrix cores idle at every step
+    // start: -1.6 to -2.2 % on the bf16 forward kernels and dgrad1, -4 to -6 % on the weight-gradient kernel with 64-deep
+    // steps (with 32-deep steps it gains nothing), -6 % on the e4m3 FC2 and dgrad1, -2 % on the e4m3 FC1.  The dgrad2 kernels
+    // gain from it once their epilogue ends with an explicit vmcnt wait (see there).
+    constexpr bool XPIPE = MODE != KSEG || NSTAGE == 2;
     if constexpr (XPIPE) {
       // A sub-step is cut into phases: the wave's fragments of its shorter side are held for the whole sub-step, those of
       // the longer side pass through PC at a time.  Phase p multiplies while the fragments of phase p + 1 are read.
       constexpr bool HOLD_A = FM <= FN;
       constexpr int FH = HOLD_A ? FM : FN, FS = HOLD_A ? FN : FM;
-      constexpr int PC = FS % 4 == 0 ? 4 : 2, NPH = FS / PC;
+      constexpr int PC = !FP8 && FS % 4 == 0 ? 4 : 2, NPH = FS / PC;
       constexpr int PHASES = KK * NPH;
-      static_assert(KK % 2 == 0 && FS % PC == 0, "fragment sets alternate by sub-step and by phase parity");
+      // One sub-step per step (e4m3): the held fragments have no second set.  In the last phase each is read again, from the
+      // next step, as soon as its last product is issued.
+      constexpr int HSETS = KK % 2 == 0 ? 2 : 1;
+      static_assert((HSETS == 2 || KK == 1) && PHASES % 2 == 0 && FS % PC == 0, "fragment sets alternate by sub-step and by phase parity");
+      static_assert(!BSCALE || (KK == 1 && HOLD_A), "group scales are read with the held fragments' order");
       // opens step s: its loads have landed (at most the younger steps' loads are outstanding; the first step of a
       // tile also drains the previous tile's epilogue stores), every wave is done with step s-1, whose stage is
       // refilled right away
@@ -805,24 +763,49 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
       if (!wave_active) {
         for (int s = 0; s < nk; ++s) open_step(s);
       } else if (nk > 0) {
-        bf16x8 held[2][FH], strm[2][PC];
-        // the fragments that phase p of the step in ring slot `slot_lds` needs beyond the ones the phase before it has
-        auto read_phase = [&](unsigned slot_lds, int p) __attribute__((always_inline)) {
-          const int kk = p / NPH, ph = p % NPH;
-          unsigned ao = fo_a + slot_lds, bo = fo_b + slot_lds;
+        using Frag = std::conditional_t<FP8, i32x8, bf16x8>;
+        Frag held[HSETS][FH], strm[2][PC];
+        auto read_a = [&](unsigned ao, int i, int kk) __attribute__((always_inline)) -> Frag {
+          if constexpr (FP8) return read_frag_fp8<BM, BKT>(ao, i, kk); else return read_frag_dma<LA, BM, BKT>(ao, i, kk);
+        };
+        auto read_b = [&](unsigned bo, int j, int kk) __attribute__((always_inline)) -> Frag {
+          if constexpr (FP8) return read_frag_fp8<BN, BKT>(bo, j, kk); else return read_frag_dma<LB, BN, BKT>(bo, j, kk);
+        };
+        auto origins = [&](unsigned slot_lds, unsigned& ao, unsigned& bo) __attribute__((always_inline)) {
+          ao = fo_a + slot_lds;
+          bo = fo_b + slot_lds;
           if constexpr (LA == MNMAJOR) asm volatile("" : "+v"(ao));
           if constexpr (LB == MNMAJOR) asm volatile("" : "+v"(bo));
-          auto read_a = [&](int i) __attribute__((always_inline)) { return read_frag_dma<LA, BM, BKT>(ao, i, kk); };
-          auto read_b = [&](int j) __attribute__((always_inline)) { return read_frag_dma<LB, BN, BKT>(bo, j, kk); };
-          if (ph == 0) {
+        };
+        // held fragment h of sub-step kk; the streamed fragments of phase p; the group scales of a step's A and B rows
+        auto read_held = [&](unsigned ao, unsigned bo, int h, int kk) __attribute__((always_inline)) {
+          held[kk % HSETS][h] = HOLD_A ? read_a(ao, h, kk) : read_b(bo, h, kk);
+        };
+        auto read_strm = [&](unsigned ao, unsigned bo, int p) __attribute__((always_inline)) {
+          const int kk = p / NPH, ph = p % NPH;
 #pragma unroll
-            for (int h = 0; h < FH; ++h) held[kk & 1][h] = HOLD_A ? read_a(h) : read_b(h);
-          }
-#pragma unroll
-          for (int c = 0; c < PC; ++c) strm[p & 1][c] = HOLD_A ? read_b(ph * PC + c) : read_a(ph * PC + c);
+          for (int c = 0; c < PC; ++c) strm[p & 1][c] = HOLD_A ? read_b(bo, ph * PC + c, kk) : read_a(ao, ph * PC + c, kk);
+        };
+        auto scale_a = [&](int step, int i) __attribute__((always_inline)) {
+          sa_cur[i] = reinterpret_cast<const unsigned char*>(scale_smem)[(step % NSTAGE) * 512 + wm * WTM + i * 16 + (lane & 15)];
+        };
+        auto scale_b = [&](int step, int j) __attribute__((always_inline)) {
+          sb_cur[j] = reinterpret_cast<const unsigned char*>(scale_smem)[(step % NSTAGE) * 512 + 256 + wn * WTN + j * 16 + (lane & 15)];
         };
         open_step(0);
-        read_phase(smem_lds, 0);
+        {
+          unsigned ao, bo;
+          origins(smem_lds, ao, bo);
+#pragma unroll
+          for (int h = 0; h < FH; ++h) read_held(ao, bo, h, 0);
+          read_strm(ao, bo, 0);
+          if constexpr (BSCALE) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i) scale_a(0, i);
+#pragma unroll
+            for (int j = 0; j < FN; ++j) scale_b(0, j);
+          }
+        }
         for (int kt = 0; kt < nk; ++kt) {
           const unsigned at = smem_lds + (unsigned)(kt % NSTAGE) * STAGE_BYTES;
 #pragma unroll
@@ -833,21 +816,72 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
                 touch4s(a_base + (long)(kt + NSTAGE) * a_step, ta_off, lds_dump);
               }
             }
-            if (p + 1 < PHASES) {
-              read_phase(at, p + 1);
-            } else if (kt + 1 < nk) {
-              open_step(kt + 1);
-              read_phase(smem_lds + (unsigned)((kt + 1) % NSTAGE) * STAGE_BYTES, 0);
+            const bool last = p + 1 == PHASES;
+            const int pn = (p + 1) % PHASES, kn = pn / NPH;
+            unsigned ao, bo;
+            auto read_next = [&](unsigned slot_lds) __attribute__((always_inline)) {
+              origins(slot_lds, ao, bo);
+              if (HSETS == 2 && pn % NPH == 0) {
+#pragma unroll
+                for (int h = 0; h < FH; ++h) read_held(ao, bo, h, kn);
+              }
+              read_strm(ao, bo, pn);
+            };
+            if (!last) {
+              read_next(at);
+            } else {
+              if constexpr (HSETS == 1) {
+                // the products issued so far stay in front of the barrier: moved behind it, as the compiler would, they
+                // keep every streamed fragment of the step in registers
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                  for (int j = 0; j < FN; ++j) asm volatile("" : "+v"(acc[i][j]));
+              }
+              // This phase's fragments are waited for on the way to both paths (the barrier needs that anyway): left to where the
+              // paths meet, the wait would also hold up this phase's products behind the reads just issued on one of them.
+              wait_lgkmcnt0();
+              if (kt + 1 < nk) {
+                open_step(kt + 1);
+                read_next(smem_lds + (unsigned)((kt + 1) % NSTAGE) * STAGE_BYTES);
+              } else {
+                if constexpr (HSETS == 1) origins(at, ao, bo);      // the last step reads its own held fragments again
+              }
             }
             const int kk = p / NPH, ph = p % NPH;
+            auto product = [&](int h, int c) __attribute__((always_inline)) {
+              const Frag fa = HOLD_A ? held[kk % HSETS][h] : strm[p & 1][c], fb = HOLD_A ? strm[p & 1][c] : held[kk % HSETS][h];
+              const int i = HOLD_A ? h : ph * PC + c, j = HOLD_A ? ph * PC + c : h;
+              // e4m3 x e4m3 (format selectors 0, 0); block scales 2^0 (E8M0 code 127) unless the operands are scaled by group
+              if constexpr (FP8)
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fb, fa, acc[i][j], 0, 0, 0, BSCALE ? sb_cur[j] : 127, 0, BSCALE ? sa_cur[i] : 127);
+              else
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb, fa, acc[i][j], 0, 0, 0);
+            };
+            if (HSETS == 1 && last) {
+              if constexpr (BSCALE) {
 #pragma unroll
-            for (int c = 0; c < PC; ++c)
+                for (int j = 0; j < FN - PC; ++j) scale_b(kt + 1 < nk ? kt + 1 : kt, j);
+              }
 #pragma unroll
               for (int h = 0; h < FH; ++h) {
-                const bf16x8 fa = HOLD_A ? held[kk & 1][h] : strm[p & 1][c], fb = HOLD_A ? strm[p & 1][c] : held[kk & 1][h];
-                const int i = HOLD_A ? h : ph * PC + c, j = HOLD_A ? ph * PC + c : h;
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb, fa, acc[i][j], 0, 0, 0);
+#pragma unroll
+                for (int c = 0; c < PC; ++c) product(h, c);
+                read_held(ao, bo, h, 0);
+                if constexpr (BSCALE) scale_a(kt + 1 < nk ? kt + 1 : kt, h);
+                __builtin_amdgcn_sched_barrier(0);
               }
+              if constexpr (BSCALE) {
+#pragma unroll
+                for (int j = FN - PC; j < FN; ++j) scale_b(kt + 1 < nk ? kt + 1 : kt, j);
+              }
+            } else {
+#pragma unroll
+              for (int c = 0; c < PC; ++c)
+#pragma unroll
+                for (int h = 0; h < FH; ++h) product(h, c);
+            }
+            if constexpr (HSETS == 1) __builtin_amdgcn_sched_barrier(0);
           }
         }
       }
@@ -861,18 +895,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
       __syncthreads();
       if (kt + NSTAGE - 1 < nk) issue(kt + NSTAGE - 1);
 
-      if constexpr (BSCALE) {
-        // this step's scale bytes landed with its tiles (same wait, same barrier)
-        const unsigned char* sc = reinterpret_cast<const unsigned char*>(scale_smem) + (kt % NSTAGE) * 512;
-#pragma unroll
-        for (int i = 0; i < FM; ++i) sa_cur[i] = sc[wm * WTM + i * 16 + (lane & 15)];
-#pragma unroll
-        for (int j = 0; j < FN; ++j) sb_cur[j] = sc[256 + wn * WTN + j * 16 + (lane & 15)];
-      }
-      const char* at = smem + (kt % NSTAGE) * STAGE_BYTES;
-      const char* bt = at + A_BYTES;
-      const unsigned at_lds = smem_lds + (unsigned)(kt % NSTAGE) * STAGE_BYTES;
-      (void)at; (void)bt; (void)at_lds;
+      const unsigned at = smem_lds + (unsigned)(kt % NSTAGE) * STAGE_BYTES;
       if constexpr (MODE == ROWSEG) {
         // A wave whose rows all lie past the expert's last row has nothing to multiply (wave-uniform; it still
         // issued its loads and takes part in the barriers).  In a nearly empty last tile of an expert only one or
@@ -892,36 +915,12 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
             touch4s(a_base + (long)(kt + NSTAGE) * a_step, ta_off, lds_dump);
           }
         }
-        if constexpr (FP8) {
-          // 16x16x128 e4m3 x e4m3 (format selectors 0, 0), both block scales 2^0 (E8M0 code 127) unless scaled by group
-          i32x8 held[FM <= FN ? FM : FN];
-          if constexpr (FM <= FN) {
-#pragma unroll
-            for (int i = 0; i < FM; ++i) held[i] = read_frag_fp8<BM, BKT>(at, wm * WTM + i * 16, kk, lane);
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-              const i32x8 fb = read_frag_fp8<BN, BKT>(bt, wn * WTN + j * 16, kk, lane);
-#pragma unroll
-              for (int i = 0; i < FM; ++i)
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fb, held[i], acc[i][j], 0, 0, 0, BSCALE ? sb_cur[j] : 127, 0, BSCALE ? sa_cur[i] : 127);
-            }
-          } else {
-#pragma unroll
-            for (int j = 0; j < FN; ++j) held[j] = read_frag_fp8<BN, BKT>(bt, wn * WTN + j * 16, kk, lane);
-#pragma unroll
-            for (int i = 0; i < FM; ++i) {
-              const i32x8 fa = read_frag_fp8<BM, BKT>(at, wm * WTM + i * 16, kk, lane);
-#pragma unroll
-              for (int j = 0; j < FN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(held[j], fa, acc[i][j], 0, 0, 0, BSCALE ? sb_cur[j] : 127, 0, BSCALE ? sa_cur[i] : 127);
-            }
-          }
-        } else {
+        {
           bf16x8 af[FM], bfr[FN];
 #pragma unroll
-          for (int i = 0; i < FM; ++i) af[i] = read_frag_dma<LA, BM, BKT>(fo_a + at_lds, i, kk);
+          for (int i = 0; i < FM; ++i) af[i] = read_frag_dma<LA, BM, BKT>(fo_a + at, i, kk);
 #pragma unroll
-          for (int j = 0; j < FN; ++j) bfr[j] = read_frag_dma<LB, BN, BKT>(fo_b + at_lds, j, kk);
+          for (int j = 0; j < FN; ++j) bfr[j] = read_frag_dma<LB, BN, BKT>(fo_b + at, j, kk);
 #pragma unroll
           for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -945,7 +944,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
     }
     // SwiGLU' (bf16): the saved G and U of the wave's first block are asked for before the hand-over, ahead of the
     // next tile's first loads in the memory queue
-    constexpr bool EARLY_GU = !FP8 && (EPI == EPI_SWIGLU_BWD || EPI == EPI_SWIGLU_BWD_W);
+    constexpr bool EARLY_GU = EPI == EPI_SWIGLU_BWD || EPI == EPI_SWIGLU_BWD_W;
     StageFetch fg_first, fu_first;
     if constexpr (EARLY_GU) {
       const int mb = m0 + wm * WTM, nb = n0 + wn * WTN;
@@ -990,17 +989,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
         }
         return b;
       };
-      // every 32x32 block goes through the wave's LDS patch (see stage_store_* above); bf16 kernels use the
-      // branch-free buffer accesses, e4m3 kernels the plain ones
-      auto store_bf16 = [&](const bf16x4 (&v)[4], bf16* g, long ld, int rv, int cv) __attribute__((always_inline)) {
-        if constexpr (PLAIN_EPI) stage_store_bf16_g(stg, v, g, ld, rv, cv, lane); else stage_store_bf16(stg, v, g, ld, rv, cv, lane);
-      };
-      auto load_bf16 = [&](bf16x4 (&v)[4], const bf16* g, long ld, int rv, int cv) __attribute__((always_inline)) {
-        if constexpr (PLAIN_EPI) stage_load_bf16_g(stg, v, g, ld, rv, cv, lane); else stage_load_bf16(stg, v, g, ld, rv, cv, lane);
-      };
-      auto store_f32 = [&](const Block& a, float* g, long ld, int rv, int cv, bool accumulate) __attribute__((always_inline)) {
-        if constexpr (PLAIN_EPI) stage_store_f32_g(stg, a, g, ld, rv, cv, accumulate, lane); else stage_store_f32(stg, a, g, ld, rv, cv, accumulate, lane);
-      };
+      // every 32x32 block goes through the wave's LDS patch (see stage_store_* above)
       if (SPLITK && ep_part_slot >= 0) {
         // one K part of a split tile: the whole fp32 tile goes to the partial buffer, no masks
         float* part_tile = p.splitk_ws + (long)ep_part_slot * (BM * BN);
@@ -1008,7 +997,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
-            store_f32(block(i, j), part_tile + (long)(wm * WTM + i * 32) * BN + wn * WTN + j * 32, BN, 32, 32, false);
+            stage_store_f32(stg, block(i, j), part_tile + (long)(wm * WTM + i * 32) * BN + wn * WTN + j * 32, BN, 32, 32, false, lane);
           }
       } else if constexpr (EPI == EPI_STORE) {
 #pragma unroll
@@ -1024,13 +1013,13 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
             const Block b = block(i, j);
             if constexpr (sizeof(TC) == 4) {
               float* g = static_cast<float*>(p.C) + (long)e * p.c_es + (long)mb * p.ldc + nb;
-              store_f32(b, g, p.ldc, rows_valid, cols_valid, p.accumulate != 0);
+              stage_store_f32(stg, b, g, p.ldc, rows_valid, cols_valid, p.accumulate != 0, lane);
             } else {
               bf16* g = static_cast<bf16*>(p.C) + (long)e * p.c_es + (long)mb * p.ldc + nb;
               bf16x4 v[4];
               if (p.accumulate) {
                 bf16x4 old[4];
-                load_bf16(old, g, p.ldc, rows_valid, cols_valid);
+                stage_load_bf16(stg, old, g, p.ldc, rows_valid, cols_valid, lane);
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -1042,7 +1031,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
 #pragma unroll
                   for (int t = 0; t < 4; ++t) v[q][t] = static_cast<bf16>(b.q[q][t]);
               }
-              store_bf16(v, g, p.ldc, rows_valid, cols_valid);
+              stage_store_bf16(stg, v, g, p.ldc, rows_valid, cols_valid, lane);
             }
           }
         }
@@ -1089,9 +1078,9 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
                 a[q][t] = static_cast<bf16>(w_row[q >> 1] * (gf * sigmoid_f32(gf) * static_cast<float>(u[q][t])));
               }
             bf16* hrow = p.H + (long)mb * 2 * p.f + nb;
-            store_bf16(g, hrow, 2L * p.f, rows_valid, cols_valid);
-            store_bf16(u, hrow + p.f, 2L * p.f, rows_valid, cols_valid);
-            store_bf16(a, p.A_out + (long)mb * p.f + nb, p.f, rows_valid, cols_valid);
+            stage_store_bf16(stg, g, hrow, 2L * p.f, rows_valid, cols_valid, lane);
+            stage_store_bf16(stg, u, hrow + p.f, 2L * p.f, rows_valid, cols_valid, lane);
+            stage_store_bf16(stg, a, p.A_out + (long)mb * p.f + nb, p.f, rows_valid, cols_valid, lane);
           }
         }
       } else {
@@ -1117,13 +1106,9 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
               a[q][t] = static_cast<bf16>(FOLD ? w_row[q >> 1] * av : av);
             }
           bf16* drow = p.dH + (long)mb * 2 * p.N + nb;
-          store_bf16(dg, drow, 2L * p.N, rows_valid, cols_valid);
-          store_bf16(du, drow + p.N, 2L * p.N, rows_valid, cols_valid);
-          if constexpr (FP8) {
-            if (p.A_out) store_bf16(a, p.A_out + (long)mb * p.N + nb, p.N, rows_valid, cols_valid);
-          } else {
-            store_bf16(a, p.A_out + (long)mb * p.N + nb, p.N, p.A_out ? rows_valid : 0, cols_valid);   // no A_out: all lanes masked
-          }
+          stage_store_bf16(stg, dg, drow, 2L * p.N, rows_valid, cols_valid, lane);
+          stage_store_bf16(stg, du, drow + p.N, 2L * p.N, rows_valid, cols_valid, lane);
+          stage_store_bf16(stg, a, p.A_out + (long)mb * p.N + nb, p.N, p.A_out ? rows_valid : 0, cols_valid, lane);   // no A_out: all lanes masked
         };
         // the four lanes with the same lane % 16 hold a row's columns.  Every row of the expert's segment gets exactly one
         // partial per (n-tile, wave along n); blocks past N contribute zero.
@@ -1148,26 +1133,7 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
           }
         };
         float w_row[2] = {1.0f, 1.0f}, dw_sum[2] = {0.f, 0.f};
-        if constexpr (FP8) {
-          // (the e4m3 instantiation has no registers to spare for reading ahead)
-#pragma unroll
-          for (int i = 0; i < TM; ++i) {
-            const int mb = m0 + wm * WTM + i * 32;
-            const int rows_valid = m_end - mb;
-            if (rows_valid <= 0) continue;
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-              const int nb = n0 + wn * WTN + j * 32;
-              const int cols_valid = p.N - nb;
-              if (cols_valid <= 0) continue;
-              bf16x4 g[4], u[4];
-              const bf16* hrow = p.H + (long)mb * 2 * p.N + nb;
-              load_bf16(g, hrow, 2L * p.N, rows_valid, cols_valid);
-              load_bf16(u, hrow + p.N, 2L * p.N, rows_valid, cols_valid);
-              swiglu_bwd_block(block(i, j), g, u, mb, nb, rows_valid, cols_valid, w_row, dw_sum);
-            }
-          }
-        } else {
+        {
           // The G and U reads of block b+1 are issued as soon as block b has been unpacked from the fetch registers,
           // so they are in flight while block b is computed and stored (one set of fetch registers: a second set
           // makes the compiler spill the loaders' tile offsets and reload them inside the k loop).
