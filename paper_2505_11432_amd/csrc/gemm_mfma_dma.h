@@ -498,8 +498,11 @@ __global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) 
 
   // Decode slot -> tile and set up this lane's source pointers.  Returns false when the list is exhausted.
   auto open_tile = [&](int sl) __attribute__((always_inline)) -> bool {
-    int l = (sl * XCDS + xcd) * window + in_window;
-    if (l >= total_items) return false;
+    // the last, partly filled round is dealt evenly: eight XCDs with a few tiles each, not two with all of them
+    const int first = sl * XCDS * window;
+    const int w = min(window, (total_items - first + XCDS - 1) / XCDS);
+    int l = first + xcd * w + in_window;
+    if (in_window >= w || l >= total_items) return false;
     int part = 0;
     part_slot = -1;
     if (l >= full_tiles) {           // only with SPLITK: parts of one tile are neighbours in the list
