@@ -97,12 +97,12 @@ static int ffn_bwd_bf16(const void* xp, const void* h_save, const void* d_yp, co
   void* dH = base + 2 * align_up((size_t)M * f * 2, 256);
   int rc = mfma_dgrad2_swiglu_bwd(d_yp, w2, offsets, M, d, E, f, h_save, dH, a_override ? nullptr : A, s);
   if (rc != MOE_OK) return rc;
-  rc = mfma_wgrad(d_yp, a_override ? a_override : A, offsets, d, f, E, d_w2, grad_dt, accumulate, s);
+  rc = mfma_wgrad(d_yp, a_override ? a_override : A, offsets, M, d, f, E, d_w2, grad_dt, accumulate, s);
   if (rc != MOE_OK) return rc;
   void* splitk = base + 2 * align_up((size_t)M * f * 2, 256) + align_up((size_t)M * 2 * f * 2, 256);
   rc = mfma_rowseg_nn(dH, w1, 2L * f * d, offsets, M, d, 2 * f, E, d_xp, splitk, s);
   if (rc != MOE_OK) return rc;
-  return mfma_wgrad(dH, xp, offsets, 2 * f, d, E, d_w1, grad_dt, accumulate, s);
+  return mfma_wgrad(dH, xp, offsets, M, 2 * f, d, E, d_w1, grad_dt, accumulate, s);
 }
 
 static int ffn_bwd_f32(const void* xp, const void* h_save, const void* d_yp, const void* a_override, const int32_t* offsets,
@@ -468,7 +468,7 @@ int moe_expert_ffn_fused_bwd(const void* x, const void* dy, const void* h_save, 
     rc = launch_gate_grad_reduce(part, mfma_dgrad2_fold_parts(M, d, E, f), M, inv_perm, M, d_topk_w, s);
     if (rc != MOE_OK) return rc;
   }
-  rc = mfma_wgrad(rows, Aw, offsets, d, f, E, d_w2, grad_dt, accumulate != 0, s);
+  rc = mfma_wgrad(rows, Aw, offsets, M, d, f, E, d_w2, grad_dt, accumulate != 0, s);
   if (rc != MOE_OK) return rc;
   if (T > 0) {
     rc = mfma_rowseg_nn(dH, w1, 2L * f * d, offsets, M, d, 2 * f, E, d_xp, splitk, s);
@@ -478,7 +478,7 @@ int moe_expert_ffn_fused_bwd(const void* x, const void* dy, const void* h_save, 
     rc = launch_dispatch(x, nullptr, MOE_BF16, inv_perm, topk_w, T, k, d, rows, nullptr, s);
     if (rc != MOE_OK) return rc;
   }
-  return mfma_wgrad(dH, rows, offsets, 2 * f, d, E, d_w1, grad_dt, accumulate != 0, s);
+  return mfma_wgrad(dH, rows, offsets, M, 2 * f, d, E, d_w1, grad_dt, accumulate != 0, s);
 }
 
 int moe_quant_fp8(const void* src, moe_dtype src_dt, int rows, int cols, moe_qmode mode, uint8_t* codes,

@@ -84,6 +84,7 @@ int launch(const Args& a, long tiles_upper_bound, hipStream_t s) {
   if (rc != MOE_OK) return rc;
   auto kern = Setup::kernel();
   constexpr int smem = Setup::smem;
+  if constexpr (2 * smem <= 160 * 1024) blocks *= 2;       // two workgroups share a CU's LDS
   Args args = a;
   constexpr bool kSplitK = MODE == ROWSEG && EPI == EPI_STORE && sizeof(TC) == 2;
   if (!kSplitK || args.accumulate || blocks > MOE_SPLITK_MAX_PARTS) args.splitk_ws = nullptr;
@@ -113,7 +114,11 @@ int launch_rowseg(Args a, hipStream_t s) {
   if (!plan.split) a.splitk_ws = nullptr;
   switch (plan.tile) {
     case RowTile::FEW: return launch<64, 128, 2 * B128, 3, 2, 2, KMAJOR, LB, ROWSEG, EPI, bf16, TIN>(a, 1, s);
-    case RowTile::MID: return launch<128, 128, B128, 3, 4, 2, KMAJOR, LB, ROWSEG, EPI, bf16, TIN>(a, 1, s);
+    case RowTile::MID:
+      if constexpr (EPI != EPI_STORE) {
+        if (plan.pair) return launch<128, 128, B128, 2, 2, 2, KMAJOR, LB, ROWSEG, EPI, bf16, TIN>(a, 1, s);
+      }
+      return launch<128, 128, B128, 3, 4, 2, KMAJOR, LB, ROWSEG, EPI, bf16, TIN>(a, 1, s);
     default: break;
   }
   if constexpr (LB == KMAJOR) return launch<256, 256, B128, 2, 4, 2, KMAJOR, LB, ROWSEG, EPI, bf16, TIN>(a, 1, s);
@@ -195,8 +200,8 @@ int mfma_dgrad2_swiglu_bwd_fold(const void* d_yp, const void* w2, const int32_t*
   return launch_rowseg<MNMAJOR, EPI_SWIGLU_BWD_W>(a, s);
 }
 
-// C[e][Mo,N] (+)= P[rows_e, Mo]^T * Q[rows_e, N]
-int mfma_wgrad(const void* P, const void* Q, const int32_t* offsets, int Mo, int N, int E, void* C, moe_dtype c_dt,
+// C[e][Mo,N] (+)= P[rows_e, Mo]^T * Q[rows_e, N]; rows: bound on all segments together
+int mfma_wgrad(const void* P, const void* Q, const int32_t* offsets, int rows, int Mo, int N, int E, void* C, moe_dtype c_dt,
                int accumulate, hipStream_t s) {
   Args a{};
   a.A = (const bf16*)P; a.lda = Mo;
@@ -204,6 +209,10 @@ int mfma_wgrad(const void* P, const void* Q, const int32_t* offsets, int Mo, int
   a.C = C; a.ldc = N; a.c_es = (long)Mo * N; a.offsets = offsets; a.E = E; a.M = Mo; a.N = N; a.K = 0;
   a.accumulate = accumulate;
   const long blocks = (long)E * cdiv(Mo, 256) * cdiv(N, 256);
+  if (wgrad_in_pairs(rows, E, Mo, N)) {
+    if (c_dt == MOE_F32) return launch<128, 128, 64, 2, 2, 2, MNMAJOR, MNMAJOR, KSEG, EPI_STORE, float>(a, blocks, s);
+    return launch<128, 128, 64, 2, 2, 2, MNMAJOR, MNMAJOR, KSEG, EPI_STORE, bf16>(a, blocks, s);
+  }
   if (c_dt == MOE_F32) return launch<256, 256, 64, 2, 2, 4, MNMAJOR, MNMAJOR, KSEG, EPI_STORE, float>(a, blocks, s);
   return launch<256, 256, 64, 2, 2, 4, MNMAJOR, MNMAJOR, KSEG, EPI_STORE, bf16>(a, blocks, s);
 }

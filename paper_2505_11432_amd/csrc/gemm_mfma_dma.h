@@ -353,7 +353,7 @@ __global__ void __launch_bounds__(256) splitk_fixup_kernel(const float* __restri
 
 template <int BM, int BN, int BKT, int NSTAGE, int WM, int WN, Layout LA, Layout LB, Mode MODE, Epi EPI, typename TC,
           typename TIN = bf16>   // TIN = uint8_t: e4m3 codes, K-major operands only
-__global__ void __launch_bounds__(WM * WN * 64) grouped_gemm_dma_kernel(Args p) {
+__global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args p) {
   constexpr int NW = WM * WN;
   constexpr int WTM = BM / WM, WTN = BN / WN;
   constexpr int FM = WTM / 16, FN = WTN / 16;         // fragments of a wave along each side

@@ -114,7 +114,7 @@ int mfma_rowseg_nn(const void* A, const void* W, long w_es, const int32_t* offse
                    void* C, void* splitk_ws, hipStream_t s);
 int mfma_dgrad2_swiglu_bwd(const void* d_yp, const void* w2, const int32_t* offsets, int M, int d, int E, int f,
                            const void* H, void* dH, void* A_out, hipStream_t s);
-int mfma_wgrad(const void* P, const void* Q, const int32_t* offsets, int Mo, int N, int E, void* C, moe_dtype c_dt,
+int mfma_wgrad(const void* P, const void* Q, const int32_t* offsets, int rows, int Mo, int N, int E, void* C, moe_dtype c_dt,
                int accumulate, hipStream_t s);
 // Section 4.1 / 4.2 operator order
 int mfma_fc1_swiglu_gather(const void* x, int T, const int32_t* row_token, const float* row_w, const void* w1,

@@ -7,7 +7,9 @@
 //     deal out, and quarter-size A tiles.
 //   FULL, 256 x 256: the tile for arithmetic, 1.3 times the rate of the next on a filled chip.
 //   MID, 128 x 128 in three stages of eight waves: where FULL leaves CUs idle: fewer tiles than CUs, or a second round for
-//     a few.  A tile is a quarter of the work in a third of the time.
+//     a few.  A tile is a quarter of the work in a third of the time.  With a fused epilogue it also exists as two
+//     workgroups of four waves per CU (pair): one's products run beside the other's epilogue.  Both are taken from 96 rows per
+//     expert on (below, the weights bound them: 8 experts, 64 rows, FC1 of 4096 x 14336 415 alone, 427 in pairs).
 // Between FULL and MID the estimated time of the rounds decides, from measured tile times: FULL 13 us + 1.5 per 128-byte
 // k-step, MID 6 + 0.58 (0.66 where the weights are read across their rows and only stored; up to 12 % less in long lists of
 // tiles), plus the epilogue's share; a split last round costs 18 or 9 us for writing and adding the parts.
@@ -31,7 +33,8 @@
 namespace moe {
 
 enum class RowTile { FEW, MID, FULL };
-struct RowPlan { RowTile tile; bool split; };        // split: the last round's tiles may be cut along K
+// split: the last round's tiles may be cut along K; pair: MID as two workgroups per CU
+struct RowPlan { RowTile tile; bool split; bool pair = false; };
 
 struct RowKind {
   bool swiglu;          // pairs gate and up columns: N is f, a tile makes half its width
@@ -52,6 +55,16 @@ inline double rounds_us(double tiles, const TileCost& c, int steps, bool split) 
     last = cut < last ? cut : last;
   }
   return whole * tile_us + last;
+}
+
+// Two workgroups per CU, 512 tiles to a round: us per round, per k-step of one, and the same for up to 256 tiles (one per CU).
+// FC1: 16 k-steps 22 us, 24 31, 32 37, 64 68 a round; SwiGLU': 16 33, 32 51, 64 87.
+struct PairCost { double fixed, step, half_fixed, half_step; };
+
+inline double pairs_us(double tiles, const PairCost& c, int steps) {
+  const double whole = (double)(long)(tiles / 512), rem = tiles - whole * 512;
+  const double round_us = c.fixed + c.step * steps, half_us = c.half_fixed + c.half_step * steps;
+  return whole * round_us + (rem < 1 ? 0 : rem <= 256 && half_us < round_us ? half_us : round_us);
 }
 
 // N: output columns (SwiGLU: f); K in elements of esz bytes
@@ -76,8 +89,25 @@ inline RowPlan plan_rows(RowKind kind, int M, int E, int N, int K, int esz) {
   const TileCost few = {5 + epi / 8, 0.4, kind.across ? 0.6 : 0.45, 9};
   if (rows <= 32 && rounds_us(gathered(64, 128), few, steps, split_few) <= rounds_us(gathered(256, 256), full, steps, split_full))
     return {RowTile::FEW, split_few};
-  return rounds_us(even(128, 128), mid, steps, split_mid) < rounds_us(even(256, 256), full, steps, split_full)
-             ? RowPlan{RowTile::MID, split_mid} : RowPlan{RowTile::FULL, split_full};
+  const double full_us = rounds_us(even(256, 256), full, steps, split_full), mid_us = rounds_us(even(128, 128), mid, steps, split_mid);
+  if (!kind.store && rows >= 96 && steps <= 48) {
+    const PairCost pair = kind.swiglu ? PairCost{7, 0.95, 5, 0.6} : PairCost{15.4, 1.12, 11, 0.6};
+    const double pair_us = pairs_us(even(128, 128), pair, steps);
+    if (pair_us < full_us && pair_us < mid_us) return {RowTile::MID, false, true};
+  }
+  return mid_us < full_us ? RowPlan{RowTile::MID, split_mid} : RowPlan{RowTile::FULL, split_full};
+}
+
+// The weight gradients on 128 x 128 tiles, two workgroups per CU, instead of 256 x 256: where the large tile leaves CUs idle in
+// its last (or only) round.  A segment is taken as the average one.  Measured, d_w2 / d_w1 (us, 256 x 256 and pairs):
+//   8 experts, 512 rows, 512 x 512 20.2/21.4, 11.0/12.5;  250 rows, 1024 x 2816 29.6/57.4, 32.2/64.4;
+//   750 rows, 1024 x 1024 28.1/33.5, 21.5/37.2;  1024 rows, 1024 x 2816 69/118, 65/130;  2048 rows, 4096 x 14336 1827/3462, 2327/5738
+inline bool wgrad_in_pairs(int rows, int E, int M, int N) {
+  auto up = [](long a, long b) { return (a + b - 1) / b; };
+  const int steps = (int)up(rows, 64L * E);
+  const double large = (double)E * up(M, 256) * up(N, 256), small = (double)E * up(M, 128) * up(N, 128);
+  const double rounds = (double)up((long)large, 256);
+  return pairs_us(small, {11, 0.75, 6, 0.8}, steps) < rounds * (9.5 + 1.5 * steps) + 6.5 * large / 256;
 }
 
 }  // namespace moe

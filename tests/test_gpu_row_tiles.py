@@ -17,6 +17,10 @@ ROWS = [[1], [0, 1, 63, 64, 65, 0, 30, 33], [2] * 70, [0, 0, 0, 128], [0, 127, 1
 # d, f: several k-steps with remainders, 16-column tails of the 128- and 64-wide tiles, one k-step and less, contractions long
 # enough to be cut into parts (bf16 from 2560 elements on with the 128-row tile, 1024 with the 64-row one)
 DIMS = [(272, 336), (512, 128), (16, 48), (144, 2752)]
+# averages from 96 rows on: 128-row tiles, two workgroups per CU, in FC1 (both), dgrad2 (the second) and the weight gradients
+# (the first); segments end before, on and after tile edges, the tiles fill less and more than one per CU
+PAIR_ROWS = [[129, 0, 300, 128, 127], [255, 257, 1, 128, 100, 0, 64], [1000]]
+PAIR_DIMS = [(272, 336), (144, 4240)]
 STEP = 2.0 ** -9            # one bf16 rounding
 # rows past the last segment (an expert-parallel share is given the bound T * k): the tile is chosen for all of them, the
 # buffers hold NaN there before the call, outputs keep what they held
@@ -50,6 +54,12 @@ def swiglu_bwd(H, dA, f):
 @pytest.mark.parametrize("d,f", DIMS)
 @pytest.mark.parametrize("rows", ROWS)
 def test_bf16_and_fused(rows, d, f):
+    check_bf16_and_fused(rows, d, f, 0)
+
+
+@pytest.mark.parametrize("d,f", PAIR_DIMS)
+@pytest.mark.parametrize("rows", PAIR_ROWS)
+def test_bf16_and_fused_in_pairs(rows, d, f):
     check_bf16_and_fused(rows, d, f, 0)
 
 
@@ -111,6 +121,12 @@ def check_bf16_and_fused(rows, d, f, spare):
 @pytest.mark.parametrize("d,f", DIMS)
 @pytest.mark.parametrize("rows", ROWS)
 def test_e4m3(rows, d, f):
+    check_e4m3(rows, d, f, 0)
+
+
+@pytest.mark.parametrize("d,f", PAIR_DIMS)
+@pytest.mark.parametrize("rows", PAIR_ROWS)
+def test_e4m3_in_pairs(rows, d, f):
     check_e4m3(rows, d, f, 0)
 
 

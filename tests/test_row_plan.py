@@ -67,3 +67,25 @@ def test_ordinary_sizes(plan):
     assert [t for t, _ in plan(gemms(4593, 24, 1040, 1424))] == ["mid", "mid", "full", "mid"]
     assert plan([FC2 + (16384, 8, 4096, 14336, 2)]) == [("full", True)]
     assert not any(s for _, s in plan([k + (M, 8, 4096, 4096, 2) for k in (FC1, DGRAD2) for M in (16, 600, 9000)]))
+
+
+PAIRS = r'''
+#include <cstdio>
+#include "row_plan.h"
+int main() {
+  int M, E, d, f;
+  while (scanf("%d %d %d %d", &M, &E, &d, &f) == 4)
+    printf("%d %d %d %d\n", (int)moe::plan_rows({true, false, false}, M, E, f, d, 2).pair, (int)moe::plan_rows({false, false, true}, M, E, f, d, 2).pair,
+           (int)moe::wgrad_in_pairs(M, E, d, f), (int)moe::wgrad_in_pairs(M, E, 2 * f, d));
+}
+'''
+
+
+def test_pairs_of_workgroups(tmp_path):
+    """FC1, dgrad2, d_w2, d_w1 on 128 x 128 tiles with two workgroups per CU: where the large tile would leave CUs idle."""
+    (tmp_path / "m.cpp").write_text(PAIRS)
+    subprocess.run([build.CXX, "-std=c++17", "-I", build.CSRC, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
+    sizes = {(4593, 24, 1040, 1424): "1 0 0 0", (2000, 8, 1024, 2816): "1 1 0 0", (4096, 8, 512, 512): "1 0 1 1", (6000, 8, 1024, 1024): "0 1 1 0",
+             (512, 8, 4096, 14336): "0 0 0 0", (16384, 8, 4096, 14336): "0 0 0 0", (131072, 64, 2048, 1408): "0 0 0 0", (0, 8, 16, 16): "0 0 1 1"}
+    out = subprocess.run([str(tmp_path / "m")], input="\n".join(" ".join(map(str, k)) for k in sizes), capture_output=True, text=True, check=True)
+    assert out.stdout.split("\n")[:-1] == list(sizes.values())
