@@ -169,7 +169,9 @@ const char* moe_status_string(int status) {
 }
 
 int moe_init(void) {
-  const int rc = mfma_configure_all();
+  int rc = mfma_configure_all();
+  if (rc != MOE_OK) return rc;
+  rc = gemm_f32_split_configure();
   if (rc != MOE_OK) return rc;
   return route_noalloc_prepare();
 }

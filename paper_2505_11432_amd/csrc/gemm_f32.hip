@@ -1,6 +1,7 @@
 // Grouped GEMM on fp32 data with the fp32 matrix instruction (v_mfma_f32_32x32x2_f32), for operands whose rows or columns
 // can be read in whole 16-byte pieces: the expert products (widths are multiples of 16, buffers 16-byte aligned) and
-// router logits of such rows.
+// router logits of such rows.  Expert products of 192 and more 64 x 64 tiles are faster on the bf16 instructions
+// (gemm_f32_split.hip); here stay the router, small problems, weight gradients of few rows per expert and very wide rows.
 //
 // Bound: the fp32 matrix rate, 256 FLOP per clock and CU, twice what unpacked fp32 FMAs give.  One instruction takes 64
 // clocks for 4 KFLOP, so the operands are cheap to feed and small tiles are affordable; what matters is that loads are
@@ -9,10 +10,9 @@
 //   64 x 64, k-steps of 32;  64 x 32, two waves per output, k-steps of 32;  32 x 32, four per output, k-steps of 64.
 // All keep two k-steps of global loads in registers ahead of the LDS stage that is being multiplied; several workgroups
 // share a CU and hide each other's latency.
-// Measured (8 experts, 2000 rows, d = 1024, f = 2816; a vector-ALU kernel of 64 x 64 x 16 first): FC1 492 -> 238 us (97 TFLOP/s), FC2
-// 601 -> 135, dgrad2 267 -> 114, dgrad1 1383 -> 265, wgrad2 211 -> 118, wgrad1 416 -> 228; router logits of 1000 tokens
-// 182 -> 13 us.  8192 x 4096 x 2048 in four experts: 110 TFLOP/s.
-#include "moe_common.h"
+// Measured (a vector-ALU kernel of 64 x 64 x 16 first): router logits of 1000 tokens 182 -> 13 us; 8 experts, 2000 rows,
+// d = 1024, f = 2816, FC2 601 -> 135 (97 TFLOP/s in FC1); 8192 x 4096 x 2048 in four experts 110 TFLOP/s.
+#include "gemm_f32_tiles.h"
 
 namespace moe {
 namespace {
@@ -21,8 +21,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kThreads = 256;
-constexpr int kGroupN = 8;         // n-tiles per group: neighbouring workgroups of an XCD form a compact block of tiles
-constexpr int kXcds = 8, kWindow = 32;
 
 // LDS image of one operand tile of EXT rows (or columns) x BK.  K-fast: [ext][BK + 4], a lane reads four consecutive k with
 // one b128 (16 lanes then cover the 64 banks once).  MN-fast: [BK][EXT + 8], a lane reads its row at one k with a b32;
@@ -76,36 +74,6 @@ __device__ __forceinline__ f32x4 frag(const float* lds, int x, int k8, int half)
   }
 }
 
-// Expert segment that holds running tile index l when every segment of n rows has cdiv(n, bm) * tiles_n tiles.  A wave
-// looks at 64 segments at a time (a lane each, prefix sum by shuffles).
-__device__ __forceinline__ bool find_segment(const int32_t* __restrict__ offsets, int E, int bm, int tiles_n, int l, int& e,
-                                             int& lo, int& hi, int& l_in) {
-  const int lane = threadIdx.x & 63;
-  int base = 0;
-  for (int e0 = 0; e0 < E; e0 += 64) {
-    const int ei = min(e0 + lane, E - 1);
-    const int o0 = offsets[ei], o1 = offsets[ei + 1];
-    const int n = e0 + lane < E ? (o1 - o0 + bm - 1) / bm * tiles_n : 0;
-    int incl = n;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int o = __shfl_up(incl, off);
-      if (lane >= off) incl += o;
-    }
-    const unsigned long long hit = __ballot(base + incl > l);
-    if (hit != 0) {
-      const int src = __builtin_ctzll(hit);
-      e = e0 + src;
-      lo = __builtin_amdgcn_readlane(o0, src);
-      hi = __builtin_amdgcn_readlane(o1, src);
-      l_in = l - base - (__builtin_amdgcn_readlane(incl, src) - __builtin_amdgcn_readlane(n, src));
-      return true;
-    }
-    base += __builtin_amdgcn_readlane(incl, 63);
-  }
-  return false;
-}
-
 template <int BM, int BN, int BK, int WM, int WN, int WK, bool AK, bool BKF>
 __global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmProblem p, int tiles_n, int tiles_m_fixed, int blocks) {
   static_assert(WM * WN * WK == 4 && BM == 32 * WM && BN == 32 * WN && BK % (8 * WK) == 0, "four waves of 32 x 32");
@@ -114,30 +82,9 @@ __global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmProblem p, int t
   __shared__ __attribute__((aligned(16))) float lds[2][TA::FLOATS + TB::FLOATS];
   static_assert(sizeof(lds) >= (WK - 1) * WM * WN * 32 * 32 * 4, "the sums that change waves fit");
 
-  // runs of kWindow consecutive tiles go to one XCD (workgroup b runs on XCD b % 8) so that its L2 serves their panels
-  int l = blockIdx.x;
-  const int span = kXcds * kWindow, first = l / span * span;
-  if (first + span <= blocks) l = first + (l % kXcds) * kWindow + (l - first) / kXcds;
-  int e = 0, m0, m_end, k0 = 0, k_end = p.K, mt_e = tiles_m_fixed;
-  int m_lo = 0;
-  m_end = p.M;
-  if (p.mode == 0) {
-    int hi, l_in;
-    if (!find_segment(p.offsets, p.E, BM, tiles_n, l, e, m_lo, hi, l_in)) return;
-    l = l_in;
-    m_end = hi;
-    mt_e = (hi - m_lo + BM - 1) / BM;
-  } else if (p.mode == 1) {
-    e = l / (mt_e * tiles_n);
-    l -= e * mt_e * tiles_n;
-    k0 = p.offsets[e];
-    k_end = p.offsets[e + 1];
-  }
-  const int ng = l / (mt_e * kGroupN), rest = l - ng * mt_e * kGroupN;
-  const int gw = min(kGroupN, tiles_n - ng * kGroupN);
-  const int mt = rest / gw, nt = ng * kGroupN + (rest - mt * gw);
-  m0 = m_lo + mt * BM;
-  const int n0 = nt * BN;
+  F32Tile t;
+  if (!f32_tile<BM, BN>(p, tiles_n, tiles_m_fixed, blocks, t)) return;
+  const int e = t.e, m0 = t.m0, m_end = t.m_end, n0 = t.n0, k0 = t.k0, k_end = t.k_end;
   const float* __restrict__ A = static_cast<const float*>(p.A);
   const float* __restrict__ B = static_cast<const float*>(p.B) + (long)e * p.b_es;
   const long lda = AK ? p.a_rs : p.a_cs, ldb = BKF ? p.b_cs : p.b_rs;
@@ -224,11 +171,8 @@ __global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmProblem p, int t
 
 template <int BM, int BN, int BK, int WM, int WN, int WK>
 int launch(const GemmProblem& p, bool a_kfast, bool b_kfast, hipStream_t s) {
-  const int tiles_n = cdiv(p.N, BN);
-  int tiles_m_fixed = cdiv(p.M, BM);
-  long blocks = (long)tiles_n * tiles_m_fixed;
-  if (p.mode == 0) blocks = (long)tiles_n * ((long)tiles_m_fixed + p.E);       // upper bound over any segment lengths
-  if (p.mode == 1) blocks *= p.E;
+  const int tiles_n = cdiv(p.N, BN), tiles_m_fixed = cdiv(p.M, BM);
+  const long blocks = f32_blocks(p, BM, BN);
   if (blocks > 0x7fffffffL) return MOE_ERR_UNSUPPORTED;
   const dim3 grid((unsigned)blocks), block(kThreads);
   if (a_kfast && b_kfast) gemm_f32_kernel<BM, BN, BK, WM, WN, WK, true, true><<<grid, block, 0, s>>>(p, tiles_n, tiles_m_fixed, (int)blocks);
@@ -262,6 +206,7 @@ bool gemm_f32_covers(const GemmProblem& p) {
 // (less than 2^32 threads).
 int launch_gemm_f32(const GemmProblem& p, hipStream_t s) {
   if (p.M <= 0 || p.N <= 0) return MOE_OK;
+  if (gemm_f32_splits(p)) return launch_gemm_f32_split(p, s);
   const bool a_kfast = p.a_cs == 1, b_kfast = p.b_rs == 1;
   const long tiles_m = (long)cdiv(p.M, 64) + (p.mode == 0 ? p.E / 2 : 0);      // segments end inside a tile
   const long tiles = (long)cdiv(p.N, 64) * tiles_m * (p.mode == 1 ? p.E : 1);

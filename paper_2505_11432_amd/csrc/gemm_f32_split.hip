@@ -1,0 +1,366 @@
+// Grouped GEMM on fp32 data with the bf16 matrix instructions: every operand element is the exact sum of three bf16 numbers.
+//
+// x = hi + mid + lo with hi = bf16(x), mid = bf16(x - hi) and lo = x - hi - mid: 24 significant bits in three times 8, nothing is lost.
+// Of the nine products of two such sums the six largest are added; the three left out are together below 2^-24 of the product, of
+// either sign and 2^-27 on average.  hi * hi has accumulators of its own, which round once per 32 products (the fp32 instruction once
+// per 2), so the sums are closer to float64 than with it.  Error of a layer's results, forward and backward, fp32 instruction and this:
+// 8 experts, 2000 rows, d = 1024, f = 2816 1.2e-6, 5.8e-7; 512 rows, d = 128, f = 256 2.8e-7, 2.0e-7 (with all sums in one accumulator
+// 1.4e-6, 4.2e-7; parts cut off instead of rounded 6.0e-7, 2.8e-7).
+//
+// Bound: six bf16 products take 0.4 of the time of one fp32 product on the matrix cores; beside them a pair of elements costs fourteen
+// vector instructions to split (16 KFLOP each), and the three parts pass through LDS.  No one of the three is alone the bound: FC1 of
+// 2000 rows and 1024 x 5632, 8 experts, takes 194 us, 150 without the loads, 130 without the split, 135 with a sixth of the products.
+// Each operand element is split once per tile by the thread that loads it, so larger tiles split less often.  Measured (us, the fp32
+// instruction and this; 8 experts, 2000 rows, d = 1024, f = 2816): FC1 300, 194; FC2 144, 109; dgrad2 131, 94; wgrad2 118, 98; dgrad1 266,
+// 211; wgrad1 231, 171.  Four experts of 1125 rows: 510, 321; 241, 183; 249, 179; 234, 162; 500, 373; 472, 307.
+// Not faster: one wave per SIMD with 64 x 64 outputs (226 us), fragments read ahead across the step barrier (the same), products and
+// split interleaved by scheduling barriers (the same), 128 x 64 tiles (196).
+#include <atomic>
+
+#include "gemm_f32_tiles.h"
+
+namespace moe {
+namespace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+
+constexpr int kStep = 32;                // contraction per step
+constexpr unsigned kSpan = 0x40000000u;  // bytes that a tile's rows span at most
+
+// Elements and results below these magnitudes (and not zero) are left to the fp32 instruction: an element's last part is down to 2^-23 of
+// it, a product's smaller terms 2^-24, and they would leave the range of normal numbers.  As 2 * bits - 1 of the float.
+constexpr unsigned kTinyIn = (24u << 24) - 1, kTinyOut = (47u << 24) - 1;       // 2^-103, 2^-80
+__device__ __forceinline__ unsigned magnitude(float v) { return (__builtin_bit_cast(unsigned, v) << 1) - 1u; }      // zero: the largest
+
+// LDS image of one part of one operand tile: EXT rows (or columns) of 32 bf16, 64 bytes.  A 16-byte read serves lanes 0-3, 12-15, 20-27 and
+// 4-11, 16-19, 28-31 together, so rows of different quads and neighbouring chunks meet: quad q of 16 rows is turned by 0, 2, 3, 1 (by q
+// itself, reads took twice as long: FC1 as above 203 -> 184 us).  Rows 16..31 of every 32 trade places pairwise, so that
+// sixteen even rows, which an operand that lies across k writes together, cover the banks once as well.
+template <int EXT> struct Part {
+  static constexpr int BYTES = EXT * 64;
+  __device__ static __forceinline__ int offset(int row, int chunk) {
+    const int q = (row >> 2) & 3;
+    return ((row ^ ((row >> 4) & 1)) << 6) + ((chunk ^ (((q << 1) ^ (q & 2) ^ (q >> 1)) & 3)) << 4);
+  }
+};
+
+// This thread's share of an operand tile: H chunks of eight consecutive k, chunk h of row row(h).  Loads are raw buffer
+// instructions on a descriptor at the tile's origin at the step's k, which moves on by scalar arithmetic; what lies past the
+// end of the contraction is out of the descriptor's range and reads as zero.
+template <bool KFAST, int EXT, int THREADS> struct Share {
+  static constexpr int H = EXT * 4 / THREADS;
+  static_assert(H == 1 || H == 2, "one or two chunks per thread");
+  __device__ static __forceinline__ int row(int h) {
+    const int t = threadIdx.x;
+    return KFAST ? h * (THREADS / 4) + (t >> 2) : t % (THREADS / 4) * H + h;
+  }
+  __device__ static __forceinline__ int chunk() { return KFAST ? threadIdx.x & 3 : threadIdx.x / (THREADS / 4); }
+
+  const char* base;             // row (column) ext0 at the first k
+  long step;                    // bytes per step
+  int ld4, left0;               // bytes from one row of the buffer to the next; across k: bytes of a row in front of the tile
+  unsigned off[KFAST ? H : 8];
+
+  // ext_n: valid rows of the tile; rows past them repeat the last ones (they only reach outputs that are not stored)
+  __device__ __forceinline__ void open(const float* p, long ld, int ext0, int ext_n, int k0) {
+    ld4 = (int)ld * 4;
+    left0 = ext0 * 4;
+    step = KFAST ? kStep * 4 : (long)kStep * ld4;
+    base = reinterpret_cast<const char*>(p + (KFAST ? (long)ext0 * ld + k0 : (long)k0 * ld + ext0));
+    if constexpr (KFAST) {
+#pragma unroll
+      for (int h = 0; h < H; ++h) off[h] = (unsigned)min(row(h), ext_n - 1) * (unsigned)ld4 + (unsigned)chunk() * 32u;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) off[i] = (unsigned)(chunk() * 8 + i) * (unsigned)ld4 + (unsigned)min(row(0), ext_n - H) * 4u;
+    }
+  }
+  // k_left: contraction left from step s on (not positive: nothing)
+  __device__ __forceinline__ void load(float (&v)[H][8], int s, int k_left) const {
+    const char* at = base + s * step;
+    const int span = KFAST ? (int)kSpan : max(min(k_left, kStep) * ld4 - left0, 0);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(at), 0, span, 0x00020000);
+    if constexpr (KFAST) {
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const unsigned o = chunk() * 8 + 4 * q < k_left ? off[h] + 16u * q : kSpan;
+          const f32x4 t = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0));
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[h][4 * q + i] = t[i];
+        }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        if constexpr (H == 2) {
+          const f32x2 t = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, off[i], 0, 0));
+          v[0][i] = t[0];
+          v[1][i] = t[1];
+        } else {
+          v[0][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off[i], 0, 0));
+        }
+      }
+    }
+  }
+
+  // The split in units of two elements, four to a chunk: unit u of the share, whose parts gather in `part` and go to lds with the
+  // chunk's last unit.  smallest: running minimum of the magnitudes.
+  static constexpr int UNITS = 4 * H;
+  __device__ static __forceinline__ void split(const float (&v)[H][8], int u, u32x4 (&part)[3], char* lds, unsigned& smallest) {
+    const int h = u / 4, i = u % 4;
+    float r0 = v[h][2 * i], r1 = v[h][2 * i + 1];
+    smallest = min(min(smallest, magnitude(r0)), magnitude(r1));
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const unsigned two = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{r0, r1}), bf16x2));
+      part[p][i] = two;
+      r0 -= __builtin_bit_cast(float, two << 16);
+      r1 -= __builtin_bit_cast(float, two & 0xffff0000u);
+    }
+    if (i == 3)
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        *reinterpret_cast<u32x4*>(lds + p * Part<EXT>::BYTES + Part<EXT>::offset(row(h), chunk())) = part[p];
+  }
+
+  // as fp32 rows of 32 k at a stride of 36
+  __device__ __forceinline__ void stash(const float (&v)[H][8], float* lds) const {
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        *reinterpret_cast<f32x4*>(lds + row(h) * 36 + chunk() * 8 + 4 * q) = f32x4{v[h][4 * q], v[h][4 * q + 1], v[h][4 * q + 2], v[h][4 * q + 3]};
+  }
+};
+
+// WM x WN waves.  While the products of step s run from one LDS buffer the operands of step s + 1 are split into the other, and those of
+// steps s + 2 and s + 3 are on their way into registers.
+template <int BM, int BN, int WM, int WN, bool AK, bool BKF>
+__global__ void __launch_bounds__(WM * WN * 64, 2) gemm_f32_split_kernel(GemmProblem p, int tiles_n, int tiles_m_fixed, int blocks) {
+  constexpr int THREADS = WM * WN * 64, WTM = BM / WM, WTN = BN / WN, FM = WTM / 16, FN = WTN / 16;
+  constexpr int A_BYTES = 3 * Part<BM>::BYTES, STAGE = A_BYTES + 3 * Part<BN>::BYTES;
+  static_assert((BM + BN) * 36 * 4 <= STAGE, "the fp32 rows of a step fit");
+  extern __shared__ __attribute__((aligned(16))) char lds[];        // two stages
+  __shared__ int redo;
+  F32Tile t;
+  if (!f32_tile<BM, BN>(p, tiles_n, tiles_m_fixed, blocks, t)) return;
+  const int m0 = t.m0, m_end = t.m_end, n0 = t.n0, klen = t.k_end - t.k0;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int i16 = lane & 15, g = lane >> 4;
+
+  Share<AK, BM, THREADS> a;
+  Share<BKF, BN, THREADS> b;
+  a.open(static_cast<const float*>(p.A), AK ? p.a_rs : p.a_cs, m0, m_end - m0, t.k0);
+  b.open(static_cast<const float*>(p.B) + (long)t.e * p.b_es, BKF ? p.b_cs : p.b_rs, n0, p.N - n0, t.k0);
+  float va[2][a.H][8], vb[2][b.H][8];
+  auto load = [&](int set, int s) __attribute__((always_inline)) {
+    a.load(va[set], s, klen - s * kStep);
+    b.load(vb[set], s, klen - s * kStep);
+  };
+  unsigned smallest = ~0u;
+  constexpr int UNITS = a.UNITS + b.UNITS;
+  u32x4 part[3];
+  auto split = [&](int set, int buf, int u) __attribute__((always_inline)) {
+    if (u < a.UNITS) a.split(va[set], u, part, lds + buf * STAGE, smallest);
+    else b.split(vb[set], u - a.UNITS, part, lds + buf * STAGE + A_BYTES, smallest);
+  };
+  f32x4 acc[FM][FN], low[FM][FN];        // the products of the first parts, the smaller ones
+  auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[i][j] = low[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  // The products of a step, and between them the split of the next one.  Blocks of FM x 2 outputs go through the six terms together, so that
+  // an accumulator is used again only after 2 * FM products.
+  auto advance = [&](int buf, int set) __attribute__((always_inline)) {
+    constexpr int PRODUCTS = 6 * FM * FN, EACH = PRODUCTS / UNITS;
+    static_assert(PRODUCTS % UNITS == 0 && FN % 2 == 0, "every unit of the split gets as many products");
+    constexpr int TB[6] = {2, 1, 0, 1, 0, 0}, TA[6] = {0, 1, 2, 0, 1, 0};        // parts of B and A, the smallest terms first
+    const char* at = lds + buf * STAGE;
+    bf16x8 fa[FM][3], fb[2][2][3];
+    auto read_a = [&](int q) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+        fa[i][q] = *reinterpret_cast<const bf16x8*>(at + q * Part<BM>::BYTES + Part<BM>::offset(wm * WTM + i * 16 + i16, g));
+    };
+    auto read_b = [&](int jp, int q) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        fb[jp & 1][j][q] =
+            *reinterpret_cast<const bf16x8*>(at + A_BYTES + q * Part<BN>::BYTES + Part<BN>::offset(wn * WTN + (2 * jp + j) * 16 + i16, g));
+    };
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      read_a(q);
+      read_b(0, 2 - q);
+    }
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+#pragma unroll
+      for (int c = 0; c < EACH; ++c) {
+        const int m = u * EACH + c, i = m % FM, j = m / FM % 2, term = m / (2 * FM) % 6, jp = m / (12 * FM);
+        if (m % (12 * FM) == 0 && jp + 1 < FN / 2)
+#pragma unroll
+          for (int q = 0; q < 3; ++q) read_b(jp + 1, 2 - q);
+        f32x4& sum = term == 5 ? acc[i][2 * jp + j] : low[i][2 * jp + j];
+        sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[jp & 1][j][TB[term]], fa[i][TA[term]], sum, 0, 0, 0);
+      }
+      split(set, buf ^ 1, u);
+    }
+  };
+  clear();
+  const int steps = (klen + kStep - 1) / kStep;
+  if (threadIdx.x == 0) redo = 0;
+  if (steps > 0) {
+    load(0, 0);
+    load(1, 1);
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) split(0, 0, u);
+    load(0, 2);
+    __syncthreads();
+    int s = 0;
+    for (; s + 2 <= steps; s += 2) {
+      advance(0, 1);
+      load(1, s + 3);
+      __syncthreads();
+      advance(1, 0);
+      load(0, s + 4);
+      __syncthreads();
+    }
+    if (s < steps) advance(0, 1);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] += low[i][j];
+  // Elements that do not split into normal numbers, or parts that overflowed (infinities and NaN among the elements give NaN
+  // here in every output they reach): the tile is made again with the fp32 instruction.
+  bool bad = smallest < kTinyIn;
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const unsigned u = magnitude(acc[i][j][r]);
+        bad |= u < kTinyOut || (u >= (0xffu << 24) - 1 && u != ~0u);
+      }
+  if (bad) redo = 1;
+  __syncthreads();
+  if (redo) {
+    float* at = reinterpret_cast<float*>(lds);
+    float* bt = at + BM * 36;
+    clear();
+    for (int s = 0; s < steps; ++s) {
+      load(0, s);
+      __syncthreads();
+      a.stash(va[0], at);
+      b.stash(vb[0], bt);
+      __syncthreads();
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          const f32x4 fb = *reinterpret_cast<const f32x4*>(bt + (wn * WTN + j * 16 + i16) * 36 + h * 16 + g * 4);
+#pragma unroll
+          for (int i = 0; i < FM; ++i) {
+            const f32x4 fa = *reinterpret_cast<const f32x4*>(at + (wm * WTM + i * 16 + i16) * 36 + h * 16 + g * 4);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[r], fa[r], acc[i][j], 0, 0, 0);
+          }
+        }
+    }
+  }
+  // a lane holds row lane % 16 and columns 4 * (lane / 16) + 0..3 of every 16 x 16 block
+  float* __restrict__ C = static_cast<float*>(p.C) + (long)t.e * p.c_es;
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    const int m = m0 + wm * WTM + i * 16 + i16;
+    if (m >= m_end) continue;
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const int n = n0 + wn * WTN + j * 16 + g * 4;
+      if (n >= p.N) continue;
+      f32x4* dst = reinterpret_cast<f32x4*>(C + (long)m * p.ldc + n);
+      *dst = p.accumulate ? acc[i][j] + *dst : acc[i][j];
+    }
+  }
+}
+
+template <int BM, int BN> constexpr int lds_bytes() { return 2 * 3 * (Part<BM>::BYTES + Part<BN>::BYTES); }
+
+template <int BM, int BN, int WM, int WN, bool AK, bool BKF>
+int launch_as(const GemmProblem& p, hipStream_t s) {
+  gemm_f32_split_kernel<BM, BN, WM, WN, AK, BKF><<<dim3((unsigned)f32_blocks(p, BM, BN)), dim3(WM * WN * 64), lds_bytes<BM, BN>(), s>>>(
+      p, cdiv(p.N, BN), cdiv(p.M, BM), (int)f32_blocks(p, BM, BN));
+  MOE_LAUNCH_CHECK();
+  return MOE_OK;
+}
+template <int BM, int BN, int WM, int WN>
+int launch(const GemmProblem& p, hipStream_t s) {
+  const bool a_kfast = p.a_cs == 1, b_kfast = p.b_rs == 1;
+  if (a_kfast && b_kfast) return launch_as<BM, BN, WM, WN, true, true>(p, s);
+  if (a_kfast) return launch_as<BM, BN, WM, WN, true, false>(p, s);
+  return launch_as<BM, BN, WM, WN, false, false>(p, s);
+}
+
+// Tiles of 64 x 64 (three workgroups per CU) that the average segment makes
+double tiles64(const GemmProblem& p) {
+  return (double)cdiv(p.N, 64) * (p.mode == 0 ? cdiv(p.M, 64) + p.E / 2 : (double)cdiv(p.M, 64) * p.E);
+}
+
+}  // namespace
+
+// Where the split is the faster way: from 192 tiles of 64 x 64 on (us, fp32 instruction and split: 216 tiles, K = 768 21.6, 18.2; 256,
+// K = 512 16.8, 13.9; 160, K = 1024 19.0, 25.2; 128, K = 2816 28, 52: few tiles are one chain of steps per CU, which the 32 x 32 tiles of the
+// fp32 kernel shorten), and for weight gradients of segments longer than one step (1536 tiles of 50 rows 15.8, 16.0; 11264 of 250
+// 231, 192; 11264 of 25 58, 67).
+bool gemm_f32_splits(const GemmProblem& p) {
+  if (p.mode == 2 || p.bias || !aligned16(p.C) || p.N % 4 || p.ldc % 4 || p.c_es % 4) return false;
+  const long lda = p.a_cs == 1 ? p.a_rs : p.a_cs, ldb = p.b_rs == 1 ? p.b_cs : p.b_rs;
+  if (lda >= 1 << 20 || ldb >= 1 << 20) return false;                   // 128 rows of a tile span less than kSpan
+  if (f32_blocks(p, 64, 64) * 256 >= 1L << 32) return false;            // threads of a launch
+  return tiles64(p) >= 192 && (p.mode == 0 || p.K > kStep * p.E);
+}
+
+// 64 x 64 or 128 x 128 tiles (one workgroup of eight waves per CU, which splits an element half as often), by the estimated time from
+// measured tiles: 64 x 64 0.85 us + 0.445 per step and CU, 128 x 128 3.5 + 1.33 in whole rounds.  (us, 64 and 128) weight gradients of 2000
+// rows, 8 experts, 1024 x 5632 192, 171, of 6 experts, 5632 x 128 45, 58; dgrad2 102, 94; FC2 109, 110, of 4500 rows, 4 experts 183, 223.
+// Segments of under four steps stay with the small tile (2816 tiles of three steps 32, 36).
+int launch_gemm_f32_split(const GemmProblem& p, hipStream_t s) {
+  const int steps = cdiv(p.mode == 0 ? p.K : p.K / p.E, kStep);
+  const double tiles128 = cdiv(p.N, 128) * (p.mode == 0 ? p.M / 128.0 + p.E / 2 : (double)cdiv(p.M, 128) * p.E);
+  const long rounds = ((long)tiles128 + 255) / 256;
+  if (steps >= 4 && rounds * (3.5 + 1.33 * steps) < tiles64(p) / 256 * (0.85 + 0.445 * steps)) {
+    const int rc = gemm_f32_split_configure();
+    return rc != MOE_OK ? rc : launch<128, 128, 4, 2>(p, s);
+  }
+  return launch<64, 64, 2, 2>(p, s);
+}
+
+// The 128 x 128 kernels need their dynamic-LDS limit raised once per device; moe_init does it ahead of a graph capture.  The
+// values are the same on every call, the bit only saves work.
+int gemm_f32_split_configure() {
+  static std::atomic<unsigned long long> done{0};
+  int dev = 0;
+  MOE_HIP_TRY(hipGetDevice(&dev));
+  if (dev < 0 || dev >= 64) return MOE_ERR_UNSUPPORTED;
+  if (done.load(std::memory_order_acquire) >> dev & 1) return MOE_OK;
+  constexpr int bytes = lds_bytes<128, 128>();
+  for (const void* k : {(const void*)gemm_f32_split_kernel<128, 128, 4, 2, true, true>, (const void*)gemm_f32_split_kernel<128, 128, 4, 2, true, false>,
+                        (const void*)gemm_f32_split_kernel<128, 128, 4, 2, false, false>})
+    MOE_HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+  done.fetch_or(1ull << dev, std::memory_order_release);
+  return MOE_OK;
+}
+
+}  // namespace moe

@@ -64,6 +64,94 @@ def test_ffn_f32_tile_edges(rows, d, f):
     assert rel(dw2, before2.double() + DW2) < tol
 
 
+# rows, E, d, f: both tiles of the split products (64 x 64, from 192 tiles on; 128 x 128), their edges, k tails of 16, odd and even
+# numbers of steps, a segment of one row, an empty one, segments of a few rows
+SPLIT = [
+    ([1, 0, 700, 130, 63], 272, 1040),
+    ([500, 511, 0, 1049], 1024, 1408),
+    ([40] * 30, 48, 528),
+    ([1027], 1552, 784),
+]
+
+
+def ffn_f32(rows, d, f, xp, dyp, w1, w2):
+    from paper_2505_11432_amd import binding as B
+    E, M = len(rows), sum(rows)
+    offsets = torch.tensor([sum(rows[:e]) for e in range(E + 1)], dtype=torch.int32, device=DEV)
+    h, yp, dxp = (torch.full((M, n), 7.0, device=DEV) for n in (2 * f, d, d))
+    dw1, dw2 = torch.full_like(w1, 7.0), torch.full_like(w2, 7.0)
+    ws = torch.empty(max(B.moe_workspace_bytes(M, d, E, 1, f, B.F32), 256), dtype=torch.uint8, device=DEV)
+    B.moe_expert_ffn_fwd(xp, None, offsets, w1, None, w2, None, h, yp, None, ws)
+    B.moe_expert_ffn_bwd(xp, h, dyp, None, offsets, w1, w2, dxp, dw1, dw2, 0, ws)
+    return h, yp, dxp, dw1, dw2
+
+
+def inputs_f32(rows, d, f):
+    E, M = len(rows), sum(rows)
+    g = torch.Generator(device=DEV).manual_seed(M + d)
+    rnd = lambda *s: torch.randn(s, generator=g, device=DEV)
+    return rnd(M, d), rnd(M, d), rnd(E, 2 * f, d) / math.sqrt(d), rnd(E, d, f) / math.sqrt(f)
+
+
+@pytest.mark.parametrize("rows,d,f", SPLIT)
+def test_split_products_are_as_close_as_fp32(rows, d, f):
+    """Every product against float64, on the operands that the library itself made: within what an fp32 sum of K terms that is rounded
+    every second term loses (sqrt(K / 2) roundings of random sign, 2^-24 at most and 0.58 of that each in the mean square)."""
+    xp, dyp, w1, w2 = inputs_f32(rows, d, f)
+    h, yp, dxp, dw1, dw2 = ffn_f32(rows, d, f, xp, dyp, w1, w2)
+    at = 0
+    for e, n in enumerate(rows):
+        s, at = slice(at, at + n), at + n
+        a, b, X, DY = w1[e].double(), w2[e].double(), xp[s].double(), dyp[s].double()
+        if n == 0:
+            assert not dw1[e].any() and not dw2[e].any()
+            continue
+        G, U = h[s, :f].double(), h[s, f:].double()
+        sg = torch.sigmoid(G)
+        A, dA = G * sg * U, DY @ b
+        dH = torch.cat([dA * U * sg * (1 + G * (1 - sg)), dA * G * sg], 1)
+        # fp32 operands in between (A, dA, dH: a few roundings per element) add up to 4 * 2^-24 in all
+        for name, got, ref, K in (("h", h[s], X @ a.t(), d), ("yp", yp[s], A @ b.t(), f), ("d_xp", dxp[s], dH @ a, 2 * f),
+                                  ("d_w1", dw1[e], dH.t() @ X, n), ("d_w2", dw2[e], DY.t() @ A, n)):
+            tol = (0.58 * math.sqrt(K / 2) + 4) * 2.0 ** -24
+            assert rel(got, ref) < tol, (name, e, rel(got, ref), tol)
+
+
+@pytest.mark.parametrize("rows,d,f", SPLIT[:2])
+@pytest.mark.parametrize("scale", [2.0 ** -60, 2.0 ** -110, 2.0 ** -126, 2.0 ** -140, 2.0 ** 120])
+def test_split_products_of_tiny_and_huge_elements(rows, d, f, scale):
+    """The whole range of fp32, subnormal numbers included (half a unit of 2^-149 per element and result is what they leave)."""
+    xp, dyp, w1, w2 = inputs_f32(rows, d, f)
+    xp[5:] *= scale                                                     # ordinary rows beside them in the first tile
+    h = ffn_f32(rows, d, f, xp, dyp, w1, w2)[0]
+    at = 0
+    for e, n in enumerate(rows):
+        s, at = slice(at, at + n), at + n
+        ref = xp[s].double() @ w1[e].double().t()
+        tol = 3 * math.sqrt(d) * 2.0 ** -24 * ref.norm() + math.sqrt(d * ref.numel()) * 2.0 ** -149
+        assert n == 0 or float((h[s].double() - ref).norm()) < float(tol), (e, float((h[s].double() - ref).norm()), float(tol))
+
+
+def test_split_products_of_infinities_and_nan():
+    rows, d, f = SPLIT[0]
+    xp, dyp, w1, w2 = inputs_f32(rows, d, f)
+    inf = float("inf")
+    xp[3, 7], xp[9, 200], xp[300, 0], xp[301, 1] = inf, -inf, float("nan"), 3.4e38         # the last: above bf16's largest
+    w1[2, 40, 11] = inf
+    xp[20] = 0.0                                                                            # 0 * inf
+    h = ffn_f32(rows, d, f, xp, dyp, w1, w2)[0]
+    at = 0
+    for e, n in enumerate(rows):
+        s, at = slice(at, at + n), at + n
+        ref = xp[s].double() @ w1[e].double().t()
+        over = ref.abs() > torch.finfo(torch.float32).max
+        ref[over] = ref[over].sign() * inf
+        got = h[s].double()
+        assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got[ref.isinf()], ref[ref.isinf()])
+        fin = ref.isfinite()
+        assert n == 0 or rel(got[fin], ref[fin]) < 3 * math.sqrt(d) * 2.0 ** -24
+
+
 @pytest.mark.parametrize("T,d,E", [(1, 16, 1), (33, 260, 5), (1000, 1024, 64), (65, 4, 3), (50, 30, 4)])
 def test_router_f32_edges(T, d, E):
     from paper_2505_11432_amd import binding as B
