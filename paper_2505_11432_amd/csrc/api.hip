@@ -65,7 +65,7 @@ static int ffn_fwd_bf16(const void* xp, const int32_t* offsets, const void* w1, 
 }
 
 // fp8 (Section 5 / Section 7 "FP8 training"): e4m3 operands with per-token and per-output-channel scales on
-// the 32x32x64 MFMA; the SwiGLU output is quantised per token before FC2; yp optionally per token as well.
+// the 16x16x128 MFMA; the SwiGLU output is quantised per token before FC2; yp optionally per token as well.
 static int ffn_fwd_fp8(const void* xp, const float* xp_scale, const int32_t* offsets, const void* w1,
                        const float* w1_scale, const void* w2, const float* w2_scale, int M, int d, int E, int f,
                        void* h_save, void* yp, float* yp_scale, moe_dtype out_dt, uint8_t* a_codes_out,

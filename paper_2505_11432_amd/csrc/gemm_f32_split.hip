@@ -37,104 +37,83 @@ constexpr unsigned kTinyIn = (24u << 24) - 1, kTinyOut = (47u << 24) - 1;       
 __device__ __forceinline__ unsigned magnitude(float v) { return (__builtin_bit_cast(unsigned, v) << 1) - 1u; }      // zero: the largest
 
 // LDS image of one part of one operand tile: EXT rows (or columns) of 32 bf16, 64 bytes.  A 16-byte read serves lanes 0-3, 12-15, 20-27 and
-// 4-11, 16-19, 28-31 together, so rows of different quads and neighbouring chunks meet: quad q of 16 rows is turned by 0, 2, 3, 1 (by q
-// itself, reads took twice as long: FC1 as above 203 -> 184 us).  Rows 16..31 of every 32 trade places pairwise, so that
-// sixteen even rows, which an operand that lies across k writes together, cover the banks once as well.
+// 4-11, 16-19, 28-31 together, so quads of rows meet others at the neighbouring chunk: quad q of 16 rows is turned by 0, 2, 3, 1 (by q
+// itself, reads took twice as long: FC1 as above 203 -> 184 us).
 template <int EXT> struct Part {
   static constexpr int BYTES = EXT * 64;
   __device__ static __forceinline__ int offset(int row, int chunk) {
     const int q = (row >> 2) & 3;
-    return ((row ^ ((row >> 4) & 1)) << 6) + ((chunk ^ (((q << 1) ^ (q & 2) ^ (q >> 1)) & 3)) << 4);
+    return (row << 6) + ((chunk ^ (((q << 1) ^ (q & 2) ^ (q >> 1)) & 3)) << 4);
   }
 };
 
-// This thread's share of an operand tile: H chunks of eight consecutive k, chunk h of row row(h).  Loads are raw buffer
-// instructions on a descriptor at the tile's origin at the step's k, which moves on by scalar arithmetic; what lies past the
-// end of the contraction is out of the descriptor's range and reads as zero.
-template <bool KFAST, int EXT, int THREADS> struct Share {
-  static constexpr int H = EXT * 4 / THREADS;
-  static_assert(H == 1 || H == 2, "one or two chunks per thread");
-  __device__ static __forceinline__ int row(int h) {
-    const int t = threadIdx.x;
-    return KFAST ? h * (THREADS / 4) + (t >> 2) : t % (THREADS / 4) * H + h;
-  }
-  __device__ static __forceinline__ int chunk() { return KFAST ? threadIdx.x & 3 : threadIdx.x / (THREADS / 4); }
+// This thread's share of an operand tile: eight consecutive k of one row.  Loads are raw buffer instructions on a descriptor at the tile's
+// origin at the step's k, which moves on by scalar arithmetic; what lies past the end of the contraction is out of the
+// descriptor's range and reads as zero.
+template <bool KFAST, int EXT> struct Share {
+  __device__ static __forceinline__ int row() { return KFAST ? threadIdx.x >> 2 : threadIdx.x % EXT; }
+  __device__ static __forceinline__ int chunk() { return KFAST ? threadIdx.x & 3 : threadIdx.x / EXT; }
 
   const char* base;             // row (column) ext0 at the first k
   long step;                    // bytes per step
   int ld4, left0;               // bytes from one row of the buffer to the next; across k: bytes of a row in front of the tile
-  unsigned off[KFAST ? H : 8];
+  unsigned off[KFAST ? 1 : 8];
 
-  // ext_n: valid rows of the tile; rows past them repeat the last ones (they only reach outputs that are not stored)
+  // ext_n: valid rows of the tile; rows past them repeat the last one (they only reach outputs that are not stored)
   __device__ __forceinline__ void open(const float* p, long ld, int ext0, int ext_n, int k0) {
     ld4 = (int)ld * 4;
     left0 = ext0 * 4;
     step = KFAST ? kStep * 4 : (long)kStep * ld4;
     base = reinterpret_cast<const char*>(p + (KFAST ? (long)ext0 * ld + k0 : (long)k0 * ld + ext0));
+    const unsigned r = min(row(), ext_n - 1);
     if constexpr (KFAST) {
-#pragma unroll
-      for (int h = 0; h < H; ++h) off[h] = (unsigned)min(row(h), ext_n - 1) * (unsigned)ld4 + (unsigned)chunk() * 32u;
+      off[0] = r * (unsigned)ld4 + (unsigned)chunk() * 32u;
     } else {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) off[i] = (unsigned)(chunk() * 8 + i) * (unsigned)ld4 + (unsigned)min(row(0), ext_n - H) * 4u;
+      for (int i = 0; i < 8; ++i) off[i] = (unsigned)(chunk() * 8 + i) * (unsigned)ld4 + r * 4u;
     }
   }
   // k_left: contraction left from step s on (not positive: nothing)
-  __device__ __forceinline__ void load(float (&v)[H][8], int s, int k_left) const {
+  __device__ __forceinline__ void load(float (&v)[8], int s, int k_left) const {
     const char* at = base + s * step;
     const int span = KFAST ? (int)kSpan : max(min(k_left, kStep) * ld4 - left0, 0);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(at), 0, span, 0x00020000);
     if constexpr (KFAST) {
 #pragma unroll
-      for (int h = 0; h < H; ++h)
+      for (int q = 0; q < 2; ++q) {
+        const unsigned o = chunk() * 8 + 4 * q < k_left ? off[0] + 16u * q : kSpan;
+        const f32x4 t = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0));
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const unsigned o = chunk() * 8 + 4 * q < k_left ? off[h] + 16u * q : kSpan;
-          const f32x4 t = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0));
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v[h][4 * q + i] = t[i];
-        }
+        for (int i = 0; i < 4; ++i) v[4 * q + i] = t[i];
+      }
     } else {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        if constexpr (H == 2) {
-          const f32x2 t = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, off[i], 0, 0));
-          v[0][i] = t[0];
-          v[1][i] = t[1];
-        } else {
-          v[0][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off[i], 0, 0));
-        }
-      }
+      for (int i = 0; i < 8; ++i) v[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off[i], 0, 0));
     }
   }
 
-  // The split in units of two elements, four to a chunk: unit u of the share, whose parts gather in `part` and go to lds with the
-  // chunk's last unit.  smallest: running minimum of the magnitudes.
-  static constexpr int UNITS = 4 * H;
-  __device__ static __forceinline__ void split(const float (&v)[H][8], int u, u32x4 (&part)[3], char* lds, unsigned& smallest) {
-    const int h = u / 4, i = u % 4;
-    float r0 = v[h][2 * i], r1 = v[h][2 * i + 1];
+  // The split in four units of two elements: unit u, whose parts gather in `part` and go to lds with the last one.  smallest:
+  // running minimum of the magnitudes.
+  __device__ static __forceinline__ void split(const float (&v)[8], int u, u32x4 (&part)[3], char* lds, unsigned& smallest) {
+    float r0 = v[2 * u], r1 = v[2 * u + 1];
     smallest = min(min(smallest, magnitude(r0)), magnitude(r1));
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       const unsigned two = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{r0, r1}), bf16x2));
-      part[p][i] = two;
+      part[p][u] = two;
       r0 -= __builtin_bit_cast(float, two << 16);
       r1 -= __builtin_bit_cast(float, two & 0xffff0000u);
     }
-    if (i == 3)
+    if (u == 3)
 #pragma unroll
-      for (int p = 0; p < 3; ++p)
-        *reinterpret_cast<u32x4*>(lds + p * Part<EXT>::BYTES + Part<EXT>::offset(row(h), chunk())) = part[p];
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x4*>(lds + p * Part<EXT>::BYTES + Part<EXT>::offset(row(), chunk())) = part[p];
   }
 
   // as fp32 rows of 32 k at a stride of 36
-  __device__ __forceinline__ void stash(const float (&v)[H][8], float* lds) const {
+  __device__ static __forceinline__ void stash(const float (&v)[8], float* lds) {
 #pragma unroll
-    for (int h = 0; h < H; ++h)
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-        *reinterpret_cast<f32x4*>(lds + row(h) * 36 + chunk() * 8 + 4 * q) = f32x4{v[h][4 * q], v[h][4 * q + 1], v[h][4 * q + 2], v[h][4 * q + 3]};
+    for (int q = 0; q < 2; ++q)
+      *reinterpret_cast<f32x4*>(lds + row() * 36 + chunk() * 8 + 4 * q) = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
   }
 };
 
@@ -144,6 +123,7 @@ template <int BM, int BN, int WM, int WN, bool AK, bool BKF>
 __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_f32_split_kernel(GemmProblem p, int tiles_n, int tiles_m_fixed, int blocks) {
   constexpr int THREADS = WM * WN * 64, WTM = BM / WM, WTN = BN / WN, FM = WTM / 16, FN = WTN / 16;
   constexpr int A_BYTES = 3 * Part<BM>::BYTES, STAGE = A_BYTES + 3 * Part<BN>::BYTES;
+  static_assert(BM * 4 == THREADS && BN * 4 == THREADS, "one chunk of each operand per thread");
   static_assert((BM + BN) * 36 * 4 <= STAGE, "the fp32 rows of a step fit");
   extern __shared__ __attribute__((aligned(16))) char lds[];        // two stages
   __shared__ int redo;
@@ -155,21 +135,21 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_f32_split_kernel(GemmPro
   const int wm = wave / WN, wn = wave % WN;
   const int i16 = lane & 15, g = lane >> 4;
 
-  Share<AK, BM, THREADS> a;
-  Share<BKF, BN, THREADS> b;
+  Share<AK, BM> a;
+  Share<BKF, BN> b;
   a.open(static_cast<const float*>(p.A), AK ? p.a_rs : p.a_cs, m0, m_end - m0, t.k0);
   b.open(static_cast<const float*>(p.B) + (long)t.e * p.b_es, BKF ? p.b_cs : p.b_rs, n0, p.N - n0, t.k0);
-  float va[2][a.H][8], vb[2][b.H][8];
+  float va[2][8], vb[2][8];
   auto load = [&](int set, int s) __attribute__((always_inline)) {
     a.load(va[set], s, klen - s * kStep);
     b.load(vb[set], s, klen - s * kStep);
   };
   unsigned smallest = ~0u;
-  constexpr int UNITS = a.UNITS + b.UNITS;
+  constexpr int UNITS = 8;
   u32x4 part[3];
   auto split = [&](int set, int buf, int u) __attribute__((always_inline)) {
-    if (u < a.UNITS) a.split(va[set], u, part, lds + buf * STAGE, smallest);
-    else b.split(vb[set], u - a.UNITS, part, lds + buf * STAGE + A_BYTES, smallest);
+    if (u < 4) a.split(va[set], u, part, lds + buf * STAGE, smallest);
+    else b.split(vb[set], u - 4, part, lds + buf * STAGE + A_BYTES, smallest);
   };
   f32x4 acc[FM][FN], low[FM][FN];        // the products of the first parts, the smaller ones
   auto clear = [&]() __attribute__((always_inline)) {
@@ -328,7 +308,7 @@ bool gemm_f32_splits(const GemmProblem& p) {
   if (p.mode == 2 || p.bias || !aligned16(p.C) || p.N % 4 || p.ldc % 4 || p.c_es % 4) return false;
   const long lda = p.a_cs == 1 ? p.a_rs : p.a_cs, ldb = p.b_rs == 1 ? p.b_cs : p.b_rs;
   if (lda >= 1 << 20 || ldb >= 1 << 20) return false;                   // 128 rows of a tile span less than kSpan
-  if (f32_blocks(p, 64, 64) * 256 >= 1L << 32) return false;            // threads of a launch
+  if (f32_blocks(p, 64, 64) * 256 >= 1L << 31) return false;            // threads of a launch, of 128 x 128 tiles at most as many and a column
   return tiles64(p) >= 192 && (p.mode == 0 || p.K > kStep * p.E);
 }
 

@@ -217,7 +217,7 @@ int mfma_wgrad(const void* P, const void* Q, const int32_t* offsets, int rows, i
   return launch<256, 256, 64, 2, 2, 4, MNMAJOR, MNMAJOR, KSEG, EPI_STORE, bf16>(a, blocks, s);
 }
 
-// e4m3 operands (codes with per-row / per-output-channel scales), 32x32x64 f8f6f4 MFMA, bf16 results:
+// e4m3 operands (codes with per-row / per-output-channel scales), 16x16x128 f8f6f4 MFMA, bf16 results:
 // H[M,2f] = (xp*sx) * (w1[e]*sw1)^T, A_out = SwiGLU(H)
 int mfma_fc1_swiglu_fp8(const void* xp, const float* xp_scale, const void* w1, const float* w1_scale,
                         const int32_t* offsets, int M, int d, int E, int f, void* H, void* A_out, hipStream_t s) {
