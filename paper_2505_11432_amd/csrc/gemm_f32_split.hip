@@ -7,14 +7,15 @@
 // 8 experts, 2000 rows, d = 1024, f = 2816 1.2e-6, 5.8e-7; 512 rows, d = 128, f = 256 2.8e-7, 2.0e-7 (with all sums in one accumulator
 // 1.4e-6, 4.2e-7; parts cut off instead of rounded 6.0e-7, 2.8e-7).
 //
-// Bound: six bf16 products take 0.4 of the time of one fp32 product on the matrix cores; beside them a pair of elements costs fourteen
-// vector instructions to split (16 KFLOP each), and the three parts pass through LDS.  No one of the three is alone the bound: FC1 of
-// 2000 rows and 1024 x 5632, 8 experts, takes 194 us, 150 without the loads, 130 without the split, 135 with a sixth of the products.
+// Bound: six bf16 products take 0.4 of the time of one fp32 product on the matrix cores, but two elements also cost fourteen vector
+// instructions to split, and the three parts pass through LDS.  These follow one another more than they overlap: FC1 of 2000 rows, 8
+// experts, 1024 x 5632 takes 188 us on 128 x 128 tiles (64 x 64: 202), 173 (171) without the arithmetic of the split, 164 (162)
+// without the loads, 114 (141) with a sixth of the products.
 // Each operand element is split once per tile by the thread that loads it, so larger tiles split less often.  Measured (us, the fp32
 // instruction and this; 8 experts, 2000 rows, d = 1024, f = 2816): FC1 300, 194; FC2 144, 109; dgrad2 131, 94; wgrad2 118, 98; dgrad1 266,
 // 211; wgrad1 231, 171.  Four experts of 1125 rows: 510, 321; 241, 183; 249, 179; 234, 162; 500, 373; 472, 307.
-// Not faster: one wave per SIMD with 64 x 64 outputs (226 us), fragments read ahead across the step barrier (the same), products and
-// split interleaved by scheduling barriers (the same), 128 x 64 tiles (196).
+// Not faster: one wave per SIMD with 64 x 64 outputs (226 us), fragments read ahead across the step barrier (182 to 185, wgrad1 172 to 190
+// against 173), products and split interleaved by scheduling barriers (184), 128 x 64 tiles (196).
 #include <atomic>
 
 #include "gemm_f32_tiles.h"
@@ -308,7 +309,7 @@ bool gemm_f32_splits(const GemmProblem& p) {
   if (p.mode == 2 || p.bias || !aligned16(p.C) || p.N % 4 || p.ldc % 4 || p.c_es % 4) return false;
   const long lda = p.a_cs == 1 ? p.a_rs : p.a_cs, ldb = p.b_rs == 1 ? p.b_cs : p.b_rs;
   if (lda >= 1 << 20 || ldb >= 1 << 20) return false;                   // 128 rows of a tile span less than kSpan
-  if (f32_blocks(p, 64, 64) * 256 >= 1L << 31) return false;            // threads of a launch, of 128 x 128 tiles at most as many and a column
+  if (f32_blocks(p, 64, 64) * 256 >= 1L << 31) return false;            // a launch holds less than 2^32 threads
   return tiles64(p) >= 192 && (p.mode == 0 || p.K > kStep * p.E);
 }
 
