@@ -5,7 +5,10 @@
 // either sign and 2^-27 on average.  hi * hi has accumulators of its own, which round once per 32 products (the fp32 instruction once
 // per 2), so the sums are closer to float64 than with it.  Error of a layer's results, forward and backward, fp32 instruction and this:
 // 8 experts, 2000 rows, d = 1024, f = 2816 1.2e-6, 5.8e-7; 512 rows, d = 128, f = 256 2.8e-7, 2.0e-7 (with all sums in one accumulator
-// 1.4e-6, 4.2e-7; parts cut off instead of rounded 6.0e-7, 2.8e-7).
+// 1.4e-6, 4.2e-7; parts cut off instead of rounded 6.0e-7, 2.8e-7).  (The splitting is that of Henry, Tang and Heinecke, "Leveraging the
+// bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", 2019.)  It does not hold for sums of one term: kFewTerms.
+// In a longer contraction that holds a single product other than zero, of two full 24-bit numbers, 4 % of the results are not the nearest
+// number (up to 1.5 units of 2^-24 off instead of 1); products by powers of two and other numbers of up to 8 bits are exact.
 //
 // Bound: six bf16 products take 0.4 of the time of one fp32 product on the matrix cores, but two elements also cost fourteen vector
 // instructions to split, and the three parts pass through LDS.  These follow one another more than they overlap: FC1 of 2000 rows, 8
@@ -30,6 +33,10 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 
 constexpr int kStep = 32;                // contraction per step
+// Contractions of so few terms (weight gradients of one or two rows) are left to the fp32 instruction: the three products left out and
+// the sum of two accumulators round more than it does on them.  Against float64 in units of 2^-24, the fp32 instruction and the split: one term
+// rms 0.43, 0.44, largest 1.0, 1.56; two 0.52, 0.44, 1.88, 2.26; three 0.60, 0.44, 2.55, 2.36; four 0.66, 0.45, 2.86, 2.25; 1024 4.9, 3.1.
+constexpr int kFewTerms = 2;
 constexpr unsigned kSpan = 0x40000000u;  // bytes that a tile's rows span at most
 
 // Elements and results below these magnitudes (and not zero) are left to the fp32 instruction: an element's last part is down to 2^-23 of
@@ -199,8 +206,9 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_f32_split_kernel(GemmPro
   };
   clear();
   const int steps = (klen + kStep - 1) / kStep;
-  if (threadIdx.x == 0) redo = 0;
-  if (steps > 0) {
+  const bool few = klen <= kFewTerms;
+  if (threadIdx.x == 0) redo = few;
+  if (!few) {
     load(0, 0);
     load(1, 1);
 #pragma unroll

@@ -74,7 +74,7 @@ SPLIT = [
 ]
 
 
-def ffn_f32(rows, d, f, xp, dyp, w1, w2):
+def ffn_f32(rows, d, f, xp, dyp, w1, w2, a_override=None):
     from paper_2505_11432_amd import binding as B
     E, M = len(rows), sum(rows)
     offsets = torch.tensor([sum(rows[:e]) for e in range(E + 1)], dtype=torch.int32, device=DEV)
@@ -82,7 +82,7 @@ def ffn_f32(rows, d, f, xp, dyp, w1, w2):
     dw1, dw2 = torch.full_like(w1, 7.0), torch.full_like(w2, 7.0)
     ws = torch.empty(max(B.moe_workspace_bytes(M, d, E, 1, f, B.F32), 256), dtype=torch.uint8, device=DEV)
     B.moe_expert_ffn_fwd(xp, None, offsets, w1, None, w2, None, h, yp, None, ws)
-    B.moe_expert_ffn_bwd(xp, h, dyp, None, offsets, w1, w2, dxp, dw1, dw2, 0, ws)
+    B.moe_expert_ffn_bwd(xp, h, dyp, a_override, offsets, w1, w2, dxp, dw1, dw2, 0, ws)
     return h, yp, dxp, dw1, dw2
 
 
@@ -115,6 +115,24 @@ def test_split_products_are_as_close_as_fp32(rows, d, f):
                                   ("d_w1", dw1[e], dH.t() @ X, n), ("d_w2", dw2[e], DY.t() @ A, n)):
             tol = (0.58 * math.sqrt(K / 2) + 4) * 2.0 ** -24
             assert rel(got, ref) < tol, (name, e, rel(got, ref), tol)
+
+
+def test_weight_gradients_of_one_and_two_rows_round_as_fp32():
+    """Beside segments that make the launch take the split: one row gives the rounded product, two rows a product rounded and the
+    other added to it and rounded, half a unit in the last place each."""
+    rows, d, f = [1, 2, 700, 1, 130, 2, 0], 272, 1040
+    xp, dyp, w1, w2 = inputs_f32(rows, d, f)
+    a = torch.randn(sum(rows), f, generator=torch.Generator(device=DEV).manual_seed(5), device=DEV)
+    dw2 = ffn_f32(rows, d, f, xp, dyp, w1, w2, a_override=a)[4]
+    at = 0
+    for e, n in enumerate(rows):
+        s, at = slice(at, at + n), at + n
+        if n == 1:
+            assert torch.equal(dw2[e], (dyp[s].double().t() * a[s].double()).float()), e
+        elif n == 2:
+            p, q = (dyp[s][i].double()[:, None] * a[s][i].double()[None] for i in (0, 1))
+            bound = (torch.maximum(p.abs(), q.abs()) + (p + q).abs()) * 2.0 ** -24 * (1 + 2.0 ** -20)
+            assert ((dw2[e].double() - p - q).abs() <= bound).all(), e
 
 
 @pytest.mark.parametrize("rows,d,f", SPLIT[:2])
