@@ -39,10 +39,12 @@ constexpr int kStep = 32;                // contraction per step
 constexpr int kFewTerms = 2;
 constexpr unsigned kSpan = 0x40000000u;  // bytes that a tile's rows span at most
 
-// Elements and results below these magnitudes (and not zero) are left to the fp32 instruction: an element's last part is down to 2^-23 of
-// it, a product's smaller terms 2^-24, and they would leave the range of normal numbers.  As 2 * bits - 1 of the float.
-constexpr unsigned kTinyIn = (24u << 24) - 1, kTinyOut = (47u << 24) - 1;       // 2^-103, 2^-80
-__device__ __forceinline__ unsigned magnitude(float v) { return (__builtin_bit_cast(unsigned, v) << 1) - 1u; }      // zero: the largest
+// Elements are scaled by this on the way in and sums by its square on the way out, exactly: the parts of every element other than zero, the
+// smallest subnormal number among them, are then normal numbers, and so is every part product that can reach a result other than zero.  What
+// leaves the range at its other end (elements from 2^104 on, sums from 2^80 on, infinities and NaN) is seen in the sums.
+// (Left as they are, elements below 2^-103 and sums below 2^-80 had to be found and their tiles made again: two vector instructions per element
+// instead of one, and FC1 as below 488 us instead of 184 with one such element per tile, as gates below -72 give.)
+constexpr float kScale = 0x1p24f, kUnscale = 0x1p-48f;
 
 // LDS image of one part of one operand tile: EXT rows (or columns) of 32 bf16, 64 bytes.  A 16-byte read serves lanes 0-3, 12-15, 20-27 and
 // 4-11, 16-19, 28-31 together, so quads of rows meet others at the neighbouring chunk: quad q of 16 rows is turned by 0, 2, 3, 1 (by q
@@ -100,11 +102,9 @@ template <bool KFAST, int EXT> struct Share {
     }
   }
 
-  // The split in four units of two elements: unit u, whose parts gather in `part` and go to lds with the last one.  smallest:
-  // running minimum of the magnitudes.
-  __device__ static __forceinline__ void split(const float (&v)[8], int u, u32x4 (&part)[3], char* lds, unsigned& smallest) {
-    float r0 = v[2 * u], r1 = v[2 * u + 1];
-    smallest = min(min(smallest, magnitude(r0)), magnitude(r1));
+  // The split in four units of two elements: unit u, whose parts gather in `part` and go to lds with the last one.
+  __device__ static __forceinline__ void split(const float (&v)[8], int u, u32x4 (&part)[3], char* lds) {
+    float r0 = v[2 * u] * kScale, r1 = v[2 * u + 1] * kScale;
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       const unsigned two = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{r0, r1}), bf16x2));
@@ -152,12 +152,11 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_f32_split_kernel(GemmPro
     a.load(va[set], s, klen - s * kStep);
     b.load(vb[set], s, klen - s * kStep);
   };
-  unsigned smallest = ~0u;
   constexpr int UNITS = 8;
   u32x4 part[3];
   auto split = [&](int set, int buf, int u) __attribute__((always_inline)) {
-    if (u < 4) a.split(va[set], u, part, lds + buf * STAGE, smallest);
-    else b.split(vb[set], u - 4, part, lds + buf * STAGE + A_BYTES, smallest);
+    if (u < 4) a.split(va[set], u, part, lds + buf * STAGE);
+    else b.split(vb[set], u - 4, part, lds + buf * STAGE + A_BYTES);
   };
   f32x4 acc[FM][FN], low[FM][FN];        // the products of the first parts, the smaller ones
   auto clear = [&]() __attribute__((always_inline)) {
@@ -227,21 +226,17 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_f32_split_kernel(GemmPro
     if (s < steps) advance(0, 1);
   }
   __syncthreads();
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] += low[i][j];
-  // Elements that do not split into normal numbers, or parts that overflowed (infinities and NaN among the elements give NaN
-  // here in every output they reach): the tile is made again with the fp32 instruction.
-  bool bad = smallest < kTinyIn;
+  // Parts or sums that overflowed (they give infinities or NaN in every output they reach): the tile is made again with the fp32 instruction.
+  bool bad = false;
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const unsigned u = magnitude(acc[i][j][r]);
-        bad |= u < kTinyOut || (u >= (0xffu << 24) - 1 && u != ~0u);
+        const float sum = acc[i][j][r] + low[i][j][r];
+        bad |= (__builtin_bit_cast(unsigned, sum) & 0x7f800000u) == 0x7f800000u;
+        acc[i][j][r] = sum * kUnscale;
       }
   if (bad) redo = 1;
   __syncthreads();

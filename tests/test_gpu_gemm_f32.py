@@ -150,6 +150,72 @@ def test_split_products_of_tiny_and_huge_elements(rows, d, f, scale):
         assert n == 0 or float((h[s].double() - ref).norm()) < float(tol), (e, float((h[s].double() - ref).norm()), float(tol))
 
 
+# rows of 8 experts whose forward, input-gradient and weight-gradient products take 128 x 128 tiles of the split kernel
+LARGE = ([240, 255, 245, 260, 262, 238, 240, 260], 1024, 2816)
+
+
+@pytest.mark.parametrize("rows,d,f", SPLIT[:2] + [LARGE])
+def test_tiny_rows_leave_the_others_alone(rows, d, f):
+    """What a row holds does not change how the rows of its tile are computed: the same bits beside it."""
+    xp, dyp, w1, w2 = inputs_f32(rows, d, f)
+    ref = ffn_f32(rows, d, f, xp, dyp, w1, w2)
+    touched = torch.arange(0, sum(rows), 37, device=DEV)
+    xp[touched] *= 2.0 ** -115
+    dyp[touched] *= 2.0 ** -115
+    got = ffn_f32(rows, d, f, xp, dyp, w1, w2)
+    rest = torch.ones(sum(rows), dtype=torch.bool, device=DEV)
+    rest[touched] = False
+    for name, i in (("h", 0), ("yp", 1), ("d_xp", 2)):
+        assert torch.equal(got[i][rest], ref[i][rest]), name
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -60, 2.0 ** -70, 2.0 ** -90, 2.0 ** -110, 2.0 ** -126, 2.0 ** -140])
+@pytest.mark.parametrize("rows,d,f", SPLIT[:2] + [LARGE])
+def test_split_products_of_mixed_magnitudes(rows, d, f, scale):
+    """Rows (in the weight gradient columns) of ordinary and of tiny elements in one tile, each judged by its own size; 2^-149 and half
+    of it are what subnormal elements and sums leave."""
+    xp, dyp, w1, w2 = inputs_f32(rows, d, f)
+    a = torch.randn(sum(rows), f, generator=torch.Generator(device=DEV).manual_seed(9), device=DEV)
+    small = torch.arange(sum(rows), device=DEV) % 16 > 5
+    xs, ys = xp.clone(), dyp.clone()
+    xs[small] *= scale
+    ys[small] *= scale
+    a[:, torch.arange(f, device=DEV) % 16 > 5] *= scale
+    h, _, _, _, dw2 = ffn_f32(rows, d, f, xs, dyp, w1, w2, a_override=a)
+    _, _, dxp, _, _ = ffn_f32(rows, d, f, xp, ys, w1, w2)
+    h0 = ffn_f32(rows, d, f, xp, ys, w1, w2)[0]
+    at = 0
+    for e, n in enumerate(rows):
+        s, at = slice(at, at + n), at + n
+        if n == 0:
+            continue
+        w1e, w2e, G, U = w1[e].double(), w2[e].double(), h0[s, :f].double(), h0[s, f:].double()
+        sg, dA = torch.sigmoid(G), ys[s].double() @ w2e
+        dX = torch.cat([dA * U * sg * (1 + G * (1 - sg)), dA * G * sg], 1) @ w1e
+        for name, got, ref, K in (("h", h[s], xs[s].double() @ w1e.t(), d), ("d_xp", dxp[s], dX, 2 * f), ("d_w2", dw2[e], dyp[s].double().t() @ a[s].double(), n)):
+            size, out = (ref.norm(dim=1), (got.double() - ref).norm(dim=1)) if name != "d_w2" else (ref.norm(dim=0), (got.double() - ref).norm(dim=0))
+            # d_xp: three products in a row, whose operands are rounded to 2^-149 as well
+            tol = 3 * 3 * math.sqrt(K) * 2.0 ** -24 * size + 3 * math.sqrt(K * (ref.numel() // size.numel())) * 2.0 ** -149
+            assert (out <= tol).all(), (name, e, float((out / tol).max()))
+
+
+@pytest.mark.parametrize("rows,d,f", SPLIT[:2] + [LARGE])
+@pytest.mark.parametrize("ex,ew", [(-70, -70), (-60, -70), (-20, -120), (10, -140), (-149, 100)])
+def test_split_products_below_the_normal_range(rows, d, f, ex, ew):
+    """Ordinary elements whose products are subnormal numbers, subnormal elements whose products are not."""
+    xp, dyp, w1, w2 = inputs_f32(rows, d, f)
+    xp, w1 = xp * 2.0 ** (ex / 2) * 2.0 ** (ex / 2), w1 * 2.0 ** (ew / 2) * 2.0 ** (ew / 2)
+    h = ffn_f32(rows, d, f, xp, dyp, w1, w2)[0]
+    at = 0
+    for e, n in enumerate(rows):
+        s, at = slice(at, at + n), at + n
+        ref = xp[s].double() @ w1[e].double().t()
+        # every element to half a unit in the last place of its own sum's terms, and to a unit of 2^-149 for each rounding
+        tol = 3 * math.sqrt(d) * 2.0 ** -24 * ref.norm() + math.sqrt(d * ref.numel()) * 2.0 ** -149
+        assert n == 0 or float((h[s].double() - ref).norm()) <= float(tol), (e, float((h[s].double() - ref).norm()), float(tol))
+        assert n == 0 or ew < -130 or h[s].any()
+
+
 def test_split_products_of_infinities_and_nan():
     rows, d, f = SPLIT[0]
     xp, dyp, w1, w2 = inputs_f32(rows, d, f)
