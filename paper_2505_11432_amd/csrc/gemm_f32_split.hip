@@ -227,6 +227,7 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_f32_split_kernel(GemmPro
   }
   __syncthreads();
   // Parts or sums that overflowed (they give infinities or NaN in every output they reach): the tile is made again with the fp32 instruction.
+  // With such an element in every tile FC1 as above takes 417 us, dgrad1 503 (488 and 557 with loads not ahead; gemm_f32.hip 252 and 268).
   bool bad = false;
 #pragma unroll
   for (int i = 0; i < FM; ++i)
@@ -241,14 +242,14 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_f32_split_kernel(GemmPro
   if (bad) redo = 1;
   __syncthreads();
   if (redo) {
-    float* at = reinterpret_cast<float*>(lds);
-    float* bt = at + BM * 36;
+    // as the split: step s in one buffer, steps s + 1 and s + 2 on their way into registers
     clear();
-    for (int s = 0; s < steps; ++s) {
-      load(0, s);
-      __syncthreads();
-      a.stash(va[0], at);
-      b.stash(vb[0], bt);
+    auto exact = [&](int set, int s) __attribute__((always_inline)) {
+      float* at = reinterpret_cast<float*>(lds + set * STAGE);
+      float* bt = at + BM * 36;
+      a.stash(va[set], at);
+      b.stash(vb[set], bt);
+      load(set, s + 2);
       __syncthreads();
 #pragma unroll
       for (int h = 0; h < 2; ++h)
@@ -262,6 +263,12 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_f32_split_kernel(GemmPro
             for (int r = 0; r < 4; ++r) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[r], fa[r], acc[i][j], 0, 0, 0);
           }
         }
+    };
+    load(0, 0);
+    load(1, 1);
+    for (int s = 0; s < steps; s += 2) {
+      exact(0, s);
+      if (s + 1 < steps) exact(1, s + 1);
     }
   }
   // a lane holds row lane % 16 and columns 4 * (lane / 16) + 0..3 of every 16 x 16 block

@@ -169,11 +169,11 @@ def test_tiny_rows_leave_the_others_alone(rows, d, f):
         assert torch.equal(got[i][rest], ref[i][rest]), name
 
 
-@pytest.mark.parametrize("scale", [2.0 ** -60, 2.0 ** -70, 2.0 ** -90, 2.0 ** -110, 2.0 ** -126, 2.0 ** -140])
+@pytest.mark.parametrize("scale", [2.0 ** -60, 2.0 ** -70, 2.0 ** -90, 2.0 ** -110, 2.0 ** -126, 2.0 ** -140, 2.0 ** 100])
 @pytest.mark.parametrize("rows,d,f", SPLIT[:2] + [LARGE])
 def test_split_products_of_mixed_magnitudes(rows, d, f, scale):
-    """Rows (in the weight gradient columns) of ordinary and of tiny elements in one tile, each judged by its own size; 2^-149 and half
-    of it are what subnormal elements and sums leave."""
+    """Rows (in the weight gradient columns) of ordinary and of tiny or huge elements in one tile, each judged by its own size; 2^-149 and
+    half of it are what subnormal elements and sums leave.  2^100: every tile goes back to the fp32 instruction."""
     xp, dyp, w1, w2 = inputs_f32(rows, d, f)
     a = torch.randn(sum(rows), f, generator=torch.Generator(device=DEV).manual_seed(9), device=DEV)
     small = torch.arange(sum(rows), device=DEV) % 16 > 5
