@@ -84,7 +84,7 @@ int launch(const Args& a, long tiles_upper_bound, hipStream_t s) {
   if (rc != MOE_OK) return rc;
   auto kern = Setup::kernel();
   constexpr int smem = Setup::smem;
-  if constexpr (2 * smem <= 160 * 1024) blocks *= 2;       // two workgroups share a CU's LDS
+  if constexpr (dma_in_pairs<BM, BN, BKT, NS, WM * WN, LA, LB, (int)sizeof(TIN)>()) blocks *= 2;
   Args args = a;
   constexpr bool kSplitK = MODE == ROWSEG && EPI == EPI_STORE && sizeof(TC) == 2;
   if (!kSplitK || args.accumulate || blocks > MOE_SPLITK_MAX_PARTS) args.splitk_ws = nullptr;

@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "gemm_mfma.h"
+#include "row_plan.h"
 
 namespace moe {
 namespace mfma {
@@ -351,6 +352,17 @@ __global__ void __launch_bounds__(256) splitk_fixup_kernel(const float* __restri
   }
 }
 
+template <int BM, int BN, int BKT, int NSTAGE, int NW, Layout LA, Layout LB, int ESZ = 2>
+constexpr int dma_smem_bytes() {
+  // the ring, the per-expert tile table and one epilogue patch per wave
+  return NSTAGE * (DmaTileBytes<LA, BM, BKT, ESZ>::value + DmaTileBytes<LB, BN, BKT, ESZ>::value) + (MOE_MAX_EXPERTS + 8) * 4 +
+         NW * STG_BYTES + 256 + 1024;       // + the dump area of the L2 touches + the block-scale ring
+}
+
+// Two workgroups of such a kernel share a CU's LDS; the launch makes twice the workgroups.
+template <int BM, int BN, int BKT, int NSTAGE, int NW, Layout LA, Layout LB, int ESZ = 2>
+constexpr bool dma_in_pairs() { return 2 * dma_smem_bytes<BM, BN, BKT, NSTAGE, NW, LA, LB, ESZ>() <= 160 * 1024; }
+
 template <int BM, int BN, int BKT, int NSTAGE, int WM, int WN, Layout LA, Layout LB, Mode MODE, Epi EPI, typename TC,
           typename TIN = bf16>   // TIN = uint8_t: e4m3 codes, K-major operands only
 __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args p) {
@@ -362,6 +374,7 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
   constexpr bool FP8 = ESZ == 1;
   constexpr int CHUNK = 16 / ESZ;                     // elements per 16-byte chunk
   static_assert(!FP8 || (LA == KMAJOR && LB == KMAJOR), "e4m3 operands are K-major");
+  constexpr bool PAIR = dma_in_pairs<BM, BN, BKT, NSTAGE, NW, LA, LB, ESZ>();
   constexpr bool BSCALE = FP8 && MODE == KSEG;        // block-scaled contraction over tokens (weight gradients)
   static_assert(!BSCALE || (BKT == 128 && NSTAGE == 2), "one 128-token scale group per k-step; scale loads rely on the vmcnt(0) wait");
   constexpr int A_BYTES = DmaTileBytes<LA, BM, BKT, ESZ>::value, B_BYTES = DmaTileBytes<LB, BN, BKT, ESZ>::value;
@@ -498,9 +511,8 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
 
   // Decode slot -> tile and set up this lane's source pointers.  Returns false when the list is exhausted.
   auto open_tile = [&](int sl) __attribute__((always_inline)) -> bool {
-    // the last, partly filled round is dealt evenly: eight XCDs with a few tiles each, not two with all of them
     const int first = sl * XCDS * window;
-    const int w = min(window, (total_items - first + XCDS - 1) / XCDS);
+    const int w = tiles_per_xcd(total_items, total_items - first, window, PAIR);
     int l = first + xcd * w + in_window;
     if (in_window >= w || l >= total_items) return false;
     int part = 0;
@@ -1187,13 +1199,6 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
     }
     if (!has_next) break;
   }
-}
-
-template <int BM, int BN, int BKT, int NSTAGE, int NW, Layout LA, Layout LB, int ESZ = 2>
-constexpr int dma_smem_bytes() {
-  // the ring, the per-expert tile table and one epilogue patch per wave
-  return NSTAGE * (DmaTileBytes<LA, BM, BKT, ESZ>::value + DmaTileBytes<LB, BN, BKT, ESZ>::value) + (MOE_MAX_EXPERTS + 8) * 4 +
-         NW * STG_BYTES + 256 + 1024;       // + the dump area of the L2 touches + the block-scale ring
 }
 
 }  // namespace mfma

@@ -98,6 +98,18 @@ inline RowPlan plan_rows(RowKind kind, int M, int E, int N, int K, int esz) {
   return mid_us < full_us ? RowPlan{RowTile::MID, split_mid} : RowPlan{RowTile::FULL, split_full};
 }
 
+// How a launch's last round is dealt.  The tile list goes to the eight XCDs in windows, one tile per CU; `left` of its `items` tiles are
+// still to come, and every XCD gets so many consecutive ones.  A partly filled round as whole windows keeps some XCDs idle, and an
+// XCD alone reaches 1.3 of the chip's 6 TB/s; dealt evenly, neighbouring tiles land on different XCDs and no longer share panels in an L2.
+// The first counts where the last round is much of the launch, up to three rounds (of pairs four), the second in longer lists.
+// Measured (us, whole windows and evenly; rounds): weight gradients of 8 experts, 250 rows, 1024 x 2816 1.4 37.1, 29.1, 2.8 55.6, 52.1; of 24
+// experts, 100 rows, 3072 x 2400 11.3 152.4, 157.2, 22.5 294.7, 299.6; of 32 experts, Zipf 0.8, 2944 x 2192 13.5 185.5, 191.9; SwiGLU' of
+// 12 experts, 3072 x 4096 0.75 97.1, 90.9, of 32, Zipf 1.2 3.1 143.0, 146.1; FC1 in pairs 2.3 262, 247, 3.8 179.7, 175.3.
+constexpr int tiles_per_xcd(int items, int left, int window, bool pair) {
+  const int even = (left + 7) / 8;
+  return items < (pair ? 4 : 3) * 8 * window && even < window ? even : window;
+}
+
 // The weight gradients on 128 x 128 tiles, two workgroups per CU, instead of 256 x 256: where the large tile leaves CUs idle in
 // its last (or only) round.  A segment is taken as the average one.  Measured, d_w2 / d_w1 (us, 256 x 256 and pairs):
 //   8 experts, 512 rows, 512 x 512 20.2/21.4, 11.0/12.5;  250 rows, 1024 x 2816 29.6/57.4, 32.2/64.4;

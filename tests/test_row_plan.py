@@ -89,3 +89,44 @@ def test_pairs_of_workgroups(tmp_path):
              (512, 8, 4096, 14336): "0 0 0 0", (16384, 8, 4096, 14336): "0 0 0 0", (131072, 64, 2048, 1408): "0 0 0 0", (0, 8, 16, 16): "0 0 1 1"}
     out = subprocess.run([str(tmp_path / "m")], input="\n".join(" ".join(map(str, k)) for k in sizes), capture_output=True, text=True, check=True)
     assert out.stdout.split("\n")[:-1] == list(sizes.values())
+
+
+DEAL = r'''
+#include <cstdio>
+#include "row_plan.h"
+int main() {
+  int items, window, pair;
+  while (scanf("%d %d %d", &items, &window, &pair) == 3) {
+    long n = 0, sum = 0;
+    int last = 0;
+    for (int first = 0; first < items; first += 8 * window) {
+      last = moe::tiles_per_xcd(items, items - first, window, pair != 0);
+      for (int xcd = 0; xcd < 8; ++xcd)
+        for (int i = 0; i < window; ++i) {
+          const int l = first + xcd * last + i;
+          if (i < last && l < items) { ++n; sum += l; }
+        }
+    }
+    printf("%d %d %d\n", last, (int)(n == items && sum == (long)items * (items - 1) / 2), last <= window);
+  }
+}
+'''
+
+
+def test_last_round_is_dealt_evenly_in_short_lists(tmp_path):
+    """Every tile once, whatever the count; an eighth of the last round to every XCD up to three rounds (pairs of workgroups: four), whole
+    windows in longer lists."""
+    (tmp_path / "m.cpp").write_text(DEAL)
+    subprocess.run([build.CXX, "-std=c++17", "-I", build.CSRC, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
+    cases = [(n, w, p) for w in (1, 4, 32, 64) for p in (0, 1) for n in [*range(1, 40), *range(8 * w - 9, 8 * w + 10), *range(24 * w - 9, 24 * w + 10), *range(32 * w - 9, 32 * w + 10)] if n > 0]
+    out = subprocess.run([str(tmp_path / "m")], input="\n".join("%d %d %d" % c for c in cases), capture_output=True, text=True, check=True)
+    got = [tuple(map(int, l.split())) for l in out.stdout.split("\n") if l]
+    assert len(got) == len(cases)
+    for (n, w, p), (last, each, fits) in zip(cases, got):
+        assert each and fits, (n, w, p)
+        left = n % (8 * w) or 8 * w
+        assert last == (-(-left // 8) if n < (4 if p else 3) * 8 * w else w), (n, w, p, last)
+    # 8 experts, 1024 x 2816: d_w2, d_w1; weight gradients of 24 experts, 3072 x 2400; FC1 of 19 row tiles in pairs
+    sizes = [(352, 32, 0, 12), (704, 32, 0, 24), (2880, 32, 0, 32), (5760, 32, 0, 32), (836, 64, 1, 41)]
+    out = subprocess.run([str(tmp_path / "m")], input="\n".join("%d %d %d" % c[:3] for c in sizes), capture_output=True, text=True, check=True)
+    assert [int(l.split()[0]) for l in out.stdout.split("\n") if l] == [c[3] for c in sizes]
