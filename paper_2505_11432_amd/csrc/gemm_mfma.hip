@@ -116,6 +116,8 @@ int launch_rowseg(Args a, hipStream_t s) {
     case RowTile::FEW: return launch<64, 128, 2 * B128, 3, 2, 2, KMAJOR, LB, ROWSEG, EPI, bf16, TIN>(a, 1, s);
     case RowTile::MID:
       if constexpr (EPI != EPI_STORE) {
+        // the rule's times are those of two workgroups per CU (pairs_us)
+        static_assert(dma_in_pairs<128, 128, B128, 2, 4, KMAJOR, LB, (int)sizeof(TIN)>(), "a pair fits a CU's LDS");
         if (plan.pair) return launch<128, 128, B128, 2, 2, 2, KMAJOR, LB, ROWSEG, EPI, bf16, TIN>(a, 1, s);
       }
       return launch<128, 128, B128, 3, 4, 2, KMAJOR, LB, ROWSEG, EPI, bf16, TIN>(a, 1, s);
@@ -210,6 +212,7 @@ int mfma_wgrad(const void* P, const void* Q, const int32_t* offsets, int rows, i
   a.accumulate = accumulate;
   const long blocks = (long)E * cdiv(Mo, 256) * cdiv(N, 256);
   if (wgrad_in_pairs(rows, E, Mo, N)) {
+    static_assert(dma_in_pairs<128, 128, 64, 2, 4, MNMAJOR, MNMAJOR>(), "a pair fits a CU's LDS");
     if (c_dt == MOE_F32) return launch<128, 128, 64, 2, 2, 2, MNMAJOR, MNMAJOR, KSEG, EPI_STORE, float>(a, blocks, s);
     return launch<128, 128, 64, 2, 2, 2, MNMAJOR, MNMAJOR, KSEG, EPI_STORE, bf16>(a, blocks, s);
   }

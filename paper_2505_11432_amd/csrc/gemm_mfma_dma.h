@@ -411,7 +411,10 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
   static_assert(!SWI || TN % 2 == 0, "SwiGLU pairs gate/up MFMA tiles inside a wave");
   static_assert(NW <= 8, "LDS is budgeted for at most 8 epilogue patches");
 
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+  // Fragments, chunks and sub-steps are told apart by flipping bits below 256 of an address (read_frag_dma, read_frag_fp8), so tiles
+  // begin at multiples of 256 bytes.
+  extern __shared__ __attribute__((aligned(256))) char smem[];
+  static_assert(A_BYTES % 256 == 0 && STAGE_BYTES % 256 == 0, "every tile of the ring begins at a multiple of 256 bytes");
   const unsigned smem_lds = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
   int* cum_tiles = reinterpret_cast<int*>(smem + RING_BYTES);          // [E+1] running count of m-tiles (ROWSEG)
   constexpr int TABLE_BYTES = (MOE_MAX_EXPERTS + 8) * 4;
