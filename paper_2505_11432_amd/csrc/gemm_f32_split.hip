@@ -22,6 +22,7 @@
 #include <atomic>
 
 #include "gemm_f32_tiles.h"
+#include "row_plan.h"
 
 namespace moe {
 namespace {
@@ -32,7 +33,7 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 
-constexpr int kStep = 32;                // contraction per step
+constexpr int kStep = kF32SplitStep;     // contraction per step
 // Contractions of so few terms (weight gradients of one or two rows) are left to the fp32 instruction: the three products left out and
 // the sum of two accumulators round more than it does on them.  Against float64 in units of 2^-24, the fp32 instruction and the split: one term
 // rms 0.43, 0.44, largest 1.0, 1.56; two 0.52, 0.44, 1.88, 2.26; three 0.60, 0.44, 2.55, 2.36; four 0.66, 0.45, 2.86, 2.25; 1024 4.9, 3.1.
@@ -304,34 +305,19 @@ int launch(const GemmProblem& p, hipStream_t s) {
   return launch_as<BM, BN, WM, WN, false, false>(p, s);
 }
 
-// Tiles of 64 x 64 (three workgroups per CU) that the average segment makes
-double tiles64(const GemmProblem& p) {
-  return (double)cdiv(p.N, 64) * (p.mode == 0 ? cdiv(p.M, 64) + p.E / 2 : (double)cdiv(p.M, 64) * p.E);
-}
-
 }  // namespace
 
-// Where the split is the faster way: from 192 tiles of 64 x 64 on (us, fp32 instruction and split: 216 tiles, K = 768 21.6, 18.2; 256,
-// K = 512 16.8, 13.9; 160, K = 1024 19.0, 25.2; 128, K = 2816 28, 52: few tiles are one chain of steps per CU, which the 32 x 32 tiles of the
-// fp32 kernel shorten), and for weight gradients of segments longer than one step (1536 tiles of 50 rows 15.8, 16.0; 11264 of 250
-// 231, 192; 11264 of 25 58, 67).
+// Operands that the kernel can take, where it is the faster way.
 bool gemm_f32_splits(const GemmProblem& p) {
   if (p.mode == 2 || p.bias || !aligned16(p.C) || p.N % 4 || p.ldc % 4 || p.c_es % 4) return false;
   const long lda = p.a_cs == 1 ? p.a_rs : p.a_cs, ldb = p.b_rs == 1 ? p.b_cs : p.b_rs;
   if (lda >= 1 << 20 || ldb >= 1 << 20) return false;                   // 128 rows of a tile span less than kSpan
   if (f32_blocks(p, 64, 64) * 256 >= 1L << 31) return false;            // a launch holds less than 2^32 threads
-  return tiles64(p) >= 192 && (p.mode == 0 || p.K > kStep * p.E);
+  return f32_split_pays({p.mode == 0, p.M, p.N, p.K, p.E});
 }
 
-// 64 x 64 or 128 x 128 tiles (one workgroup of eight waves per CU, which splits an element half as often), by the estimated time from
-// measured tiles: 64 x 64 0.85 us + 0.445 per step and CU, 128 x 128 3.5 + 1.33 in whole rounds.  (us, 64 and 128) weight gradients of 2000
-// rows, 8 experts, 1024 x 5632 192, 171, of 6 experts, 5632 x 128 45, 58; dgrad2 102, 94; FC2 109, 110, of 4500 rows, 4 experts 183, 223.
-// Segments of under four steps stay with the small tile (2816 tiles of three steps 32, 36).
 int launch_gemm_f32_split(const GemmProblem& p, hipStream_t s) {
-  const int steps = cdiv(p.mode == 0 ? p.K : p.K / p.E, kStep);
-  const double tiles128 = cdiv(p.N, 128) * (p.mode == 0 ? p.M / 128.0 + p.E / 2 : (double)cdiv(p.M, 128) * p.E);
-  const long rounds = ((long)tiles128 + 255) / 256;
-  if (steps >= 4 && rounds * (3.5 + 1.33 * steps) < tiles64(p) / 256 * (0.85 + 0.445 * steps)) {
+  if (f32_split_in_128({p.mode == 0, p.M, p.N, p.K, p.E})) {
     const int rc = gemm_f32_split_configure();
     return rc != MOE_OK ? rc : launch<128, 128, 4, 2>(p, s);
   }

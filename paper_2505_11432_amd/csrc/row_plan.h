@@ -1,4 +1,5 @@
-// Tile of the row-segmented grouped GEMMs (host code without HIP: the choice is a function of sizes).
+// Tile of the row-segmented grouped GEMMs, dealing of tiles, kernel and tile of the fp32 products (code without HIP: the choices are functions
+// of sizes).
 //
 // The host knows the bound M on the rows and E, not the segments (any segments are correct with any tile), so the choice goes
 // by the average: max(E, M / rows-of-a-tile + E / 2) row tiles.
@@ -120,6 +121,34 @@ inline bool wgrad_in_pairs(int rows, int E, int M, int N) {
   const double large = (double)E * up(M, 256) * up(N, 256), small = (double)E * up(M, 128) * up(N, 128);
   const double rounds = (double)up((long)large, 256);
   return pairs_us(small, {11, 0.75, 6, 0.8}, steps) < rounds * (9.5 + 1.5 * steps) + 6.5 * large / 256;
+}
+
+// ---- fp32 expert products (gemm_f32_split.hip): the split into bf16 parts or the fp32 instruction, 64 x 64 or 128 x 128 tiles.
+constexpr int kF32SplitStep = 32;        // contraction per step
+struct F32Product { bool rows; int M, N, K, E; };      // rows: the segments lie along M (forward, dgrad), else along K (weight gradients)
+
+// Tiles of 64 x 64 (three workgroups per CU) that the average segment makes
+inline double f32_tiles64(const F32Product& p) {
+  auto up = [](long a, long b) { return (a + b - 1) / b; };
+  return (double)up(p.N, 64) * (p.rows ? up(p.M, 64) + p.E / 2 : (double)up(p.M, 64) * p.E);
+}
+
+// Where the split is the faster way: from 192 tiles of 64 x 64 on (us, fp32 instruction and split: 216 tiles, K = 768 21.6, 18.2; 256,
+// K = 512 16.8, 13.9; 160, K = 1024 19.0, 25.2; 128, K = 2816 28, 52: few tiles are one chain of steps per CU, which the 32 x 32 tiles of the
+// fp32 kernel shorten), and for weight gradients of segments longer than one step (1536 tiles of 50 rows 15.8, 16.0; 11264 of 250
+// 231, 192; 11264 of 25 58, 67).
+inline bool f32_split_pays(const F32Product& p) { return f32_tiles64(p) >= 192 && (p.rows || p.K > (long)kF32SplitStep * p.E); }
+
+// 128 x 128 tiles (one workgroup of eight waves per CU, which splits an element half as often), by the estimated time from
+// measured tiles: 64 x 64 0.85 us + 0.445 per step and CU, 128 x 128 3.5 + 1.33 in whole rounds.  (us, 64 and 128) weight gradients of 2000
+// rows, 8 experts, 1024 x 5632 192, 171, of 6 experts, 5632 x 128 45, 58; dgrad2 102, 94; FC2 109, 110, of 4500 rows, 4 experts 183, 223.
+// Segments of under four steps stay with the small tile (2816 tiles of three steps 32, 36).
+inline bool f32_split_in_128(const F32Product& p) {
+  auto up = [](long a, long b) { return (a + b - 1) / b; };
+  const int steps = (int)up(p.rows ? p.K : p.K / p.E, kF32SplitStep);
+  const double tiles = up(p.N, 128) * (p.rows ? p.M / 128.0 + p.E / 2 : (double)up(p.M, 128) * p.E);
+  const long rounds = ((long)tiles + 255) / 256;
+  return steps >= 4 && rounds * (3.5 + 1.33 * steps) < f32_tiles64(p) / 256 * (0.85 + 0.445 * steps);
 }
 
 }  // namespace moe

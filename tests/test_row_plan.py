@@ -86,7 +86,8 @@ def test_pairs_of_workgroups(tmp_path):
     (tmp_path / "m.cpp").write_text(PAIRS)
     subprocess.run([build.CXX, "-std=c++17", "-I", build.CSRC, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
     sizes = {(4593, 24, 1040, 1424): "1 0 0 0", (2000, 8, 1024, 2816): "1 1 0 0", (4096, 8, 512, 512): "1 0 1 1", (6000, 8, 1024, 1024): "0 1 1 0",
-             (512, 8, 4096, 14336): "0 0 0 0", (16384, 8, 4096, 14336): "0 0 0 0", (131072, 64, 2048, 1408): "0 0 0 0", (0, 8, 16, 16): "0 0 1 1"}
+             (512, 8, 4096, 14336): "0 0 0 0", (16384, 8, 4096, 14336): "0 0 0 0", (131072, 64, 2048, 1408): "0 0 0 0", (0, 8, 16, 16): "0 0 1 1",
+             (1222, 6, 272, 336): "1 0 1 1", (4096, 16, 1024, 1024): "1 1 0 0"}
     out = subprocess.run([str(tmp_path / "m")], input="\n".join(" ".join(map(str, k)) for k in sizes), capture_output=True, text=True, check=True)
     assert out.stdout.split("\n")[:-1] == list(sizes.values())
 
@@ -130,3 +131,30 @@ def test_last_round_is_dealt_evenly_in_short_lists(tmp_path):
     sizes = [(352, 32, 0, 12), (704, 32, 0, 24), (2880, 32, 0, 32), (5760, 32, 0, 32), (836, 64, 1, 41)]
     out = subprocess.run([str(tmp_path / "m")], input="\n".join("%d %d %d" % c[:3] for c in sizes), capture_output=True, text=True, check=True)
     assert [int(l.split()[0]) for l in out.stdout.split("\n") if l] == [c[3] for c in sizes]
+
+
+F32 = r'''
+#include <cstdio>
+#include "row_plan.h"
+int main() {
+  int M, E, d, f;
+  while (scanf("%d %d %d %d", &M, &E, &d, &f) == 4) {
+    const moe::F32Product p[] = {{true, M, 2 * f, d, E}, {true, M, d, f, E}, {true, M, f, d, E}, {true, M, d, 2 * f, E}, {false, d, f, M, E}, {false, 2 * f, d, M, E}};
+    for (const auto& q : p) printf("%s ", !moe::f32_split_pays(q) ? "-" : moe::f32_split_in_128(q) ? "128" : "64");
+    printf("\n");
+  }
+}
+'''
+
+
+def test_fp32_products(tmp_path):
+    """FC1, FC2, dgrad2, dgrad1, d_w2, d_w1: the fp32 instruction (-) or the split on one of its tiles, at the sizes of the fp32 GEMM tests
+    (which rely on each tile being taken in each layout) and at small ones."""
+    (tmp_path / "m.cpp").write_text(F32)
+    subprocess.run([build.CXX, "-std=c++17", "-I", build.CSRC, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
+    sizes = {(2000, 8, 1024, 2816): "128 64 128 64 128 128", (2060, 4, 1024, 1408): "64 64 64 64 64 128", (894, 5, 272, 1040): "64 - 64 - 64 64",
+             (1200, 30, 48, 528): "64 - 64 - 64 64", (1027, 1, 1552, 784): "64 64 64 64 64 64", (512, 8, 128, 256): "- - - - - -",
+             (160, 8, 256, 512): "- - - - - -", (199, 8, 512, 1408): "64 - - - - -"}
+    out = subprocess.run([str(tmp_path / "m")], input="\n".join(" ".join(map(str, k)) for k in sizes), capture_output=True, text=True, check=True)
+    got = [l.strip() for l in out.stdout.split("\n") if l]
+    assert got == list(sizes.values()), list(zip(sizes, got))
