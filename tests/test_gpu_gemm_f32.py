@@ -8,14 +8,16 @@ from tests.gpu_util import DEV
 
 pytestmark = pytest.mark.gpu
 
-# rows per expert, d, f: segments around the 32- and 64-row tiles, widths with 16-column tails, and sizes that reach the
-# 64 x 32 and 64 x 64 tiles (from 256 and 1024 tiles on)
+# rows per expert, d, f: segments around the 32- and 64-row tiles, widths with 16-column tails; weight gradients of few rows per expert on
+# 64 x 32 (from 256 tiles of 64 x 64 on) and 64 x 64 tiles (d_w2 and d_w1 of the last, from 1024 on); the fourth takes the split products
 CASES = [
     ([1, 31, 0, 32], 16, 48),
     ([33, 63, 64, 65], 144, 80),
     ([0, 0, 129, 0], 48, 272),
     ([500, 511, 0, 1049], 272, 2000),
     ([3] * 70, 64, 32),                    # more segments than lanes in a wave
+    ([20, 32, 0, 33, 7, 31, 17, 20], 256, 512),
+    ([20, 25, 31, 0, 40, 25, 30, 28], 512, 1408),
 ]
 
 
@@ -64,14 +66,16 @@ def test_ffn_f32_tile_edges(rows, d, f):
     assert rel(dw2, before2.double() + DW2) < tol
 
 
-# rows, E, d, f: both tiles of the split products (64 x 64, from 192 tiles on; 128 x 128), their edges, k tails of 16, odd and even
-# numbers of steps, a segment of one row, an empty one, segments of a few rows
+# rows, d, f: split products on 64 x 64 tiles (d_w1 of the second on 128 x 128; which product takes which is pinned in test_row_plan.py), edges
+# of tiles, k tails of 16, odd and even numbers of steps, a segment of one row, an empty one, segments of a few rows
 SPLIT = [
     ([1, 0, 700, 130, 63], 272, 1040),
     ([500, 511, 0, 1049], 1024, 1408),
     ([40] * 30, 48, 528),
     ([1027], 1552, 784),
 ]
+# 128 x 128 tiles in FC1, dgrad2 and both weight gradients
+LARGE = ([240, 255, 245, 260, 262, 238, 240, 260], 1024, 2816)
 
 
 def ffn_f32(rows, d, f, xp, dyp, w1, w2, a_override=None):
@@ -93,10 +97,11 @@ def inputs_f32(rows, d, f):
     return rnd(M, d), rnd(M, d), rnd(E, 2 * f, d) / math.sqrt(d), rnd(E, d, f) / math.sqrt(f)
 
 
-@pytest.mark.parametrize("rows,d,f", SPLIT)
+@pytest.mark.parametrize("rows,d,f", SPLIT + [LARGE])
 def test_split_products_are_as_close_as_fp32(rows, d, f):
     """Every product against float64, on the operands that the library itself made: within what an fp32 sum of K terms that is rounded
-    every second term loses (sqrt(K / 2) roundings of random sign, 2^-24 at most and 0.58 of that each in the mean square)."""
+    every second term loses (sqrt(K / 2) roundings of random sign, 2^-24 at most and 0.58 of that each in the mean square).  Sums of one
+    and two terms have a test of their own below: here the operands' own roundings cover them."""
     xp, dyp, w1, w2 = inputs_f32(rows, d, f)
     h, yp, dxp, dw1, dw2 = ffn_f32(rows, d, f, xp, dyp, w1, w2)
     at = 0
@@ -115,6 +120,20 @@ def test_split_products_are_as_close_as_fp32(rows, d, f):
                                   ("d_w1", dw1[e], dH.t() @ X, n), ("d_w2", dw2[e], DY.t() @ A, n)):
             tol = (0.58 * math.sqrt(K / 2) + 4) * 2.0 ** -24
             assert rel(got, ref) < tol, (name, e, rel(got, ref), tol)
+
+
+@pytest.mark.parametrize("rows,d,f", [SPLIT[1], LARGE])
+def test_split_weight_gradients_accumulate(rows, d, f):
+    """accumulate = 1 adds the product, the same bits as without it, to what is there."""
+    xp, dyp, w1, w2 = inputs_f32(rows, d, f)
+    from paper_2505_11432_amd import binding as B
+    h, _, dxp, dw1, dw2 = ffn_f32(rows, d, f, xp, dyp, w1, w2)
+    offsets = torch.tensor([sum(rows[:e]) for e in range(len(rows) + 1)], dtype=torch.int32, device=DEV)
+    ws = torch.empty(B.moe_workspace_bytes(sum(rows), d, len(rows), 1, f, B.F32), dtype=torch.uint8, device=DEV)
+    a1, a2 = torch.randn_like(dw1), torch.randn_like(dw2)
+    r1, r2 = a1 + dw1, a2 + dw2
+    B.moe_expert_ffn_bwd(xp, h, dyp, None, offsets, w1, w2, dxp, a1, a2, 1, ws)
+    assert torch.equal(a1, r1) and torch.equal(a2, r2)
 
 
 def test_weight_gradients_of_one_and_two_rows_round_as_fp32():
@@ -148,10 +167,6 @@ def test_split_products_of_tiny_and_huge_elements(rows, d, f, scale):
         ref = xp[s].double() @ w1[e].double().t()
         tol = 3 * math.sqrt(d) * 2.0 ** -24 * ref.norm() + math.sqrt(d * ref.numel()) * 2.0 ** -149
         assert n == 0 or float((h[s].double() - ref).norm()) < float(tol), (e, float((h[s].double() - ref).norm()), float(tol))
-
-
-# rows of 8 experts whose forward, input-gradient and weight-gradient products take 128 x 128 tiles of the split kernel
-LARGE = ([240, 255, 245, 260, 262, 238, 240, 260], 1024, 2816)
 
 
 @pytest.mark.parametrize("rows,d,f", SPLIT[:2] + [LARGE])
@@ -234,6 +249,34 @@ def test_split_products_of_infinities_and_nan():
         assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got[ref.isinf()], ref[ref.isinf()])
         fin = ref.isfinite()
         assert n == 0 or rel(got[fin], ref[fin]) < 3 * math.sqrt(d) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("rows,d,f", [SPLIT[0], LARGE])
+def test_split_products_of_infinities_and_nan_in_every_layout(rows, d, f):
+    """The other operand layouts (weights across their rows, weight gradients) on both tiles: what a row or column that holds no such
+    element gets is finite and as close as ever, also inside a tile that is made again."""
+    inf, nan = float("inf"), float("nan")
+    xp, dyp, w1, w2 = inputs_f32(rows, d, f)
+    a = torch.randn(sum(rows), f, generator=torch.Generator(device=DEV).manual_seed(3), device=DEV)
+    clean = ffn_f32(rows, d, f, xp, dyp, w1, w2, a_override=a)
+    bad, cols = torch.tensor([4, 70, 261, 703], device=DEV), torch.tensor([5, 130, 200, f - 1], device=DEV)
+    ys, ab = dyp.clone(), a.clone()
+    ys[bad, torch.tensor([0, 17, d - 1, 100], device=DEV)] = torch.tensor([inf, nan, -inf, nan], device=DEV)
+    ab[bad, cols] = torch.tensor([nan, inf, -inf, nan], device=DEV)
+    dxp = ffn_f32(rows, d, f, xp, ys, w1, w2)[2]
+    dw2 = ffn_f32(rows, d, f, xp, dyp, w1, w2, a_override=ab)[4]
+    good = torch.ones(sum(rows), dtype=torch.bool, device=DEV)
+    good[bad] = False
+    # two results of the same product, each off by at most what one product (d_xp: three in a row) may be
+    K = max(rows + [2 * f])
+    assert not dxp[bad].isfinite().any()
+    assert dxp[good].isfinite().all() and rel(dxp[good], clean[2][good].double()) < 2 * 3 * 3 * math.sqrt(K) * 2.0 ** -24
+    ok = torch.ones(f, dtype=torch.bool, device=DEV)
+    ok[cols] = False
+    assert dw2[:, :, ok].isfinite().all() and rel(dw2[:, :, ok], clean[4][:, :, ok].double()) < 2 * 3 * math.sqrt(max(rows)) * 2.0 ** -24
+    for r, c in zip(bad.tolist(), cols.tolist()):
+        e = next(i for i in range(len(rows)) if r < sum(rows[: i + 1]))
+        assert not dw2[e, :, c].isfinite().any(), (r, c)
 
 
 @pytest.mark.parametrize("T,d,E", [(1, 16, 1), (33, 260, 5), (1000, 1024, 64), (65, 4, 3), (50, 30, 4)])

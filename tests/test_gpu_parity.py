@@ -257,8 +257,9 @@ def test_layer_many_tiles_short_contraction(B, cfg):
     check_layer(cfg, inp, z, layer, TOL["bf16"])
 
 
-def test_layer_bf16_gradients_in_bf16_and_accumulate(B):
-    cfg = SMALL_BF16[0]
+# the first on 128 x 128 tiles of the weight-gradient kernel, the second on 256 x 256 (pinned in test_row_plan.py)
+@pytest.mark.parametrize("cfg", [SMALL_BF16[0], MANY_TILES_BF16[1]], ids=lambda c: c.name)
+def test_layer_bf16_gradients_in_bf16_and_accumulate(B, cfg):
     inp = make_inputs(cfg, seed=2)
     z = O.router_logits(inp["x"], inp["W_r"]).astype(np.float32)
     layer = run_layer(B, cfg, inp, z, grad_dtype=torch.bfloat16)
