@@ -10,8 +10,7 @@
 //   64 x 64, k-steps of 32;  64 x 32, two waves per output, k-steps of 32;  32 x 32, four per output, k-steps of 64.
 // All keep two k-steps of global loads in registers ahead of the LDS stage that is being multiplied; several workgroups
 // share a CU and hide each other's latency.
-// Measured (a vector-ALU kernel of 64 x 64 x 16 first): router logits of 1000 tokens 182 -> 13 us; 8 experts, 2000 rows,
-// d = 1024, f = 2816, FC2 601 -> 135 (97 TFLOP/s in FC1); 8192 x 4096 x 2048 in four experts 110 TFLOP/s.
+// Measured (a vector-ALU kernel of 64 x 64 x 16 first): router logits of 1000 tokens 182 -> 13 us.
 #include "gemm_f32_tiles.h"
 
 namespace moe {
@@ -199,11 +198,13 @@ bool gemm_f32_covers(const GemmProblem& p) {
 }
 
 // Which shape: smaller tiles read more per FLOP but spread a problem over more workgroups and shorten its serial chain of
-// k-steps.  Fewer 64 x 64 tiles than CUs: 32 x 32 (512 rows of 8 experts, N = 512, K = 1408: 21 us against 26 with
-// 64 x 32 and 36 with 64 x 64).  Up to four per CU the last round of tiles is what counts: 64 x 32 (560 tiles, K = 2816:
-// 135 us against 152).  Beyond that 64 x 64 where an operand is read across its rows (1408 tiles: 114 us against 127),
-// 64 x 32 still where both are read along k (2816 tiles: 238 us against 262), unless a launch could not hold its workgroups
-// (less than 2^32 threads).
+// k-steps.  Fewer 64 x 64 tiles than CUs: 32 x 32 (512 rows of 8 experts, N = 512, K = 1408: 21 us against 26 with 64 x 32 and 36 with
+// 64 x 64; router logits of 4000 tokens, 64 experts, d = 1024 14.5, 19.6, 25.8; of 15000 29.6, 29.9, 29.1).  Beyond that come router
+// logits (20000 tokens 38.7, 37.6, 41.9; 66000 111, 99, 98; 120000 201, 180, 168) and weight gradients of up to 32 rows per expert (8
+// experts, 20 rows, 256 x 512 6.9, 5.8, 4.5; 4 experts, 7 rows, 1024 x 1024 21.4, 12.5, 8.7; 8 experts, 25 rows, 512 x 1408 29, 16, 11): 64 x 32 for
+// the logits and up to four 64 x 64 tiles per CU, where two waves share an output and each sums half as long a chain (the average
+// segment is short, the longest may not be), 64 x 64 for longer lists of weight gradients and for what a launch of 64 x 32 could not hold
+// (less than 2^32 threads).  Other expert products of so many tiles come only with rows of 2^20 elements and at the limit of a launch.
 int launch_gemm_f32(const GemmProblem& p, hipStream_t s) {
   if (p.M <= 0 || p.N <= 0) return MOE_OK;
   if (gemm_f32_splits(p)) return launch_gemm_f32_split(p, s);

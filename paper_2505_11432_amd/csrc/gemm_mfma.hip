@@ -14,7 +14,7 @@ using namespace mfma;
 
 constexpr int kMaxDevices = 64;
 
-// One persistent workgroup per CU, in whole rounds of 8 (one per XCD).  The CU count of a device is looked up once;
+// Persistent workgroups, one per CU (launch doubles them where two fit a CU), in whole rounds of 8 (one per XCD).  The CU count of a device is looked up once;
 // concurrent first calls may both look it up and store the same value.
 int persistent_grid(int dev, int* grid) {
   static std::atomic<int> cached[kMaxDevices];

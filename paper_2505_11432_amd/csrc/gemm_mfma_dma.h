@@ -13,7 +13,7 @@
 // them 1.50 against 1.42 (random e4m3 codes 3.95 against 3.67, fed from LDS 3.37 against 3.20).  A layer of 8 experts, 16384 rows,
 // 4096 x 14336, forward and backward: bf16 15.79 -> 15.21 ms.
 //
-// The kernel is persistent: one workgroup per CU walks a static list of tiles.  When the last k-step of
+// The kernel is persistent: one workgroup per CU (two where they fit its LDS) walks a static list of tiles.  When the last k-step of
 // a tile is done the ring is free, so the first stages of the NEXT tile are put in flight before the
 // current tile's epilogue runs; workgroup launch, tile lookup, pointer set-up and the cold first loads
 // all disappear behind the epilogue's stores.
@@ -905,6 +905,7 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
       }
     } else
     for (int kt = 0; kt < nk; ++kt) {
+      static_assert(XPIPE || !FP8, "reads bf16 fragments");
       // my loads for step kt have landed once at most the younger steps' loads are outstanding; the first
       // step of a tile also drains the previous tile's epilogue stores, which share the counter
       if (!is_toucher) {                    // (the touching wave has no tile loads of its own to wait for)
@@ -914,21 +915,10 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
       if (kt + NSTAGE - 1 < nk) issue(kt + NSTAGE - 1);
 
       const unsigned at = smem_lds + (unsigned)(kt % NSTAGE) * STAGE_BYTES;
-      if constexpr (MODE == ROWSEG) {
-        // A wave whose rows all lie past the expert's last row has nothing to multiply (wave-uniform; it still
-        // issued its loads and takes part in the barriers).  In a nearly empty last tile of an expert only one or
-        // two waves per CU then use the matrix cores, and the k-step shrinks to what the loads need.
-        if (m0 + wm * WTM >= m_end) continue;
-      }
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) {
-        if constexpr (TOUCH) {
-          // late in the step, when the tile loads of this step have left the texture-address queue
-          if (kk == KK - 1 && is_toucher && (kt + NSTAGE + 1) * BKT <= klen) {   // whole k-steps only: every touched address exists
-            touch4s(a_base + (long)(kt + NSTAGE) * a_step, ta_off, lds_dump);
-          }
-        }
         if constexpr (TOUCH_K) {
+          // late in the step, when the tile loads of this step have left the texture-address queue
           if (kk == KK - 1 && is_toucher && (kt & 1) == 0 && (kt + NSTAGE + 2) * BKT <= klen) {
             touch4s(a_base + (long)(kt + NSTAGE) * a_step, ta_off, lds_dump);
           }
