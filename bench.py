@@ -262,7 +262,7 @@ def ceilings(cfg, fp8_path=False):
     ms = timed(lambda: torch.matmul(dh.t(), xe, out=c), 10)
     out["library_gemm_wgrad1_one_expert_tflops"] = 2.0 * rows_e * cfg.d * 2 * cfg.f / ms / 1e9
     del dh, xe, c
-    out["note"] = ("mfma_loop_*: register-only loop of 32x32 MFMAs, 8 waves per CU; const = all-ones operands, random = "
+    out["note"] = ("mfma_loop_*: register-only loop of 16x16 MFMAs, 8 waves per CU; const = all-ones operands, random = "
                    "N(0,1) bf16 / uniformly random finite e4m3 codes, weightlike = N(0, 0.02); mfma_lds_fed_loop: the bf16 loop with "
                    "its fragments read from LDS (N(0,1) data) at the grouped GEMM's ratio; _with_loads / _loads_wait / _loads_wait_barrier: "
                    "plus 64 KiB of direct-to-LDS loads per workgroup and 64-deep k-step from an L2-resident buffer, the loading waves' "

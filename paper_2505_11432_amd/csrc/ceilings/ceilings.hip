@@ -7,141 +7,101 @@
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+// A wave's outputs in all three matrix loops, as in the grouped GEMM: 64 x 128 in 4 x 8 blocks of 16 x 16.
+constexpr int FM = 4, FN = 8;
+
+__device__ __forceinline__ void clear(f32x4 (&acc)[FM][FN]) {
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+__device__ __forceinline__ float total(const f32x4 (&acc)[FM][FN]) {
+  float t = 0.f;
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) t += acc[i][j][r];
+  return t;
+}
 
 template <bool FP8>
 __global__ void __launch_bounds__(512) mfma_loop_kernel(const char* __restrict__ operands, int iters, float* __restrict__ sink) {
   const int lane = threadIdx.x & 63;
-  // fragment f of set s for this lane: 32 bytes at ((s * 6 + f) * 64 + lane) * 32
-  i32x8 frag[2][6];
+  // fragment f for this lane: 32 bytes at (f * 64 + lane) * 32
+  i32x8 frag[FM + FN];
 #pragma unroll
-  for (int s = 0; s < 2; ++s)
-#pragma unroll
-    for (int f = 0; f < 6; ++f) frag[s][f] = *reinterpret_cast<const i32x8*>(operands + ((s * 6 + f) * 64 + lane) * 32);
-  f32x16 acc[2][4];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  for (int f = 0; f < FM + FN; ++f) frag[f] = *reinterpret_cast<const i32x8*>(operands + (f * 64 + lane) * 32);
+  f32x4 acc[FM][FN];
+  clear(acc);
   for (int it = 0; it < iters; it += 2) {
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if constexpr (FP8) {
-            acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(frag[s][2 + j], frag[s][i], acc[i][j], 0, 0, 0, 127, 0, 127);
-          } else {
-            const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(frag[s][i], frag[s][i], 0, 1, 2, 3));
-            const bf16x8 b = __builtin_bit_cast(bf16x8, __builtin_shufflevector(frag[s][2 + j], frag[s][2 + j], 0, 1, 2, 3));
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, acc[i][j], 0, 0, 0);
-          }
+      for (int j = 0; j < FN; ++j) {
+        const i32x8 fa = frag[i], fb = frag[FM + j];
+        if constexpr (FP8) {
+          acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fb, fa, acc[i][j], 0, 0, 0, 127, 0, 127);
+        } else {
+          const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(fa, fa, 0, 1, 2, 3));
+          const bf16x8 b = __builtin_bit_cast(bf16x8, __builtin_shufflevector(fb, fb, 0, 1, 2, 3));
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a, acc[i][j], 0, 0, 0);
         }
+      }
   }
-  float total = 0.f;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) total += acc[i][j][r];
-  sink[(size_t)blockIdx.x * 512 + threadIdx.x] = total;
+  sink[(size_t)blockIdx.x * 512 + threadIdx.x] = total(acc);
 }
 
-// The same loop with its operands streamed from LDS at the grouped GEMM's ratio (2 + 4 fragment reads of 16 bytes per
-// lane for 8 MFMAs, read two sub-steps ahead): the matrix cores' rate when every MFMA sees fresh operand bits and the
-// LDS read path runs beside them, still without global loads, barriers or an epilogue.
-__global__ void __launch_bounds__(512) mfma_lds_loop_kernel(const uint4* __restrict__ lds_image, int iters, float* __restrict__ sink) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  constexpr int LDS_BYTES = 131072;
-  for (int i = threadIdx.x; i < LDS_BYTES / 16; i += 512) reinterpret_cast<uint4*>(smem)[i] = lds_image[i];
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  f32x16 acc[2][4];
+// The fragments of a sub-step of 32 from the LDS image: conflict-free (consecutive lanes read consecutive 16-byte chunks), from a
+// region that moves with the sub-step.
+constexpr int LDS_BYTES = 131072;
+struct Fragments { bf16x8 a[FM], b[FN]; };
+__device__ __forceinline__ void read_fragments(const char* smem, int substep, int wave, int lane, Fragments& f) {
+  const int base = ((substep * 1031 + wave * 67) & 63) * 2048 + lane * 16;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < FM; ++i) f.a[i] = *reinterpret_cast<const bf16x8*>(smem + ((base + i * 1024) & (LDS_BYTES - 1)));
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+  for (int j = 0; j < FN; ++j) f.b[j] = *reinterpret_cast<const bf16x8*>(smem + ((base + (FM + j) * 1024) & (LDS_BYTES - 1)));
+}
+__device__ __forceinline__ void multiply(const Fragments& f, f32x4 (&acc)[FM][FN]) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  bf16x8 a[2][2], b[2][4];
-  auto read_set = [&](int set, int step) __attribute__((always_inline)) {
-    // conflict-free: consecutive lanes read consecutive 16-byte chunks; the region moves with the step
-    const int base = ((step * 1031 + wave * 67) & 63) * 2048;
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int i = 0; i < 2; ++i) a[set][i] = *reinterpret_cast<const bf16x8*>(smem + ((base + i * 1024 + lane * 16) & (LDS_BYTES - 1)));
-#pragma unroll
-    for (int j = 0; j < 4; ++j) b[set][j] = *reinterpret_cast<const bf16x8*>(smem + ((base + (2 + j) * 1024 + lane * 16) & (LDS_BYTES - 1)));
-  };
-  read_set(0, 0);
-  read_set(1, 1);
-  for (int it = 0; it < iters; it += 2) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      bf16x8 ca[2], cb[4];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) ca[i] = a[s][i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) cb[j] = b[s][j];
-      read_set(s, it + s + 2);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cb[j], ca[i], acc[i][j], 0, 0, 0);
-    }
-  }
-  float total = 0.f;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) total += acc[i][j][r];
-  sink[(size_t)blockIdx.x * 512 + threadIdx.x] = total;
+    for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.b[j], f.a[i], acc[i][j], 0, 0, 0);
 }
 
-// The LDS-fed loop with the grouped GEMM's global -> LDS traffic beside it: every four sub-steps (one k-step of 64)
+// The same loop with its operands streamed from LDS at the grouped GEMM's ratio (4 + 8 fragment reads of 16 bytes per
+// lane for 32 MFMAs, read one sub-step ahead): the matrix cores' rate when every MFMA sees fresh operand bits and the
+// LDS read path runs beside them, still without an epilogue.  On request
+// the grouped GEMM's global -> LDS traffic runs beside it: every two sub-steps (one k-step of 64)
 // the lower four waves issue sixteen 1 KiB direct-to-LDS loads each (64 KiB per workgroup and step) from a small
 // buffer that all workgroups read alike, so the loads hit in L2 after the first touch: the address unit, the L2 -> LDS
 // path and the LDS write port run at the kernel's rate, without its miss latency.  flags: 1 = issue the loads,
 // 2 = the loading waves wait for their loads at the end of the step (one stage in flight, as in the kernel),
 // 4 = a workgroup barrier per step.  The loads overwrite the LDS image the fragments are read from (with values of
 // the same distribution; which of the two a fragment read sees does not matter here).
-__global__ void __launch_bounds__(512) mfma_lds_dma_loop_kernel(const uint4* __restrict__ lds_image, const char* __restrict__ src,
-                                                                unsigned src_bytes, int iters, int flags, float* __restrict__ sink) {
+__global__ void __launch_bounds__(512) mfma_lds_loop_kernel(const uint4* __restrict__ lds_image, const char* __restrict__ src,
+                                                            unsigned src_bytes, int iters, int flags, float* __restrict__ sink) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  constexpr int LDS_BYTES = 131072;
   for (int i = threadIdx.x; i < LDS_BYTES / 16; i += 512) reinterpret_cast<uint4*>(smem)[i] = lds_image[i];
   __syncthreads();
   const unsigned smem_lds = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  f32x16 acc[2][4];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  bf16x8 a[2][2], b[2][4];
-  auto read_set = [&](int set, int step) __attribute__((always_inline)) {
-    const int base = ((step * 1031 + wave * 67) & 63) * 2048;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) a[set][i] = *reinterpret_cast<const bf16x8*>(smem + ((base + i * 1024 + lane * 16) & (LDS_BYTES - 1)));
-#pragma unroll
-    for (int j = 0; j < 4; ++j) b[set][j] = *reinterpret_cast<const bf16x8*>(smem + ((base + (2 + j) * 1024 + lane * 16) & (LDS_BYTES - 1)));
-  };
+  f32x4 acc[FM][FN];
+  clear(acc);
   const bool loader = wave < 4;
   const unsigned voff = (unsigned)lane * 16u;
-  read_set(0, 0);
-  read_set(1, 1);
-  for (int it = 0; it < iters; it += 4) {            // one k-step: four sub-steps of 8 MFMAs per wave
-    const int kstep = it >> 2;
+  Fragments f[2];
+  read_fragments(smem, 0, wave, lane, f[0]);
+  const int substeps = (iters + 1) / 2;
+  for (int kstep = 0; kstep < substeps / 2; ++kstep) {
     if ((flags & 1) && loader) {
       // 64 KiB of this step: slice (kstep mod slices) of src, ring half (kstep & 1) of the LDS image
       const unsigned slices = src_bytes >> 16;
@@ -153,32 +113,16 @@ __global__ void __launch_bounds__(512) mfma_lds_dma_loop_kernel(const uint4* __r
                      "s"(dst + (unsigned)j * 1024u)
                      : "m0");
     }
-#pragma unroll
-    for (int ss = 0; ss < 4; ++ss) {
-      const int s = ss & 1;
-      bf16x8 ca[2], cb[4];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) ca[i] = a[s][i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) cb[j] = b[s][j];
-      read_set(s, it + ss + 2);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cb[j], ca[i], acc[i][j], 0, 0, 0);
-    }
+    read_fragments(smem, 2 * kstep + 1, wave, lane, f[1]);
+    multiply(f[0], acc);
+    read_fragments(smem, 2 * kstep + 2, wave, lane, f[0]);
+    multiply(f[1], acc);
     if ((flags & 2) && loader) __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));      // vmcnt(0), other counters open
     if (flags & 4) __syncthreads();
   }
+  if (substeps & 1) multiply(f[0], acc);
   __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));       // no load may still be on its way into LDS at the end
-  float total = 0.f;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) total += acc[i][j][r];
-  sink[(size_t)blockIdx.x * 512 + threadIdx.x] = total;
+  sink[(size_t)blockIdx.x * 512 + threadIdx.x] = total(acc);
 }
 
 __global__ void __launch_bounds__(256) copy_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, size_t n) {
@@ -216,7 +160,7 @@ int moe_ceiling_mfma_lds_loop(const void* lds_image, int iters, int workgroups, 
   hipError_t e = hipFuncSetAttribute((const void*)mfma_lds_loop_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 131072);
   if (e != hipSuccess) return -4;
   mfma_lds_loop_kernel<<<dim3((unsigned)workgroups), dim3(512), 131072, reinterpret_cast<hipStream_t>(stream)>>>(
-      static_cast<const uint4*>(lds_image), iters, sink);
+      static_cast<const uint4*>(lds_image), nullptr, 0, iters, 0, sink);
   return status(hipGetLastError());
 }
 
@@ -224,9 +168,9 @@ int moe_ceiling_mfma_lds_dma_loop(const void* lds_image, const void* src, size_t
                                   float* sink, void* stream) {
   if (!lds_image || !src || !sink || iters < 0 || iters % 4 != 0 || workgroups < 1 || workgroups > 65535) return -1;
   if (src_bytes < 65536 || src_bytes % 65536 != 0 || src_bytes > (1u << 30) || flags < 0 || flags > 7) return -1;
-  hipError_t e = hipFuncSetAttribute((const void*)mfma_lds_dma_loop_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 131072);
+  hipError_t e = hipFuncSetAttribute((const void*)mfma_lds_loop_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 131072);
   if (e != hipSuccess) return -4;
-  mfma_lds_dma_loop_kernel<<<dim3((unsigned)workgroups), dim3(512), 131072, reinterpret_cast<hipStream_t>(stream)>>>(
+  mfma_lds_loop_kernel<<<dim3((unsigned)workgroups), dim3(512), 131072, reinterpret_cast<hipStream_t>(stream)>>>(
       static_cast<const uint4*>(lds_image), static_cast<const char*>(src), (unsigned)src_bytes, iters, flags, sink);
   return status(hipGetLastError());
 }

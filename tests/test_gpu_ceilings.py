@@ -23,8 +23,8 @@ def lib():
 
 
 def test_mfma_loop_counts_every_mfma(lib):
-    """All-ones bf16 operands: every MFMA adds K = 16 to each accumulator element, so a lane's sum over its 8
-    accumulators of 16 elements after `iters` MFMAs per accumulator is 8 * 16 * iters * 16 (exact in fp32 here)."""
+    """All-ones bf16 operands: every MFMA adds K = 32 to each accumulator element, so a lane's sum over its 32 accumulators of
+    4 elements after an MFMA per accumulator and two iterations is 32 * 4 * iters / 2 * 32 = 8 * 16 * iters * 16 (exact in fp32 here)."""
     stream = torch.cuda.current_stream().cuda_stream
     ops = torch.zeros((2 * 6 * 64, 16), dtype=torch.bfloat16)
     ops[:, :8] = 1.0
@@ -34,7 +34,7 @@ def test_mfma_loop_counts_every_mfma(lib):
     assert lib.moe_ceiling_mfma_loop(0, ops.data_ptr(), iters, wgs, sink.data_ptr(), stream) == 0
     torch.cuda.synchronize()
     assert torch.all(sink == 8 * 16 * iters * 16)
-    # e4m3: code 0x38 is 1.0; K = 64
+    # e4m3: code 0x38 is 1.0; K = 128
     ops8 = torch.full((2 * 6 * 64, 32), 0x38, dtype=torch.uint8, device="cuda")
     assert lib.moe_ceiling_mfma_loop(1, ops8.data_ptr(), iters, wgs, sink.data_ptr(), stream) == 0
     torch.cuda.synchronize()
