@@ -10,15 +10,16 @@
 // In a longer contraction that holds a single product other than zero, of two full 24-bit numbers, 4 % of the results are not the nearest
 // number (up to 1.5 units of 2^-24 off instead of 1); products by powers of two and other numbers of up to 8 bits are exact.
 //
-// Bound: six bf16 products take 0.4 of the time of one fp32 product on the matrix cores, but two elements also cost fourteen vector
-// instructions to split, and the three parts pass through LDS.  These follow one another more than they overlap: FC1 of 2000 rows, 8
-// experts, 1024 x 5632 takes 188 us on 128 x 128 tiles (64 x 64: 202), 173 (171) without the arithmetic of the split, 164 (162)
-// without the loads, 114 (141) with a sixth of the products.
+// Bound: six bf16 products take 0.4 of the time of one fp32 product on the matrix cores, but two elements also cost thirteen vector
+// instructions to scale and split, and the three parts pass through LDS.  These follow one another more than they overlap: FC1 of 2000
+// rows, 8 experts, 1024 x 5632 takes 185 us on 128 x 128 tiles (64 x 64: 177), 175 (155) without the arithmetic of the split, 151 (131)
+// without the loads, 108 (120) with a sixth of the products.
 // Each operand element is split once per tile by the thread that loads it, so larger tiles split less often.  Measured (us, the fp32
-// instruction and this; 8 experts, 2000 rows, d = 1024, f = 2816): FC1 300, 194; FC2 144, 109; dgrad2 131, 94; wgrad2 118, 98; dgrad1 266,
-// 211; wgrad1 231, 171.  Four experts of 1125 rows: 510, 321; 241, 183; 249, 179; 234, 162; 500, 373; 472, 307.
-// Not faster: one wave per SIMD with 64 x 64 outputs (226 us), fragments read ahead across the step barrier (182 to 185, wgrad1 172 to 190
-// against 173), products and split interleaved by scheduling barriers (184), 128 x 64 tiles (196).
+// instruction and this; 8 experts, 2000 rows, d = 1024, f = 2816, one product over and over): FC1 252, 181; FC2 139, 105; dgrad2 130, 95;
+// wgrad2 120, 99; dgrad1 270, 216; wgrad1 231, 174.  In passes of a whole layer, operands from memory: 238, 196; 137, 115; 115, 108; 117, 103;
+// 271, 241; 229, 188.  4500 rows: 508, 320; 265, 194; 240, 184; 238, 171; 502, 402; 468, 321.
+// Not faster (FC1, against 184 us at the time): one wave per SIMD with 64 x 64 outputs (226), fragments read ahead across the step barrier (182
+// to 185, wgrad1 172 to 190 against 173), products and split interleaved by scheduling barriers (184), 128 x 64 tiles (196).
 #include <atomic>
 
 #include "gemm_f32_tiles.h"
@@ -44,7 +45,7 @@ constexpr unsigned kSpan = 0x40000000u;  // bytes that a tile's rows span at mos
 // smallest subnormal number among them, are then normal numbers, and so is every part product that can reach a result other than zero.  What
 // leaves the range at its other end (elements from 2^104 on, sums from 2^80 on, infinities and NaN) is seen in the sums.
 // (Left as they are, elements below 2^-103 and sums below 2^-80 had to be found and their tiles made again: two vector instructions per element
-// instead of one, and FC1 as below 488 us instead of 184 with one such element per tile, as gates below -72 give.)
+// instead of one, and FC1 as above 488 us instead of 184 with one such element per tile, as gates below -72 give.)
 constexpr float kScale = 0x1p24f, kUnscale = 0x1p-48f;
 
 // LDS image of one part of one operand tile: EXT rows (or columns) of 32 bf16, 64 bytes.  A 16-byte read serves lanes 0-3, 12-15, 20-27 and

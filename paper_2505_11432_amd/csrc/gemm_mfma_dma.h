@@ -7,11 +7,12 @@
 // One s_barrier per k-step: after it every wave's loads for the step have landed and every wave has
 // left the previous step, whose buffer the new loads may overwrite.
 //
-// The products run on the 16x16 matrix instructions (16x16x32 bf16, 16x16x128 e4m3).  What bounds the large layers is the power
-// the chip grants its matrix cores, and these need less of it than the 32x32 ones: register-only loops of eight waves per CU on
-// N(0,1) bf16 operands reach 2.00 PFLOP/s against 1.78, fed from LDS 1.71 against 1.55, with this kernel's load traffic beside
-// them 1.50 against 1.42 (random e4m3 codes 3.95 against 3.67, fed from LDS 3.37 against 3.20).  A layer of 8 experts, 16384 rows,
-// 4096 x 14336, forward and backward: bf16 15.79 -> 15.21 ms.
+// The products run on the 16x16 matrix instructions (16x16x32 bf16, 16x16x128 e4m3), which do the same products for less power, and power
+// sets the clock: register-only loops of eight waves per CU on N(0,1) bf16 operands reach 2.07 PFLOP/s against 1.78 with the 32x32
+// ones, fed from LDS 1.67 against 1.54, with this kernel's load traffic, waits and barriers beside them 1.48 against 1.41 (random
+// e4m3 codes 4.13 against 3.75).  8 experts, 16384 rows, 4096 x 14336, bf16 (us): FC1 3261 -> 3064, FC2 1547 -> 1449, dgrad1 3041 -> 2880,
+// dgrad2 2096 -> 2020, weight gradients 1892 -> 1843 and 3628 -> 3585.  FC1, FC2 and dgrad1 take 1.06 to 1.14 of what their products
+// take in the last of these loops, dgrad2 and the weight gradients 1.3 to 1.5, with their epilogues and stores in between.
 //
 // The kernel is persistent: one workgroup per CU (two where they fit its LDS) walks a static list of tiles.  When the last k-step of
 // a tile is done the ring is free, so the first stages of the NEXT tile are put in flight before the
