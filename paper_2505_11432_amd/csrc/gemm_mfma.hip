@@ -112,6 +112,7 @@ int launch_rowseg(Args a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return MOE_OK;
   const RowPlan plan = plan_for<LB, EPI>(a.M, a.E, a.N, a.K, (int)sizeof(TIN));
   if (!plan.split) a.splitk_ws = nullptr;
+  a.stagger = plan.stagger;
   switch (plan.tile) {
     case RowTile::FEW: return launch<64, 128, 2 * B128, 3, 2, 2, KMAJOR, LB, ROWSEG, EPI, bf16, TIN>(a, 1, s);
     case RowTile::MID:
@@ -216,6 +217,7 @@ int mfma_wgrad(const void* P, const void* Q, const int32_t* offsets, int rows, i
     if (c_dt == MOE_F32) return launch<128, 128, 64, 2, 2, 2, MNMAJOR, MNMAJOR, KSEG, EPI_STORE, float>(a, blocks, s);
     return launch<128, 128, 64, 2, 2, 2, MNMAJOR, MNMAJOR, KSEG, EPI_STORE, bf16>(a, blocks, s);
   }
+  a.stagger = wgrad_stagger(blocks, false);
   if (c_dt == MOE_F32) return launch<256, 256, 64, 2, 2, 4, MNMAJOR, MNMAJOR, KSEG, EPI_STORE, float>(a, blocks, s);
   return launch<256, 256, 64, 2, 2, 4, MNMAJOR, MNMAJOR, KSEG, EPI_STORE, bf16>(a, blocks, s);
 }
@@ -273,6 +275,7 @@ int mfma_wgrad_fp8(const void* Pt, const uint8_t* p_e8m0, const void* Qt, const 
   a.accumulate = accumulate;
   a.a_e8m0 = p_e8m0; a.a_e8_ld = Mo; a.b_e8m0 = q_e8m0; a.b_e8_ld = N;
   const long blocks = (long)E * cdiv(Mo, 256) * cdiv(N, 256);
+  a.stagger = wgrad_stagger(blocks, true);
   if (c_dt == MOE_F32) return launch<256, 256, 128, 2, 4, 2, KMAJOR, KMAJOR, KSEG, EPI_STORE, float, uint8_t>(a, blocks, s);
   return launch<256, 256, 128, 2, 4, 2, KMAJOR, KMAJOR, KSEG, EPI_STORE, bf16, uint8_t>(a, blocks, s);
 }

@@ -458,10 +458,18 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
   const int window = gridDim.x / XCDS;           // tiles per window = CUs per XCD
   const int in_window = blockIdx.x / XCDS;
   int slot = 0;                                  // this XCD's window counter
+  // All workgroups walk tiles of one length, so without more their epilogues coincide, and 256 epilogues at once write at what the
+  // memory takes: 256 KB per workgroup in 12 us (5.6 TB/s), where 64 of them need 3 us (probe of the store pattern: 8, 32, 64, 128, 256
+  // workgroups 2.2, 2.3, 3.0, 5.9, 12.1 us; 32 of one XCD alone 6.6).  The workgroups of an XCD therefore start in groups, each `lag`
+  // k-steps of time after the one before, and walk the contraction from as many k-steps further on, wrapping around: at any moment
+  // all of them are at the same k and go on sharing panels in their L2.  (Late starts without the rotation bring nothing: the late ones
+  // find their panels in L2, run faster and catch up.)  Sizes and figures: stagger in row_plan.h.
+  constexpr bool STAGGER = MODE != PLAIN && BM == 256 && BN == 256;
+  const int lag = STAGGER ? __builtin_amdgcn_readfirstlane(in_window * p.stagger.groups / window * p.stagger.lag) : 0;
 
   // tile state
   int e = 0, m0 = 0, m_end = 0, n0 = 0, klen = 0, nk = 0;
-  int k_start = 0;                  // k-step this workgroup's walk begins at (see issue)
+  int k_start = 0;                  // k-step this workgroup's walk begins at (see walk)
   int part_slot = -1;               // >= 0: this work item is one K part of a split tile; index of its partial tile
   const bool is_loader = !SPLIT || wave < NL;            // wave-uniform; the lower waves win issue arbitration
   const int lw = wave & (NL - 1);                        // loader index
@@ -569,7 +577,8 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
       klen = min(klen, s1 * BKT) - s0 * BKT;
       nk = s1 - s0;
     }
-    k_start = (xcd * 2 + in_window * 2 / window) * nk / (2 * XCDS);
+    if constexpr (STAGGER) k_start = nk > 0 ? lag % nk : 0;
+    else k_start = (xcd * 2 + in_window * 2 / window) * nk / (2 * XCDS);
     const char* Ag = static_cast<const char*>(p.A);
     const char* Bg = static_cast<const char*>(p.B) + (long)e * p.b_es * ESZ;
     // Base of each operand at the tile's first k (wave-uniform) and this lane's fixed byte offset from it.
@@ -660,21 +669,27 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
   // sixteenth after that.  Measured on the 64-row tile (us; one start, one per XCD, this): 8 experts, 4 rows, FC1 of 4096 x
   // 14336 334, 303, 304, FC2 180, 168, 155; 64 experts, 32 rows, FC1 of 2048 x 1408 164, 143, 143; 8 experts, 8 rows, FC1 of
   // 2048 x 8192 116, 96, 97.  A start of its own for every workgroup of an XCD: 362, 159, 141, 106.
-  constexpr bool KROT = MODE == ROWSEG && BM <= 128;
+  constexpr bool KROT = (MODE == ROWSEG && BM <= 128) || STAGGER;
+  // k-step of the contraction that step s of this workgroup's walk multiplies
+  auto walk = [&](int s) __attribute__((always_inline)) -> int {
+    if constexpr (KROT) {
+      s += k_start;
+      if (s >= nk) s -= nk;
+    }
+    return s;
+  };
   // Issue the loads of k-step `ks` of the open tile into ring slot ks % NSTAGE.  Only the last step can be ragged.
   auto issue = [&](int ks) __attribute__((always_inline)) {
     if (!is_loader) return;
-    const unsigned stage = smem_lds + (unsigned)(ks % NSTAGE) * STAGE_BYTES;
-    if constexpr (KROT) {
-      ks += k_start;
-      if (ks >= nk) ks -= nk;
-    }
+    const int ring = ks % NSTAGE;
+    const unsigned stage = smem_lds + (unsigned)ring * STAGE_BYTES;
+    ks = walk(ks);
     const int k_left = klen - ks * BKT;          // valid k in this step
     const char* ab = a_base + (long)ks * a_step;     // scalar arithmetic
     const char* bb = b_base + (long)ks * b_step;
     if constexpr (BSCALE) {
       if (lw == 0) {
-        const unsigned dst = scale_lds + (unsigned)(ks % NSTAGE) * 512u;
+        const unsigned dst = scale_lds + (unsigned)ring * 512u;
         touch4s(sa_base + (long)ks * p.a_e8_ld, sa_voff, dst);
         touch4s(sb_base + (long)ks * p.b_e8_ld, sb_voff, dst + 256u);
       }
@@ -714,6 +729,10 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
       }
     }
   };
+  auto touch = [&](int s) __attribute__((always_inline)) {
+    const int ks = walk(s);
+    if ((ks + 1) * BKT <= klen) touch4s(a_base + (long)ks * a_step, ta_off, lds_dump);      // whole k-steps only: every touched address exists
+  };
   auto issue_prologue = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int s = 0; s < NSTAGE - 1; ++s)
@@ -721,6 +740,11 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
   };
 
   if (!open_tile(slot)) return;
+  if constexpr (STAGGER) {
+    // (a k-step takes 1.5 us; the counter runs at 100 MHz)
+    const unsigned long long until = __builtin_amdgcn_s_memrealtime() + (unsigned)lag * 150u;
+    while ((long long)(__builtin_amdgcn_s_memrealtime() - until) < 0) __builtin_amdgcn_s_sleep(8);
+  }
   issue_prologue();
 
   for (;;) {
@@ -831,9 +855,7 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
           for (int p = 0; p < PHASES; ++p) {
             constexpr int TOUCH_AT = PHASES >= 2 ? PHASES - 2 : 0;      // one phase ahead of the refill it runs before (later: slower)
             if constexpr (TOUCH || TOUCH_K2) {
-              if (p == TOUCH_AT && is_toucher && (kt + NSTAGE + 1) * BKT <= klen) {   // whole k-steps only: every touched address exists
-                touch4s(a_base + (long)(kt + NSTAGE) * a_step, ta_off, lds_dump);
-              }
+              if (p == TOUCH_AT && is_toucher && kt + NSTAGE < nk) touch(kt + NSTAGE);
             }
             const bool last = p + 1 == PHASES;
             const int pn = (p + 1) % PHASES, kn = pn / NPH;
@@ -966,6 +988,11 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
     const bool has_next = open_tile(slot);
     if (has_next) {
       issue_prologue();
+      // the first touch of the k loop is for step 2.  (8 experts, 16384 rows, 4096 x 14336, staggered: d_w1 3460 -> 3365 us, d_w2 1722 ->
+      // 1714; FC1 2803 -> 2828, without stagger nothing)
+      if constexpr (TOUCH_K2) {
+        if (is_toucher && nk > 1) touch(1);
+      }
     }
     {
       const int e = ep_e, m0 = ep_m0, m_end = ep_m_end, n0 = ep_n0;

@@ -34,8 +34,10 @@
 namespace moe {
 
 enum class RowTile { FEW, MID, FULL };
+// The workgroups of an XCD start in `groups` groups, each `lag` k-steps after the one before (0: all at once)
+struct Stagger { int groups = 0, lag = 0; };
 // split: the last round's tiles may be cut along K; pair: MID as two workgroups per CU
-struct RowPlan { RowTile tile; bool split; bool pair = false; };
+struct RowPlan { RowTile tile; bool split; bool pair = false; Stagger stagger = {}; };
 
 struct RowKind {
   bool swiglu;          // pairs gate and up columns: N is f, a tile makes half its width
@@ -68,6 +70,22 @@ inline double pairs_us(double tiles, const PairCost& c, int steps) {
   return whole * round_us + (rem < 1 ? 0 : rem <= 256 && half_us < round_us ? half_us : round_us);
 }
 
+// Groups of workgroups that start one after another (see STAGGER in gemm_mfma_dma.h), so that their epilogues do not meet.  The late
+// groups end late, (groups - 1) * lag steps of 1.5 us; a round gains 2 to 5 us, less where the epilogue only stores bf16: from five rounds
+// on, ten with SwiGLU', twelve and short contractions for the stores (224 k-steps, 4 rounds: 1375 -> 1399 us).  Launches of 8 experts,
+// 16384 rows, 4096 x 14336 (us, at once and {groups, lag}; a few passes on a cool chip): FC1 2942, {4, 3} 2855, {8, 1} 2835, {8, 3} 2852; d_w2 1838,
+// {2, 3} 1715, {4, 3} 1715, {8, 1} 1681; d_w1 3507, {2, 3} 3442, {4, 3} 3383, {8, 1} 3500; SwiGLU' 1960, {4, 5} 1931, {8, 1} 1956; e4m3 FC1 1698,
+// {4, 3} 1604, {8, 2} 1568, d_w2 1143, {8, 3} 1065, d_w1 2268, {4, 3} 2377, {8, 3} 2253, SwiGLU' 1091, {4, 5} 1102.  64 experts, 131072
+// rows, 2048 x 1408: FC1 1379, {8, 1} 1300; FC2 677, {4, 3} 661; d_w2 736, {4, 3} 727; d_w1 1405, {4, 3} 1357.  In passes without a pause
+// the chip lowers its clock for what the launches no longer wait: whole layers 1.005, 1.015 (e4m3) and 1.016 of the speed.
+inline Stagger row_stagger(RowKind kind, bool e4m3, double tiles, int steps) {
+  const double rounds = tiles / 256;
+  if (kind.swiglu) return rounds < 5 ? Stagger{} : e4m3 ? Stagger{8, 2} : Stagger{8, 1};
+  if (kind.store) return rounds < 12 || steps > 64 || e4m3 ? Stagger{} : Stagger{4, 3};
+  return rounds < 10 || e4m3 ? Stagger{} : Stagger{4, 5};
+}
+inline Stagger wgrad_stagger(long tiles, bool e4m3) { return tiles < 5 * 256 ? Stagger{} : e4m3 ? Stagger{8, 3} : Stagger{4, 3}; }
+
 // N: output columns (SwiGLU: f); K in elements of esz bytes
 inline RowPlan plan_rows(RowKind kind, int M, int E, int N, int K, int esz) {
   auto up = [](long a, long b) { return (a + b - 1) / b; };
@@ -96,7 +114,8 @@ inline RowPlan plan_rows(RowKind kind, int M, int E, int N, int K, int esz) {
     const double pair_us = pairs_us(even(128, 128), pair, steps);
     if (pair_us < full_us && pair_us < mid_us) return {RowTile::MID, false, true};
   }
-  return mid_us < full_us ? RowPlan{RowTile::MID, split_mid} : RowPlan{RowTile::FULL, split_full};
+  if (mid_us < full_us) return {RowTile::MID, split_mid};
+  return {RowTile::FULL, split_full, false, row_stagger(kind, esz == 1, even(256, 256), steps)};
 }
 
 // How a launch's last round is dealt.  The tile list goes to the eight XCDs in windows, one tile per CU; `left` of its `items` tiles are

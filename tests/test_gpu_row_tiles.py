@@ -68,6 +68,12 @@ def test_bf16_and_fused_below_the_bound(rows, spare):
     check_bf16_and_fused(rows, 272, 336, spare)
 
 
+def test_bf16_and_fused_in_staggered_groups():
+    """Five and more rounds of 256 x 256 tiles (FC1, d_w1): workgroups start in groups and walk the contraction from different
+    steps on; segments of fewer steps than the groups lie apart, of none, one and two, and with a remainder."""
+    check_bf16_and_fused([0, 3, 700, 64, 2500, 65, 3668, 1000], 1040, 6160, 0)
+
+
 def check_bf16_and_fused(rows, d, f, spare):
     from paper_2505_11432_amd import binding as B
     E, M, off, offsets, w1, w2, x, dy = setup(rows, d, f, spare)
