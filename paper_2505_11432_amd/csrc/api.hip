@@ -35,8 +35,9 @@ static bool sizes_ok(int T, int d, int E, int k, int f) {
 }
 
 static int ffn_fwd_f32(const void* xp, const int32_t* offsets, const void* w1, const void* w2, int M, int d, int E, int f,
-                       void* h_save, void* yp, void* ws, hipStream_t s) {
+                       void* h_save, void* yp, void* ws, size_t ws_bytes, hipStream_t s) {
   void* A = ws;
+  const size_t a_bytes = align_up((size_t)M * f * sizeof(float), 256);
   GemmProblem g{};
   g.offsets = offsets; g.E = E; g.mode = 0; g.M = M; g.accumulate = 0; g.bias = nullptr;
   // FC1: H[M,2f] = xp[M,d] * w1[e]^T
@@ -51,6 +52,9 @@ static int ffn_fwd_f32(const void* xp, const int32_t* offsets, const void* w1, c
   g.A = A; g.a_rs = f; g.a_cs = 1;
   g.B = w2; g.b_es = (long)d * f; g.b_rs = 1; g.b_cs = f;
   g.C = yp; g.ldc = d; g.N = d; g.K = f;
+  // a workspace sized for the backward as well has room behind A
+  g.scratch = reinterpret_cast<float*>(static_cast<char*>(ws) + a_bytes);
+  g.scratch_floats = (ws_bytes - a_bytes) / sizeof(float);
   return launch_gemm_f32(g, s);
 }
 
@@ -133,13 +137,15 @@ static int ffn_bwd_f32(const void* xp, const void* h_save, const void* d_yp, con
   g.C = d_w2; g.c_es = (long)d * f; g.ldc = f; g.M = d; g.N = f; g.K = M;
   rc = launch_gemm_f32(g, s);
   if (rc != MOE_OK) return rc;
-  // d_xp[M,d] = dH[M,2f] * w1[e]   (contraction over 2f)
+  // d_xp[M,d] = dH[M,2f] * w1[e]   (contraction over 2f); A and dA are done with
   g.mode = 0; g.accumulate = 0;
+  g.scratch = static_cast<float*>(A); g.scratch_floats = 2 * align_up((size_t)M * f * es, 256) / es;
   g.A = dH; g.a_rs = 2L * f; g.a_cs = 1;
   g.B = w1; g.b_es = 2L * f * d; g.b_rs = d; g.b_cs = 1;
   g.C = d_xp; g.c_es = 0; g.ldc = d; g.M = M; g.N = d; g.K = 2 * f;
   rc = launch_gemm_f32(g, s);
   if (rc != MOE_OK) return rc;
+  g.scratch = nullptr;
   // d_w1[e][2f,d] = dH_e^T * xp_e
   g.mode = 1; g.accumulate = accumulate;
   g.A = dH; g.a_rs = 1; g.a_cs = 2L * f;
@@ -170,8 +176,6 @@ const char* moe_status_string(int status) {
 
 int moe_init(void) {
   int rc = mfma_configure_all();
-  if (rc != MOE_OK) return rc;
-  rc = gemm_f32_split_configure();
   if (rc != MOE_OK) return rc;
   return route_noalloc_prepare();
 }
@@ -367,7 +371,7 @@ int moe_expert_ffn_fwd(const void* xp, const float* xp_scale, moe_dtype act_dt, 
   }
   if (act_dt == MOE_BF16)
     return ffn_fwd_bf16(xp, offsets, w1, w2, M, d, E, f, h_save, yp, a_codes_out, workspace, as_stream(stream));
-  return ffn_fwd_f32(xp, offsets, w1, w2, M, d, E, f, h_save, yp, workspace, as_stream(stream));
+  return ffn_fwd_f32(xp, offsets, w1, w2, M, d, E, f, h_save, yp, workspace, ws_bytes, as_stream(stream));
 }
 
 int moe_expert_ffn_bwd(const void* xp, const void* h_save, const void* d_yp, const void* a_override,

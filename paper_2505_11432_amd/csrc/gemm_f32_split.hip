@@ -11,17 +11,16 @@
 // number (up to 1.5 units of 2^-24 off instead of 1); products by powers of two and other numbers of up to 8 bits are exact.
 //
 // Bound: six bf16 products take 0.4 of the time of one fp32 product on the matrix cores, but two elements also cost thirteen vector
-// instructions to scale and split, and the three parts pass through LDS.  These follow one another more than they overlap: FC1 of 2000
-// rows, 8 experts, 1024 x 5632 takes 185 us on 128 x 128 tiles (64 x 64: 177), 175 (155) without the arithmetic of the split, 151 (131)
-// without the loads, 108 (120) with a sixth of the products.
-// Each operand element is split once per tile by the thread that loads it, so larger tiles split less often.  Measured (us, the fp32
-// instruction and this; 8 experts, 2000 rows, d = 1024, f = 2816, one product over and over): FC1 252, 181; FC2 139, 105; dgrad2 130, 95;
-// wgrad2 120, 99; dgrad1 270, 216; wgrad1 231, 174.  In passes of a whole layer, operands from memory: 238, 196; 137, 115; 115, 108; 117, 103;
-// 271, 241; 229, 188.  4500 rows: 508, 320; 265, 194; 240, 184; 238, 171; 502, 402; 468, 321.
-// Not faster (FC1, against 184 us at the time): one wave per SIMD with 64 x 64 outputs (226), fragments read ahead across the step barrier (182
-// to 185, wgrad1 172 to 190 against 173), products and split interleaved by scheduling barriers (184), 128 x 64 tiles (196).
-#include <atomic>
-
+// instructions to scale and split, and the three parts pass through LDS.  Products, split and LDS take about as long each, and a SIMD issues
+// either a matrix or a vector instruction; what they overlap comes back in part as a lower clock (2.0 GHz).
+// Each operand element is split once per tile by the thread that loads it, so larger tiles split less often.  Measured (us, operands from
+// memory; the fp32 instruction, then the split as it is now; 8 experts, 2000 rows, d = 1024, f = 2816): FC1 238, 218; FC2 137, 111; dgrad2 115, 106;
+// wgrad2 117, 105; dgrad1 271, 189; wgrad1 229, 188.  128 x 128 tiles by eight waves of 32 x 64 with two stages in LDS, one workgroup per CU, on
+// the same box: 229, 137, 121, 115, 286, 207 (4400 rows 353, 199, 205, 182, 423, 335, now 325, 199, 171, 166, 322, 305).
+// Not faster (FC1, 2000 rows, against 195): the two workgroups as one, taking turns by barriers (191, weight gradients 15 % slower); 32 x 32
+// instructions with the split between their products, the parts written behind the barrier (200; loads of whole lines by four k per lane
+// changed nothing); a higher wave priority while multiplying (180 to 225, dgrad1 15 % slower).  64 x 64 tiles: one wave per SIMD,
+// fragments read ahead across the step barrier, products and split interleaved by scheduling barriers changed nothing or lost.
 #include "gemm_f32_tiles.h"
 #include "row_plan.h"
 
@@ -127,6 +126,14 @@ template <bool KFAST, int EXT> struct Share {
   }
 };
 
+// Products of row segments may be cut along K (gridDim.y parts): the whole steps of this workgroup's part.
+__device__ __forceinline__ void part_of_tile(F32Tile& t) {
+  if (gridDim.y == 1) return;
+  const int steps = (t.k_end - t.k0 + kStep - 1) / kStep, q = blockIdx.y, n = gridDim.y, k0 = t.k0;
+  t.k0 = k0 + q * steps / n * kStep;
+  t.k_end = min(t.k_end, k0 + (q + 1) * steps / n * kStep);
+}
+
 // WM x WN waves.  While the products of step s run from one LDS buffer the operands of step s + 1 are split into the other, and those of
 // steps s + 2 and s + 3 are on their way into registers.
 template <int BM, int BN, int WM, int WN, bool AK, bool BKF>
@@ -139,6 +146,7 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_f32_split_kernel(GemmPro
   __shared__ int redo;
   F32Tile t;
   if (!f32_tile<BM, BN>(p, tiles_n, tiles_m_fixed, blocks, t)) return;
+  part_of_tile(t);
   const int m0 = t.m0, m_end = t.m_end, n0 = t.n0, klen = t.k_end - t.k0;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -274,7 +282,7 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_f32_split_kernel(GemmPro
     }
   }
   // a lane holds row lane % 16 and columns 4 * (lane / 16) + 0..3 of every 16 x 16 block
-  float* __restrict__ C = static_cast<float*>(p.C) + (long)t.e * p.c_es;
+  float* __restrict__ C = static_cast<float*>(p.C) + (long)t.e * p.c_es + (long)blockIdx.y * p.part_stride;
 #pragma unroll
   for (int i = 0; i < FM; ++i) {
     const int m = m0 + wm * WTM + i * 16 + i16;
@@ -289,21 +297,266 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_f32_split_kernel(GemmPro
   }
 }
 
-template <int BM, int BN> constexpr int lds_bytes() { return 2 * 3 * (Part<BM>::BYTES + Part<BN>::BYTES); }
+// The same with CH chunks of eight k per thread.
+template <bool KFAST, int EXT, int THREADS> struct Shares {
+  static constexpr int CH = EXT * 4 / THREADS;
+  static_assert(EXT * 4 % THREADS == 0 && (KFAST || THREADS % EXT == 0), "whole chunks per thread");
+  __device__ static __forceinline__ int row(int c) { return KFAST ? (threadIdx.x >> 2) + c * (THREADS / 4) : threadIdx.x % EXT; }
+  __device__ static __forceinline__ int chunk(int c) { return KFAST ? threadIdx.x & 3 : threadIdx.x / EXT + c * (THREADS / EXT); }
 
-template <int BM, int BN, int WM, int WN, bool AK, bool BKF>
-int launch_as(const GemmProblem& p, hipStream_t s) {
-  gemm_f32_split_kernel<BM, BN, WM, WN, AK, BKF><<<dim3((unsigned)f32_blocks(p, BM, BN)), dim3(WM * WN * 64), lds_bytes<BM, BN>(), s>>>(
-      p, cdiv(p.N, BN), cdiv(p.M, BM), (int)f32_blocks(p, BM, BN));
+  const char* base;             // row (column) ext0 at the first k
+  long step;                    // bytes per step
+  int ld4, left0;               // bytes from one row of the buffer to the next; across k: bytes of a row in front of the tile
+  unsigned off[KFAST ? CH : 8];
+
+  // ext_n: valid rows of the tile; rows past them repeat the last one (they only reach outputs that are not stored)
+  __device__ __forceinline__ void open(const float* p, long ld, int ext0, int ext_n, int k0) {
+    ld4 = (int)ld * 4;
+    left0 = ext0 * 4;
+    step = KFAST ? kStep * 4 : (long)kStep * ld4;
+    base = reinterpret_cast<const char*>(p + (KFAST ? (long)ext0 * ld + k0 : (long)k0 * ld + ext0));
+    if constexpr (KFAST) {
+#pragma unroll
+      for (int c = 0; c < CH; ++c) off[c] = (unsigned)min(row(c), ext_n - 1) * (unsigned)ld4 + (unsigned)chunk(c) * 32u;
+    } else {
+      const unsigned r = min(row(0), ext_n - 1);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) off[i] = (unsigned)(chunk(0) * 8 + i) * (unsigned)ld4 + r * 4u;
+    }
+  }
+  // k_left: contraction left from step s on (not positive: nothing)
+  __device__ __forceinline__ void load(float (&v)[8], int c, int s, int k_left) const {
+    const char* at = base + s * step;
+    if constexpr (KFAST) {
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(at), 0, (int)kSpan, 0x00020000);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const unsigned o = chunk(c) * 8 + 4 * q < k_left ? off[c] + 16u * q : kSpan;
+        const f32x4 t = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[4 * q + i] = t[i];
+      }
+    } else {
+      const int k0 = c * (THREADS / EXT) * 8;        // chunks of one thread lie so far apart
+      const int span = max(min(k_left - k0, kStep - k0) * ld4 - left0, 0);
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(at + (long)k0 * ld4), 0, span, 0x00020000);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off[i], 0, 0));
+    }
+  }
+
+  // The split in four units of two elements: unit u, whose parts gather in `part` and go to lds with the last one.
+  __device__ static __forceinline__ void split(const float (&v)[8], int c, int u, u32x4 (&part)[3], char* lds) {
+    float r0 = v[2 * u] * kScale, r1 = v[2 * u + 1] * kScale;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const unsigned two = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{r0, r1}), bf16x2));
+      part[p][u] = two;
+      r0 -= __builtin_bit_cast(float, two << 16);
+      r1 -= __builtin_bit_cast(float, two & 0xffff0000u);
+    }
+    if (u == 3)
+#pragma unroll
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x4*>(lds + p * Part<EXT>::BYTES + Part<EXT>::offset(row(c), chunk(c))) = part[p];
+  }
+
+  // as fp32 rows of 32 k at a stride of 36
+  __device__ static __forceinline__ void stash(const float (&v)[8], int c, float* lds) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      *reinterpret_cast<f32x4*>(lds + row(c) * 36 + chunk(c) * 8 + 4 * q) = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+  }
+};
+
+// 128 x 128 outputs by four waves of 64 x 64.  With one stage in LDS and 256 registers two workgroups share a CU, and while one splits and writes
+// the other multiplies; a wave of 64 x 64 reads two thirds of what two of 64 x 32 read, and an element is split half as often as in tiles of
+// 64 x 64.
+template <bool AK, bool BKF>
+__global__ void __launch_bounds__(256, 2) gemm_f32_split128_kernel(GemmProblem p, int tiles_n, int tiles_m_fixed, int blocks) {
+  constexpr int BM = 128, BN = 128, WM = 2, WN = 2, THREADS = 256, WTM = BM / WM, WTN = BN / WN, FM = WTM / 16, FN = WTN / 16;
+  constexpr int A_BYTES = 3 * Part<BM>::BYTES, STAGE = A_BYTES + 3 * Part<BN>::BYTES;
+  typedef Shares<AK, BM, THREADS> ShareA;
+  typedef Shares<BKF, BN, THREADS> ShareB;
+  constexpr int CA = ShareA::CH, CB = ShareB::CH;
+  static_assert((BM + BN) * 36 * 4 <= STAGE, "the fp32 rows of a step fit");
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  __shared__ int redo;
+  F32Tile t;
+  if (!f32_tile<BM, BN>(p, tiles_n, tiles_m_fixed, blocks, t)) return;
+  part_of_tile(t);
+  const int m0 = t.m0, m_end = t.m_end, n0 = t.n0, klen = t.k_end - t.k0;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int i16 = lane & 15, g = lane >> 4;
+
+  ShareA a;
+  ShareB b;
+  a.open(static_cast<const float*>(p.A), AK ? p.a_rs : p.a_cs, m0, m_end - m0, t.k0);
+  b.open(static_cast<const float*>(p.B) + (long)t.e * p.b_es, BKF ? p.b_cs : p.b_rs, n0, p.N - n0, t.k0);
+  float va[CA][8], vb[CB][8];
+  auto load_a = [&](int c, int s) __attribute__((always_inline)) { a.load(va[c], c, s, klen - s * kStep); };
+  auto load_b = [&](int c, int s) __attribute__((always_inline)) { b.load(vb[c], c, s, klen - s * kStep); };
+  auto load = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < CA; ++c) load_a(c, s);
+#pragma unroll
+    for (int c = 0; c < CB; ++c) load_b(c, s);
+  };
+  constexpr int UNITS = 4 * (CA + CB);
+  u32x4 part[3];
+  auto split = [&](int u) __attribute__((always_inline)) {
+    if (u < 4 * CA) a.split(va[u / 4], u / 4, u % 4, part, lds);
+    else b.split(vb[u / 4 - CA], u / 4 - CA, u % 4, part, lds + A_BYTES);
+  };
+  f32x4 acc[FM][FN], low[FM][FN];        // the products of the first parts, the smaller ones
+  auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[i][j] = low[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  // The products of a step: column by column through the six terms, so that an accumulator is used again only after FM products.
+  auto multiply = [&]() __attribute__((always_inline)) {
+    constexpr int TB[6] = {2, 1, 0, 1, 0, 0}, TA[6] = {0, 1, 2, 0, 1, 0};        // parts of B and A, the smallest terms first
+    bf16x8 fa[FM][3], fb[2][3];
+    auto read_a = [&](int q) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+        fa[i][q] = *reinterpret_cast<const bf16x8*>(lds + q * Part<BM>::BYTES + Part<BM>::offset(wm * WTM + i * 16 + i16, g));
+    };
+    auto read_b = [&](int j, int q) __attribute__((always_inline)) {
+      fb[j & 1][q] = *reinterpret_cast<const bf16x8*>(lds + A_BYTES + q * Part<BN>::BYTES + Part<BN>::offset(wn * WTN + j * 16 + i16, g));
+    };
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      read_a(q);
+      read_b(0, 2 - q);
+    }
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      if (j + 1 < FN)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) read_b(j + 1, 2 - q);
+#pragma unroll
+      for (int term = 0; term < 6; ++term)
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+          f32x4& sum = term == 5 ? acc[i][j] : low[i][j];
+          sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j & 1][TB[term]], fa[i][TA[term]], sum, 0, 0, 0);
+        }
+    }
+  };
+  clear();
+  const int steps = (klen + kStep - 1) / kStep;
+  const bool few = klen <= kFewTerms;
+  if (threadIdx.x == 0) redo = few;
+  if (!few) {
+    load(0);
+    for (int s = 0; s < steps; ++s) {
+      // a chunk's registers take the next step's as soon as it is split
+#pragma unroll
+      for (int u = 0; u < UNITS; ++u) {
+        split(u);
+        if (u % 4 == 3) {
+          if (u < 4 * CA) load_a(u / 4, s + 1);
+          else load_b(u / 4 - CA, s + 1);
+        }
+      }
+      __syncthreads();
+      multiply();
+      __syncthreads();
+    }
+  }
+  __syncthreads();
+  // as above: what overflowed is made again with the fp32 instruction
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float sum = acc[i][j][r] + low[i][j][r];
+        bad |= (__builtin_bit_cast(unsigned, sum) & 0x7f800000u) == 0x7f800000u;
+        acc[i][j][r] = sum * kUnscale;
+      }
+  if (bad) redo = 1;
+  __syncthreads();
+  if (redo) {
+    clear();
+    float* at = reinterpret_cast<float*>(lds);
+    float* bt = at + BM * 36;
+    load(0);
+    for (int s = 0; s < steps; ++s) {
+#pragma unroll
+      for (int c = 0; c < CA; ++c) a.stash(va[c], c, at);
+#pragma unroll
+      for (int c = 0; c < CB; ++c) b.stash(vb[c], c, bt);
+      load(s + 1);
+      __syncthreads();
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          const f32x4 fb = *reinterpret_cast<const f32x4*>(bt + (wn * WTN + j * 16 + i16) * 36 + h * 16 + g * 4);
+#pragma unroll
+          for (int i = 0; i < FM; ++i) {
+            const f32x4 fa = *reinterpret_cast<const f32x4*>(at + (wm * WTM + i * 16 + i16) * 36 + h * 16 + g * 4);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[r], fa[r], acc[i][j], 0, 0, 0);
+          }
+        }
+      __syncthreads();
+    }
+  }
+  // a lane holds row lane % 16 and columns 4 * (lane / 16) + 0..3 of every 16 x 16 block
+  float* __restrict__ C = static_cast<float*>(p.C) + (long)t.e * p.c_es + (long)blockIdx.y * p.part_stride;
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    const int m = m0 + wm * WTM + i * 16 + i16;
+    if (m >= m_end) continue;
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const int n = n0 + wn * WTN + j * 16 + g * 4;
+      if (n >= p.N) continue;
+      f32x4* dst = reinterpret_cast<f32x4*>(C + (long)m * p.ldc + n);
+      *dst = p.accumulate ? acc[i][j] + *dst : acc[i][j];
+    }
+  }
+}
+
+// C = the sum of the K parts of a product, in their order; rows outside the segments are left as they are
+__global__ void __launch_bounds__(256) f32_add_parts_kernel(const float* __restrict__ parts, long stride, int n, const int32_t* __restrict__ offsets,
+                                                            int E, int M, int N, float* __restrict__ C, long ldc) {
+  const int per_row = N / 4, first = offsets[0], rows = min(offsets[E], M) - first;
+  const long total = (long)rows * per_row;
+  for (long i = blockIdx.x * 256L + threadIdx.x; i < total; i += gridDim.x * 256L) {
+    const long r = first + i / per_row;
+    const int c = (int)(i % per_row) * 4;
+    const float* src = parts + r * N + c;
+    f32x4 sum = *reinterpret_cast<const f32x4*>(src);
+    for (int q = 1; q < n; ++q) sum += *reinterpret_cast<const f32x4*>(src + q * stride);
+    *reinterpret_cast<f32x4*>(C + r * ldc + c) = sum;
+  }
+}
+
+
+template <bool AK, bool BKF> int launch_as(const GemmProblem& p, F32Plan plan, hipStream_t s) {
+  const int b = plan.large ? 128 : 64;
+  const long blocks = f32_blocks(p, b, b);
+  const dim3 grid((unsigned)blocks, (unsigned)plan.parts);
+  const int bytes = 6 * Part<64>::BYTES * 2;          // two stages of 64 x 64, one of 128 x 128
+  static_assert(Part<128>::BYTES == 2 * Part<64>::BYTES, "the same bytes");
+  if (plan.large) gemm_f32_split128_kernel<AK, BKF><<<grid, dim3(256), bytes, s>>>(p, cdiv(p.N, b), cdiv(p.M, b), (int)blocks);
+  else gemm_f32_split_kernel<64, 64, 2, 2, AK, BKF><<<grid, dim3(256), bytes, s>>>(p, cdiv(p.N, b), cdiv(p.M, b), (int)blocks);
   MOE_LAUNCH_CHECK();
   return MOE_OK;
 }
-template <int BM, int BN, int WM, int WN>
-int launch(const GemmProblem& p, hipStream_t s) {
+int launch(const GemmProblem& p, F32Plan plan, hipStream_t s) {
   const bool a_kfast = p.a_cs == 1, b_kfast = p.b_rs == 1;
-  if (a_kfast && b_kfast) return launch_as<BM, BN, WM, WN, true, true>(p, s);
-  if (a_kfast) return launch_as<BM, BN, WM, WN, true, false>(p, s);
-  return launch_as<BM, BN, WM, WN, false, false>(p, s);
+  if (a_kfast && b_kfast) return launch_as<true, true>(p, plan, s);
+  return a_kfast ? launch_as<true, false>(p, plan, s) : launch_as<false, false>(p, plan, s);
 }
 
 }  // namespace
@@ -318,26 +571,18 @@ bool gemm_f32_splits(const GemmProblem& p) {
 }
 
 int launch_gemm_f32_split(const GemmProblem& p, hipStream_t s) {
-  if (f32_split_in_128({p.mode == 0, p.M, p.N, p.K, p.E})) {
-    const int rc = gemm_f32_split_configure();
-    return rc != MOE_OK ? rc : launch<128, 128, 4, 2>(p, s);
+  const size_t one = (size_t)p.M * p.N;
+  const F32Plan plan = f32_plan({p.mode == 0, p.M, p.N, p.K, p.E}, p.scratch && !p.accumulate ? (long)(p.scratch_floats / one) : 0);
+  GemmProblem q = p;
+  if (plan.parts > 1) {
+    q.C = p.scratch; q.ldc = p.N; q.part_stride = (long)one;
   }
-  return launch<64, 64, 2, 2>(p, s);
-}
-
-// The 128 x 128 kernels need their dynamic-LDS limit raised once per device; moe_init does it ahead of a graph capture.  The
-// values are the same on every call, the bit only saves work.
-int gemm_f32_split_configure() {
-  static std::atomic<unsigned long long> done{0};
-  int dev = 0;
-  MOE_HIP_TRY(hipGetDevice(&dev));
-  if (dev < 0 || dev >= 64) return MOE_ERR_UNSUPPORTED;
-  if (done.load(std::memory_order_acquire) >> dev & 1) return MOE_OK;
-  constexpr int bytes = lds_bytes<128, 128>();
-  for (const void* k : {(const void*)gemm_f32_split_kernel<128, 128, 4, 2, true, true>, (const void*)gemm_f32_split_kernel<128, 128, 4, 2, true, false>,
-                        (const void*)gemm_f32_split_kernel<128, 128, 4, 2, false, false>})
-    MOE_HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
-  done.fetch_or(1ull << dev, std::memory_order_release);
+  const int rc = launch(q, plan, s);
+  if (rc != MOE_OK || plan.parts == 1) return rc;
+  const long quads = (long)(one / 4);
+  f32_add_parts_kernel<<<dim3((unsigned)(quads < 256 * 2048 ? (quads + 255) / 256 : 2048)), dim3(256), 0, s>>>(
+      p.scratch, q.part_stride, plan.parts, p.offsets, p.E, p.M, p.N, static_cast<float*>(p.C), p.ldc);
+  MOE_LAUNCH_CHECK();
   return MOE_OK;
 }
 

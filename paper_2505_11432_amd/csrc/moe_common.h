@@ -68,10 +68,12 @@ struct GemmProblem {
   int M, N, K;                               // mode 0: M = upper bound on rows; mode 1: K = upper bound
   int accumulate;                            // C += instead of C =
   const float* bias;                         // per-column fp32 bias added in the epilogue, or NULL
+  // fp32 products of mode 0 may be cut along K, the parts going here: scratch_floats floats, or NULL (no cutting)
+  float* scratch; size_t scratch_floats;
+  long part_stride;                          // (kernel argument: floats from one part to the next)
 };
 bool gemm_f32_covers(const GemmProblem& p);      // the operands can be read in 16-byte pieces; launch_gemm_f32 needs that
 int launch_gemm_f32(const GemmProblem& p, hipStream_t s);
-int gemm_f32_split_configure();                  // per-device set-up of the split kernels (moe_init)
 
 int launch_route(const float* logits, int T, int E, int k, int renorm, int e_lo, int e_hi, int n_groups, int capacity,
                  int32_t* idx, float* w, float* score, int32_t* counts, int32_t* offsets, int32_t* perm,

@@ -158,16 +158,55 @@ inline double f32_tiles64(const F32Product& p) {
 // 231, 192; 11264 of 25 58, 67).
 inline bool f32_split_pays(const F32Product& p) { return f32_tiles64(p) >= 192 && (p.rows || p.K > (long)kF32SplitStep * p.E); }
 
-// 128 x 128 tiles (one workgroup of eight waves per CU, which splits an element half as often), by the estimated time from
-// measured tiles: 64 x 64 0.85 us + 0.445 per step and CU, 128 x 128 3.5 + 1.33 in whole rounds.  (us, 64 and 128) weight gradients of 2000
-// rows, 8 experts, 1024 x 5632 192, 171, of 6 experts, 5632 x 128 45, 58; dgrad2 102, 94; FC2 109, 110, of 4500 rows, 4 experts 183, 223.
-// Segments of under four steps stay with the small tile (2816 tiles of three steps 32, 36).
-inline bool f32_split_in_128(const F32Product& p) {
+// 128 x 128 tiles (four waves, two workgroups per CU, an element split half as often) instead of 64 x 64 (three per CU): where they give
+// most CUs both, by the estimated time.  64 x 64 0.9 us + 0.5 per step for every tile of a CU; 128 x 128, up to 512 at a time, 6 us + 1.7 to
+// 3.3 per step, by how many of them there are.
+inline double f32_us64(double tiles, int steps) {
+  const double per_cu = (double)(((long)tiles + 255) / 256), step = 0.5 * per_cu;
+  return 0.9 * per_cu + (step > 0.7 ? step : 0.7) * steps;
+}
+inline double f32_us128(double tiles, int steps) {
+  const long whole = (long)tiles / 512;
+  const double rest = tiles - whole * 512.0;
+  const double rate = rest <= 256 ? 1.7 + 0.3 * rest / 256 : 2.45 + 0.9 * (rest - 256) / 256;
+  return whole * (6 + 3.35 * steps) + (rest < 1 ? 0 : 6 + rate * steps);
+}
+inline double f32_tiles128(const F32Product& p) {
   auto up = [](long a, long b) { return (a + b - 1) / b; };
-  const int steps = (int)up(p.rows ? p.K : p.K / p.E, kF32SplitStep);
-  const double tiles = up(p.N, 128) * (p.rows ? p.M / 128.0 + p.E / 2 : (double)up(p.M, 128) * p.E);
-  const long rounds = ((long)tiles + 255) / 256;
-  return steps >= 4 && rounds * (3.5 + 1.33 * steps) < f32_tiles64(p) / 256 * (0.85 + 0.445 * steps);
+  const double mt = p.rows ? p.M / 128.0 + p.E / 2 : (double)up(p.M, 128) * p.E;
+  return up(p.N, 128) * mt;
+}
+inline int f32_steps(const F32Product& p) {
+  const int k = p.rows ? p.K : p.K / p.E;
+  return (k + kF32SplitStep - 1) / kF32SplitStep;
+}
+inline bool f32_split_in_128(const F32Product& p) {
+  const double tiles = f32_tiles128(p);
+  return tiles >= 400 && f32_us128(tiles, f32_steps(p)) < f32_us64(f32_tiles64(p), f32_steps(p));
+}
+
+struct F32Plan { int large, parts; };      // 128 x 128 tiles; parts along K
+// With scratch for `room` results a product of row segments may be cut into up to that many parts (at most 6), which a kernel of its own adds:
+// 4 us and 1 per 8 MB.  FC2 and dgrad1 have few tiles and long contractions.  Measured (us with the addition, whole on 64 x 64 and cut): 8
+// experts, 1024 x 2816, 2000 rows FC2 138, 113 (128 x 128 in 3), dgrad1 288, 196 (in 3; in 2 247, in 5 223); 512 rows 62, 53 (64 x 64 in 4), 139, 104;
+// 16 experts, 768 x 2048, 1600 rows dgrad1 133, 115; 6 experts, 512 x 1408, 3000 rows dgrad1 90, 69; 4 experts, 1024 x 1408, 2060 rows 61, 56 and 125, 115.
+inline F32Plan f32_plan(const F32Product& p, long room) {
+  F32Plan best = {f32_split_in_128(p) ? 1 : 0, 1};
+  if (!p.rows || room < 2) return best;
+  const int steps = f32_steps(p);
+  const double t64 = f32_tiles64(p), t128 = f32_tiles128(p);
+  double best_us = best.large ? f32_us128(t128, steps) : f32_us64(t64, steps);
+  for (int n = 2; n <= (room < 6 ? room : 6) && steps / n >= 8; ++n) {
+    const int each = (steps + n - 1) / n;
+    const double add = 4 + (n + 1.0) * p.M * p.N * 4 / 8e6;
+    const double us64 = f32_us64(t64 * n, each) + add, us128 = f32_us128(t128 * n, each) + add;
+    const double us = us128 < us64 ? us128 : us64;
+    if (us < 0.95 * best_us) {
+      best_us = us;
+      best = {us128 < us64 ? 1 : 0, n};
+    }
+  }
+  return best;
 }
 
 }  // namespace moe

@@ -122,6 +122,46 @@ def test_split_products_are_as_close_as_fp32(rows, d, f):
             assert rel(got, ref) < tol, (name, e, rel(got, ref), tol)
 
 
+# FC2 and dgrad1 cut along K: 64 x 64 and 128 x 128 tiles, numbers of steps that the parts do not divide, a k tail of 16, rows past the
+# segments.  With the workspace of the forward alone FC2 is not cut.
+CUT = [([64, 0, 127, 1, 64, 40, 90, 126], 1024, 2832, 0), ([255, 1, 0, 700, 129, 300, 415, 200], 1024, 2832, 77), ([500, 511, 0, 1049], 1024, 1408, 3)]
+
+
+@pytest.mark.parametrize("rows,d,f,spare", CUT)
+def test_products_cut_along_k(rows, d, f, spare):
+    from paper_2505_11432_amd import binding as B
+    E, n = len(rows), sum(rows)
+    M = n + spare
+    xp, dyp, w1, w2 = inputs_f32(rows + [spare], d, f)
+    w1, w2 = w1[:E].contiguous(), w2[:E].contiguous()
+    offsets = torch.tensor([sum(rows[:e]) for e in range(E + 1)], dtype=torch.int32, device=DEV)
+    full, least = B.moe_workspace_bytes(M, d, E, 1, f, B.F32), -(-M * f * 4 // 256) * 256
+    out = []
+    for nbytes in (full, least):
+        h, yp = torch.full((M, 2 * f), 7.0, device=DEV), torch.full((M, d), 7.0, device=DEV)
+        ws = torch.full((nbytes + 256,), 0xff, dtype=torch.uint8, device=DEV)          # (NaN where a part would be read unwritten)
+        B.moe_expert_ffn_fwd(xp, None, offsets, w1, None, w2, None, h, yp, None, ws[:nbytes])
+        assert bool((ws[nbytes:] == 0xff).all()) and bool((yp[n:] == 7.0).all())
+        out.append(yp)
+    dxp, dw1, dw2 = torch.full((M, d), 7.0, device=DEV), torch.empty_like(w1), torch.empty_like(w2)
+    ws = torch.full((full,), 0xff, dtype=torch.uint8, device=DEV)
+    B.moe_expert_ffn_bwd(xp, h, dyp, None, offsets, w1, w2, dxp, dw1, dw2, 0, ws)
+    assert bool((dxp[n:] == 7.0).all())
+    at = 0
+    for e, k in enumerate(rows):
+        s, at = slice(at, at + k), at + k
+        if k == 0:
+            continue
+        a, b, DY = w1[e].double(), w2[e].double(), dyp[s].double()
+        G, U = h[s, :f].double(), h[s, f:].double()
+        sg = torch.sigmoid(G)
+        dA = DY @ b
+        dH = torch.cat([dA * U * sg * (1 + G * (1 - sg)), dA * G * sg], 1)
+        # the bound of the uncut products: sqrt(K / 2) roundings, and the operands' own
+        for got, ref, K in ((out[0][s], (G * sg * U) @ b.t(), f), (out[1][s], (G * sg * U) @ b.t(), f), (dxp[s], dH @ a, 2 * f)):
+            assert rel(got, ref) < (4 + 0.58 * math.sqrt(K / 2)) * 2.0 ** -24, (e, rel(got, ref))
+
+
 @pytest.mark.parametrize("rows,d,f", [SPLIT[1], LARGE])
 def test_split_weight_gradients_accumulate(rows, d, f):
     """accumulate = 1 adds the product, the same bits as without it, to what is there."""
