@@ -4,6 +4,7 @@
 //   d_w_r  two passes, no float atomics: each block owns a slab of columns of x and a chunk of tokens and
 //          keeps the sums of an expert tile in registers, gate gradients staged in LDS; a second kernel adds
 //          the per-chunk partials in a fixed order, so the result is reproducible.
+//   (small problems: d_w_r's first pass and dx in one launch)
 //   dx     one pass over dx: a block keeps its 512 columns of w_r in LDS, a lane owns 8 of them and walks the experts.
 #include "moe_common.h"
 
@@ -37,16 +38,14 @@ constexpr int kChunkTokens = 64;
 constexpr int kTokUnroll = 8;         // rows of x in flight per thread
 
 template <typename T, int ETILE, int COLS, bool TOK>
-__global__ void __launch_bounds__(256) router_dwr_partial_kernel(const T* __restrict__ x,
-                                                                 const float* __restrict__ d_logits, int Tn, int d,
-                                                                 int E, int tokens_per_chunk,
-                                                                 float* __restrict__ partial) {
+__device__ __forceinline__ void dwr_partial(int block, const T* __restrict__ x, const float* __restrict__ d_logits, int Tn, int d, int E,
+                                            int tokens_per_chunk, float* __restrict__ partial) {
   constexpr int kPart = !TOK ? 1 : ETILE * COLS < 32 ? ETILE : 32 / COLS;      // experts added through LDS at a time
   __shared__ __attribute__((aligned(16))) float g_lds[kChunkTokens][ETILE];
   __shared__ float part[TOK ? 3 : 1][kPart * COLS][64];
   constexpr int kSlab = (TOK ? 64 : 256) * COLS;
   const int slabs = (d + kSlab - 1) / kSlab;
-  const int slab = blockIdx.x % slabs, chunk = blockIdx.x / slabs;
+  const int slab = block % slabs, chunk = block / slabs;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = slab * kSlab + (TOK ? lane : (int)threadIdx.x) * COLS;
   const int t0 = chunk * tokens_per_chunk, t1 = min(t0 + tokens_per_chunk, Tn);
@@ -119,6 +118,12 @@ __global__ void __launch_bounds__(256) router_dwr_partial_kernel(const T* __rest
   }
 }
 
+template <typename T, int ETILE, int COLS, bool TOK>
+__global__ void __launch_bounds__(256) router_dwr_partial_kernel(const T* __restrict__ x, const float* __restrict__ d_logits, int Tn, int d,
+                                                                 int E, int tokens_per_chunk, float* __restrict__ partial) {
+  dwr_partial<T, ETILE, COLS, TOK>(blockIdx.x, x, d_logits, Tn, d, E, tokens_per_chunk, partial);
+}
+
 // d_w_r[i] = sum over the chunks of partial[c][i] in a fixed order: a block owns 64 outputs, its four waves each add
 // every fourth chunk (ascending), then the four sums are added in wave order.
 __global__ void __launch_bounds__(256) router_dwr_reduce_kernel(const float* __restrict__ partial, int chunks,
@@ -153,12 +158,12 @@ __global__ void __launch_bounds__(256) router_dwr_reduce_kernel(const float* __r
 constexpr int kDxCols = 512;
 
 template <typename T, int ETILE, bool kLaneGrads>
-__global__ void __launch_bounds__(256) router_dx_kernel(const T* __restrict__ w_r, const float* __restrict__ d_logits,
-                                                        int Tn, int d, int E, int token_groups, T* __restrict__ dx) {
+__device__ __forceinline__ void dx_slab(int block, const T* __restrict__ w_r, const float* __restrict__ d_logits, int Tn, int d, int E,
+                                        int token_groups, T* __restrict__ dx) {
   constexpr int V = 8;                                  // columns per lane
   __shared__ __attribute__((aligned(16))) T w_lds[ETILE][kDxCols];
   const int slabs = (d + kDxCols - 1) / kDxCols;
-  const int slab = blockIdx.x % slabs, tg = blockIdx.x / slabs;
+  const int slab = block % slabs, tg = block / slabs;
   const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
   const int col = slab * kDxCols + lane * V;
   const bool active = col < d;
@@ -236,6 +241,22 @@ __global__ void __launch_bounds__(256) router_dx_kernel(const T* __restrict__ w_
   }
 }
 
+template <typename T, int ETILE, bool kLaneGrads>
+__global__ void __launch_bounds__(256) router_dx_kernel(const T* __restrict__ w_r, const float* __restrict__ d_logits,
+                                                        int Tn, int d, int E, int token_groups, T* __restrict__ dx) {
+  dx_slab<T, ETILE, kLaneGrads>(blockIdx.x, w_r, d_logits, Tn, d, E, token_groups, dx);
+}
+
+// The partial sums of d_w_r and dx in one launch: both are chains of dependent loads with few blocks, and neither needs the other.  Blocks from
+// dwr_blocks on make dx.
+template <typename T, int ETILE, int COLS>
+__global__ void __launch_bounds__(256) router_bwd_kernel(const T* __restrict__ x, const T* __restrict__ w_r, const float* __restrict__ d_logits,
+                                                         int Tn, int d, int E, int tokens_per_chunk, float* __restrict__ partial,
+                                                         int dwr_blocks, int token_groups, T* __restrict__ dx) {
+  if ((int)blockIdx.x < dwr_blocks) dwr_partial<T, ETILE, COLS, true>(blockIdx.x, x, d_logits, Tn, d, E, tokens_per_chunk, partial);
+  else dx_slab<T, ETILE, true>(blockIdx.x - dwr_blocks, w_r, d_logits, Tn, d, E, token_groups, dx);
+}
+
 // ---- d_w_r on the matrix cores (many experts) -----------------------------------------------------------------
 // d_w_r = d_logits^T x is a weight-gradient GEMM with the tokens as contraction index: E output rows, d columns.
 // With 32 experts or more the vector-ALU kernel above is bound by its FMAs, so the grouped weight-gradient kernel is
@@ -308,10 +329,41 @@ int launch_router_bwd(const void* x, const void* w_r, const float* d_logits, moe
       router_dwr_reduce_kernel<<<(int)((nout + 63) / 64), 256, 0, s>>>(partial, chunks, nout, d_w_r);
       MOE_LAUNCH_CHECK();
     }
-  } else if (d_w_r) {
+  }
+  const int slabs = cdiv(d, kDxCols);
+  // bf16: what the LDS slab allows.  fp32 moves twice the bytes and is slower with more (T = 4096, d = 4096: E = 8 27.4, 29.3,
+  // 36.1 us with 2, 4, 8, E = 16 32.8, 36.5, 49.8).
+  const int per_cu = dt == MOE_F32 ? 2 : E <= 16 ? 8 : E <= 32 ? 4 : 2;
+  int token_groups = cdiv(256 * per_cu, slabs);
+  if (token_groups > cdiv(T, 16)) token_groups = cdiv(T, 16);
+  const int dx_blocks = slabs * token_groups;
+  bool dx_done = false;
+  if (!mfma_path && d_w_r) {
     const int chunks = dwr_chunks(T);
     const int tpc = dwr_tokens_per_chunk(T);
     float* partial = static_cast<float*>(ws);
+    // One launch with dx where d_w_r shares its tokens by waves and both together are at most four blocks per CU.  The whole call, two launches
+    // and one (us): fp32 256 tokens, d = 128, 8 experts 10.7, 6.4, 1000 x 1024 12.7, 8.3, 2000 x 2048, 16 experts 28.9, 22.3; bf16 1531 x 1040, 24
+    // experts 19.3, 16.1, 2000 x 2048, 16 experts 18.5, 14.6, 8000 x 256, 8 experts 14.2, 12.2.  (More experts: the two LDS shares together
+    // leave a CU one block.)
+    const int co = E <= 16 ? 4 : 2, dwr_blocks = cdiv(d, 64 * co) * chunks;
+    const size_t x_bytes = (size_t)T * d * dtype_size(dt);          // (dx written over x: in two launches, as d_w_r needs x as it was)
+    const bool apart = static_cast<const char*>(x) + x_bytes <= static_cast<const char*>(dx) || static_cast<const char*>(dx) + x_bytes <= static_cast<const char*>(x);
+    if (dx && apart && T > 8 && cdiv(d, 256 * co) * chunks < 256 && E <= (dt == MOE_F32 ? 16 : 32) && dwr_blocks + dx_blocks <= 1024) {
+#define MOE_JOINT_CASE(TT, ET, CO)                                                                                                  \
+  router_bwd_kernel<TT, ET, CO><<<dwr_blocks + dx_blocks, 256, 0, s>>>((const TT*)x, (const TT*)w_r, d_logits, T, d, E, tpc, partial, \
+                                                                       dwr_blocks, token_groups, (TT*)dx)
+      if (dt == MOE_F32) {
+        if (E <= 8) MOE_JOINT_CASE(float, 8, 4);
+        else MOE_JOINT_CASE(float, 16, 4);
+      } else {
+        if (E <= 8) MOE_JOINT_CASE(bf16, 8, 4);
+        else if (E <= 16) MOE_JOINT_CASE(bf16, 16, 4);
+        else MOE_JOINT_CASE(bf16, 32, 2);
+      }
+#undef MOE_JOINT_CASE
+      dx_done = true;
+    } else {
 #define MOE_DWR_CASE(TT, ET, CO)                                                                                    \
   do {                                                                                                              \
     if (T > 8 && cdiv(d, 256 * CO) * chunks < 256)                                                                  \
@@ -331,6 +383,7 @@ int launch_router_bwd(const void* x, const void* w_r, const float* d_logits, moe
       else MOE_DWR_CASE(bf16, 64, 2);
     }
 #undef MOE_DWR_CASE
+    }
     MOE_LAUNCH_CHECK();
     const long n = (long)E * d;
     const long blocks = (n + 63) / 64;
@@ -341,16 +394,9 @@ int launch_router_bwd(const void* x, const void* w_r, const float* d_logits, moe
     // dx is bf16: the hi part of the gate gradient alone is below its rounding (lo is 2^-9 of hi)
     const int rc = mfma_router_dx(hi, w_r, T, d, E, dx, s);
     if (rc != MOE_OK) return rc;
-  } else if (dx && T > 0) {
-    const int slabs = cdiv(d, kDxCols);
-    // bf16: what the LDS slab allows.  fp32 moves twice the bytes and is slower with more (T = 4096, d = 4096: E = 8 27.4, 29.3,
-    // 36.1 us with 2, 4, 8, E = 16 32.8, 36.5, 49.8).
-    const int per_cu = dt == MOE_F32 ? 2 : E <= 16 ? 8 : E <= 32 ? 4 : 2;
-    int token_groups = cdiv(256 * per_cu, slabs);
-    if (token_groups > cdiv(T, 16)) token_groups = cdiv(T, 16);
-    const int blocks = slabs * token_groups;
-    const bool scalar = dt == MOE_BF16 && E > 16 && blocks > 256 && (E <= 32 || d <= 2048);
-#define MOE_DX_CASE(TT, ET, LANE) router_dx_kernel<TT, ET, LANE><<<blocks, 256, 0, s>>>((const TT*)w_r, d_logits, T, d, E, token_groups, (TT*)dx)
+  } else if (dx && T > 0 && !dx_done) {
+    const bool scalar = dt == MOE_BF16 && E > 16 && dx_blocks > 256 && (E <= 32 || d <= 2048);
+#define MOE_DX_CASE(TT, ET, LANE) router_dx_kernel<TT, ET, LANE><<<dx_blocks, 256, 0, s>>>((const TT*)w_r, d_logits, T, d, E, token_groups, (TT*)dx)
 #define MOE_DX_TYPE(TT)                        \
   if (E <= 8) MOE_DX_CASE(TT, 8, true);        \
   else if (E <= 16) MOE_DX_CASE(TT, 16, true); \

@@ -203,3 +203,29 @@ def test_route_lane_keys(T, E, k, quantum):
 @pytest.mark.parametrize("T,E,k", [(33000, 20, 3), (32768, 256, 4)])
 def test_route_nan_last_of_many_tokens(T, E, k):
     test_route_nan_last(T, E, k)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("T,d,E", [(9, 16, 1), (65, 528, 8), (257, 272, 9), (1000, 1040, 16), (300, 4096, 17), (1531, 1040, 24), (70, 48, 31),
+                                   (16000, 256, 8), (4097, 272, 12)])
+def test_router_gradients_in_one_launch(T, d, E, dtype):
+    """d_w_r and dx asked for together (one launch up to 1024 blocks, 16 experts in fp32 and 31 in bf16) and one by one: the same sums in
+    the same order, bit for bit; against float64 (sums of T and of E terms); and dx written over x."""
+    from paper_2505_11432_amd import binding as B
+    g = torch.Generator(device=DEV).manual_seed(T + d)
+    rnd = lambda *s: torch.randn(s, generator=g, device=DEV)
+    x, w, dz, dx0 = rnd(T, d).to(dtype), rnd(E, d).to(dtype), rnd(T, E), rnd(T, d).to(dtype)
+    ws = torch.empty(max(B.moe_workspace_bytes(T, d, E, 1, 16, B.dtype_code(dtype)), 256), dtype=torch.uint8, device=DEV)
+    both_w, one_w = torch.empty((E, d), device=DEV), torch.empty((E, d), device=DEV)
+    both_x, one_x, over_x = dx0.clone(), dx0.clone(), x.clone()
+    B.moe_router_bwd(x, w, dz, both_w, both_x, ws)
+    B.moe_router_bwd(x, w, dz, one_w, None, ws)
+    B.moe_router_bwd(x, w, dz, None, one_x, ws)
+    assert torch.equal(both_w, one_w) and torch.equal(both_x, one_x)
+    ref_w, ref_x = dz.double().t() @ x.double(), dz.double() @ w.double()
+    assert float((both_w.double() - ref_w).norm() / ref_w.norm()) < 2.0 ** -24 * (T ** 0.5 + 4)
+    want = dx0.double() + ref_x
+    assert float((both_x.double() - want).norm() / want.norm()) < (2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -24 * (E ** 0.5 + 4))
+    over_w = torch.empty((E, d), device=DEV)
+    B.moe_router_bwd(over_x, w, dz, over_w, over_x, ws)
+    assert torch.equal(over_w, one_w)
