@@ -135,23 +135,19 @@ static int ffn_bwd_f32(const void* xp, const void* h_save, const void* d_yp, con
   g.A = d_yp; g.a_rs = 1; g.a_cs = d;
   g.B = A_used; g.b_es = 0; g.b_rs = f; g.b_cs = 1;
   g.C = d_w2; g.c_es = (long)d * f; g.ldc = f; g.M = d; g.N = f; g.K = M;
-  rc = launch_gemm_f32(g, s);
-  if (rc != MOE_OK) return rc;
-  // d_xp[M,d] = dH[M,2f] * w1[e]   (contraction over 2f); A and dA are done with
+  const GemmProblem dw2 = g;
+  // d_w1[e][2f,d] = dH_e^T * xp_e
+  g.A = dH; g.a_rs = 1; g.a_cs = 2L * f;
+  g.B = xp; g.b_es = 0; g.b_rs = d; g.b_cs = 1;
+  g.C = d_w1; g.c_es = 2L * f * d; g.ldc = d; g.M = 2 * f; g.N = d; g.K = M;
+  const GemmProblem dw1 = g;
+  // d_xp[M,d] = dH[M,2f] * w1[e]   (contraction over 2f); where it is cut along K, A and dA are done with by then
   g.mode = 0; g.accumulate = 0;
   g.scratch = static_cast<float*>(A); g.scratch_floats = 2 * align_up((size_t)M * f * es, 256) / es;
   g.A = dH; g.a_rs = 2L * f; g.a_cs = 1;
   g.B = w1; g.b_es = 2L * f * d; g.b_rs = d; g.b_cs = 1;
   g.C = d_xp; g.c_es = 0; g.ldc = d; g.M = M; g.N = d; g.K = 2 * f;
-  rc = launch_gemm_f32(g, s);
-  if (rc != MOE_OK) return rc;
-  g.scratch = nullptr;
-  // d_w1[e][2f,d] = dH_e^T * xp_e
-  g.mode = 1; g.accumulate = accumulate;
-  g.A = dH; g.a_rs = 1; g.a_cs = 2L * f;
-  g.B = xp; g.b_es = 0; g.b_rs = d; g.b_cs = 1;
-  g.C = d_w1; g.c_es = 2L * f * d; g.ldc = d; g.M = 2 * f; g.N = d; g.K = M;
-  return launch_gemm_f32(g, s);
+  return launch_gemm_f32_trio(dw2, g, dw1, s);
 }
 
 }  // namespace moe

@@ -73,16 +73,20 @@ __device__ __forceinline__ f32x4 frag(const float* lds, int x, int k8, int half)
   }
 }
 
+// Floats of LDS of a workgroup: two stages
+template <int BM, int BN, int BK, bool AK, bool BKF> constexpr int kLdsFloats = 2 * (Tile<AK, BM, BK>::FLOATS + Tile<BKF, BN, BK>::FLOATS);
+
+// The tile of workgroup `block` of `blocks`
 template <int BM, int BN, int BK, int WM, int WN, int WK, bool AK, bool BKF>
-__global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmProblem p, int tiles_n, int tiles_m_fixed, int blocks) {
+__device__ __forceinline__ void gemm_f32_tile(const GemmProblem& p, int tiles_n, int tiles_m_fixed, int block, int blocks, float* lds_floats) {
   static_assert(WM * WN * WK == 4 && BM == 32 * WM && BN == 32 * WN && BK % (8 * WK) == 0, "four waves of 32 x 32");
   using TA = Tile<AK, BM, BK>;
   using TB = Tile<BKF, BN, BK>;
-  __shared__ __attribute__((aligned(16))) float lds[2][TA::FLOATS + TB::FLOATS];
-  static_assert(sizeof(lds) >= (WK - 1) * WM * WN * 32 * 32 * 4, "the sums that change waves fit");
+  constexpr int STAGE = TA::FLOATS + TB::FLOATS;
+  static_assert(2 * STAGE >= (WK - 1) * WM * WN * 32 * 32, "the sums that change waves fit");
 
   F32Tile t;
-  if (!f32_tile<BM, BN>(p, tiles_n, tiles_m_fixed, blocks, t)) return;
+  if (!f32_tile<BM, BN>(p, tiles_n, tiles_m_fixed, block, blocks, t)) return;
   const int e = t.e, m0 = t.m0, m_end = t.m_end, n0 = t.n0, k0 = t.k0, k_end = t.k_end;
   const float* __restrict__ A = static_cast<const float*>(p.A);
   const float* __restrict__ B = static_cast<const float*>(p.B) + (long)e * p.b_es;
@@ -102,12 +106,12 @@ __global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmProblem p, int t
     fetch<BKF, BN, BK>(B, ldb, n0, p.N - n0, k, k_end, rb[set]);
   };
   auto put = [&](int set, int buf) __attribute__((always_inline)) {
-    stash<AK, BM, BK>(lds[buf], ra[set]);
-    stash<BKF, BN, BK>(lds[buf] + TA::FLOATS, rb[set]);
+    stash<AK, BM, BK>(lds_floats + buf * STAGE, ra[set]);
+    stash<BKF, BN, BK>(lds_floats + buf * STAGE + TA::FLOATS, rb[set]);
   };
   auto multiply = [&](int buf) __attribute__((always_inline)) {
-    const float* at = lds[buf];
-    const float* bt = lds[buf] + TA::FLOATS;
+    const float* at = lds_floats + buf * STAGE;
+    const float* bt = at + TA::FLOATS;
 #pragma unroll
     for (int g = 0; g < BK / 8 / WK; ++g) {
       const int k8 = (wk * (BK / 8 / WK) + g) * 8;
@@ -141,7 +145,7 @@ __global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmProblem p, int t
   if constexpr (WK > 1) {
     // (the loop ended with a barrier, or never started) the other waves of an output hand their sums to its first one,
     // which adds them in wave order
-    float* part = &lds[0][0] + (wm * WN + wn) * (WK - 1) * 1024;
+    float* part = lds_floats + (wm * WN + wn) * (WK - 1) * 1024;
     if (wk > 0)
 #pragma unroll
       for (int r = 0; r < 16; ++r) part[((wk - 1) * 16 + r) * 64 + lane] = acc[r];
@@ -166,6 +170,32 @@ __global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmProblem p, int t
     if (p.accumulate) v += *dst;
     *dst = v;
   }
+}
+
+template <int BM, int BN, int BK, int WM, int WN, int WK, bool AK, bool BKF>
+__global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmProblem p, int tiles_n, int tiles_m_fixed, int blocks) {
+  __shared__ __attribute__((aligned(16))) float lds[kLdsFloats<BM, BN, BK, AK, BKF>];
+  gemm_f32_tile<BM, BN, BK, WM, WN, WK, AK, BKF>(p, tiles_n, tiles_m_fixed, blockIdx.x, blocks, lds);
+}
+
+// The three products at the end of a backward, d_w2, d_xp and d_w1, in one launch where each is small: none needs another, and alone each leaves
+// most of the chip idle behind a chain of dependent loads.
+constexpr int kSmall = 32, kSmallK = 64;
+struct SmallTrio { GemmProblem p[3]; int tiles_n[3], tiles_m[3], blocks[3]; };
+__global__ void __launch_bounds__(kThreads) gemm_f32_trio_kernel(SmallTrio t) {
+  constexpr int kWgrad = kLdsFloats<kSmall, kSmall, kSmallK, false, false>, kDgrad = kLdsFloats<kSmall, kSmall, kSmallK, true, false>;
+  __shared__ __attribute__((aligned(16))) float lds[kWgrad > kDgrad ? kWgrad : kDgrad];
+  int b = blockIdx.x;
+  if (b < t.blocks[0]) {
+    gemm_f32_tile<kSmall, kSmall, kSmallK, 1, 1, 4, false, false>(t.p[0], t.tiles_n[0], t.tiles_m[0], b, t.blocks[0], lds);
+    return;
+  }
+  b -= t.blocks[0];
+  if (b < t.blocks[1]) {
+    gemm_f32_tile<kSmall, kSmall, kSmallK, 1, 1, 4, true, false>(t.p[1], t.tiles_n[1], t.tiles_m[1], b, t.blocks[1], lds);
+    return;
+  }
+  gemm_f32_tile<kSmall, kSmall, kSmallK, 1, 1, 4, false, false>(t.p[2], t.tiles_n[2], t.tiles_m[2], b - t.blocks[1], t.blocks[2], lds);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int WK>
@@ -205,16 +235,47 @@ bool gemm_f32_covers(const GemmProblem& p) {
 // the logits and up to four 64 x 64 tiles per CU, where two waves share an output and each sums half as long a chain (the average
 // segment is short, the longest may not be), 64 x 64 for longer lists of weight gradients and for what a launch of 64 x 32 could not hold
 // (less than 2^32 threads).  Other expert products of so many tiles come only with rows of 2^20 elements and at the limit of a launch.
+static long tiles64(const GemmProblem& p) {
+  const long tiles_m = (long)cdiv(p.M, 64) + (p.mode == 0 ? p.E / 2 : 0);      // segments end inside a tile
+  return (long)cdiv(p.N, 64) * tiles_m * (p.mode == 1 ? p.E : 1);
+}
 int launch_gemm_f32(const GemmProblem& p, hipStream_t s) {
   if (p.M <= 0 || p.N <= 0) return MOE_OK;
   if (gemm_f32_splits(p)) return launch_gemm_f32_split(p, s);
   const bool a_kfast = p.a_cs == 1, b_kfast = p.b_rs == 1;
-  const long tiles_m = (long)cdiv(p.M, 64) + (p.mode == 0 ? p.E / 2 : 0);      // segments end inside a tile
-  const long tiles = (long)cdiv(p.N, 64) * tiles_m * (p.mode == 1 ? p.E : 1);
+  const long tiles = tiles64(p);
   if (tiles < 256) return launch<32, 32, 64, 1, 1, 4>(p, a_kfast, b_kfast, s);
   const long narrow = (long)cdiv(p.N, 32) * (cdiv(p.M, 64) + (p.mode == 0 ? (long)p.E : 0)) * (p.mode == 1 ? p.E : 1);      // 64 x 32 workgroups
   if (tiles < 1024 || (b_kfast && narrow * kThreads < 1L << 32)) return launch<64, 32, 32, 2, 1, 2>(p, a_kfast, b_kfast, s);
   return launch<64, 64, 32, 2, 2, 1>(p, a_kfast, b_kfast, s);
+}
+
+// d_w2, d_xp and d_w1 of a backward: one launch where each would go to 32 x 32 tiles, else one by one in this order.
+int launch_gemm_f32_trio(const GemmProblem& dw2, const GemmProblem& dxp, const GemmProblem& dw1, hipStream_t s) {
+  const GemmProblem* p[3] = {&dw2, &dxp, &dw1};
+  SmallTrio t{};
+  long all = 0;
+  bool small = true;
+  for (int i = 0; i < 3; ++i) {
+    const bool a_kfast = p[i]->a_cs == 1, b_kfast = p[i]->b_rs == 1;
+    small = small && p[i]->M > 0 && p[i]->N > 0 && a_kfast == (i == 1) && !b_kfast && !gemm_f32_splits(*p[i]) && tiles64(*p[i]) < 256;
+    const long blocks = f32_blocks(*p[i], kSmall, kSmall);
+    t.p[i] = *p[i];
+    t.tiles_n[i] = cdiv(p[i]->N, kSmall);
+    t.tiles_m[i] = cdiv(p[i]->M, kSmall);
+    t.blocks[i] = (int)blocks;
+    all += blocks;
+  }
+  if (small && all <= 0x7fffff) {
+    gemm_f32_trio_kernel<<<dim3((unsigned)all), dim3(kThreads), 0, s>>>(t);
+    MOE_LAUNCH_CHECK();
+    return MOE_OK;
+  }
+  for (int i = 0; i < 3; ++i) {
+    const int rc = launch_gemm_f32(*p[i], s);
+    if (rc != MOE_OK) return rc;
+  }
+  return MOE_OK;
 }
 
 }  // namespace moe

@@ -145,7 +145,7 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_f32_split_kernel(GemmPro
   extern __shared__ __attribute__((aligned(16))) char lds[];        // two stages
   __shared__ int redo;
   F32Tile t;
-  if (!f32_tile<BM, BN>(p, tiles_n, tiles_m_fixed, blocks, t)) return;
+  if (!f32_tile<BM, BN>(p, tiles_n, tiles_m_fixed, blockIdx.x, blocks, t)) return;
   part_of_tile(t);
   const int m0 = t.m0, m_end = t.m_end, n0 = t.n0, klen = t.k_end - t.k0;
   const int lane = threadIdx.x & 63;
@@ -382,7 +382,7 @@ __global__ void __launch_bounds__(256, 2) gemm_f32_split128_kernel(GemmProblem p
   extern __shared__ __attribute__((aligned(16))) char lds[];
   __shared__ int redo;
   F32Tile t;
-  if (!f32_tile<BM, BN>(p, tiles_n, tiles_m_fixed, blocks, t)) return;
+  if (!f32_tile<BM, BN>(p, tiles_n, tiles_m_fixed, blockIdx.x, blocks, t)) return;
   part_of_tile(t);
   const int m0 = t.m0, m_end = t.m_end, n0 = t.n0, klen = t.k_end - t.k0;
   const int lane = threadIdx.x & 63;

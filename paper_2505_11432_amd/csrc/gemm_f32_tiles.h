@@ -42,11 +42,11 @@ struct F32Tile {
   int k0, k_end;                // the contraction
 };
 
-// The tile of this workgroup; false where the grid, which is sized for any segments, has one too many.
+// The tile of workgroup `block` of `blocks`; false where the grid, which is sized for any segments, has one too many.
 template <int BM, int BN>
-__device__ __forceinline__ bool f32_tile(const GemmProblem& p, int tiles_n, int tiles_m_fixed, int blocks, F32Tile& t) {
+__device__ __forceinline__ bool f32_tile(const GemmProblem& p, int tiles_n, int tiles_m_fixed, int block, int blocks, F32Tile& t) {
   // runs of kF32Window consecutive tiles go to one XCD (workgroup b runs on XCD b % 8) so that its L2 serves their panels
-  int l = blockIdx.x;
+  int l = block;
   const int span = kF32Xcds * kF32Window, first = l / span * span;
   if (first + span <= blocks) l = first + (l % kF32Xcds) * kF32Window + (l - first) / kF32Xcds;
   int m_lo = 0, mt_e = tiles_m_fixed;

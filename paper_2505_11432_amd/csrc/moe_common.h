@@ -74,6 +74,7 @@ struct GemmProblem {
 };
 bool gemm_f32_covers(const GemmProblem& p);      // the operands can be read in 16-byte pieces; launch_gemm_f32 needs that
 int launch_gemm_f32(const GemmProblem& p, hipStream_t s);
+int launch_gemm_f32_trio(const GemmProblem& dw2, const GemmProblem& dxp, const GemmProblem& dw1, hipStream_t s);
 
 int launch_route(const float* logits, int T, int E, int k, int renorm, int e_lo, int e_hi, int n_groups, int capacity,
                  int32_t* idx, float* w, float* score, int32_t* counts, int32_t* offsets, int32_t* perm,
