@@ -46,16 +46,14 @@ static int ffn_fwd_f32(const void* xp, const int32_t* offsets, const void* w1, c
   g.C = h_save; g.c_es = 0; g.ldc = 2L * f; g.N = 2 * f; g.K = d;
   int rc = launch_gemm_f32(g, s);
   if (rc != MOE_OK) return rc;
-  rc = launch_swiglu_fwd(h_save, A, M, f, offsets + E, MOE_F32, s);
-  if (rc != MOE_OK) return rc;
-  // FC2: yp[M,d] = A[M,f] * w2[e]^T
+  // A = SwiGLU(H), FC2: yp[M,d] = A[M,f] * w2[e]^T
   g.A = A; g.a_rs = f; g.a_cs = 1;
   g.B = w2; g.b_es = (long)d * f; g.b_rs = 1; g.b_cs = f;
   g.C = yp; g.ldc = d; g.N = d; g.K = f;
   // a workspace sized for the backward as well has room behind A
   g.scratch = reinterpret_cast<float*>(static_cast<char*>(ws) + a_bytes);
   g.scratch_floats = (ws_bytes - a_bytes) / sizeof(float);
-  return launch_gemm_f32(g, s);
+  return launch_gemm_f32_fc2(g, h_save, A, s);
 }
 
 // bf16: every GEMM on the matrix cores, SwiGLU and its derivative fused into the FC1 / dgrad2 epilogues.
@@ -121,14 +119,12 @@ static int ffn_bwd_f32(const void* xp, const void* h_save, const void* d_yp, con
   const void* A_used = a_override ? a_override : A;
   GemmProblem g{};
   g.offsets = offsets; g.E = E; g.bias = nullptr;
-  // dA[M,f] = d_yp[M,d] * w2[e]   (contraction over d)
+  // dA[M,f] = d_yp[M,d] * w2[e]   (contraction over d), then SwiGLU'
   g.mode = 0; g.M = M; g.accumulate = 0;
   g.A = d_yp; g.a_rs = d; g.a_cs = 1;
   g.B = w2; g.b_es = (long)d * f; g.b_rs = f; g.b_cs = 1;
   g.C = dA; g.c_es = 0; g.ldc = f; g.N = f; g.K = d;
-  rc = launch_gemm_f32(g, s);
-  if (rc != MOE_OK) return rc;
-  rc = launch_swiglu_bwd(h_save, dA, dH, a_override ? nullptr : A, M, f, offsets + E, MOE_F32, s);   // recomputes the FC2 input
+  rc = launch_gemm_f32_dgrad2(g, h_save, dH, a_override ? nullptr : A, s);      // recomputes the FC2 input
   if (rc != MOE_OK) return rc;
   // d_w2[e][d,f] = d_yp_e^T * A_e   (contraction over the expert's rows)
   g.mode = 1; g.accumulate = accumulate;

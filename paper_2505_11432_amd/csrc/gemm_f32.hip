@@ -10,6 +10,8 @@
 //   64 x 64, k-steps of 32;  64 x 32, two waves per output, k-steps of 32;  32 x 32, four per output, k-steps of 64.
 // All keep two k-steps of global loads in registers ahead of the LDS stage that is being multiplied; several workgroups
 // share a CU and hide each other's latency.
+// A small layer (256 tokens, d = 128, f = 256, 8 experts) is launches, not arithmetic: its backward's last three products share one (80.8 ->
+// 71.0 us, forward and backward), and the SwiGLU passes go into the products beside them (71.0 -> 67.2).
 // Measured (a vector-ALU kernel of 64 x 64 x 16 first): router logits of 1000 tokens 182 -> 13 us.
 #include "gemm_f32_tiles.h"
 
@@ -38,9 +40,10 @@ template <bool KFAST, int EXT, int BK> struct Tile {
 // Operand piece -> registers.  ext0 / ext_n: first row (column) of the tile and the number of valid ones; k is absolute,
 // k_end its end.  Rows past the end repeat the last valid one (they only reach outputs that are not stored); pieces past
 // the end of the contraction are zero.
-template <bool KFAST, int EXT, int BK>
+// GLU: the operand is SwiGLU(G, U), G at `base` and U `glu` elements further on in every row.
+template <bool KFAST, int EXT, int BK, bool GLU = false>
 __device__ __forceinline__ void fetch(const float* __restrict__ base, long ld, int ext0, int ext_n, int k, int k_end,
-                                      f32x4 (&out)[Tile<KFAST, EXT, BK>::VECS]) {
+                                      f32x4 (&out)[Tile<KFAST, EXT, BK>::VECS], int glu = 0) {
   using TL = Tile<KFAST, EXT, BK>;
 #pragma unroll
   for (int v = 0; v < TL::VECS; ++v) {
@@ -49,7 +52,14 @@ __device__ __forceinline__ void fetch(const float* __restrict__ base, long ld, i
     const int x = KFAST ? min(r, ext_n - 1) : min(c, ext_n - 4);
     const float* p = base + (KFAST ? (long)(ext0 + x) * ld + kk : (long)kk * ld + ext0 + x);
     f32x4 t = {0.f, 0.f, 0.f, 0.f};
-    if (kk < k_end) t = *reinterpret_cast<const f32x4*>(p);
+    if (kk < k_end) {
+      t = *reinterpret_cast<const f32x4*>(p);
+      if constexpr (GLU) {
+        const f32x4 u = *reinterpret_cast<const f32x4*>(p + glu);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) t[j] = t[j] * sigmoid_f32(t[j]) * u[j];
+      }
+    }
     out[v] = t;
   }
 }
@@ -76,9 +86,15 @@ __device__ __forceinline__ f32x4 frag(const float* lds, int x, int k8, int half)
 // Floats of LDS of a workgroup: two stages
 template <int BM, int BN, int BK, bool AK, bool BKF> constexpr int kLdsFloats = 2 * (Tile<AK, BM, BK>::FLOATS + Tile<BKF, BN, BK>::FLOATS);
 
+// What a small layer's products take over from the SwiGLU passes: FC2 makes its A operand from H = [G|U] as it loads it; dgrad2 turns the dA
+// it has summed into dH and, where A_out is given, the SwiGLU output.
+enum Fuse { PLAIN, FROM_H, TO_DH };
+struct SwigluArgs { const float* H; float* dH; float* A_out; };
+
 // The tile of workgroup `block` of `blocks`
-template <int BM, int BN, int BK, int WM, int WN, int WK, bool AK, bool BKF>
-__device__ __forceinline__ void gemm_f32_tile(const GemmProblem& p, int tiles_n, int tiles_m_fixed, int block, int blocks, float* lds_floats) {
+template <int BM, int BN, int BK, int WM, int WN, int WK, bool AK, bool BKF, Fuse FUSE = PLAIN>
+__device__ __forceinline__ void gemm_f32_tile(const GemmProblem& p, int tiles_n, int tiles_m_fixed, int block, int blocks, float* lds_floats,
+                                              const SwigluArgs& sw = SwigluArgs{}) {
   static_assert(WM * WN * WK == 4 && BM == 32 * WM && BN == 32 * WN && BK % (8 * WK) == 0, "four waves of 32 x 32");
   using TA = Tile<AK, BM, BK>;
   using TB = Tile<BKF, BN, BK>;
@@ -102,7 +118,7 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmProblem& p, int tiles_n,
 
   f32x4 ra[2][TA::VECS], rb[2][TB::VECS];
   auto load = [&](int set, int k) __attribute__((always_inline)) {
-    fetch<AK, BM, BK>(A, lda, m0, m_end - m0, k, k_end, ra[set]);
+    fetch<AK, BM, BK, FUSE == FROM_H>(A, lda, m0, m_end - m0, k, k_end, ra[set], p.K);
     fetch<BKF, BN, BK>(B, ldb, n0, p.N - n0, k, k_end, rb[set]);
   };
   auto put = [&](int set, int buf) __attribute__((always_inline)) {
@@ -142,6 +158,36 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmProblem& p, int tiles_n,
       __syncthreads();
     }
   }
+  if constexpr (FUSE == TO_DH) {
+    // every wave takes a quarter of the rows (a lane's values r = 4 * wk + i), summed in the order of the waves
+    static_assert(BM == 32 && BN == 32 && WK == 4, "one output of 32 x 32");
+    static_assert(2 * STAGE >= 4 * 1024, "the sums of all waves fit");
+    const int n = n0 + (lane & 31), f = p.N, mb = m0 + wk * 8 + half * 4;
+    float gate[4], up[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float* h = sw.H + (long)min(mb + i, m_end - 1) * 2 * f + min(n, f - 1);
+      gate[i] = h[0];
+      up[i] = h[f];
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) lds_floats[(wk * 16 + r) * 64 + lane] = acc[r];
+    __syncthreads();
+    if (n >= f) return;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (mb + i >= m_end) continue;
+      float d = lds_floats[(wk * 4 + i) * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) d += lds_floats[(w * 16 + wk * 4 + i) * 64 + lane];
+      const float g = gate[i], u = up[i], s = sigmoid_f32(g);
+      float* dh = sw.dH + (long)(mb + i) * 2 * f + n;
+      dh[0] = d * u * s * (1.0f + g * (1.0f - s));
+      dh[f] = d * g * s;
+      if (sw.A_out) sw.A_out[(long)(mb + i) * f + n] = g * s * u;
+    }
+    return;
+  }
   if constexpr (WK > 1) {
     // (the loop ended with a barrier, or never started) the other waves of an output hand their sums to its first one,
     // which adds them in wave order
@@ -178,9 +224,15 @@ __global__ void __launch_bounds__(kThreads) gemm_f32_kernel(GemmProblem p, int t
   gemm_f32_tile<BM, BN, BK, WM, WN, WK, AK, BKF>(p, tiles_n, tiles_m_fixed, blockIdx.x, blocks, lds);
 }
 
+constexpr int kSmall = 32, kSmallK = 64;
+template <bool BKF, Fuse FUSE>
+__global__ void __launch_bounds__(kThreads) gemm_f32_swiglu_kernel(GemmProblem p, int tiles_n, int blocks, SwigluArgs sw) {
+  __shared__ __attribute__((aligned(16))) float lds[kLdsFloats<kSmall, kSmall, kSmallK, true, BKF>];
+  gemm_f32_tile<kSmall, kSmall, kSmallK, 1, 1, 4, true, BKF, FUSE>(p, tiles_n, 0, blockIdx.x, blocks, lds, sw);
+}
+
 // The three products at the end of a backward, d_w2, d_xp and d_w1, in one launch where each is small: none needs another, and alone each leaves
 // most of the chip idle behind a chain of dependent loads.
-constexpr int kSmall = 32, kSmallK = 64;
 struct SmallTrio { GemmProblem p[3]; int tiles_n[3], tiles_m[3], blocks[3]; };
 __global__ void __launch_bounds__(kThreads) gemm_f32_trio_kernel(SmallTrio t) {
   constexpr int kWgrad = kLdsFloats<kSmall, kSmall, kSmallK, false, false>, kDgrad = kLdsFloats<kSmall, kSmall, kSmallK, true, false>;
@@ -250,15 +302,45 @@ int launch_gemm_f32(const GemmProblem& p, hipStream_t s) {
   return launch<64, 64, 32, 2, 2, 1>(p, a_kfast, b_kfast, s);
 }
 
+// True for a product that goes to 32 x 32 tiles.
+static bool small(const GemmProblem& p) { return p.M > 0 && p.N > 0 && !gemm_f32_splits(p) && tiles64(p) < 256; }
+
+// H -> yp: SwiGLU into A and FC2 (fc2, which reads A), or both in one launch of small tiles.
+int launch_gemm_f32_fc2(const GemmProblem& fc2, const void* H, void* A, hipStream_t s) {
+  if (small(fc2)) {
+    GemmProblem p = fc2;
+    p.A = H;
+    p.a_rs = 2L * fc2.K;
+    const int blocks = (int)f32_blocks(p, kSmall, kSmall);
+    gemm_f32_swiglu_kernel<true, FROM_H><<<dim3((unsigned)blocks), dim3(kThreads), 0, s>>>(p, cdiv(p.N, kSmall), blocks, SwigluArgs{});
+    MOE_LAUNCH_CHECK();
+    return MOE_OK;
+  }
+  const int rc = launch_swiglu_fwd(H, A, fc2.M, fc2.K, fc2.offsets + fc2.E, MOE_F32, s);
+  return rc != MOE_OK ? rc : launch_gemm_f32(fc2, s);
+}
+// d_yp -> dH and, unless A is NULL, the FC2 input again: dgrad2 (which writes dA) and SwiGLU', or both in one launch of small tiles.
+int launch_gemm_f32_dgrad2(const GemmProblem& dgrad2, const void* H, void* dH, void* A, hipStream_t s) {
+  if (small(dgrad2)) {
+    const int blocks = (int)f32_blocks(dgrad2, kSmall, kSmall);
+    gemm_f32_swiglu_kernel<false, TO_DH><<<dim3((unsigned)blocks), dim3(kThreads), 0, s>>>(
+        dgrad2, cdiv(dgrad2.N, kSmall), blocks, SwigluArgs{static_cast<const float*>(H), static_cast<float*>(dH), static_cast<float*>(A)});
+    MOE_LAUNCH_CHECK();
+    return MOE_OK;
+  }
+  const int rc = launch_gemm_f32(dgrad2, s);
+  return rc != MOE_OK ? rc : launch_swiglu_bwd(H, dgrad2.C, dH, A, dgrad2.M, dgrad2.N, dgrad2.offsets + dgrad2.E, MOE_F32, s);
+}
+
 // d_w2, d_xp and d_w1 of a backward: one launch where each would go to 32 x 32 tiles, else one by one in this order.
 int launch_gemm_f32_trio(const GemmProblem& dw2, const GemmProblem& dxp, const GemmProblem& dw1, hipStream_t s) {
   const GemmProblem* p[3] = {&dw2, &dxp, &dw1};
   SmallTrio t{};
   long all = 0;
-  bool small = true;
+  bool joint = true;
   for (int i = 0; i < 3; ++i) {
     const bool a_kfast = p[i]->a_cs == 1, b_kfast = p[i]->b_rs == 1;
-    small = small && p[i]->M > 0 && p[i]->N > 0 && a_kfast == (i == 1) && !b_kfast && !gemm_f32_splits(*p[i]) && tiles64(*p[i]) < 256;
+    joint = joint && small(*p[i]) && a_kfast == (i == 1) && !b_kfast;
     const long blocks = f32_blocks(*p[i], kSmall, kSmall);
     t.p[i] = *p[i];
     t.tiles_n[i] = cdiv(p[i]->N, kSmall);
@@ -266,7 +348,7 @@ int launch_gemm_f32_trio(const GemmProblem& dw2, const GemmProblem& dxp, const G
     t.blocks[i] = (int)blocks;
     all += blocks;
   }
-  if (small && all <= 0x7fffff) {
+  if (joint && all <= 0x7fffff) {
     gemm_f32_trio_kernel<<<dim3((unsigned)all), dim3(kThreads), 0, s>>>(t);
     MOE_LAUNCH_CHECK();
     return MOE_OK;

@@ -74,6 +74,8 @@ struct GemmProblem {
 };
 bool gemm_f32_covers(const GemmProblem& p);      // the operands can be read in 16-byte pieces; launch_gemm_f32 needs that
 int launch_gemm_f32(const GemmProblem& p, hipStream_t s);
+int launch_gemm_f32_fc2(const GemmProblem& fc2, const void* H, void* A, hipStream_t s);
+int launch_gemm_f32_dgrad2(const GemmProblem& dgrad2, const void* H, void* dH, void* A, hipStream_t s);
 int launch_gemm_f32_trio(const GemmProblem& dw2, const GemmProblem& dxp, const GemmProblem& dw1, hipStream_t s);
 
 int launch_route(const float* logits, int T, int E, int k, int renorm, int e_lo, int e_hi, int n_groups, int capacity,

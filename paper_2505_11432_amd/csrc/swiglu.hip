@@ -1,6 +1,6 @@
 // SwiGLU between FC1 and FC2 (Section 4.1) and its derivative, as stand-alone HBM-bound
 // kernels: A = G/(1+exp(-G)) * U on H = [G|U], and (dG, dU) from (G, U, dA), with A again when asked (one pass over H
-// instead of two for the fp32 backward: 29 -> 19 us on 2000 x 5632).
+// instead of two for the fp32 backward: 29 -> 19 us on 2000 x 5632).  Small fp32 layers have both inside their products (gemm_f32.hip).
 // 16-byte vectors per lane, one row segment per block column; rows at or beyond *row_limit
 // (the number of dispatched rows, read on the device) are left untouched.
 #include "moe_common.h"
