@@ -464,7 +464,8 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
   // k-steps of time after the one before, and walk the contraction from as many k-steps further on, wrapping around: at any moment
   // all of them are at the same k and go on sharing panels in their L2.  (Late starts without the rotation bring nothing: the late ones
   // find their panels in L2, run faster and catch up.)  Sizes and figures: stagger in row_plan.h.
-  constexpr bool STAGGER = MODE != PLAIN && BM == 256 && BN == 256;
+  // (FC1 and the weight gradients; what the rotated walk costs in the loop, up to a percent, the others do not get back.)
+  constexpr bool STAGGER = (MODE == KSEG || SWI) && BM == 256 && BN == 256;
   const int lag = STAGGER ? __builtin_amdgcn_readfirstlane(in_window * p.stagger.groups / window * p.stagger.lag) : 0;
 
   // tile state
@@ -729,9 +730,10 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
       }
     }
   };
+  // whole k-steps only: every touched address exists
   auto touch = [&](int s) __attribute__((always_inline)) {
     const int ks = walk(s);
-    if ((ks + 1) * BKT <= klen) touch4s(a_base + (long)ks * a_step, ta_off, lds_dump);      // whole k-steps only: every touched address exists
+    if (is_toucher & (s < nk) & ((ks + 1) * BKT <= klen)) touch4s(a_base + (long)ks * a_step, ta_off, lds_dump);
   };
   auto issue_prologue = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -855,7 +857,11 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
           for (int p = 0; p < PHASES; ++p) {
             constexpr int TOUCH_AT = PHASES >= 2 ? PHASES - 2 : 0;      // one phase ahead of the refill it runs before (later: slower)
             if constexpr (TOUCH || TOUCH_K2) {
-              if (p == TOUCH_AT && is_toucher && kt + NSTAGE < nk) touch(kt + NSTAGE);
+              if constexpr (STAGGER) {
+                if (p == TOUCH_AT) touch(kt + NSTAGE);
+              } else {
+                if (p == TOUCH_AT && is_toucher && (kt + NSTAGE + 1) * BKT <= klen) touch4s(a_base + (long)(kt + NSTAGE) * a_step, ta_off, lds_dump);
+              }
             }
             const bool last = p + 1 == PHASES;
             const int pn = (p + 1) % PHASES, kn = pn / NPH;
@@ -991,7 +997,7 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
       // the first touch of the k loop is for step 2.  (8 experts, 16384 rows, 4096 x 14336, staggered: d_w1 3460 -> 3365 us, d_w2 1722 ->
       // 1714; FC1 2803 -> 2828, without stagger nothing)
       if constexpr (TOUCH_K2) {
-        if (is_toucher && nk > 1) touch(1);
+        touch(1);
       }
     }
     {
