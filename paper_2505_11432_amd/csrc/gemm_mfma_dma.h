@@ -422,7 +422,9 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
+  // Waves w and w + 4 of eight share a SIMD: they lie in opposite halves of the tile along both sides, so that a tile whose second half holds
+  // nothing, along either, leaves every SIMD one wave to multiply.
+  const int wm = wave / WN, wn = wave % WN ^ (SPLIT && wave >= NL ? WN / 2 : 0);
   const char* zero = reinterpret_cast<const char*>(g_zero_block);
   char* stg = smem + RING_BYTES + TABLE_BYTES + wave * STG_BYTES;      // this wave's epilogue patch
   // where this lane's fragments of the wave's first rows lie in a ring slot
@@ -801,10 +803,13 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
         __syncthreads();
         if (s + NSTAGE - 1 < nk) issue(s + NSTAGE - 1);
       };
-      // A wave whose rows all lie past the expert's last row has nothing to multiply (wave-uniform; it still issues
-      // its loads and takes part in the barriers).  In a nearly empty last tile of an expert only one or two waves
-      // per CU then use the matrix cores, and the k-step shrinks to what the loads need.
-      const bool wave_active = MODE != ROWSEG || m0 + wm * WTM < m_end;
+      // A wave whose rows all lie past the last one (of the expert, or of the gradient), or whose columns all lie past the width, has nothing
+      // to multiply (wave-uniform; it still issues its loads and takes part in the barriers).  In a nearly empty last tile only one or two
+      // waves per CU then use the matrix cores, and the k-step shrinks to what the loads need.
+      // Eight waves, columns and gradient rows as well (us): 64 experts, 131072 rows, 2048 x 1408 d_w2 741 -> 717, dgrad1 1252 -> 1231; 8 experts,
+      // 16384 rows, 1040 x 1424 d_w2 59 -> 57, dgrad1 127 -> 123, d_w1 117 -> 112, FC2 94 -> 92.  (Four waves have no partner on their SIMD.)
+      const bool wave_active = SPLIT ? m0 + wm * WTM < m_end && n0 + wn * (SWI ? WTN / 2 : WTN) < (SWI ? p.f : p.N)
+                                     : MODE != ROWSEG || m0 + wm * WTM < m_end;
       if (!wave_active) {
         for (int s = 0; s < nk; ++s) open_step(s);
       } else if (nk > 0) {
