@@ -40,10 +40,9 @@ template <bool KFAST, int EXT, int BK> struct Tile {
 // Operand piece -> registers.  ext0 / ext_n: first row (column) of the tile and the number of valid ones; k is absolute,
 // k_end its end.  Rows past the end repeat the last valid one (they only reach outputs that are not stored); pieces past
 // the end of the contraction are zero.
-// GLU: the operand is SwiGLU(G, U), G at `base` and U `glu` elements further on in every row.
-template <bool KFAST, int EXT, int BK, bool GLU = false>
+template <bool KFAST, int EXT, int BK>
 __device__ __forceinline__ void fetch(const float* __restrict__ base, long ld, int ext0, int ext_n, int k, int k_end,
-                                      f32x4 (&out)[Tile<KFAST, EXT, BK>::VECS], int glu = 0) {
+                                      f32x4 (&out)[Tile<KFAST, EXT, BK>::VECS]) {
   using TL = Tile<KFAST, EXT, BK>;
 #pragma unroll
   for (int v = 0; v < TL::VECS; ++v) {
@@ -52,14 +51,7 @@ __device__ __forceinline__ void fetch(const float* __restrict__ base, long ld, i
     const int x = KFAST ? min(r, ext_n - 1) : min(c, ext_n - 4);
     const float* p = base + (KFAST ? (long)(ext0 + x) * ld + kk : (long)kk * ld + ext0 + x);
     f32x4 t = {0.f, 0.f, 0.f, 0.f};
-    if (kk < k_end) {
-      t = *reinterpret_cast<const f32x4*>(p);
-      if constexpr (GLU) {
-        const f32x4 u = *reinterpret_cast<const f32x4*>(p + glu);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) t[j] = t[j] * sigmoid_f32(t[j]) * u[j];
-      }
-    }
+    if (kk < k_end) t = *reinterpret_cast<const f32x4*>(p);
     out[v] = t;
   }
 }
@@ -86,7 +78,7 @@ __device__ __forceinline__ f32x4 frag(const float* lds, int x, int k8, int half)
 // Floats of LDS of a workgroup: two stages
 template <int BM, int BN, int BK, bool AK, bool BKF> constexpr int kLdsFloats = 2 * (Tile<AK, BM, BK>::FLOATS + Tile<BKF, BN, BK>::FLOATS);
 
-// What a small layer's products take over from the SwiGLU passes: FC2 makes its A operand from H = [G|U] as it loads it; dgrad2 turns the dA
+// What a small layer's products take over from the SwiGLU passes: FC2 makes its A operand from H = [G|U] on the way to LDS; dgrad2 turns the dA
 // it has summed into dH and, where A_out is given, the SwiGLU output.
 enum Fuse { PLAIN, FROM_H, TO_DH };
 struct SwigluArgs { const float* H; float* dH; float* A_out; };
@@ -117,11 +109,18 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmProblem& p, int tiles_n,
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 
   f32x4 ra[2][TA::VECS], rb[2][TB::VECS];
+  f32x4 up_in[2][FUSE == FROM_H ? TA::VECS : 1];         // U beside the G in ra
   auto load = [&](int set, int k) __attribute__((always_inline)) {
-    fetch<AK, BM, BK, FUSE == FROM_H>(A, lda, m0, m_end - m0, k, k_end, ra[set], p.K);
+    fetch<AK, BM, BK>(A, lda, m0, m_end - m0, k, k_end, ra[set]);
+    if constexpr (FUSE == FROM_H) fetch<AK, BM, BK>(A + p.K, lda, m0, m_end - m0, k, k_end, up_in[set]);
     fetch<BKF, BN, BK>(B, ldb, n0, p.N - n0, k, k_end, rb[set]);
   };
   auto put = [&](int set, int buf) __attribute__((always_inline)) {
+    if constexpr (FUSE == FROM_H)
+#pragma unroll
+      for (int v = 0; v < TA::VECS; ++v)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) ra[set][v][j] = ra[set][v][j] * sigmoid_f32(ra[set][v][j]) * up_in[set][v][j];
     stash<AK, BM, BK>(lds_floats + buf * STAGE, ra[set]);
     stash<BKF, BN, BK>(lds_floats + buf * STAGE + TA::FLOATS, rb[set]);
   };
