@@ -11,7 +11,7 @@
 // All keep two k-steps of global loads in registers ahead of the LDS stage that is being multiplied; several workgroups
 // share a CU and hide each other's latency.
 // A small layer (256 tokens, d = 128, f = 256, 8 experts) is launches, not arithmetic: its backward's last three products share one (80.8 ->
-// 71.0 us, forward and backward), and the SwiGLU passes go into the products beside them (71.0 -> 67.2).
+// 71.0 us, forward and backward), and the SwiGLU passes go into the products beside them (71.0 -> 65.2).
 // Measured (a vector-ALU kernel of 64 x 64 x 16 first): router logits of 1000 tokens 182 -> 13 us.
 #include "gemm_f32_tiles.h"
 
@@ -304,13 +304,16 @@ int launch_gemm_f32(const GemmProblem& p, hipStream_t s) {
 // True for a product that goes to 32 x 32 tiles.
 static bool small(const GemmProblem& p) { return p.M > 0 && p.N > 0 && !gemm_f32_splits(p) && tiles64(p) < 256; }
 
-// H -> yp: SwiGLU into A and FC2 (fc2, which reads A), or both in one launch of small tiles.
+// H -> yp: SwiGLU into A and FC2 (fc2, which reads A), or both in one launch of small tiles.  Every column of tiles makes A again, which costs
+// more than a launch where a CU has a long contraction or several tiles.  SwiGLU and FC2, one launch (us, 32 x 32 tiles on a CU times K): 1024
+// 20.5, 18.4; 1024 17.0, 14.4; 1536 28.0, 26.6; 2816 47, 57; 3072 28.8, 30.3; 5632 49.6, 54.
 int launch_gemm_f32_fc2(const GemmProblem& fc2, const void* H, void* A, hipStream_t s) {
-  if (small(fc2)) {
+  const long blocks32 = f32_blocks(fc2, kSmall, kSmall);
+  if (small(fc2) && (blocks32 + 255) / 256 * fc2.K <= 2048) {
     GemmProblem p = fc2;
     p.A = H;
     p.a_rs = 2L * fc2.K;
-    const int blocks = (int)f32_blocks(p, kSmall, kSmall);
+    const int blocks = (int)blocks32;
     gemm_f32_swiglu_kernel<true, FROM_H><<<dim3((unsigned)blocks), dim3(kThreads), 0, s>>>(p, cdiv(p.N, kSmall), blocks, SwigluArgs{});
     MOE_LAUNCH_CHECK();
     return MOE_OK;
