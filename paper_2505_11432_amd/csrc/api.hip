@@ -169,6 +169,8 @@ const char* moe_status_string(int status) {
 int moe_init(void) {
   int rc = mfma_configure_all();
   if (rc != MOE_OK) return rc;
+  rc = gemm_f32_split_configure();
+  if (rc != MOE_OK) return rc;
   return route_noalloc_prepare();
 }
 

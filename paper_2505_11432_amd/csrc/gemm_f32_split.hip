@@ -16,11 +16,13 @@
 // Each operand element is split once per tile by the thread that loads it, so larger tiles split less often.  Measured (us, operands from
 // memory; the fp32 instruction, then the split as it is now; 8 experts, 2000 rows, d = 1024, f = 2816): FC1 238, 218; FC2 137, 111; dgrad2 115, 106;
 // wgrad2 117, 105; dgrad1 271, 189; wgrad1 229, 188.  128 x 128 tiles by eight waves of 32 x 64 with two stages in LDS, one workgroup per CU, on
-// the same box: 229, 137, 121, 115, 286, 207 (4400 rows 353, 199, 205, 182, 423, 335, now 325, 199, 171, 166, 322, 305).
+// the same box: 229, 137, 121, 115, 286, 207 (4400 rows 353, 199, 205, 182, 423, 335, now 325, 199, 171, 166, 322, 305).  They stay for a single round (f32_split_in_eight).
 // Not faster (FC1, 2000 rows, against 195): the two workgroups as one, taking turns by barriers (191, weight gradients 15 % slower); 32 x 32
 // instructions with the split between their products, the parts written behind the barrier (200; loads of whole lines by four k per lane
 // changed nothing); a higher wave priority while multiplying (180 to 225, dgrad1 15 % slower).  64 x 64 tiles: one wave per SIMD,
 // fragments read ahead across the step barrier, products and split interleaved by scheduling barriers changed nothing or lost.
+#include <atomic>
+
 #include "gemm_f32_tiles.h"
 #include "row_plan.h"
 
@@ -541,15 +543,16 @@ __global__ void __launch_bounds__(256) f32_add_parts_kernel(const float* __restr
   }
 }
 
+constexpr int kLds = 12 * Part<64>::BYTES, kLdsEight = 12 * Part<128>::BYTES;      // two stages
+static_assert(kLds == 6 * Part<128>::BYTES, "one stage of 128 x 128");
 
 template <bool AK, bool BKF> int launch_as(const GemmProblem& p, F32Plan plan, hipStream_t s) {
-  const int b = plan.large ? 128 : 64;
-  const long blocks = f32_blocks(p, b, b);
+  const int b = plan.tile == F32_64 ? 64 : 128;
+  const int blocks = (int)f32_blocks(p, b, b), tiles_n = cdiv(p.N, b), tiles_m = cdiv(p.M, b);
   const dim3 grid((unsigned)blocks, (unsigned)plan.parts);
-  const int bytes = 6 * Part<64>::BYTES * 2;          // two stages of 64 x 64, one of 128 x 128
-  static_assert(Part<128>::BYTES == 2 * Part<64>::BYTES, "the same bytes");
-  if (plan.large) gemm_f32_split128_kernel<AK, BKF><<<grid, dim3(256), bytes, s>>>(p, cdiv(p.N, b), cdiv(p.M, b), (int)blocks);
-  else gemm_f32_split_kernel<64, 64, 2, 2, AK, BKF><<<grid, dim3(256), bytes, s>>>(p, cdiv(p.N, b), cdiv(p.M, b), (int)blocks);
+  if (plan.tile == F32_128_EIGHT) gemm_f32_split_kernel<128, 128, 4, 2, AK, BKF><<<grid, dim3(512), kLdsEight, s>>>(p, tiles_n, tiles_m, blocks);
+  else if (plan.tile == F32_128) gemm_f32_split128_kernel<AK, BKF><<<grid, dim3(256), kLds, s>>>(p, tiles_n, tiles_m, blocks);
+  else gemm_f32_split_kernel<64, 64, 2, 2, AK, BKF><<<grid, dim3(256), kLds, s>>>(p, tiles_n, tiles_m, blocks);
   MOE_LAUNCH_CHECK();
   return MOE_OK;
 }
@@ -573,6 +576,8 @@ bool gemm_f32_splits(const GemmProblem& p) {
 int launch_gemm_f32_split(const GemmProblem& p, hipStream_t s) {
   const size_t one = (size_t)p.M * p.N;
   const F32Plan plan = f32_plan({p.mode == 0, p.M, p.N, p.K, p.E}, p.scratch && !p.accumulate ? (long)(p.scratch_floats / one) : 0);
+  if (plan.tile == F32_128_EIGHT)
+    if (const int rc = gemm_f32_split_configure()) return rc;
   GemmProblem q = p;
   if (plan.parts > 1) {
     q.C = p.scratch; q.ldc = p.N; q.part_stride = (long)one;
@@ -583,6 +588,21 @@ int launch_gemm_f32_split(const GemmProblem& p, hipStream_t s) {
   f32_add_parts_kernel<<<dim3((unsigned)(quads < 256 * 2048 ? (quads + 255) / 256 : 2048)), dim3(256), 0, s>>>(
       p.scratch, q.part_stride, plan.parts, p.offsets, p.E, p.M, p.N, static_cast<float*>(p.C), p.ldc);
   MOE_LAUNCH_CHECK();
+  return MOE_OK;
+}
+
+// The tiles of eight waves need their dynamic-LDS limit raised once per device; moe_init does it ahead of a graph capture.  The
+// values are the same on every call, the bit only saves work.
+int gemm_f32_split_configure() {
+  static std::atomic<unsigned long long> done{0};
+  int dev = 0;
+  MOE_HIP_TRY(hipGetDevice(&dev));
+  if (dev < 0 || dev >= 64) return MOE_ERR_UNSUPPORTED;
+  if (done.load(std::memory_order_acquire) >> dev & 1) return MOE_OK;
+  for (const void* k : {(const void*)gemm_f32_split_kernel<128, 128, 4, 2, true, true>, (const void*)gemm_f32_split_kernel<128, 128, 4, 2, true, false>,
+                        (const void*)gemm_f32_split_kernel<128, 128, 4, 2, false, false>})
+    MOE_HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsEight));
+  done.fetch_or(1ull << dev, std::memory_order_release);
   return MOE_OK;
 }
 

@@ -77,6 +77,7 @@ int launch_gemm_f32(const GemmProblem& p, hipStream_t s);
 int launch_gemm_f32_fc2(const GemmProblem& fc2, const void* H, void* A, hipStream_t s);
 int launch_gemm_f32_dgrad2(const GemmProblem& dgrad2, const void* H, void* dH, void* A, hipStream_t s);
 int launch_gemm_f32_trio(const GemmProblem& dw2, const GemmProblem& dxp, const GemmProblem& dw1, hipStream_t s);
+int gemm_f32_split_configure();                  // per-device set-up of the split kernels (moe_init)
 
 int launch_route(const float* logits, int T, int E, int k, int renorm, int e_lo, int e_hi, int n_groups, int capacity,
                  int32_t* idx, float* w, float* score, int32_t* counts, int32_t* offsets, int32_t* perm,

@@ -185,17 +185,26 @@ inline bool f32_split_in_128(const F32Product& p) {
   return tiles >= 400 && f32_us128(tiles, f32_steps(p)) < f32_us64(f32_tiles64(p), f32_steps(p));
 }
 
-struct F32Plan { int large, parts; };      // 128 x 128 tiles; parts along K
+// One round of 128 x 128 tiles by eight waves with two stages, 3.5 us + 1.33 per step: alone on a CU they beat four waves with one.  Weight
+// gradients of 256 such tiles (us, 64 x 64, four waves, eight): 10 steps 26.1, -, 22.1; 16 steps -, 37.3, 31.4; 24 steps -, 50.5, 42.8; 4 steps 14.6, -, 13.4.
+inline double f32_us_eight(int steps) { return 3.5 + 1.33 * steps; }
+inline bool f32_split_in_eight(const F32Product& p) {
+  const int steps = f32_steps(p);
+  return steps >= 4 && f32_tiles128(p) <= 256 && f32_us_eight(steps) < f32_tiles64(p) / 256 * (0.85 + 0.445 * steps);
+}
+
+enum F32Shape { F32_64, F32_128, F32_128_EIGHT };
+struct F32Plan { F32Shape tile; int parts; };      // parts along K
 // With scratch for `room` results a product of row segments may be cut into up to that many parts (at most 6), which a kernel of its own adds:
 // 4 us and 1 per 8 MB.  FC2 and dgrad1 have few tiles and long contractions.  Measured (us with the addition, whole on 64 x 64 and cut): 8
 // experts, 1024 x 2816, 2000 rows FC2 138, 113 (128 x 128 in 3), dgrad1 288, 196 (in 3; in 2 247, in 5 223); 512 rows 62, 53 (64 x 64 in 4), 139, 104;
 // 16 experts, 768 x 2048, 1600 rows dgrad1 133, 115; 6 experts, 512 x 1408, 3000 rows dgrad1 90, 69; 4 experts, 1024 x 1408, 2060 rows 61, 56 and 125, 115.
 inline F32Plan f32_plan(const F32Product& p, long room) {
-  F32Plan best = {f32_split_in_128(p) ? 1 : 0, 1};
+  F32Plan best = {f32_split_in_128(p) ? F32_128 : f32_split_in_eight(p) ? F32_128_EIGHT : F32_64, 1};
   if (!p.rows || room < 2) return best;
   const int steps = f32_steps(p);
   const double t64 = f32_tiles64(p), t128 = f32_tiles128(p);
-  double best_us = best.large ? f32_us128(t128, steps) : f32_us64(t64, steps);
+  double best_us = best.tile == F32_128 ? f32_us128(t128, steps) : best.tile == F32_128_EIGHT ? f32_us_eight(steps) : f32_us64(t64, steps);
   for (int n = 2; n <= (room < 6 ? room : 6) && steps / n >= 8; ++n) {
     const int each = (steps + n - 1) / n;
     const double add = 4 + (n + 1.0) * p.M * p.N * 4 / 8e6;
@@ -203,7 +212,7 @@ inline F32Plan f32_plan(const F32Product& p, long room) {
     const double us = us128 < us64 ? us128 : us64;
     if (us < 0.95 * best_us) {
       best_us = us;
-      best = {us128 < us64 ? 1 : 0, n};
+      best = {us128 < us64 ? F32_128 : F32_64, n};
     }
   }
   return best;
