@@ -50,7 +50,7 @@ struct Args {
   // that run on different workgroups and write fp32 partial tiles here ([part][BM][BN]); splitk_fixup_kernel
   // adds the parts and writes C.  NULL: no splitting.
   float* splitk_ws;
-  Stagger stagger;                   // FC1 and weight gradients on 256 x 256 tiles: groups of workgroups that start one after another
+  Stagger stagger;                   // e4m3 FC1 and weight gradients on 256 x 256 tiles: groups of workgroups that start one after another
   // Section 4.1 / 4.2 order (EPI_SWIGLU_W, EPI_SWIGLU_BWD_W)
   const int32_t* a_rowmap;           // EPI_SWIGLU_W: logical row r of A is row a_rowmap[r] of the buffer ([M] entries)
   int a_phys_rows;                   //   rows of that buffer (for the 32-bit offset check)

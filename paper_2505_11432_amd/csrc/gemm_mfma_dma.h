@@ -465,14 +465,15 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
   // workgroups 2.2, 2.3, 3.0, 5.9, 12.1 us; 32 of one XCD alone 6.6).  The workgroups of an XCD therefore start in groups, each `lag`
   // k-steps of time after the one before, and walk the contraction from as many k-steps further on, wrapping around: at any moment
   // all of them are at the same k and go on sharing panels in their L2.  (Late starts without the rotation bring nothing: the late ones
-  // find their panels in L2, run faster and catch up.)  Sizes and figures: stagger in row_plan.h.
-  // (FC1 and the weight gradients; what the rotated walk costs in the loop, up to a percent, the others do not get back.)
-  constexpr bool STAGGER = (MODE == KSEG || SWI) && BM == 256 && BN == 256;
+  // find their panels in L2, run faster and catch up.)  Sizes and figures: Stagger in row_plan.h.
+  // Only for e4m3: the walk decides the order in which a tile's products are added.  In bf16 equal rows and weights get equal bits whichever
+  // workgroup has the tile, and whole layers gained no more than 1 % by it.
+  constexpr bool STAGGER = FP8 && (MODE == KSEG || SWI) && BM == 256 && BN == 256;
   const int lag = STAGGER ? __builtin_amdgcn_readfirstlane(in_window * p.stagger.groups / window * p.stagger.lag) : 0;
 
   // tile state
   int e = 0, m0 = 0, m_end = 0, n0 = 0, klen = 0, nk = 0;
-  int k_start = 0;                  // k-step this workgroup's walk begins at (see walk)
+  int k_start = 0;                  // k-step this workgroup's walk begins at (see issue)
   int part_slot = -1;               // >= 0: this work item is one K part of a split tile; index of its partial tile
   const bool is_loader = !SPLIT || wave < NL;            // wave-uniform; the lower waves win issue arbitration
   const int lw = wave & (NL - 1);                        // loader index
@@ -673,20 +674,15 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
   // 14336 334, 303, 304, FC2 180, 168, 155; 64 experts, 32 rows, FC1 of 2048 x 1408 164, 143, 143; 8 experts, 8 rows, FC1 of
   // 2048 x 8192 116, 96, 97.  A start of its own for every workgroup of an XCD: 362, 159, 141, 106.
   constexpr bool KROT = (MODE == ROWSEG && BM <= 128) || STAGGER;
-  // k-step of the contraction that step s of this workgroup's walk multiplies
-  auto walk = [&](int s) __attribute__((always_inline)) -> int {
-    if constexpr (KROT) {
-      s += k_start;
-      if (s >= nk) s -= nk;
-    }
-    return s;
-  };
   // Issue the loads of k-step `ks` of the open tile into ring slot ks % NSTAGE.  Only the last step can be ragged.
   auto issue = [&](int ks) __attribute__((always_inline)) {
     if (!is_loader) return;
     const int ring = ks % NSTAGE;
     const unsigned stage = smem_lds + (unsigned)ring * STAGE_BYTES;
-    ks = walk(ks);
+    if constexpr (KROT) {
+      ks += k_start;
+      if (ks >= nk) ks -= nk;
+    }
     const int k_left = klen - ks * BKT;          // valid k in this step
     const char* ab = a_base + (long)ks * a_step;     // scalar arithmetic
     const char* bb = b_base + (long)ks * b_step;
@@ -731,11 +727,6 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
         dma16(b_k0 + ((j + rot_b) % B_DMA) * B_KSTEP >= k_left ? zero : bb + off, stage + A_BYTES + (unsigned)(lw + ((j + rot_b) % B_DMA) * NL) * 1024u);
       }
     }
-  };
-  // whole k-steps only: every touched address exists
-  auto touch = [&](int s) __attribute__((always_inline)) {
-    const int ks = walk(s);
-    if (is_toucher & (s < nk) & ((ks + 1) * BKT <= klen)) touch4s(a_base + (long)ks * a_step, ta_off, lds_dump);
   };
   auto issue_prologue = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -862,10 +853,8 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
           for (int p = 0; p < PHASES; ++p) {
             constexpr int TOUCH_AT = PHASES >= 2 ? PHASES - 2 : 0;      // one phase ahead of the refill it runs before (later: slower)
             if constexpr (TOUCH || TOUCH_K2) {
-              if constexpr (STAGGER) {
-                if (p == TOUCH_AT) touch(kt + NSTAGE);
-              } else {
-                if (p == TOUCH_AT && is_toucher && (kt + NSTAGE + 1) * BKT <= klen) touch4s(a_base + (long)(kt + NSTAGE) * a_step, ta_off, lds_dump);
+              if (p == TOUCH_AT && is_toucher && (kt + NSTAGE + 1) * BKT <= klen) {   // whole k-steps only: every touched address exists
+                touch4s(a_base + (long)(kt + NSTAGE) * a_step, ta_off, lds_dump);
               }
             }
             const bool last = p + 1 == PHASES;
@@ -999,11 +988,6 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
     const bool has_next = open_tile(slot);
     if (has_next) {
       issue_prologue();
-      // the first touch of the k loop is for step 2.  (8 experts, 16384 rows, 4096 x 14336, staggered: d_w1 3460 -> 3365 us, d_w2 1722 ->
-      // 1714; FC1 2803 -> 2828, without stagger nothing)
-      if constexpr (TOUCH_K2) {
-        touch(1);
-      }
     }
     {
       const int e = ep_e, m0 = ep_m0, m_end = ep_m_end, n0 = ep_n0;

@@ -70,21 +70,12 @@ inline double pairs_us(double tiles, const PairCost& c, int steps) {
   return whole * round_us + (rem < 1 ? 0 : rem <= 256 && half_us < round_us ? half_us : round_us);
 }
 
-// Groups of workgroups that start one after another (see STAGGER in gemm_mfma_dma.h), so that their epilogues do not meet.  The late
-// groups end late, (groups - 1) * lag steps of 1.5 us; a round gains 2 to 5 us: from five rounds on, and not where a tile has fewer steps
-// than the groups lie apart (16 experts, 115 rows, 16832 x 432, two steps 129 -> 142 us).  Launches of 8 experts, 16384 rows, 4096 x 14336
-// (us, at once and {groups, lag}; a few passes on a cool chip): FC1 2942, {4, 3} 2855, {8, 1} 2835, {8, 3} 2852; d_w2 1838, {2, 3} 1715,
-// {4, 3} 1715, {8, 1} 1681; d_w1 3507, {2, 3} 3442, {4, 3} 3383, {8, 1} 3500; e4m3 FC1 1698, {4, 3} 1604, {8, 2} 1568, d_w2 1143, {8, 3} 1065,
-// d_w1 2268, {4, 3} 2377, {8, 3} 2253.  64 experts, 131072 rows, 2048 x 1408: FC1 1379, {8, 1} 1300; d_w2 736, {4, 3} 727; d_w1 1405, {4, 3}
-// 1357.  Short contractions lie closer, or their groups spend most of a tile on different panels: d_w2 / d_w1 of 16 experts, 1024 x 8192, 400
-// rows 192/363, {4, 3} 179/336, {4, 1} 169/326; of 8, 2048 x 8192, 512 rows 210/385, 201/391, 190/380; of 4, 4096 x 14336, 768 rows 456/870,
-// 460/895, 433/893; of 16, 2048 x 4096, 1024 rows 324/608, 313/621, 309/613.  In passes without a pause the chip lowers its clock for what the launches no longer wait: whole layers 1.005, 1.015
-// (e4m3) and 1.016 of the speed.
-inline Stagger fc1_stagger(bool e4m3, double tiles, int steps) { return tiles < 5 * 256 || steps < 4 ? Stagger{} : e4m3 ? Stagger{8, 2} : Stagger{8, 1}; }
-inline Stagger wgrad_stagger(long tiles, int steps, bool e4m3) {
-  if (tiles < 5 * 256 || steps < 4) return {};
-  return e4m3 ? Stagger{8, 3} : Stagger{4, steps < 20 ? 1 : steps < 30 ? 2 : 3};
-}
+// Groups of workgroups that start one after another (e4m3, see STAGGER in gemm_mfma_dma.h), so that their epilogues do not meet.  The late
+// groups end late, (groups - 1) * lag steps of 1.5 us; a round gains 2 to 5 us: from five rounds on.  Launches of 8 experts, 16384 rows,
+// 4096 x 14336 (us, at once and {groups, lag}; a few passes on a cool chip): FC1 1698, {4, 3} 1604, {8, 2} 1568, d_w2 1143, {8, 3} 1065, d_w1
+// 2268, {4, 3} 2377, {8, 3} 2253.
+inline Stagger fc1_stagger(double tiles, int steps) { return tiles < 5 * 256 || steps < 4 ? Stagger{} : Stagger{8, 2}; }
+inline Stagger wgrad_stagger(long tiles, int steps) { return tiles < 5 * 256 || steps < 4 ? Stagger{} : Stagger{8, 3}; }
 
 // N: output columns (SwiGLU: f); K in elements of esz bytes
 inline RowPlan plan_rows(RowKind kind, int M, int E, int N, int K, int esz) {
@@ -115,7 +106,7 @@ inline RowPlan plan_rows(RowKind kind, int M, int E, int N, int K, int esz) {
     if (pair_us < full_us && pair_us < mid_us) return {RowTile::MID, false, true};
   }
   if (mid_us < full_us) return {RowTile::MID, split_mid};
-  return {RowTile::FULL, split_full, false, kind.swiglu ? fc1_stagger(esz == 1, even(256, 256), steps) : Stagger{}};
+  return {RowTile::FULL, split_full, false, kind.swiglu && esz == 1 ? fc1_stagger(even(256, 256), steps) : Stagger{}};
 }
 
 // How a launch's last round is dealt.  The tile list goes to the eight XCDs in windows, one tile per CU; `left` of its `items` tiles are

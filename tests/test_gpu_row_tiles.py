@@ -68,10 +68,32 @@ def test_bf16_and_fused_below_the_bound(rows, spare):
     check_bf16_and_fused(rows, 272, 336, spare)
 
 
-def test_bf16_and_fused_in_staggered_groups():
-    """Five and more rounds of 256 x 256 tiles (FC1, d_w1): workgroups start in groups and walk the contraction from different
-    steps on; segments of fewer steps than the groups lie apart, of none, one and two, and with a remainder."""
+def test_bf16_and_fused_in_many_rounds():
+    """Six and more rounds of 256 x 256 tiles (FC1, d_w1): segments of no, one and two steps of contraction, and with a remainder."""
     check_bf16_and_fused([0, 3, 700, 64, 2500, 65, 3668, 1000], 1040, 6160, 0)
+
+
+def test_equal_tiles_get_equal_bits():
+    """On 256 x 256 tiles FC1 and the weight gradients add their products in the order of the contraction, whichever workgroup has the tile:
+    experts that hold the same rows and weights get the same bits.  Seven rounds of tiles and more, and no expert's tiles are a multiple of
+    the 32 workgroups of an XCD, so that other workgroups get the next expert's."""
+    from paper_2505_11432_amd import binding as B
+    E, n, d, f = 8, 512, 4096, 10368
+    M = E * n
+    g = torch.Generator(device=DEV).manual_seed(1)
+    rnd = lambda *s: torch.randn(s, generator=g, device=DEV, dtype=torch.bfloat16)
+    same = lambda t: t.expand(E, *t.shape).contiguous()
+    x, dy, w1, w2 = same(rnd(n, d)).view(M, d), same(rnd(n, d)).view(M, d), same(rnd(2 * f, d) / 64), same(rnd(d, f) / 101)
+    offsets = torch.arange(E + 1, dtype=torch.int32, device=DEV) * n
+    bf = dict(dtype=torch.bfloat16, device=DEV)
+    h, yp, dxp = torch.empty((M, 2 * f), **bf), torch.empty((M, d), **bf), torch.empty((M, d), **bf)
+    dw1, dw2 = torch.empty((E, 2 * f, d), device=DEV), torch.empty((E, d, f), device=DEV)
+    ws = torch.empty(B.moe_workspace_bytes(M, d, E, 1, f, B.BF16), dtype=torch.uint8, device=DEV)
+    B.moe_expert_ffn_fwd(x, None, offsets, w1, None, w2, None, h, yp, None, ws)
+    B.moe_expert_ffn_bwd(x, h, dy, None, offsets, w1, w2, dxp, dw1, dw2, 0, ws)
+    for name, t in (("h", h.view(E, n, 2 * f)), ("d_w1", dw1), ("d_w2", dw2)):
+        for e in range(1, E):
+            assert torch.equal(t[e], t[0]), (name, e)
 
 
 def check_bf16_and_fused(rows, d, f, spare):
