@@ -334,7 +334,16 @@ int launch_gemm_f32_dgrad2(const GemmProblem& dgrad2, const void* H, void* dH, v
   return rc != MOE_OK ? rc : launch_swiglu_bwd(H, dgrad2.C, dH, A, dgrad2.M, dgrad2.N, dgrad2.offsets + dgrad2.E, MOE_F32, s);
 }
 
-// d_w2, d_xp and d_w1 of a backward: one launch where each would go to 32 x 32 tiles, else one by one in this order.
+// Whether `q` may run beside `p`: what it writes is neither read nor written by `p` (operands dense, rows or segments up to their bound).
+static bool writes_apart(const GemmProblem& q, const GemmProblem& p) {
+  auto c_floats = [](const GemmProblem& g) { return (size_t)(g.mode == 1 ? g.E * g.c_es : g.M * g.ldc); };
+  const size_t a = (size_t)(p.mode == 1 ? p.K * p.a_cs : p.M * p.a_rs), b = (size_t)(p.mode == 1 ? p.K * p.b_rs : p.E * p.b_es);
+  const size_t out = c_floats(q) * 4;
+  return apart(q.C, out, p.A, a * 4) && apart(q.C, out, p.B, b * 4) && apart(q.C, out, p.C, c_floats(p) * 4);
+}
+
+// d_w2, d_xp and d_w1 of a backward: one launch where each would go to 32 x 32 tiles, else one by one in this order.  A caller may
+// write d_xp over d_yp or a_override, or d_w1 over w1, which d_w2 and d_xp read before: those go one by one.
 int launch_gemm_f32_trio(const GemmProblem& dw2, const GemmProblem& dxp, const GemmProblem& dw1, hipStream_t s) {
   const GemmProblem* p[3] = {&dw2, &dxp, &dw1};
   SmallTrio t{};
@@ -343,6 +352,7 @@ int launch_gemm_f32_trio(const GemmProblem& dw2, const GemmProblem& dxp, const G
   for (int i = 0; i < 3; ++i) {
     const bool a_kfast = p[i]->a_cs == 1, b_kfast = p[i]->b_rs == 1;
     joint = joint && small(*p[i]) && a_kfast == (i == 1) && !b_kfast;
+    for (int j = 0; j < 3; ++j) joint = joint && (i == j || writes_apart(*p[i], *p[j]));
     const long blocks = f32_blocks(*p[i], kSmall, kSmall);
     t.p[i] = *p[i];
     t.tiles_n[i] = cdiv(p[i]->N, kSmall);

@@ -26,6 +26,12 @@ static inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 static inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 static inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+
+// True where two buffers share no byte.
+static inline bool apart(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x + a_bytes <= y || y + b_bytes <= x;
+}
 static inline size_t dtype_size(moe_dtype t) { return t == MOE_F32 ? 4 : (t == MOE_BF16 ? 2 : 1); }
 
 // Number of token chunks the routing kernels split T into (one histogram row per chunk).

@@ -348,8 +348,8 @@ int launch_router_bwd(const void* x, const void* w_r, const float* d_logits, moe
     // leave a CU one block.)
     const int co = E <= 16 ? 4 : 2, dwr_blocks = cdiv(d, 64 * co) * chunks;
     const size_t x_bytes = (size_t)T * d * dtype_size(dt);          // (dx written over x: in two launches, as d_w_r needs x as it was)
-    const bool apart = static_cast<const char*>(x) + x_bytes <= static_cast<const char*>(dx) || static_cast<const char*>(dx) + x_bytes <= static_cast<const char*>(x);
-    if (dx && apart && T > 8 && cdiv(d, 256 * co) * chunks < 256 && E <= (dt == MOE_F32 ? 16 : 32) && dwr_blocks + dx_blocks <= 1024) {
+    if (dx && apart(x, x_bytes, dx, x_bytes) && T > 8 && cdiv(d, 256 * co) * chunks < 256 && E <= (dt == MOE_F32 ? 16 : 32) &&
+        dwr_blocks + dx_blocks <= 1024) {
 #define MOE_JOINT_CASE(TT, ET, CO)                                                                                                  \
   router_bwd_kernel<TT, ET, CO><<<dwr_blocks + dx_blocks, 256, 0, s>>>((const TT*)x, (const TT*)w_r, d_logits, T, d, E, tpc, partial, \
                                                                        dwr_blocks, token_groups, (TT*)dx)

@@ -163,6 +163,35 @@ def test_products_cut_along_k(rows, d, f, spare):
             assert rel(got, ref) < (4 + 0.58 * math.sqrt(K / 2)) * 2.0 ** -24, (e, rel(got, ref))
 
 
+# small layers, whose last three products of a backward share a launch, and one whose products do not
+@pytest.mark.parametrize("rows,d,f", [([1, 31, 0, 32], 16, 48), ([70, 3, 129, 0, 64, 31, 95, 120], 128, 256), ([20, 32, 0, 33], 272, 272), CASES[3]])
+@pytest.mark.parametrize("over", ["d_yp", "a_override", "w1", "d_yp, part"])
+def test_gradients_written_over_what_earlier_products_read(rows, d, f, over):
+    """d_xp over d_yp or a_override (d_w2 reads both), d_w1 over w1 (d_xp reads it): the bits of the call with separate buffers."""
+    from paper_2505_11432_amd import binding as B
+    E, M = len(rows), sum(rows)
+    xp, dyp, w1, w2 = inputs_f32(rows, d, f)
+    a = torch.randn(M * max(d, f), generator=torch.Generator(device=DEV).manual_seed(7), device=DEV)[:M * f].view(M, f)
+    a = a if over == "a_override" else None
+    ref = ffn_f32(rows, d, f, xp, dyp, w1, w2, a_override=a)
+    offsets = torch.tensor([sum(rows[:e]) for e in range(E + 1)], dtype=torch.int32, device=DEV)
+    ws = torch.empty(max(B.moe_workspace_bytes(M, d, E, 1, f, B.F32), 256), dtype=torch.uint8, device=DEV)
+    dxp, dw1, dw2 = torch.full_like(xp, 7.0), torch.full_like(w1, 7.0), torch.full_like(w2, 7.0)
+    if over == "d_yp":
+        dxp = dyp
+    elif over == "d_yp, part":                       # the second half of d_yp
+        both = torch.full((2 * M, d), 7.0, device=DEV)
+        both[:M] = dyp
+        dyp, dxp = both[:M], both[M // 2:M // 2 + M]
+    elif over == "a_override":
+        dxp = torch.as_strided(a, (M, d), (d, 1))
+    else:
+        dw1 = w1
+    B.moe_expert_ffn_bwd(xp, ref[0], dyp, a, offsets, w1, w2, dxp, dw1, dw2, 0, ws)
+    for name, got, want in (("d_xp", dxp, ref[2]), ("d_w1", dw1, ref[3]), ("d_w2", dw2, ref[4])):
+        assert torch.equal(got, want), name
+
+
 @pytest.mark.parametrize("rows,d,f", [SPLIT[1], LARGE])
 def test_split_weight_gradients_accumulate(rows, d, f):
     """accumulate = 1 adds the product, the same bits as without it, to what is there."""
