@@ -163,6 +163,23 @@ def test_products_cut_along_k(rows, d, f, spare):
             assert rel(got, ref) < (4 + 0.58 * math.sqrt(K / 2)) * 2.0 ** -24, (e, rel(got, ref))
 
 
+@pytest.mark.parametrize("rows,d,f", CASES[:2] + [([70, 3, 129, 0, 64, 31, 95, 120], 128, 256), ([20, 32, 0, 33], 272, 1040), CASES[3]])
+@pytest.mark.parametrize("at", [0, 1])
+def test_output_written_over_the_saved_activations(rows, d, f, at):
+    """A forward without a backward may give yp the room of H (from its start, from its second half on): the bits of the call with
+    separate buffers."""
+    from paper_2505_11432_amd import binding as B
+    E, M = len(rows), sum(rows)
+    xp, dyp, w1, w2 = inputs_f32(rows, d, f)
+    want = ffn_f32(rows, d, f, xp, dyp, w1, w2)[1]
+    offsets = torch.tensor([sum(rows[:e]) for e in range(E + 1)], dtype=torch.int32, device=DEV)
+    room = torch.full((M * (f + max(2 * f, d)),), 7.0, device=DEV)
+    yp = room[at * M * f:][:M * d].view(M, d)
+    ws = torch.empty(max(B.moe_workspace_bytes(M, d, E, 1, f, B.F32), 256), dtype=torch.uint8, device=DEV)
+    B.moe_expert_ffn_fwd(xp, None, offsets, w1, None, w2, None, room[:2 * M * f].view(M, 2 * f), yp, None, ws)
+    assert torch.equal(yp, want)
+
+
 # small layers, whose last three products of a backward share a launch, and one whose products do not
 @pytest.mark.parametrize("rows,d,f", [([1, 31, 0, 32], 16, 48), ([70, 3, 129, 0, 64, 31, 95, 120], 128, 256), ([20, 32, 0, 33], 272, 272), CASES[3]])
 @pytest.mark.parametrize("over", ["d_yp", "a_override", "w1", "d_yp, part"])
