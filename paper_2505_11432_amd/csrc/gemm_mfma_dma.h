@@ -422,9 +422,10 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // Waves w and w + 4 of eight share a SIMD: they lie in opposite halves of the tile along both sides, so that a tile whose second half holds
-  // nothing, along either, leaves every SIMD one wave to multiply.
-  const int wm = wave / WN, wn = wave % WN ^ (SPLIT && wave >= NL ? WN / 2 : 0);
+  // Waves w and w + 4 of eight share a SIMD.  In FC1 they lie in opposite halves of the tile along both sides, elsewhere along one.  Of 8
+  // experts, 16384 rows, 4096 x 14336 (us, one side and both): FC1 3093, 3078, dgrad1 2920, 2955; of 4, 24576 rows 4415, 4385 and 4257,
+  // 4281; of 64, 131072 rows, 2048 x 1408 1384, 1376 and 1216, 1220; the others the same.
+  const int wm = wave / WN, wn = wave % WN ^ (SPLIT && SWI && wave >= NL ? WN / 2 : 0);
   const char* zero = reinterpret_cast<const char*>(g_zero_block);
   char* stg = smem + RING_BYTES + TABLE_BYTES + wave * STG_BYTES;      // this wave's epilogue patch
   // where this lane's fragments of the wave's first rows lie in a ring slot
@@ -797,8 +798,8 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) grouped_gemm_dma_kernel(Args 
       // A wave whose rows all lie past the last one (of the expert, or of the gradient), or whose columns all lie past the width, has nothing
       // to multiply (wave-uniform; it still issues its loads and takes part in the barriers).  In a nearly empty last tile only one or two
       // waves per CU then use the matrix cores, and the k-step shrinks to what the loads need.
-      // Eight waves, columns and gradient rows as well (us): 64 experts, 131072 rows, 2048 x 1408 d_w2 741 -> 717, dgrad1 1252 -> 1231; 8 experts,
-      // 16384 rows, 1040 x 1424 d_w2 59 -> 57, dgrad1 127 -> 123, d_w1 117 -> 112, FC2 94 -> 92.  (Four waves have no partner on their SIMD.)
+      // Eight waves, columns and gradient rows as well (us): 64 experts, 131072 rows, 2048 x 1408 d_w2 766 -> 749, dgrad1 1260 -> 1250, d_w1 1443 ->
+      // 1427; 8 experts, 16384 rows, 1040 x 1424 d_w2 61 -> 58, dgrad1 127 -> 122, d_w1 119 -> 111.  (Four waves have no partner on their SIMD.)
       const bool wave_active = SPLIT ? m0 + wm * WTM < m_end && n0 + wn * (SWI ? WTN / 2 : WTN) < (SWI ? p.f : p.N)
                                      : MODE != ROWSEG || m0 + wm * WTM < m_end;
       if (!wave_active) {
