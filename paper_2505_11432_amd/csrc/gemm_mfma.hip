@@ -274,7 +274,7 @@ int mfma_wgrad_fp8(const void* Pt, const uint8_t* p_e8m0, const void* Qt, const 
   a.accumulate = accumulate;
   a.a_e8m0 = p_e8m0; a.a_e8_ld = Mo; a.b_e8m0 = q_e8m0; a.b_e8_ld = N;
   const long blocks = (long)E * cdiv(Mo, 256) * cdiv(N, 256);
-  a.stagger = wgrad_stagger(blocks, cdiv((int)(ldt / 128), E));
+  a.stagger = wgrad_stagger(Mo, N, blocks, cdiv((int)(ldt / 128), E));
   if (c_dt == MOE_F32) return launch<256, 256, 128, 2, 4, 2, KMAJOR, KMAJOR, KSEG, EPI_STORE, float, uint8_t>(a, blocks, s);
   return launch<256, 256, 128, 2, 4, 2, KMAJOR, KMAJOR, KSEG, EPI_STORE, bf16, uint8_t>(a, blocks, s);
 }

@@ -70,12 +70,29 @@ inline double pairs_us(double tiles, const PairCost& c, int steps) {
   return whole * round_us + (rem < 1 ? 0 : rem <= 256 && half_us < round_us ? half_us : round_us);
 }
 
-// Groups of workgroups that start one after another (e4m3, see STAGGER in gemm_mfma_dma.h), so that their epilogues do not meet.  The late
-// groups end late, (groups - 1) * lag steps of 1.5 us; a round gains 2 to 5 us: from five rounds on.  Launches of 8 experts, 16384 rows,
-// 4096 x 14336 (us, at once and {groups, lag}; a few passes on a cool chip): FC1 1698, {4, 3} 1604, {8, 2} 1568, d_w2 1143, {8, 3} 1065, d_w1
-// 2268, {4, 3} 2377, {8, 3} 2253.
-inline Stagger fc1_stagger(double tiles, int steps) { return tiles < 5 * 256 || steps < 4 ? Stagger{} : Stagger{8, 2}; }
-inline Stagger wgrad_stagger(long tiles, int steps) { return tiles < 5 * 256 || steps < 4 ? Stagger{} : Stagger{8, 3}; }
+// Groups of workgroups that start one after another (e4m3, see STAGGER in gemm_mfma_dma.h), so that their epilogues do not meet.  A round gains
+// 2 to 5 us, from five rounds on, and the last group ends (groups - 1) * lag steps of 1.5 us late: a fixed cost, so that short launches take
+// few groups and short tiles lie close.
+// FC1 (us, sustained: at once, {4, 1}, {8, 1}, {8, 2}): 32 steps, 4096 x 14336 of 8 experts 512 rows 535, 524, 520, 516; 2048 rows 1769, 1697, 1657,
+// 1643; 4096 rows 3380, 3273, 3241, 3229.  16 steps, of 64 experts 2048 x 1408, 2048 rows 920, 866, 836, 835; of 4, 2048 x 14336, 700 rows 229,
+// 215, 212, 216.  8 steps, of 16, 1024 x 8192, 1024 rows 475, 448, 420, 426; of 8, 1024 x 14336, 2048 rows 775, 720, 696, 709.  4 steps, 512 x
+// 14336, 4096 rows 1208, 1044, 1092, 1205.
+inline Stagger fc1_stagger(double tiles, int steps) {
+  if (tiles < 5 * 256 || steps < 4) return {};
+  return steps < 8 ? Stagger{4, 1} : Stagger{8, steps < 24 ? 1 : 2};
+}
+// Gradients of M x N, `tiles` of 256 x 256 (us, sustained: at once, {4, 1}, {8, 1}, {8, 3}).  Narrow ones: 4 column tiles leave a group of eight
+// without a common panel.  Tall ones of many steps gain nothing.
+//   d_w2, 4 steps, 8 experts, 4096 x 14336 598, 503, 532, 539;  8 802, 715, 700, 698;  16 1166, 1088, 1075, 1095;  32 1880, 1804, 1806, 1797
+//   d_w1 of these                          1264, 1244, 1182, 1158;  1623, 1625, 1571, 1541;  2332, 2332, 2316, 2300;  3739, 3838, 3818, 3824
+//   16 steps, 8 experts, d_w2, d_w1 of 2048 x 8192 326, 316, 324, 360; 646, 636, 640, 688;  of 1024 x 14336 292, 282, 276, 275; 596, 593, 623, 647
+//   16 steps, 64 experts, 2048 x 1408 486, 472, 471, 481; 985, 935, 929, 942;  4 steps 241, 226, 225, 237; 517, 487, 494, 497
+//   8 steps, 16 experts, 1024 x 8192 231, 220, 222, 234; 460, 452, 485, 514;  32 experts, 1024 x 4096 235, 229, 242, 245; 489, 465, 492, 520
+//   12 steps, 8 experts, 4096 x 4096 273, 262, 259, 282; 626, 523, 509, 538;  6 steps, 4 experts, 2048 x 14336 155, 145, 147, 169; 343, 350, 322, 344
+inline Stagger wgrad_stagger(int M, int N, long tiles, int steps) {
+  if (tiles < 5 * 256 || steps < 4 || (steps >= 28 && M > N)) return {};
+  return {tiles >= 10 * 256 && N >= 2048 ? 8 : 4, 1};
+}
 
 // N: output columns (SwiGLU: f); K in elements of esz bytes
 inline RowPlan plan_rows(RowKind kind, int M, int E, int N, int K, int esz) {

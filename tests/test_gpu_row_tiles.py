@@ -163,6 +163,13 @@ def test_e4m3_below_the_bound(rows, spare):
     check_e4m3(rows, 272, 336, spare)
 
 
+@pytest.mark.parametrize("d,f", [(1040, 6160), (2048, 8192)])
+def test_e4m3_in_groups(d, f):
+    """Workgroups that start in groups and walk the contraction from different steps on: eight of them in FC1, four (first) and eight in
+    d_w1; segments of no, one and a few steps, fewer than the groups lie apart, and with a remainder."""
+    check_e4m3([0, 3, 700, 64, 2500, 65, 3668, 1000], d, f, 0)
+
+
 def check_e4m3(rows, d, f, spare):
     from paper_2505_11432_amd import binding as B
     E, M, off, offsets, w1, w2, x, dy = setup(rows, d, f, spare)

@@ -69,6 +69,39 @@ def test_ordinary_sizes(plan):
     assert not any(s for _, s in plan([k + (M, 8, 4096, 4096, 2) for k in (FC1, DGRAD2) for M in (16, 600, 9000)]))
 
 
+GROUPS = r'''
+#include <cstdio>
+#include "row_plan.h"
+int main() {
+  int M, E, d, f;
+  while (scanf("%d %d %d %d", &M, &E, &d, &f) == 4) {
+    auto up = [](long a, long b) { return (a + b - 1) / b; };
+    const int steps = (int)up(up(M, 128) + E, E);
+    const moe::RowPlan plan = moe::plan_rows({true, false, false}, M, E, f, d, 1), bf16 = moe::plan_rows({true, false, false}, M, E, f, d, 2);
+    const moe::Stagger s[] = {plan.stagger, moe::wgrad_stagger(d, f, E * up(d, 256) * up(f, 256), steps),
+                              moe::wgrad_stagger(2 * f, d, E * up(2 * f, 256) * up(d, 256), steps)};
+    for (const auto& q : s) printf("%dx%d ", q.groups, q.lag);
+    printf("%s %d\n", plan.tile == moe::RowTile::FULL ? "full" : "other", bf16.stagger.groups);
+  }
+}
+'''
+
+
+def test_groups_that_start_one_after_another(tmp_path):
+    """e4m3 FC1, d_w2, d_w1: number of groups and steps between them; none in short launches, short tiles and tall gradients of many
+    steps, none in bf16."""
+    (tmp_path / "m.cpp").write_text(GROUPS)
+    subprocess.run([build.CXX, "-std=c++17", "-I", build.CSRC, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
+    sizes = {(16384, 8, 4096, 14336): "8x2 8x1 8x1", (4096, 8, 4096, 14336): "8x2 8x1 8x1", (32768, 8, 4096, 14336): "8x2 8x1 0x0",
+             (16384, 8, 2048, 8192): "8x1 4x1 8x1", (16384, 16, 1024, 8192): "8x1 4x1 4x1", (131072, 64, 2048, 1408): "8x1 4x1 8x1",
+             (32768, 8, 512, 14336): "4x1 0x0 0x0", (32768, 8, 256, 14336): "0x0 0x0 0x0", (2000, 8, 1024, 2816): "0x0 0x0 0x0",
+             (8000, 8, 1040, 6160): "8x1 0x0 4x1", (2048, 8, 4096, 14336): "0x0 0x0 0x0"}
+    out = subprocess.run([str(tmp_path / "m")], input="\n".join(" ".join(map(str, k)) for k in sizes), capture_output=True, text=True, check=True)
+    got = out.stdout.split("\n")[:-1]
+    assert [" ".join(l.split()[:3]) for l in got] == list(sizes.values())
+    assert all(l.split()[4] == "0" for l in got)
+
+
 PAIRS = r'''
 #include <cstdio>
 #include "row_plan.h"
