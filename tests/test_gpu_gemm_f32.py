@@ -66,8 +66,8 @@ def test_ffn_f32_tile_edges(rows, d, f):
     assert rel(dw2, before2.double() + DW2) < tol
 
 
-# rows, d, f: split products on 64 x 64 tiles (d_w1 of the second on 128 x 128; which product takes which is pinned in test_row_plan.py), edges
-# of tiles, k tails of 16, odd and even numbers of steps, a segment of one row, an empty one, segments of a few rows
+# rows, d, f: split products on 64 x 64 tiles (of the second FC2 and d_w1 on 128 x 128; which product takes which is pinned in
+# test_row_plan.py), edges of tiles, k tails of 16, odd and even numbers of steps, a segment of one row, an empty one, segments of a few rows
 SPLIT = [
     ([1, 0, 700, 130, 63], 272, 1040),
     ([500, 511, 0, 1049], 1024, 1408),
@@ -76,6 +76,8 @@ SPLIT = [
 ]
 # 128 x 128 tiles in FC1, dgrad2 and both weight gradients
 LARGE = ([240, 255, 245, 260, 262, 238, 240, 260], 1024, 2816)
+# 128 x 128 tiles of eight waves in FC1 and d_w2, in dgrad2 and d_w1 (FC2 of the last in six parts): edges, k tails of 16, a segment of one row
+EIGHT = [([871, 1, 628], 1008, 1040), ([1500], 784, 2064)]
 
 
 def ffn_f32(rows, d, f, xp, dyp, w1, w2, a_override=None):
@@ -97,7 +99,7 @@ def inputs_f32(rows, d, f):
     return rnd(M, d), rnd(M, d), rnd(E, 2 * f, d) / math.sqrt(d), rnd(E, d, f) / math.sqrt(f)
 
 
-@pytest.mark.parametrize("rows,d,f", SPLIT + [LARGE])
+@pytest.mark.parametrize("rows,d,f", SPLIT + [LARGE] + EIGHT)
 def test_split_products_are_as_close_as_fp32(rows, d, f):
     """Every product against float64, on the operands that the library itself made: within what an fp32 sum of K terms that is rounded
     every second term loses (sqrt(K / 2) roundings of random sign, 2^-24 at most and 0.58 of that each in the mean square).  Sums of one
@@ -123,7 +125,7 @@ def test_split_products_are_as_close_as_fp32(rows, d, f):
 
 
 # FC2 and dgrad1 cut along K: 64 x 64 and 128 x 128 tiles, numbers of steps that the parts do not divide, a k tail of 16, rows past the
-# segments.  With the workspace of the forward alone FC2 is not cut.  The last: d_w1 in one round of 128 x 128 tiles, not cut.
+# segments.  With the workspace of the forward alone FC2 is not cut.  The last: d_w1 in one round of 128 x 128 tiles of eight waves, not cut.
 CUT = [([64, 0, 127, 1, 64, 40, 90, 126], 1024, 2832, 0), ([255, 1, 0, 700, 129, 300, 415, 200], 1024, 2832, 77), ([500, 511, 0, 1049], 1024, 1408, 3),
        ([300, 333, 0, 567], 496, 1008, 5)]
 
@@ -152,6 +154,7 @@ def test_products_cut_along_k(rows, d, f, spare):
     for e, k in enumerate(rows):
         s, at = slice(at, at + k), at + k
         if k == 0:
+            assert not dw1[e].any() and not dw2[e].any()
             continue
         a, b, DY = w1[e].double(), w2[e].double(), dyp[s].double()
         G, U = h[s, :f].double(), h[s, f:].double()
@@ -159,7 +162,9 @@ def test_products_cut_along_k(rows, d, f, spare):
         dA = DY @ b
         dH = torch.cat([dA * U * sg * (1 + G * (1 - sg)), dA * G * sg], 1)
         # the bound of the uncut products: sqrt(K / 2) roundings, and the operands' own
-        for got, ref, K in ((out[0][s], (G * sg * U) @ b.t(), f), (out[1][s], (G * sg * U) @ b.t(), f), (dxp[s], dH @ a, 2 * f)):
+        A = G * sg * U
+        for got, ref, K in ((out[0][s], A @ b.t(), f), (out[1][s], A @ b.t(), f), (dxp[s], dH @ a, 2 * f),
+                            (dw1[e], dH.t() @ xp[s].double(), k), (dw2[e], DY.t() @ A, k)):
             assert rel(got, ref) < (4 + 0.58 * math.sqrt(K / 2)) * 2.0 ** -24, (e, rel(got, ref))
 
 
@@ -256,7 +261,7 @@ def test_split_products_of_tiny_and_huge_elements(rows, d, f, scale):
         assert n == 0 or float((h[s].double() - ref).norm()) < float(tol), (e, float((h[s].double() - ref).norm()), float(tol))
 
 
-@pytest.mark.parametrize("rows,d,f", SPLIT[:2] + [LARGE])
+@pytest.mark.parametrize("rows,d,f", SPLIT[:2] + [LARGE] + EIGHT)
 def test_tiny_rows_leave_the_others_alone(rows, d, f):
     """What a row holds does not change how the rows of its tile are computed: the same bits beside it."""
     xp, dyp, w1, w2 = inputs_f32(rows, d, f)
@@ -318,8 +323,8 @@ def test_split_products_below_the_normal_range(rows, d, f, ex, ew):
         assert n == 0 or ew < -130 or h[s].any()
 
 
-def test_split_products_of_infinities_and_nan():
-    rows, d, f = SPLIT[0]
+@pytest.mark.parametrize("rows,d,f", [SPLIT[0], EIGHT[0]])
+def test_split_products_of_infinities_and_nan(rows, d, f):
     xp, dyp, w1, w2 = inputs_f32(rows, d, f)
     inf = float("inf")
     xp[3, 7], xp[9, 200], xp[300, 0], xp[301, 1] = inf, -inf, float("nan"), 3.4e38         # the last: above bf16's largest
@@ -338,9 +343,9 @@ def test_split_products_of_infinities_and_nan():
         assert n == 0 or rel(got[fin], ref[fin]) < 3 * math.sqrt(d) * 2.0 ** -24
 
 
-@pytest.mark.parametrize("rows,d,f", [SPLIT[0], LARGE])
+@pytest.mark.parametrize("rows,d,f", [SPLIT[0], LARGE] + EIGHT)
 def test_split_products_of_infinities_and_nan_in_every_layout(rows, d, f):
-    """The other operand layouts (weights across their rows, weight gradients) on both tiles: what a row or column that holds no such
+    """The other operand layouts (weights across their rows, weight gradients) on every tile: what a row or column that holds no such
     element gets is finite and as close as ever, also inside a tile that is made again."""
     inf, nan = float("inf"), float("nan")
     xp, dyp, w1, w2 = inputs_f32(rows, d, f)

@@ -64,6 +64,7 @@ def test_no_small_tile_where_gathered_rows_would_be_slow(plan):
 def test_ordinary_sizes(plan):
     assert [t for t, _ in plan(gemms(16384, 8, 4096, 14336))] == ["full"] * 4
     assert [t for t, _ in plan(gemms(131072, 64, 2048, 1408))] == ["full"] * 4
+    assert plan([FC1 + (8000, 8, 6160, 1040, 2), FC1 + (4096, 8, 10368, 4096, 2)]) == [("full", False)] * 2
     assert [t for t, _ in plan(gemms(4593, 24, 1040, 1424))] == ["mid", "mid", "full", "mid"]
     assert plan([FC2 + (16384, 8, 4096, 14336, 2)]) == [("full", True)]
     assert not any(s for _, s in plan([k + (M, 8, 4096, 4096, 2) for k in (FC1, DGRAD2) for M in (16, 600, 9000)]))
@@ -94,6 +95,7 @@ def test_groups_that_start_one_after_another(tmp_path):
     subprocess.run([build.CXX, "-std=c++17", "-I", build.CSRC, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
     sizes = {(16384, 8, 4096, 14336): "8x2 8x1 8x1", (4096, 8, 4096, 14336): "8x2 8x1 8x1", (32768, 8, 4096, 14336): "8x2 8x1 0x0",
              (16384, 8, 2048, 8192): "8x1 4x1 8x1", (16384, 16, 1024, 8192): "8x1 4x1 4x1", (131072, 64, 2048, 1408): "8x1 4x1 8x1",
+             (8000, 8, 2048, 8192): "8x1 4x1 8x1",
              (32768, 8, 512, 14336): "4x1 0x0 0x0", (32768, 8, 256, 14336): "0x0 0x0 0x0", (2000, 8, 1024, 2816): "0x0 0x0 0x0",
              (8000, 8, 1040, 6160): "8x1 0x0 4x1", (2048, 8, 4096, 14336): "0x0 0x0 0x0"}
     out = subprocess.run([str(tmp_path / "m")], input="\n".join(" ".join(map(str, k)) for k in sizes), capture_output=True, text=True, check=True)
@@ -120,7 +122,8 @@ def test_pairs_of_workgroups(tmp_path):
     subprocess.run([build.CXX, "-std=c++17", "-I", build.CSRC, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
     sizes = {(4593, 24, 1040, 1424): "1 0 0 0", (2000, 8, 1024, 2816): "1 1 0 0", (4096, 8, 512, 512): "1 0 1 1", (6000, 8, 1024, 1024): "0 1 1 0",
              (512, 8, 4096, 14336): "0 0 0 0", (16384, 8, 4096, 14336): "0 0 0 0", (131072, 64, 2048, 1408): "0 0 0 0", (0, 8, 16, 16): "0 0 1 1",
-             (1222, 6, 272, 336): "1 0 1 1", (4096, 16, 1024, 1024): "1 1 0 0"}
+             (1222, 6, 272, 336): "1 0 1 1", (4096, 16, 1024, 1024): "1 1 0 0",
+             (8000, 8, 1040, 6160): "0 0 0 0", (4096, 8, 4096, 10368): "0 0 0 0"}
     out = subprocess.run([str(tmp_path / "m")], input="\n".join(" ".join(map(str, k)) for k in sizes), capture_output=True, text=True, check=True)
     assert out.stdout.split("\n")[:-1] == list(sizes.values())
 
@@ -173,7 +176,14 @@ int main() {
   int M, E, d, f;
   while (scanf("%d %d %d %d", &M, &E, &d, &f) == 4) {
     const moe::F32Product p[] = {{true, M, 2 * f, d, E}, {true, M, d, f, E}, {true, M, f, d, E}, {true, M, d, 2 * f, E}, {false, d, f, M, E}, {false, 2 * f, d, M, E}};
-    for (const auto& q : p) printf("%s ", !moe::f32_split_pays(q) ? "-" : moe::f32_split_in_128(q) ? "128" : "64");
+    // results that fit behind A in the full workspace (FC2), in A and dA (dgrad1)
+    const long a = ((long)M * f * 4 + 255) / 256 * 64, dh = ((long)M * 2 * f * 4 + 255) / 256 * 64, out = (long)M * d;
+    const long room[] = {0, (a + dh) / out, 0, 2 * a / out, 0, 0};
+    for (int i = 0; i < 6; ++i) {
+      const moe::F32Plan q = moe::f32_plan(p[i], room[i]);
+      if (!moe::f32_split_pays(p[i])) printf("- ");
+      else printf(q.parts > 1 ? "%s/%d " : "%s ", q.tile == moe::F32_128 ? "128" : q.tile == moe::F32_128_EIGHT ? "eight" : "64", q.parts);
+    }
     printf("\n");
   }
 }
@@ -181,13 +191,16 @@ int main() {
 
 
 def test_fp32_products(tmp_path):
-    """FC1, FC2, dgrad2, dgrad1, d_w2, d_w1: the fp32 instruction (-) or the split on one of its tiles, at the sizes of the fp32 GEMM tests
-    (which rely on each tile being taken in each layout) and at small ones."""
+    """FC1, FC2, dgrad2, dgrad1, d_w2, d_w1: the fp32 instruction (-) or the split on 64 x 64 tiles, on 128 x 128 of four waves, of eight
+    waves, cut along K into so many parts, at the sizes of the fp32 GEMM tests (which rely on each being taken in each layout) and at small ones."""
     (tmp_path / "m.cpp").write_text(F32)
     subprocess.run([build.CXX, "-std=c++17", "-I", build.CSRC, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
-    sizes = {(2000, 8, 1024, 2816): "128 64 128 64 128 128", (2060, 4, 1024, 1408): "64 64 64 64 64 128", (894, 5, 272, 1040): "64 - 64 - 64 64",
-             (1200, 30, 48, 528): "64 - 64 - 64 64", (1027, 1, 1552, 784): "64 64 64 64 64 64", (512, 8, 128, 256): "- - - - - -",
-             (160, 8, 256, 512): "- - - - - -", (199, 8, 512, 1408): "64 - - - - -"}
+    sizes = {(2000, 8, 1024, 2816): "128 128/3 128 128/3 128 128", (2060, 4, 1024, 1408): "64 128/3 64 64/2 64 128",
+             (894, 5, 272, 1040): "64 - 64 - 64 64", (1200, 30, 48, 528): "64 - 64 - 64 64", (1027, 1, 1552, 784): "64 64 64 64 64 64",
+             (512, 8, 1024, 2832): "64 64/4 64 64/4 128 128", (2077, 8, 1024, 2832): "128 128/3 128 128/3 128 128",
+             (2063, 4, 1024, 1408): "64 128/3 64 64/2 64 128", (1205, 4, 496, 1008): "64 - 64 - 64 eight",
+             (1500, 3, 1008, 1040): "eight 64 64 64 eight 128", (1500, 1, 784, 2064): "64 128/6 eight 64/3 64 eight",
+             (512, 8, 128, 256): "- - - - - -", (160, 8, 256, 512): "- - - - - -", (199, 8, 512, 1408): "64 - - - - -"}
     out = subprocess.run([str(tmp_path / "m")], input="\n".join(" ".join(map(str, k)) for k in sizes), capture_output=True, text=True, check=True)
     got = [l.strip() for l in out.stdout.split("\n") if l]
     assert got == list(sizes.values()), list(zip(sizes, got))
