@@ -214,7 +214,11 @@ int moe_gate_grad(const void* dy /*[T,d]*/, moe_dtype dy_dt, const void* yp /*[T
  * instead of the workspace; passing it to moe_expert_ffn_bwd as a_override spares the backward
  * the second write of A (the paper recomputes the FC2 input, Section 4.1: keeping it trades
  * M*f*2 bytes for that write).  The plain paths touch no row >= offsets[E]; the fp8 path
- * requires offsets[E] = M. */
+ * requires offsets[E] = M.
+ * MOE_F32: M*f*4 bytes of workspace (rounded up to 256) are enough.  With more, such as
+ * moe_workspace_bytes gives, FC2 may be summed in up to six parts along f, which is faster where it has
+ * few tiles; yp then differs in the rounding of its sums, so calls that are to agree bit for bit need
+ * the same ws_bytes. */
 int moe_expert_ffn_fwd(const void* xp, const float* xp_scale, moe_dtype act_dt,
                        const int32_t* offsets /*[E+1], device*/,
                        const void* w1 /*[E,2f,d]*/, const float* w1_scale,
