@@ -304,13 +304,14 @@ int launch_gemm_f32(const GemmProblem& p, hipStream_t s) {
 // True for a product that goes to 32 x 32 tiles.
 static bool small(const GemmProblem& p) { return p.M > 0 && p.N > 0 && !gemm_f32_splits(p) && tiles64(p) < 256; }
 
-// H -> yp: SwiGLU into A and FC2 (fc2, which reads A), or both in one launch of small tiles.  Every column of tiles makes A again, which costs
-// more than a launch where a CU has a long contraction or several tiles; and yp may be written over H, which a column of tiles must not do
-// before the others have read it.  SwiGLU and FC2, one launch (us, 32 x 32 tiles on a CU times K): 1024
-// 20.5, 18.4; 1024 17.0, 14.4; 1536 28.0, 26.6; 2816 47, 57; 3072 28.8, 30.3; 5632 49.6, 54.
+// H -> yp: SwiGLU into A and FC2 (fc2, which reads A), or both in one launch of small tiles.  Every column of tiles makes A again, at 0.1 us per
+// k-step of 64, which costs more than a launch where a CU has a long contraction or several tiles; and yp may be written over H, which a column
+// of tiles must not do before the others have read it.  Whole forwards back to back, SwiGLU and FC2, one launch (us; 32 x 32 tiles on a CU times
+// K): 256 16.0, 14.5; 17.1, 15.7; 336 24.0, 22.8; 512 19.2, 18.7; 22.7, 22.3; 20.6, 18.9; 640 22.8, 22.4; 768 22.5, 22.6; 1024 28.1, 28.8; 31.2, 31.9;
+// 1280 28.3, 29.8; 1536 31.2, 34.1; 2000 40.2, 43.6.
 int launch_gemm_f32_fc2(const GemmProblem& fc2, const void* H, void* A, hipStream_t s) {
   const long blocks32 = f32_blocks(fc2, kSmall, kSmall);
-  if (small(fc2) && (blocks32 + 255) / 256 * fc2.K <= 2048 && apart(H, 8 * (size_t)fc2.M * fc2.K, fc2.C, 4 * (size_t)fc2.M * fc2.ldc)) {
+  if (small(fc2) && (blocks32 + 255) / 256 * fc2.K <= 640 && apart(H, 8 * (size_t)fc2.M * fc2.K, fc2.C, 4 * (size_t)fc2.M * fc2.ldc)) {
     GemmProblem p = fc2;
     p.A = H;
     p.a_rs = 2L * fc2.K;
