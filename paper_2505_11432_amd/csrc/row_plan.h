@@ -188,9 +188,23 @@ inline int f32_steps(const F32Product& p) {
   const int k = p.rows ? p.K : p.K / p.E;
   return (k + kF32SplitStep - 1) / kF32SplitStep;
 }
+// Tiles of b x b that row segments within a tenth of the average make.  Balanced routing leaves that much, and a last round is made or missed by it:
+// 8 segments of 145 rows are 16 row tiles of 128, 13 by the half tile per segment that the other counts take.
+inline double f32_tiles_near(const F32Product& p, int b) {
+  const double mean = (double)p.M / p.E;
+  auto sum = [&](double x) {                    // of the tiles of segments up to x rows long
+    const long k = (long)(x / b);
+    return b * (k * (k + 1) / 2.0) + (k + 1) * (x - (double)k * b);
+  };
+  return (p.N + b - 1) / b * p.E * (sum(1.1 * mean) - sum(0.9 * mean)) / (0.2 * mean);
+}
+// The larger tile has to be the faster one by both counts, above three tiles for every two CUs (8 experts, 1161 rows, FC1 of 528 x 2176: 444 and
+// 544 tiles; 56.6 us, 128 x 128 74.2; d_w1 of 390 and 392 tiles: 1.18 and 1.15 of the time on 64 x 64).
 inline bool f32_split_in_128(const F32Product& p) {
+  const int steps = f32_steps(p);
   const double tiles = f32_tiles128(p);
-  return tiles >= 400 && f32_us128(tiles, f32_steps(p)) < f32_us64(f32_tiles64(p), f32_steps(p));
+  if (tiles <= 1.5 * 256 || f32_us128(tiles, steps) >= f32_us64(f32_tiles64(p), steps)) return false;
+  return !p.rows || f32_us128(f32_tiles_near(p, 128), steps) < f32_us64(f32_tiles_near(p, 64), steps);
 }
 
 // One round of 128 x 128 tiles by eight waves with two stages, 3.5 us + 1.33 per step: alone on a CU they beat four waves with one.  Weight
@@ -205,20 +219,27 @@ enum F32Shape { F32_64, F32_128, F32_128_EIGHT };
 struct F32Plan { F32Shape tile; int parts; };      // parts along K
 // With scratch for `room` results a product of row segments may be cut into up to that many parts (at most 6), which a kernel of its own adds:
 // 4 us and 1 per 8 MB.  FC2 and dgrad1 have few tiles and long contractions.  Measured (us with the addition, whole on 64 x 64 and cut): 8
-// experts, 1024 x 2816, 2000 rows FC2 138, 113 (128 x 128 in 3), dgrad1 288, 196 (in 3; in 2 247, in 5 223); 512 rows 62, 53 (64 x 64 in 4), 139, 104;
-// 16 experts, 768 x 2048, 1600 rows dgrad1 133, 115; 6 experts, 512 x 1408, 3000 rows dgrad1 90, 69; 4 experts, 1024 x 1408, 2060 rows 61, 56 and 125, 115.
+// experts, 1024 x 2816, 2000 rows FC2 138, 113 (128 x 128 in 3), dgrad1 288, 196 (in 3; in 2 247, in 5 223); 512 rows 62, 53 (64 x 64 in 4), 139, 104.
+// Parts fill a round or just miss it, and then a cut costs as much as it gains elsewhere: 16 experts, 2008 rows, 784 x 1424 FC2 1.62 of the time
+// whole, dgrad1 1.34.  So the tiles of a cut are counted by the half tile per segment and by f32_tiles_near, and the higher count goes, with 3 % more of
+// the small and 6 % more of the large ones (XCDs fill unevenly), against the whole product by f32_tiles_near.  Over 680 shapes (300 to 4500 rows, 1 to
+// 32 experts, even and skewed, widths of 384 to 2816) FC2 then takes 0.976 and dgrad1 0.907 of the time whole on 64 x 64 or eight waves, 11 of 1360 more
+// than 1.03 and the worst 1.15; by the first count alone 0.978 and 0.898, but 50 more than 1.03 and the worst 1.62.
 inline F32Plan f32_plan(const F32Product& p, long room) {
-  F32Plan best = {f32_split_in_128(p) ? F32_128 : f32_split_in_eight(p) ? F32_128_EIGHT : F32_64, 1};
-  if (!p.rows || room < 2) return best;
+  const F32Plan whole = {f32_split_in_128(p) ? F32_128 : f32_split_in_eight(p) ? F32_128_EIGHT : F32_64, 1};
+  if (!p.rows || room < 2) return whole;
   const int steps = f32_steps(p);
-  const double t64 = f32_tiles64(p), t128 = f32_tiles128(p);
-  double best_us = best.tile == F32_128 ? f32_us128(t128, steps) : best.tile == F32_128_EIGHT ? f32_us_eight(steps) : f32_us64(t64, steps);
+  const double t64 = f32_tiles64(p), t128 = f32_tiles128(p), near64 = f32_tiles_near(p, 64), near128 = f32_tiles_near(p, 128);
+  const double whole_us = whole.tile == F32_128 ? f32_us128(t128, steps) : whole.tile == F32_128_EIGHT ? f32_us_eight(steps) : f32_us64(near64, steps);
+  const double cut64 = 1.03 * (near64 > t64 ? near64 : t64), cut128 = 1.06 * (near128 > t128 ? near128 : t128);
+  F32Plan best = whole;
+  double best_us = 0.95 * whole_us;
   for (int n = 2; n <= (room < 6 ? room : 6) && steps / n >= 8; ++n) {
     const int each = (steps + n - 1) / n;
     const double add = 4 + (n + 1.0) * p.M * p.N * 4 / 8e6;
-    const double us64 = f32_us64(t64 * n, each) + add, us128 = f32_us128(t128 * n, each) + add;
+    const double us64 = f32_us64(cut64 * n, each) + add, us128 = f32_us128(cut128 * n, each) + add;
     const double us = us128 < us64 ? us128 : us64;
-    if (us < 0.95 * best_us) {
+    if (us < best_us) {
       best_us = us;
       best = {us128 < us64 ? F32_128 : F32_64, n};
     }

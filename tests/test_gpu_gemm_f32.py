@@ -66,7 +66,7 @@ def test_ffn_f32_tile_edges(rows, d, f):
     assert rel(dw2, before2.double() + DW2) < tol
 
 
-# rows, d, f: split products on 64 x 64 tiles (of the second FC2 and d_w1 on 128 x 128; which product takes which is pinned in
+# rows, d, f: split products on 64 x 64 tiles (of the second FC1, FC2 and d_w1 on 128 x 128; which product takes which is pinned in
 # test_row_plan.py), edges of tiles, k tails of 16, odd and even numbers of steps, a segment of one row, an empty one, segments of a few rows
 SPLIT = [
     ([1, 0, 700, 130, 63], 272, 1040),
@@ -76,7 +76,8 @@ SPLIT = [
 ]
 # 128 x 128 tiles in FC1, dgrad2 and both weight gradients
 LARGE = ([240, 255, 245, 260, 262, 238, 240, 260], 1024, 2816)
-# 128 x 128 tiles of eight waves in FC1 and d_w2, in dgrad2 and d_w1 (FC2 of the last in six parts): edges, k tails of 16, a segment of one row
+# 128 x 128 tiles of eight waves in FC1 and d_w2, in dgrad2 and d_w1 (dgrad1 of the last in five parts of 128 x 128): edges, k tails of 16, a segment of
+# one row
 EIGHT = [([871, 1, 628], 1008, 1040), ([1500], 784, 2064)]
 
 
@@ -125,7 +126,7 @@ def test_split_products_are_as_close_as_fp32(rows, d, f):
 
 
 # FC2 and dgrad1 cut along K: 64 x 64 and 128 x 128 tiles, numbers of steps that the parts do not divide, a k tail of 16, rows past the
-# segments.  With the workspace of the forward alone FC2 is not cut.  The last: d_w1 in one round of 128 x 128 tiles of eight waves, not cut.
+# segments.  With the workspace of the forward alone FC2 is not cut.  The last is not cut: 64 x 64 tiles, d_w1 on eight waves.
 CUT = [([64, 0, 127, 1, 64, 40, 90, 126], 1024, 2832, 0), ([255, 1, 0, 700, 129, 300, 415, 200], 1024, 2832, 77), ([500, 511, 0, 1049], 1024, 1408, 3),
        ([300, 333, 0, 567], 496, 1008, 5)]
 

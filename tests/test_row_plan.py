@@ -195,11 +195,12 @@ def test_fp32_products(tmp_path):
     waves, cut along K into so many parts, at the sizes of the fp32 GEMM tests (which rely on each being taken in each layout) and at small ones."""
     (tmp_path / "m.cpp").write_text(F32)
     subprocess.run([build.CXX, "-std=c++17", "-I", build.CSRC, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
-    sizes = {(2000, 8, 1024, 2816): "128 128/3 128 128/3 128 128", (2060, 4, 1024, 1408): "64 128/3 64 64/2 64 128",
+    sizes = {(2000, 8, 1024, 2816): "128 128/3 128 128/3 128 128", (2060, 4, 1024, 1408): "128 128/3 64 64/2 64 128",
              (894, 5, 272, 1040): "64 - 64 - 64 64", (1200, 30, 48, 528): "64 - 64 - 64 64", (1027, 1, 1552, 784): "64 64 64 64 64 64",
-             (512, 8, 1024, 2832): "64 64/4 64 64/4 128 128", (2077, 8, 1024, 2832): "128 128/3 128 128/3 128 128",
-             (2063, 4, 1024, 1408): "64 128/3 64 64/2 64 128", (1205, 4, 496, 1008): "64 - 64 - 64 eight",
-             (1500, 3, 1008, 1040): "eight 64 64 64 eight 128", (1500, 1, 784, 2064): "64 128/6 eight 64/3 64 eight",
+             (512, 8, 1024, 2832): "64 64/5 64 64/5 128 128", (2077, 8, 1024, 2832): "128 64/2 128 64/2 128 128",
+             (2063, 4, 1024, 1408): "128 128/3 64 64/2 64 128", (1205, 4, 496, 1008): "64 - 64 - 64 eight",
+             (1500, 3, 1008, 1040): "eight 64 64 64 eight 128", (1500, 1, 784, 2064): "128 64/3 eight 128/5 64 eight",
+             (1161, 8, 528, 2176): "64 64/2 64 64/2 64 128", (2008, 16, 784, 1424): "64 64 64 64 64 64", (2388, 8, 800, 2320): "64 64/3 64 64/5 64 64",
              (512, 8, 128, 256): "- - - - - -", (160, 8, 256, 512): "- - - - - -", (199, 8, 512, 1408): "64 - - - - -"}
     out = subprocess.run([str(tmp_path / "m")], input="\n".join(" ".join(map(str, k)) for k in sizes), capture_output=True, text=True, check=True)
     got = [l.strip() for l in out.stdout.split("\n") if l]
