@@ -344,8 +344,9 @@ int launch_router_bwd(const void* x, const void* w_r, const float* d_logits, moe
     float* partial = static_cast<float*>(ws);
     // One launch with dx where d_w_r shares its tokens by waves and both together are at most four blocks per CU.  The whole call, two launches
     // and one (us): fp32 256 tokens, d = 128, 8 experts 10.7, 6.4, 1000 x 1024 12.7, 8.3, 2000 x 2048, 16 experts 28.9, 22.3; bf16 1531 x 1040, 24
-    // experts 19.3, 16.1, 2000 x 2048, 16 experts 18.5, 14.6, 8000 x 256, 8 experts 14.2, 12.2.  (More experts: the two LDS shares together
-    // leave a CU one block.)
+    // experts 19.3, 16.1, 2000 x 2048, 16 experts 18.5, 14.6, 8000 x 256, 8 experts 14.2, 12.2.  (Calls back to back.  Inside a layer, operands from
+    // memory, the joint kernel takes as long as both: 1531 x 1040 20.2 us, 10.8 and 10.6, and a launch is saved.  More
+    // experts: the two LDS shares together leave a CU one block.)
     const int co = E <= 16 ? 4 : 2, dwr_blocks = cdiv(d, 64 * co) * chunks;
     const size_t x_bytes = (size_t)T * d * dtype_size(dt);          // (dx written over x: in two launches, as d_w_r needs x as it was)
     if (dx && apart(x, x_bytes, dx, x_bytes) && T > 8 && cdiv(d, 256 * co) * chunks < 256 && E <= (dt == MOE_F32 ? 16 : 32) &&

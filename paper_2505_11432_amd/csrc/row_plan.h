@@ -198,8 +198,8 @@ inline double f32_tiles_near(const F32Product& p, int b) {
   };
   return (p.N + b - 1) / b * p.E * (sum(1.1 * mean) - sum(0.9 * mean)) / (0.2 * mean);
 }
-// The larger tile has to be the faster one by both counts, above three tiles for every two CUs (8 experts, 1161 rows, FC1 of 528 x 2176: 444 and
-// 544 tiles; 56.6 us, 128 x 128 74.2; d_w1 of 390 and 392 tiles: 1.18 and 1.15 of the time on 64 x 64).
+// The larger tile has to be the faster one by both counts (8 experts, 1161 rows, FC1 of 528 x 2176, 444 and 544 tiles: 74.2 us, 64 x 64 56.6), and
+// there have to be more than three tiles for every two CUs (d_w1 of 384: 1.04 of the time on 64 x 64, of 390 and 392: 0.85 and 0.87).
 inline bool f32_split_in_128(const F32Product& p) {
   const int steps = f32_steps(p);
   const double tiles = f32_tiles128(p);
